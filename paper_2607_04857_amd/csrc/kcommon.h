@@ -114,6 +114,10 @@ __device__ __forceinline__ int32_t wave_min(int32_t v)
     return min(min(a, b), min(c, d));
 }
 
+// N consecutive words at any word address, read in one load.
+template <int N>
+using ivec = int32_t __attribute__((ext_vector_type(N), aligned(4)));
+
 // Global (address space 1) view of a table pointer: loads then take a
 // uniform base in SGPRs and a lane offset, instead of 64-bit flat addresses.
 using gint32 = __attribute__((address_space(1))) const int32_t;
@@ -133,6 +137,18 @@ __device__ __forceinline__ void pin_vec(int32_t (&e)[MC])
     for (int j = 0; j < MC; j++) asm("" : "+v"(e[j]));
 }
 
+// Wave-wide sum, the same in every lane: DPP inside each row of 16 lanes,
+// then the four row results through the scalar unit.
+__device__ __forceinline__ int32_t wave_sum(int32_t v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xF, 0xF, false);   // quad_perm 1,0,3,2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xF, 0xF, false);   // quad_perm 2,3,0,1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x124, 0xF, 0xF, false);  // row_ror:4
+    v += __builtin_amdgcn_update_dpp(0, v, 0x128, 0xF, 0xF, false);  // row_ror:8
+    return __builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16) +
+           __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
+}
+
 __device__ __forceinline__ int64_t wave_sum64(int64_t v)
 {
 #pragma unroll
@@ -149,47 +165,47 @@ __device__ __forceinline__ void lexmin(int64_t &bE, uint64_t &bI, int64_t e, uin
 }
 
 // Greedy single-flip descent of the calling wave from start state `start`
-// (all-zero for start 0, a hashed state otherwise).  Lane l holds variable l
-// (n <= 60 < 64) and its field f_l = T_ll + the couplings with the set
-// variables, so flipping l changes E by +-f_l; the largest decrease is taken
-// (lowest lane on ties) until no flip lowers E.  Returns the local minimum's
-// energy in E_out and its variables (bit l = variable l) in xm_out, the same
-// in every lane.
-__device__ inline void greedy_descent(const int32_t *T, int n, uint32_t start, int32_t &E_out,
+// (all-zero for start 0, a hashed state otherwise), over the symmetric matrix
+// S (S_ij = S_ji = T_ij, n x n).  Lane l holds variable l (n <= 60 < 64) and
+// its field f_l = T_ll + the couplings with the set variables, so flipping l
+// changes E by +-f_l; the largest decrease is taken (lowest lane on ties)
+// until no flip lowers E.  Returns the local minimum's energy in E_out and
+// its variables (bit l = variable l) in xm_out, the same in every lane.
+__device__ inline void greedy_descent(const int32_t *S, int n, uint32_t start, int32_t &E_out,
                                       uint64_t &xm_out)
 {
     const int lane = int(threadIdx.x) % kWave;
+    const int l = lane < n ? lane : 0;
     uint32_t h = start * 0x9E3779B9u + uint32_t(lane) * 0x85EBCA6Bu;
     h ^= h >> 15;
     h *= 0xC2B2AE35u;
     h ^= h >> 13;
-    int x = (start != 0 && lane < n) ? int(h & 1u) : 0;
-    const uint64_t xm = __builtin_amdgcn_ballot_w64(x != 0);
-    int32_t f = 0, own = 0;   // field; sum of row l over the set j >= l
-    if (lane < n) {
-        f = T[lane * n + lane];
-        own = x ? T[lane * n + lane] : 0;
+    uint64_t xm = __builtin_amdgcn_ballot_w64(start != 0 && lane < n && (h & 1u));
+    const int32_t diag = S[l * n + l];
+    int32_t f = diag, own = diag;   // field; diagonal + couplings with the set j > l
+    if (xm) {
         for (int j = 0; j < n; j++) {
-            if (j == lane || !((xm >> j) & 1)) continue;
-            const int32_t c = j < lane ? T[j * n + lane] : T[lane * n + j];
+            const int32_t c = (((xm >> j) & 1) && j != lane) ? S[j * n + l] : 0;
             f += c;
-            if (x && j > lane) own += c;
+            own += j > lane ? c : 0;
         }
     }
-    int32_t E = int32_t(wave_sum64(own));
+    // partial sums of distinct entries of T: within the int32 bound
+    int32_t E = wave_sum(((xm >> lane) & 1) ? own : 0);
     for (int it = 0; it < 4 * n; it++) {
+        const bool x = (xm >> lane) & 1;
         const int32_t gain = lane < n ? (x ? -f : f) : INT32_MAX;
         // smallest gain (DPP minimum), lowest lane on ties
         const int32_t g = wave_min(gain);
         if (g >= 0) break;
         const int k = int(__builtin_ctzll(__builtin_amdgcn_ballot_w64(gain == g)));
-        const int32_t sgn = __shfl(x, k, kWave) ? -1 : 1;   // 1 -> 0 subtracts couplings
+        const int32_t c = S[k * n + l];
         E += g;
-        if (lane == k) x ^= 1;
-        else if (lane < n) f += sgn * (k < lane ? T[k * n + lane] : T[lane * n + k]);
+        if (lane != k) f += ((xm >> k) & 1) ? -c : c;   // 1 -> 0 subtracts couplings
+        xm ^= 1ull << k;
     }
     E_out = E;
-    xm_out = __builtin_amdgcn_ballot_w64(x != 0);
+    xm_out = xm;
 }
 
 }  // namespace qk

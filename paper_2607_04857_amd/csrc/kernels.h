@@ -2,16 +2,21 @@
 //
 // Layout in HBM per instance (all int32 unless noted; built by table_kernel):
 //   T   [n][n]        folded upper-triangular matrix (input of the table build)
-//   M   [A][2^B]      interaction rows M_int[v][s] = sum over set suffix bits t
-//                     of T[v][A+t] (Sec. II-C: M_int = Q_ps U_B^T), column s
-//                     stored at s = j*64 + lane so lane `lane` owns columns
-//                     {j*64 + lane}, j < 2^B/64 (column-wise split, Sec. III-C.2)
-//   EB  [2^B]         suffix energies E_s(U_B) (Sec. III-A, preprocessing 2)
-//                     Packed instances (tiers 4, 5) store 2^(B-1) words per row:
-//                     word c holds column c in its low 16 bits and column
-//                     c + 2^(B-1) (suffix variable A set) in its high 16
-//                     bits, EB biased by kPackBias in each half, so one
-//                     32-bit add moves both energies (see kPackSumLimit)
+//   ML  [2A][64]      lane parts of the interaction rows M_int[v][s] = sum over
+//                     set suffix bits t of T[v][A+t] (Sec. II-C: M_int =
+//                     Q_ps U_B^T).  Lane `lane` owns columns s = j*64 + lane,
+//                     j < MC (column-wise split, Sec. III-C.2), and the sum
+//                     over the six lowest suffix bits depends on the lane
+//                     only, the sum over the others on j only:
+//                     M_int[v][j*64 + lane] = ML[v][lane] + MH[v][j].
+//                     Rows A..2A-1 are the negated ones
+//   EB  [64 MC]       suffix energies E_s(U_B) (Sec. III-A, preprocessing 2)
+//                     Packed instances (tiers 4, 5) hold 2^(B-1) words: word c
+//                     holds column c in its low 16 bits and column c + 2^(B-1)
+//                     (suffix variable A set) in its high 16 bits, EB biased
+//                     by kPackBias in each half and ML, MH words the sums of
+//                     the two columns' parts (low + high 2^16, mod 2^32), so
+//                     one 32-bit add moves both energies (see kPackSumLimit)
 //   S   [A][64]       S[w][l] = T[min(l,w)][max(l,w)] for l != w < A, else 0:
 //                     the prefix couplings, one lane per variable
 //   K   [6][32]+[12]  (all instances' K tables are contiguous) tier-2 bound
@@ -26,7 +31,9 @@
 //                     table half for 16-step ones; 12 entries); then
 //                     SL[64][5]: SL[w][t] = coupling of prefix variable w
 //                     with the low variable A-1-t (0 when equal), so a flip
-//                     of w moves the low fields by scalar loads only
+//                     of w moves the low fields by scalar loads only; then
+//                     MH[2A][MC]: the column parts of the interaction rows
+//                     (see ML), read by scalar loads
 //   Qf  [n][n] fp32   caller's float32 Q (fp32 instances only, for rescoring)
 #pragma once
 
@@ -51,11 +58,13 @@ __host__ __device__ constexpr int kc2min_slot(int seg_steps, int tab, int h)
 {
     return seg_steps == 32 ? kKC2Min + tab : kKC2Min + 3 + 2 * tab + (h & 1);
 }
-constexpr int kKTable = kKBound + kLowLevels * kWave;  // + SL[w][t], t < kLowLevels
+constexpr int kMaxCols = 16;          // words per lane (MC) of the widest variant
 constexpr int kMaxVgprLevels = 12;    // at most Gray levels 0..11 keep their M_int row in VGPRs
 constexpr int32_t kNoEnergy = 1 << 30;  // above every energy the walk can meet
 constexpr int kMaxVars = 60;          // largest n the planner accepts
 constexpr int kMaxPrefixRows = 60 - 6;   // A = n - B <= 60 - 6
+constexpr int kKHigh = kKBound + kLowLevels * kWave;   // MH[2A][MC], after SL[w][t]
+constexpr int kKTable = kKHigh + 2 * kMaxPrefixRows * kMaxCols;
 // Packed walk (tiers 4 and 5, the int16 energies of Sec. IV-B "Data types"
 // at two per 32-bit word).  Word = (E_lo + c + kPackBias) + (E_hi + c +
 // kPackBias) 2^16 and a row word = m_lo + m_hi 2^16 (mod 2^32), with c the
@@ -89,7 +98,7 @@ struct PrepOut {
 
 struct Inst {
     const int32_t *T;
-    int32_t *M;
+    int32_t *ML;
     int32_t *EB;
     int32_t *S;
     int32_t *K;            // this instance's K table (kslot-th table of the K array)
@@ -105,7 +114,7 @@ struct Inst {
     int n, A, B, L;
     int direct;            // 1: no walk, direct evaluation of all 2^n states
     int kslot;             // index of the K table in the launch's K array
-    int packed;            // 1: M and EB in the packed 16-bit layout (tiers 4, 5)
+    int packed;            // 1: ML, MH and EB in the packed 16-bit layout (tiers 4, 5)
     int32_t pack_shift;    // c added to every chunk energy in EB and taken
                            // off the prefix energy: tiers 4, 5 make every
                            // E_sd + c a signed 16-bit value, the int32 walk
@@ -117,7 +126,7 @@ struct Inst {
     uint64_t n_items;      // item records of the instance (res[0 .. n_items), bitmap
                            // words bits[0 .. ceil(n_items / 32)))
     int32_t *gbest;        // best energy any wave has found for the instance
-                           // (kNoEnergy from the table build on)
+                           // (kNoEnergy in the uploaded image)
     const PrepOut *prep;   // device-prepared instance: its preparation (an error
                            // makes the walk skip all items), else null
 };
@@ -191,10 +200,11 @@ struct FinalRes {
 hipError_t launch_prepare(const void *dQ, int n, int is_fp32, int32_t *d_T, PrepOut *d_prep,
                           Inst *d_inst, hipStream_t stream);
 
-// Builds M, EB, S, K for every instance, clears each instance's item bitmap
-// and shared best, and zeroes n_counters item counters (for a device-prepared
-// instance whose preparation failed, the counters are set past every item).
-hipError_t launch_tables(const Inst *d_insts, int n_inst, int max_A, unsigned long long *d_counters,
+// Builds ML, EB, S, K for every instance, clears each instance's item bitmap,
+// lowers its shared best by greedy descents (over an uploaded kNoEnergy), and
+// zeroes n_counters item counters (for a device-prepared instance whose
+// preparation failed, the counters are set past every item).
+hipError_t launch_tables(const Inst *d_insts, int n_inst, unsigned long long *d_counters,
                          int n_counters, hipStream_t stream);
 
 // Persistent Gray walk over all items; `waves` resident wavefronts.  d_k is

@@ -17,9 +17,11 @@
 //  * the rows M_int[k] of the most frequently flipped Gray levels stay on
 //    chip: by default levels 0-2 and 5 in VGPRs and 3-4 in LDS (8 KB per
 //    wave), which fits 128 VGPRs and so four waves per SIMD; other variants
-//    keep 5, 6, 8 or 12 levels in VGPRs; higher levels are read from L2 when
-//    they flip (level 6 once per 128 steps; level 5, in the 5-level variants,
-//    once per 64);
+//    keep 5, 6, 8 or 12 levels in VGPRs; higher levels are formed when they
+//    flip (level 6 once per 128 steps; level 5, in the 5-level variants, once
+//    per 64) from the row's two parts: column j*64 + lane of a row is a sum
+//    over the lane's bits plus a sum over the bits of j, so a row is one load
+//    per lane, 2^B / 64 scalars and a three-operand add per word;
 //  * wavefronts take work items (2^L consecutive Gray steps of the prefix,
 //    the "straightforward" split of Sec. III-C.1 along the Gray index) from an
 //    atomic counter, one at a time; the grid is persistent;
@@ -49,178 +51,185 @@ namespace qk {
 // state's energy is a valid threshold for the walk (the state's own chunk
 // still passes it), and a local minimum of a dense QUBO is usually close to
 // the global one, so walk waves start with a near-final threshold.
-__device__ void seed_best(const Inst &I, int wave)
+__device__ void seed_best(const int32_t *S, int n, int32_t *gbest, int wave)
 {
     int32_t bestE = kNoEnergy;
     for (int rep = 0; rep < 2; rep++) {
         int32_t E;
         uint64_t xm;
-        greedy_descent(I.T, I.n, uint32_t(wave) * 2u + uint32_t(rep), E, xm);
+        greedy_descent(S, n, uint32_t(wave) * 2u + uint32_t(rep), E, xm);
         bestE = min(bestE, E);
     }
-    if (int(threadIdx.x) % kWave == 0) atomicMin(I.gbest, bestE);
+    if (int(threadIdx.x) % kWave == 0) atomicMin(gbest, bestE);
 }
 
-__global__ __launch_bounds__(256) void tables_kernel(const Inst *__restrict__ insts,
-                                                     unsigned long long *__restrict__ counters,
-                                                     int n_counters)
+// One block per (instance, part of its tables), blockIdx.x naming the part.
+// Every part stages T in LDS first, as the symmetric matrix: everything below
+// is sums of a few entries, so what bounds the build is latency, and no part
+// waits for another.  M_int is never formed: its lane and column parts (ML,
+// MH) are, and the bound constants have closed forms over the suffix bits.
+// Measured: a lone build 9-16 us and 4096 batch instances 132 us; 60-92 us and
+// 950 us when 8 blocks per instance wrote the whole M_int (2A x 2^B words) and
+// reduced the bound constants over its columns.
+enum { kPartSeed = 0, kPartK, kPartEB, kPartRows, kTableParts };
+constexpr int kTableThreads = 256;
+
+__global__ __launch_bounds__(kTableThreads) void tables_kernel(
+    const Inst *__restrict__ insts, unsigned long long *__restrict__ counters, int n_counters)
 {
+    __shared__ int32_t sS[kMaxVars * kMaxVars];   // T made symmetric
     const Inst I = insts[blockIdx.y];
-    if (blockIdx.x == 0 && blockIdx.y == 0) {
+    const int part = int(blockIdx.x);
+    const int tid = int(threadIdx.x);
+    if (part == kPartSeed && blockIdx.y == 0) {
         // a device-prepared instance whose input was refused walks no item
         const unsigned long long c0 = (I.prep && I.prep->status != 0) ? (1ull << 62) : 0ull;
-        for (int c = int(threadIdx.x); c < n_counters; c += int(blockDim.x)) counters[c] = c0;
+        for (int c = tid; c < n_counters; c += kTableThreads) counters[c] = c0;
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0 && I.gbest) {
-        atomicExch(I.gbest, kNoEnergy);
-        __threadfence();
-    }
-    if (I.bits) {   // no item has reported yet
+    if (part == kPartRows && I.bits) {   // no item has reported yet
         const uint64_t words = (I.n_items + 31) / 32;
-        for (uint64_t w = uint64_t(blockIdx.x) * blockDim.x + threadIdx.x; w < words;
-             w += uint64_t(gridDim.x) * blockDim.x)
-            I.bits[w] = 0u;
+        for (uint64_t w = uint64_t(tid); w < words; w += kTableThreads) I.bits[w] = 0u;
     }
     if (I.direct) return;
     const int n = I.n, A = I.A, B = I.B;
-    const uint32_t NS = 1u << B;
-    const uint32_t tid = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t stride = gridDim.x * blockDim.x;
-    const int32_t *T = I.T;
-    // M_int[v][s] = sum over the set suffix bits t of s of T[v][A + t]
-    // (Sec. II-C; bit t of the suffix row is (s >> (B-1-t)) & 1), as the sum
-    // of two partial sums built first in LDS: part[v][s & 31] over the five
-    // lowest bits of s and part[v][32 + (s >> 5)] over the others (B <= 11).
-    constexpr int kPartW = 32 + 64;
-    __shared__ int32_t part[kMaxPrefixRows][kPartW];
-    const uint32_t pw = 32u + (NS >> 5);
-    for (uint32_t e = threadIdx.x; e < uint32_t(A) * pw; e += blockDim.x) {
-        const int v = int(e / pw), x = int(e % pw);
-        int32_t acc = 0;
-        if (x < 32) {
-            for (int u = 0; u < 5; u++)
-                if ((x >> u) & 1) acc += T[v * n + A + B - 1 - u];
-        } else {
-            const int hi = x - 32;
-            for (int u = 0; u < B - 5; u++)
-                if ((hi >> u) & 1) acc += T[v * n + A + B - 6 - u];
-        }
-        part[v][x] = acc;
+    for (int e = tid; e < n * n; e += kTableThreads) {
+        const int i = e / n, j = e % n;
+        if (i > j) continue;
+        const int32_t t = I.T[e];
+        sS[e] = t;
+        sS[j * n + i] = t;
     }
     __syncthreads();
-    auto mval = [&](int v, uint32_t s) { return part[v][s & 31u] + part[v][32u + (s >> 5)]; };
-    // E_s(U_B)[s] = sum_{t <= u, both set} T[A+t][A+u] (Sec. III-A, step 2)
-    auto esuf = [&](uint32_t s) {
-        int32_t acc = 0;
-        for (int t = 0; t < B; t++) {
-            if (!((s >> (B - 1 - t)) & 1u)) continue;
-            for (int u = t; u < B; u++)
-                if ((s >> (B - 1 - u)) & 1u) acc += T[(A + t) * n + A + u];
+    const int MC = 1 << (I.packed ? B - 7 : B - 6);   // words per lane
+    // Packed words: a part x shared by both columns is x in each half, and
+    // the high column (c + 2^(B-1)) also has suffix variable A set.
+    auto both = [&](int32_t x) { return I.packed ? uint32_t(x) * 0x10001u : uint32_t(x); };
+
+    if (part == kPartSeed) {
+        // (only when the walk covers every state: a restricted item range must
+        // not start from an energy found outside it)
+        if (I.gbest && I.item_local0 == 0 && I.n_items == (uint64_t(1) << (A - I.L)))
+            seed_best(sS, n, I.gbest, tid / kWave);
+    } else if (part == kPartRows) {
+        for (int e = tid; e < A * kWave; e += kTableThreads) {
+            const int v = e / kWave, l = e % kWave;
+            // the six lowest suffix bits of column j*64 + l are those of l:
+            // bit u is suffix variable n-1-u
+            int32_t m = 0;
+#pragma unroll
+            for (int u = 0; u < 6; u++) m += -((l >> u) & 1) & sS[v * n + n - 1 - u];
+            const uint32_t w = both(m);
+            I.ML[e] = int32_t(w);
+            I.ML[A * kWave + e] = int32_t(0u - w);
+            // prefix couplings, one lane per variable
+            const int32_t c = (l < A && l != v) ? sS[v * n + l] : 0;
+            I.S[e] = c;
+            I.S[A * kWave + e] = -c;
         }
-        return acc;
-    };
-    // rows A..2A-1 hold -M_int: a flip whose direction is known only at
-    // run time then adds one row or the other, without a branch.  Packed:
-    // word c of a row is m(c) + m(c + NW) 2^16 and its negation the
-    // negated word (both mod 2^32, the packed map being additive).
-    const int lw = I.packed ? B - 1 : B;
-    const uint32_t NW = 1u << lw;   // words per row
-    for (uint32_t e = tid; e < uint32_t(A) * NW; e += stride) {
-        const int v = int(e >> lw);
-        const uint32_t c = e & (NW - 1);
-        uint32_t m = uint32_t(mval(v, c));
-        if (I.packed) m += uint32_t(mval(v, c + NW)) << 16;
-        I.M[e] = int32_t(m);
-        I.M[uint32_t(A) * NW + e] = int32_t(0u - m);
-    }
-    for (uint32_t c = tid; c < NW; c += stride) {
-        if (I.packed) {
-            const int32_t b = I.pack_shift + kPackBias;
-            I.EB[c] = int32_t(uint32_t(esuf(c) + b) + (uint32_t(esuf(c + NW) + b) << 16));
+    } else if (part == kPartEB) {
+        // E_s(U_B)[s] = sum_{t <= u, both set} T[A+t][A+u] (Sec. III-A, step
+        // 2), s = tid + 256 hp: the low eight bits' energy and their fields
+        // on the (at most three) high variables once per thread, then one
+        // sum per high pattern hp.  Bit b of s is variable n-1-b.
+        int32_t base = 0, h[3] = {0, 0, 0}, hh[3][3];
+#pragma unroll
+        for (int b = 0; b < 8; b++) {
+            const int32_t mb = -((tid >> b) & 1);
+            int32_t row = sS[(n - 1 - b) * n + n - 1 - b];
+#pragma unroll
+            for (int c = 0; c < b; c++) row += -((tid >> c) & 1) & sS[(n - 1 - b) * n + n - 1 - c];
+            base += mb & row;
         }
-        else
-            I.EB[c] = esuf(c) + I.pack_shift;
-    }
-    // prefix couplings, one lane per variable
-    for (uint32_t e = tid; e < uint32_t(A) * kWave; e += stride) {
-        const int w = int(e / kWave), l = int(e % kWave);
-        int32_t v = 0;
-        if (l < A && l != w) v = (l < w) ? T[l * n + w] : T[w * n + l];
-        I.S[e] = v;
-        I.S[uint32_t(A) * kWave + e] = -v;   // negated rows, as for M_int
-    }
-    if (blockIdx.x != 0) return;
-    __syncthreads();
-    // (only when the walk covers every state: a restricted item range must
-    // not start from an energy found outside it)
-    if (I.gbest && I.item_local0 == 0 && I.n_items == (uint64_t(1) << (A - I.L)))
-        seed_best(I, int(threadIdx.x) / kWave);
-    for (uint32_t e = threadIdx.x; e < uint32_t(A) * kLowLevels; e += blockDim.x) {
-        const int w = int(e / kLowLevels), t = int(e % kLowLevels), l = A - 1 - t;
-        int32_t v = 0;
-        if (l != w) v = (l < w) ? T[l * n + w] : T[w * n + l];
-        I.K[kKBound + e] = v;
-    }
-    // Tier-2 bound constants.  Inside a 64-step super-block the five lowest
-    // Gray levels follow the static pattern p(o) = g(o) & 31 from 0, and the
-    // level-5 bit moves once (by cm = +-1) at o = 32, so
-    //   E_sd(o) - E_sd(0) = sum_{t<5} p_t(o) M[A-1-t] + [o >= 32] cm M[A-6].
-    // D = its minimum over all 2^B columns, a lower bound of how far the
-    // chunk minimum can fall from its value at the super-block start.
-    // All 96 (table, offset) minima at once: per-thread minima over the
-    // thread's columns, wave minima by shuffles, one exchange through LDS.
-    constexpr int NQ = 3 * kPatterns;
-    __shared__ int32_t red[256 / kWave][NQ];
-    __shared__ int32_t c2s[NQ];
-    constexpr int kCols = 2048 / 256;  // columns per thread (B <= 11)
-    int32_t mcol[kCols][kLowLevels + 1];   // M rows of levels 0..kLowLevels at this thread's columns
-    for (int k = 0; k < kCols; k++) {
-        const uint32_t col = threadIdx.x + 256u * uint32_t(k);
-        for (int t = 0; t <= kLowLevels; t++)
-            mcol[k][t] = col < NS ? part[A - 1 - t][col & 31u] + part[A - 1 - t][32u + (col >> 5)] : 0;
-    }
-    const int wl = int(threadIdx.x) % kWave, wv = int(threadIdx.x) / kWave;
-    for (int q = 0; q < NQ; q++) {
-        const int tab = q / kPatterns, oo = q % kPatterns;
-        const int cm = tab == 0 ? 0 : (tab == 1 ? 1 : -1);
-        const int o = tab == 0 ? oo : kPatterns + oo;
-        const int pat = (o ^ (o >> 1)) & (kPatterns - 1);
-        int32_t mn = INT32_MAX;
-        for (int k = 0; k < kCols; k++) {
-            if (threadIdx.x + 256u * uint32_t(k) >= NS) continue;
-            int32_t v = cm * mcol[k][kLowLevels];
+#pragma unroll
+        for (int x = 0; x < 3; x++) {
+            const int r = n - 1 - (8 + x);   // n > 14: a row of T either way
+            h[x] = sS[r * n + r];
+#pragma unroll
+            for (int b = 0; b < 8; b++) h[x] += -((tid >> b) & 1) & sS[r * n + n - 1 - b];
+#pragma unroll
+            for (int y = 0; y < x; y++) hh[x][y] = sS[r * n + n - 1 - (8 + y)];
+        }
+        auto esuf = [&](int hp) {
+            int32_t e = base;
+#pragma unroll
+            for (int x = 0; x < 3; x++) {
+                if (!((hp >> x) & 1)) continue;
+                e += h[x];
+#pragma unroll
+                for (int y = 0; y < x; y++)
+                    if ((hp >> y) & 1) e += hh[x][y];
+            }
+            return e;
+        };
+        const int NW = MC * kWave;
+        for (int c = tid; c < NW; c += kTableThreads) {
+            const int hp = c >> 8;
+            if (I.packed) {
+                const int32_t b = I.pack_shift + kPackBias;
+                I.EB[c] = int32_t(uint32_t(esuf(hp) + b) +
+                                  (uint32_t(esuf(hp + (1 << (B - 9))) + b) << 16));
+            } else {
+                I.EB[c] = esuf(hp) + I.pack_shift;
+            }
+        }
+    } else {
+        for (int e = tid; e < A * kLowLevels; e += kTableThreads) {
+            const int w = e / kLowLevels, l = A - 1 - e % kLowLevels;
+            I.K[kKBound + e] = l != w ? sS[w * n + l] : 0;
+        }
+        // column parts of M_int: bit u of j is suffix variable n-7-u
+        for (int e = tid; e < A * MC; e += kTableThreads) {
+            const int v = e / MC, j = e % MC;
+            int32_t m = 0;
+            for (int u = 0; (MC >> u) > 1; u++) m += -((j >> u) & 1) & sS[v * n + n - 7 - u];
+            uint32_t w = both(m);
+            if (I.packed) w += uint32_t(sS[v * n + A]) << 16;
+            I.K[kKHigh + e] = int32_t(w);
+            I.K[kKHigh + A * MC + e] = int32_t(0u - w);
+        }
+        // Tier-2 bound constants.  Inside a 64-step super-block the five lowest
+        // Gray levels follow the static pattern p(o) = g(o) & 31 from 0, and the
+        // level-5 bit moves once (by cm = +-1) at o = 32, so
+        //   E_sd(o) - E_sd(0) = sum_{t<5} p_t(o) M[A-1-t] + [o >= 32] cm M[A-6].
+        // D = its minimum over all 2^B columns, a lower bound of how far the
+        // chunk minimum can fall from its value at the super-block start.  In
+        // column s the difference is the sum over the set suffix bits u of
+        //   c_u = sum_{t<5} p_t(o) T[A-1-t][A+u] + [o >= 32] cm T[A-6][A+u],
+        // so its minimum over the columns is sum_u min(0, c_u).
+        constexpr int NQ = 3 * kPatterns;
+        __shared__ int32_t c2s[NQ];
+        if (tid < NQ) {
+            const int q = tid, tab = q / kPatterns, oo = q % kPatterns;
+            const int cm = tab == 0 ? 0 : (tab == 1 ? 1 : -1);
+            const int o = tab == 0 ? oo : kPatterns + oo;
+            const int pat = (o ^ (o >> 1)) & (kPatterns - 1);
+            int32_t d = 0;
+            for (int u = A; u < n; u++) {
+                int32_t c = cm * sS[(A - 1 - kLowLevels) * n + u];
+#pragma unroll
+                for (int t = 0; t < kLowLevels; t++) c += -((pat >> t) & 1) & sS[(A - 1 - t) * n + u];
+                d += min(0, c);
+            }
+            int32_t elow = 0;   // couplings among the set low variables
+#pragma unroll
             for (int t = 0; t < kLowLevels; t++)
-                if ((pat >> t) & 1) v += mcol[k][t];
-            mn = min(mn, v);
+#pragma unroll
+                for (int u = t + 1; u < kLowLevels; u++)
+                    elow += -((pat >> t) & (pat >> u) & 1) & sS[(A - 1 - u) * n + (A - 1 - t)];
+            I.K[(3 + tab) * kPatterns + oo] = d;
+            I.K[tab * kPatterns + oo] = elow + d;
+            c2s[q] = elow + d;
         }
-        mn = wave_min(mn);
-        if (wl == 0) red[wv][q] = mn;
+        __syncthreads();
+        if (tid < 9) {   // min of C2 over each bound-test segment (kc2min_slot)
+            const int tab = tid < 3 ? tid : (tid - 3) / 2;
+            const int lo = tid < 3 ? 0 : ((tid - 3) % 2) * 16, hi = tid < 3 ? kPatterns : lo + 16;
+            int32_t m = INT32_MAX;
+            for (int oo = lo; oo < hi; oo++) m = min(m, c2s[tab * kPatterns + oo]);
+            I.K[kKC2Min + tid] = m;
+        }
+        if (tid >= 9 && tid < 12) I.K[kKC2Min + tid] = 0;
     }
-    __syncthreads();
-    if (int(threadIdx.x) < NQ) {
-        const int q = int(threadIdx.x), tab = q / kPatterns, oo = q % kPatterns;
-        const int o = tab == 0 ? oo : kPatterns + oo;
-        const int pat = (o ^ (o >> 1)) & (kPatterns - 1);
-        int32_t d = red[0][q];
-        for (int w = 1; w < 256 / kWave; w++) d = min(d, red[w][q]);
-        int32_t elow = 0;   // couplings among the set low variables
-        for (int t = 0; t < kLowLevels; t++)
-            for (int u = t + 1; u < kLowLevels; u++)
-                if (((pat >> t) & 1) && ((pat >> u) & 1)) elow += T[(A - 1 - u) * n + (A - 1 - t)];
-        I.K[(3 + tab) * kPatterns + oo] = d;
-        I.K[tab * kPatterns + oo] = elow + d;
-        c2s[q] = elow + d;
-    }
-    __syncthreads();
-    if (threadIdx.x < 9) {   // min of C2 over each bound-test segment (kc2min_slot)
-        const int x = int(threadIdx.x);
-        const int tab = x < 3 ? x : (x - 3) / 2;
-        const int lo = x < 3 ? 0 : ((x - 3) % 2) * 16, hi = x < 3 ? kPatterns : lo + 16;
-        int32_t m = INT32_MAX;
-        for (int oo = lo; oo < hi; oo++) m = min(m, c2s[tab * kPatterns + oo]);
-        I.K[kKC2Min + x] = m;
-    }
-    if (threadIdx.x >= 9 && threadIdx.x < 12) I.K[kKC2Min + threadIdx.x] = 0;
 }
 
 // ---------------------------------------------------------------- prepare
@@ -553,16 +562,11 @@ hipError_t launch_prepare(const void *dQ, int n, int is_fp32, int32_t *d_T, Prep
     return hipGetLastError();
 }
 
-hipError_t launch_tables(const Inst *d_insts, int n_inst, int max_A, unsigned long long *d_counters,
+hipError_t launch_tables(const Inst *d_insts, int n_inst, unsigned long long *d_counters,
                          int n_counters, hipStream_t stream)
 {
-    // a few blocks per instance: each builds the partial sums it needs, so
-    // more blocks mostly add scheduling work (4096-instance batches)
-    int bx = (max_A * 1024 + 4095) / 4096;
-    if (bx < 1) bx = 1;
-    if (bx > 8) bx = 8;
-    hipLaunchKernelGGL(tables_kernel, dim3(bx, n_inst), dim3(256), 0, stream, d_insts, d_counters,
-                       n_counters);
+    hipLaunchKernelGGL(tables_kernel, dim3(kTableParts, n_inst), dim3(kTableThreads), 0, stream,
+                       d_insts, d_counters, n_counters);
     return hipGetLastError();
 }
 

@@ -20,7 +20,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 struct JobOffsets {
     size_t insts = 0, counter = 0, res = 0, out = 0, K = 0, gbest = 0, prep = 0;
-    std::vector<size_t> T, Qf, M, EB, S, bits;
+    std::vector<size_t> T, Qf, ML, EB, S, bits;
     // top-k (k > 1, one instance)
     size_t gthr = 0, hist = 0, lowbin = 0, candN = 0, candE = 0, candR = 0, listE = 0, listR = 0, listCount = 0, chunkE = 0, chunkR = 0, chunkCount = 0,
            stE = 0, stI = 0, segCount = 0, selE = 0, selR = 0, selCount = 0, topk = 0;
@@ -81,6 +81,8 @@ static JobOffsets compute_offsets(const Job &job, size_t *stage_bytes, size_t *b
             o.Qf.push_back(size_t(-1));
         }
     }
+    o.gbest = off;   // the shared bests start at kNoEnergy in the uploaded image
+    off = align_up(off + ni * sizeof(int32_t), 256);
     const size_t k = size_t(job.topk);
     if (k > 1) {   // the shared top-k bound and histogram start in the uploaded image
         o.gthr = off;
@@ -97,12 +99,12 @@ static JobOffsets compute_offsets(const Job &job, size_t *stage_bytes, size_t *b
     off = align_up(off + std::max<size_t>(1, job.groups.size()) * sizeof(unsigned long long), 256);
     for (size_t i = 0; i < ni; i++) {
         const qplan::Plan &P = job.plans[i];
-        // words per M_int row: 2^B, or 2^(B-1) packed (two columns a word)
-        const size_t A = P.direct ? 0 : size_t(P.A),
-                     NS = P.direct ? 0 : (size_t(1) << (P.tier >= 4 ? P.B - 1 : P.B));
-        // M_int and the prefix couplings, each followed by its negation
-        o.M.push_back(off);
-        off = align_up(off + 2 * A * NS * sizeof(int32_t), 256);
+        // words per chunk vector: 2^B, or 2^(B-1) packed (two columns a word)
+        const size_t A = P.direct ? 0 : size_t(P.A), NS = size_t(P.mcols) * qk::kWave;
+        // the lane parts of M_int and the prefix couplings, each followed by
+        // its negation
+        o.ML.push_back(off);
+        off = align_up(off + 2 * A * qk::kWave * sizeof(int32_t), 256);
         o.EB.push_back(off);
         off = align_up(off + NS * sizeof(int32_t), 256);
         o.S.push_back(off);
@@ -121,8 +123,6 @@ static JobOffsets compute_offsets(const Job &job, size_t *stage_bytes, size_t *b
     }
     o.out = off;
     off = align_up(off + ni * sizeof(qk::FinalRes), 256);
-    o.gbest = off;
-    off = align_up(off + ni * sizeof(int32_t), 256);
     o.prep = off;
     off = align_up(off + sizeof(qk::PrepOut), 256);
     if (k > 1) {
@@ -160,7 +160,6 @@ bool same_variant(const qplan::Plan &a, const qplan::Plan &b)
 
 qubo_status_t job_layout(Job *job, int waves_per_cu)
 {
-    job->max_A = 0;
     job->total_items = 0;
     job->states = 0.0;
     job->groups.clear();
@@ -187,7 +186,6 @@ qubo_status_t job_layout(Job *job, int waves_per_cu)
         WalkGroup &g = job->groups.back();
         g.count = int(i) + 1 - g.first;
         g.items += P.walk_items();
-        if (P.A > job->max_A) job->max_A = P.A;
         job->total_items += P.walk_items();
     }
     if (job->topk > 1 && (job->plans.size() != 1 ||
@@ -240,7 +238,7 @@ qubo_status_t job_bind(Job *job, void *d_mem)
         const qplan::Plan &P = job->plans[i];
         qk::Inst &I = insts[i];
         I.T = reinterpret_cast<const int32_t *>(base + o.T[i]);
-        I.M = reinterpret_cast<int32_t *>(base + o.M[i]);
+        I.ML = reinterpret_cast<int32_t *>(base + o.ML[i]);
         I.EB = reinterpret_cast<int32_t *>(base + o.EB[i]);
         I.S = reinterpret_cast<int32_t *>(base + o.S[i]);
         I.K = reinterpret_cast<int32_t *>(base + o.K) + i * qk::kKTable;
@@ -274,6 +272,8 @@ qubo_status_t job_bind(Job *job, void *d_mem)
         if (job->qf[i]) std::memcpy(job->stage.data() + o.Qf[i], job->qf[i], nn * sizeof(float));
     }
     std::memcpy(job->stage.data() + o.insts, insts.data(), insts.size() * sizeof(qk::Inst));
+    std::fill_n(reinterpret_cast<int32_t *>(job->stage.data() + o.gbest), insts.size(),
+                qk::kNoEnergy);
     if (job->topk > 1) {
         const int32_t none = qk::kNoEnergy, nobin = qk::kTopkBins;
         std::memcpy(job->stage.data() + o.gthr, &none, sizeof(none));
@@ -320,8 +320,7 @@ qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, hipEvent_t
         QRT_HIP(qk::launch_prepare(job.dq, job.plans[0].n, job.plans[0].dtype == QUBO_FP32 ? 1 : 0,
                                    job.d_T0, job.d_prep, job.d_insts, stream),
                 "prepare kernel");
-    QRT_HIP(qk::launch_tables(job.d_insts, ni, job.max_A, job.d_counter, int(job.groups.size()),
-                              stream),
+    QRT_HIP(qk::launch_tables(job.d_insts, ni, job.d_counter, int(job.groups.size()), stream),
             "tables kernel");
     if (walk_begin) QRT_HIP(hipEventRecord(walk_begin, stream), "hipEventRecord");
     if (job.topk > 1) {

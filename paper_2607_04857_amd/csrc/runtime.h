@@ -45,7 +45,6 @@ struct Job {
     std::vector<qplan::Plan> plans;
     std::vector<const float *> qf;       // caller's fp32 Q per instance (host) or null
     std::vector<WalkGroup> groups;
-    int max_A = 0;
     uint64_t total_items = 0;
     double states = 0.0;                 // sum of 2^n
 

@@ -204,14 +204,12 @@ qubo_status_t setup_request(qubo_server *s, Request *r)
 qubo_status_t build_tables(qubo_server *s, const std::vector<Request *> &adm)
 {
     if (adm.empty()) return QUBO_OK;
-    int max_A = 0;
     for (size_t k = 0; k < adm.size(); k++) {
         QRT_HIP(hipMemcpyAsync(s->d_setup + k, adm[k]->job.d_insts, sizeof(qk::Inst),
                                hipMemcpyDeviceToDevice, s->stream),
                 "hipMemcpyAsync descriptor");
-        max_A = std::max(max_A, adm[k]->job.max_A);
     }
-    QRT_HIP(qk::launch_tables(s->d_setup, int(adm.size()), max_A, nullptr, 0, s->stream),
+    QRT_HIP(qk::launch_tables(s->d_setup, int(adm.size()), nullptr, 0, s->stream),
             "tables kernel");
     return QUBO_OK;
 }

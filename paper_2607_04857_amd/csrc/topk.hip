@@ -275,6 +275,11 @@ __global__ __launch_bounds__(256) void topk_rescan_kernel(const Inst *__restrict
             stI[p] = (row << B) | s;
         }
     };
+    // word c of M_int's row v, NW words a row, from its lane and column parts
+    auto mrow = [&](int v, uint32_t c, uint32_t NW) {
+        return I.ML[uint32_t(v) * kWave + c % kWave] +
+               I.K[kKHigh + uint32_t(v) * (NW / kWave) + c / kWave];
+    };
     // NS (and NS / 2) is a multiple of 64: every lane of a wave that enters
     // runs each pass
     if (I.packed) {
@@ -285,7 +290,7 @@ __global__ __launch_bounds__(256) void topk_rescan_kernel(const Inst *__restrict
         for (uint32_t c = threadIdx.x; c < NW; c += blockDim.x) {
             uint32_t w = uint32_t(I.EB[c]);
             for (int v = 0; v < A; v++)
-                if ((row >> (A - 1 - v)) & 1) w += uint32_t(I.M[uint32_t(v) * NW + c]);
+                if ((row >> (A - 1 - v)) & 1) w += uint32_t(mrow(v, c, NW));
             offer(Ep + int32_t(w & 0xffffu) - off, c);
             offer(Ep + int32_t(w >> 16) - off, c + NW);
         }
@@ -293,7 +298,7 @@ __global__ __launch_bounds__(256) void topk_rescan_kernel(const Inst *__restrict
         for (uint32_t s = threadIdx.x; s < NS; s += blockDim.x) {
             int32_t e = Ep - I.pack_shift + I.EB[s];   // E_s carries the walk's shift
             for (int v = 0; v < A; v++)
-                if ((row >> (A - 1 - v)) & 1) e += I.M[uint32_t(v) * NS + s];
+                if ((row >> (A - 1 - v)) & 1) e += mrow(v, s, NS);
             offer(e, s);
         }
     }
@@ -417,8 +422,8 @@ __global__ __launch_bounds__(kSeedThreads) void topk_seed_kernel(const Inst *__r
 {
     const Inst &I = *inst;
     const int n = I.n, A = I.A;
-    const int32_t *T = I.T;
     const int tid = int(threadIdx.x), lane = tid % kWave, wave = tid / kWave;
+    __shared__ int32_t T[kMaxVars * kMaxVars];   // T made symmetric
     __shared__ int32_t wE[kSeedThreads / kWave];
     __shared__ uint64_t wX[kSeedThreads / kWave];
     __shared__ int32_t d[kWave];
@@ -428,6 +433,14 @@ __global__ __launch_bounds__(kSeedThreads) void topk_seed_kernel(const Inst *__r
     __shared__ uint64_t sXm;
     __shared__ uint32_t sCount;
 
+    for (int e = tid; e < n * n; e += kSeedThreads) {
+        const int i = e / n, j = e % n;
+        if (i > j) continue;
+        const int32_t t = I.T[e];
+        T[e] = t;
+        T[j * n + i] = t;
+    }
+    __syncthreads();
     // 1. the best local minimum of eight descents (two per wave)
     int32_t bE = kNoEnergy;
     uint64_t bX = 0;
@@ -463,7 +476,7 @@ __global__ __launch_bounds__(kSeedThreads) void topk_seed_kernel(const Inst *__r
         const int xl = int((xm >> tid) & 1);
         int32_t f = T[tid * n + tid];
         for (int j = 0; j < n; j++)
-            if (j != tid && ((xm >> j) & 1)) f += j < tid ? T[j * n + tid] : T[tid * n + j];
+            if (j != tid && ((xm >> j) & 1)) f += T[j * n + tid];
         d[tid] = xl ? -f : f;
         sg[tid] = xl ? -1 : 1;
     }

@@ -304,8 +304,8 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
     constexpr int NSEG = (1 << kSuperLog) / SEG;
     const int lane = int(threadIdx.x);
     const uint32_t ulane = threadIdx.x;
-    // row v of a lane-major [rows][MC*64] table: uniform base pointer
-    auto trow = [](const gint32 *t, int v) { return t + size_t(v) * (MC * kWave); };
+    // log2 of the words per lane, and the suffix bits of a chunk
+    constexpr int JB = cx_ctz(MC), B = JB + (PK ? 7 : 6);
     // this lane's chunk minimum (packed: over both halves of every word)
     auto lane_min = [](const int32_t(&e)[MC]) {
         if constexpr (PK) return tree_min_packed<MC>(e);
@@ -318,8 +318,14 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
     int cur = -1;
     // the tables, addressed as global memory (uniform base + lane offset +
     // immediate), not through generic pointers
-    const gint32 *M = nullptr, *EB = nullptr, *S = nullptr;
+    const gint32 *ML = nullptr, *EB = nullptr, *S = nullptr;
     int kbase = 0;                // this instance's K table: kall[kbase ...] (scalar loads)
+    // word j of this lane in M_int's (signed) row v: its lane part, one load
+    // per lane, plus its column part, a scalar load
+    auto lrow = [&](int v) { return ML[v * kWave + ulane]; };
+    auto hrow = [&](int v) {
+        return *reinterpret_cast<const ivec<MC> *>(kall + (kbase + kKHigh + v * MC));
+    };
     int A = 0, L = 0;
     uint64_t item_begin = 0, item_local0 = 0;
     int32_t R[G][MC];        // M_int rows of Gray levels 0..G-1 (variable A-1-t)
@@ -350,7 +356,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         if (lo != cur) {
             cur = lo;
             const Inst &I = insts[lo];
-            M = to_global(I.M);
+            ML = to_global(I.ML);
             EB = to_global(I.EB);
             S = to_global(I.S);
             kbase = I.kslot * kKTable;
@@ -362,15 +368,17 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
                 constexpr int t = decltype(tc)::value;
                 const bool have = t < A;
                 const int v = have ? A - 1 - t : 0;
+                const int32_t ml = lrow(v);
+                const ivec<MC> mh = hrow(v);
                 if constexpr (LR && (t == 3 || t == 4)) {
                     // each lane writes and later reads only its own columns
 #pragma unroll
                     for (int j = 0; j < MC; j++)
                         ldsR[(t - 3) * (MC * kWave) + j * kWave + lane] =
-                            have ? trow(M, v)[j * kWave + ulane] : 0;
+                            have ? ml + mh[j] : 0;
                 } else {
 #pragma unroll
-                    for (int j = 0; j < MC; j++) R[t][j] = have ? trow(M, v)[j * kWave + ulane] : 0;
+                    for (int j = 0; j < MC; j++) R[t][j] = have ? ml + mh[j] : 0;
                 }
             });
             Smid = S[size_t(A - 1 - kLowLevels) * kWave + ulane];
@@ -429,25 +437,66 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         const uint64_t sbEnd = sb0 + (1ull << (L - kSuperLog));
         const uint64_t row0 = i0 ^ (i0 >> 1);
 
-        int32_t E[MC];
-#pragma unroll
-        for (int j = 0; j < MC; j++) E[j] = EB[j * kWave + ulane];
-        for (int v = 0; v < A; v++) {
-            if ((row0 >> (A - 1 - v)) & 1) {
-#pragma unroll
-                for (int j = 0; j < MC; j++) E[j] += trow(M, v)[j * kWave + ulane];
+        // (Loads are masked, not branched over, so that they are in flight
+        // together; reading the set bits' rows one after another had cost a
+        // dependent L2 round trip each: 274 -> 248 us for an n = 33 walk.)
+        // Chunk vector E_s + x_p M_int: M_int[v][s] sums T[v][A+t] over the set
+        // suffix bits t of s, so x_p M_int[s] sums, over the same bits, the
+        // suffix fields h_t = sum over the set prefix variables v of
+        // T[v][A+t].  Lane 16 q + t adds up the rows v = q (mod 4).
+        int32_t h = 0;
+        {
+            const gint32 *T = to_global(Tm);
+            const int t = lane & 15;
+#pragma unroll 4
+            for (int v0 = 0; v0 < A; v0 += 4) {
+                const int v = v0 + (lane >> 4);
+                const bool on = t < B && v < A && ((row0 >> ((A - 1 - v) & 63)) & 1);
+                const int32_t x = T[on ? v * nT + A + t : 0];
+                h += on ? x : 0;
             }
+            h += __shfl_xor(h, 16, kWave);
+            h += __shfl_xor(h, 32, kWave);
+        }
+        int32_t E[MC];
+        {
+            uint32_t lsum = 0;   // over the six bits of the lane
+            static_for<0, 6>([&](auto uc) {
+                constexpr int u = decltype(uc)::value;
+                lsum += uint32_t(-((lane >> u) & 1) & __builtin_amdgcn_readlane(h, B - 1 - u));
+            });
+            uint32_t hsum[MC];   // over the bits of j
+            hsum[0] = 0;
+            static_for<1, MC>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                hsum[j] = hsum[j & (j - 1)] +
+                          uint32_t(__builtin_amdgcn_readlane(h, B - 7 - cx_ctz(j)));
+            });
+            // packed: both columns of a word, the high one with variable A set
+            const uint32_t top = PK ? uint32_t(__builtin_amdgcn_readlane(h, 0)) << 16 : 0u;
+            if constexpr (PK) lsum *= 0x10001u;
+            static_for<0, MC>([&](auto jc) {
+                constexpr int j = decltype(jc)::value;
+                const uint32_t hj = PK ? hsum[j] * 0x10001u + top : hsum[j];
+                E[j] = int32_t(uint32_t(EB[j * kWave + ulane]) + lsum + hj);
+            });
         }
         // F: field of every prefix variable from the non-low ones (levels >=
         // kLowLevels, variables 0..A-1-kLowLevels), plus its diagonal; one
-        // lane per variable.
-        const int32_t diagl = lane < A ? Tm[lane * nT + lane] : 0;   // T[l][l], lane l < A
-        int32_t F = diagl;
-        for (int w = 0; w <= A - 1 - kLowLevels; w++)
-            if ((row0 >> (A - 1 - w)) & 1) F += S[size_t(w) * kWave + ulane];
-        // E_nl = energy of the non-low prefix bits = (sum_set F_w + T_ww) / 2
+        // lane per variable.  own: the part from the variables before it, so
+        // that the energy E_nl of the non-low prefix bits is the sum of own
+        // over the set ones (a partial sum of T at every point).
+        int32_t F = lane < A ? Tm[lane * nT + lane] : 0;   // T[l][l], lane l < A
+        int32_t own = F;
+#pragma unroll 4
+        for (int w = 0; w <= A - 1 - kLowLevels; w++) {
+            const int32_t on = -int32_t((row0 >> (A - 1 - w)) & 1);
+            const int32_t c = S[w * kWave + ulane] & on;
+            F += c;
+            own += w < lane ? c : 0;
+        }
         const bool lbit = lane <= A - 1 - kLowLevels && ((row0 >> (A - 1 - lane)) & 1);
-        int32_t Enl = int32_t(wave_sum64(lbit ? int64_t(F) + diagl : 0) / 2);
+        int32_t Enl = wave_sum(lbit ? own : 0);
         // the chunk energies carry the instance's shift c (packed: into the
         // 16-bit range; int32: non-negative), the prefix energy the opposite
         // one, so every sum is the true energy
@@ -597,24 +646,45 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
                 }
             } else {
                 const int ws = up ? A - 1 - tm : 2 * A - 1 - tm;
+                const int32_t ml = lrow(ws);
+                const ivec<MC> mh = hrow(ws);
 #pragma unroll
-                for (int j = 0; j < MC; j++) E[j] += trow(M, ws)[j * kWave + ulane];
+                for (int j = 0; j < MC; j++) E[j] += ml + mh[j];
             }
             pin_vec<MC>(E);
             nonlow_flip(A - 1 - tm, up, up ? Smid : -Smid, SmidL);
             return up;
         };
-        // Flip entering super-block sb + 1 (Gray level >= kSuperLog).
-        auto boundary_flip = [&](uint64_t sb) {
+        // Flip entering super-block sb + 1 (Gray level >= kSuperLog): its
+        // signed row (M_int's or the negated one: one code path whatever the
+        // direction) is `row`, and the lane part and coupling column of that
+        // row are loaded a super-block ahead, which hides their latency (two
+        // VGPRs; n = 44 walk 0.7% and n = 36 3% shorter than loading them
+        // at the flip).
+        struct Boundary {
+            int w;
+            bool up;
+            int row;
+            int32_t ml, sd;
+        };
+        auto boundary_load = [&](uint64_t sb) {
+            Boundary b;
             const uint64_t ip1 = (sb + 1) << kSuperLog;
             const int t = __builtin_ctzll(ip1);
-            const bool up = ((ip1 >> (t + 1)) & 1) == 0;
-            const int w = A - 1 - t;
+            b.up = ((ip1 >> (t + 1)) & 1) == 0;
+            // (past the last super-block t can be A: any row will do there)
+            b.w = max(A - 1 - t, 0);
+            b.row = b.up ? b.w : b.w + A;
+            b.ml = lrow(b.row);
+            b.sd = S[b.row * kWave + ulane];
+            return b;
+        };
+        auto boundary_flip = [&](const Boundary &b) {
             bool done = false;
             static_for<kSuperLog, G>([&](auto tc) {
                 constexpr int tt = decltype(tc)::value;
-                if (t == tt) {
-                    if (up) {
+                if (b.w == A - 1 - tt) {
+                    if (b.up) {
 #pragma unroll
                         for (int j = 0; j < MC; j++) E[j] += R[tt][j];
                     } else {
@@ -624,24 +694,23 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
                     done = true;
                 }
             });
-            // signed row (M_int or its negation) for levels read from L2:
-            // one code path whatever the direction
-            const int ws = up ? w : w + A;
             if (!done) {
+                const ivec<MC> mh = hrow(b.row);
 #pragma unroll
-                for (int j = 0; j < MC; j++) E[j] += trow(M, ws)[j * kWave + ulane];
+                for (int j = 0; j < MC; j++) E[j] += b.ml + mh[j];
             }
             pin_vec<MC>(E);
             int32_t SLw[kLowLevels];
             static_for<0, kLowLevels>([&](auto tc) {
                 constexpr int tt = decltype(tc)::value;
-                SLw[tt] = kall[kbase + kKBound + w * kLowLevels + tt];
+                SLw[tt] = kall[kbase + kKBound + b.w * kLowLevels + tt];
             });
-            nonlow_flip(w, up, S[size_t(ws) * kWave + ulane], SLw);
+            nonlow_flip(b.w, b.up, b.sd, SLw);
         };
 
         if constexpr (TIER == 1) {
             for (uint64_t sb = sb0; sb < sbEnd; sb++) {
+                const Boundary next = boundary_load(sb);
                 static_for<0, (1 << kSuperLog)>([&](auto oc) {
                     constexpr int o = decltype(oc)::value;
                     constexpr int pat = (o ^ (o >> 1)) & (kPatterns - 1);
@@ -656,7 +725,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
                             build_thr();
                         }
                     } else if (sb + 1 < sbEnd) {
-                        boundary_flip(sb);
+                        boundary_flip(next);
                         build_thr();
                     }
                 });
@@ -666,6 +735,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
             const uint32_t nsb = uint32_t(sbEnd - sb0);
             for (uint32_t ks = 0; ks < nsb; ks++) {
                 const uint64_t sb = sb0 + ks;
+                const Boundary next = boundary_load(sb);
                 lm0 = lane_min(E);
                 tab2 = 0;
                 // NSEG segments of SEG steps (tier 2: the two halves around
@@ -764,7 +834,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
                         constexpr bool up = (((o ^ (o >> 1)) >> t) & 1) != 0;
                         low_flip(std::integral_constant<int, t>{}, std::integral_constant<bool, up>{});
                     } else if (ks + 1 < nsb) {
-                        boundary_flip(sb);
+                        boundary_flip(next);
                     }
                 });
             }
