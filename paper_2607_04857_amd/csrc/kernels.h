@@ -200,14 +200,29 @@ struct FinalRes {
 hipError_t launch_prepare(const void *dQ, int n, int is_fp32, int32_t *d_T, PrepOut *d_prep,
                           Inst *d_inst, hipStream_t stream);
 
+// Item counters of one walk launch: kQueues of them, kQueueStride words apart.
+// Wave b walks item b first, without a claim, and then claims from queue b mod
+// kQueues, whose items are those of the same residue.  Atomics on one address
+// complete one per 12.4 ns: a single counter kept the waves of a fresh grid
+// (4096 at once) waiting for up to 50 us, and no walk could hand out items
+// faster.  Workgroups go to the eight XCDs in turn, so a queue is an XCD's.
+constexpr int kQueues = 8;
+constexpr int kQueueStride = 32;
+constexpr int kCounterWords = kQueues * kQueueStride;
+// Where items are long (2^kStealSteps steps and more), a wave whose queue is
+// empty takes items of the others: the XCDs do not run at one speed (queues
+// left alone cost 1.2% at n = 44 and 2.5% on 4096 instances).  Shorter items
+// end together anyway, and the tries would cost what they save.
+constexpr int kStealSteps = 12;
+
 // Builds ML, EB, S, K for every instance, clears each instance's item bitmap,
 // lowers its shared best by greedy descents (over an uploaded kNoEnergy), and
-// zeroes n_counters item counters (for a device-prepared instance whose
-// preparation failed, the counters are set past every item).
+// zeroes the item counters of n_groups walk launches (kCounterWords each).
 hipError_t launch_tables(const Inst *d_insts, int n_inst, unsigned long long *d_counters,
-                         int n_counters, hipStream_t stream);
+                         int n_groups, hipStream_t stream);
 
-// Persistent Gray walk over all items; `waves` resident wavefronts.  d_k is
+// Persistent Gray walk over all items (d_counter: the launch's kCounterWords
+// zeroed words, max_L: log2 of the longest item's steps); `waves` resident wavefronts.  d_k is
 // the contiguous array of K tables (instance i's at insts[i].kslot*kKTable).
 // Variant: mcols words per lane (B = 6 + log2 mcols, 7 + log2 mcols for
 // tiers 4 and 5), the M_int rows of Gray levels below vgpr_levels cached in
@@ -215,7 +230,8 @@ hipError_t launch_tables(const Inst *d_insts, int n_inst, unsigned long long *d_
 // Tiers 3 and 5 (top-k lists) need `tk` and exactly one instance; tiers 1,
 // 2 and 4 ignore it (may be null).
 hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts, int n_inst,
-                       uint64_t total_items, unsigned long long *d_counter, const int32_t *d_k,
+                       uint64_t total_items, int max_L, unsigned long long *d_counter,
+                       const int32_t *d_k,
                        int waves, hipStream_t stream, const TopkWalk *tk = nullptr);
 
 // Whether a (mcols, vgpr_levels) walk variant is compiled in, and whether

@@ -23,8 +23,9 @@
 //    over the lane's bits plus a sum over the bits of j, so a row is one load
 //    per lane, 2^B / 64 scalars and a three-operand add per word;
 //  * wavefronts take work items (2^L consecutive Gray steps of the prefix,
-//    the "straightforward" split of Sec. III-C.1 along the Gray index) from an
-//    atomic counter, one at a time; the grid is persistent;
+//    the "straightforward" split of Sec. III-C.1 along the Gray index), the
+//    first by its own number and the others from atomic counters, one at a
+//    time; the grid is persistent;
 //  * the scalar unit keeps the prefix self-energy E_p: the walk is unrolled
 //    over 64-step super-blocks in which the five lowest Gray levels follow a
 //    static pattern and level 5 flips once, in the middle, so the flip
@@ -75,16 +76,14 @@ enum { kPartSeed = 0, kPartK, kPartEB, kPartRows, kTableParts };
 constexpr int kTableThreads = 256;
 
 __global__ __launch_bounds__(kTableThreads) void tables_kernel(
-    const Inst *__restrict__ insts, unsigned long long *__restrict__ counters, int n_counters)
+    const Inst *__restrict__ insts, unsigned long long *__restrict__ counters, int n_groups)
 {
     __shared__ int32_t sS[kMaxVars * kMaxVars];   // T made symmetric
     const Inst I = insts[blockIdx.y];
     const int part = int(blockIdx.x);
     const int tid = int(threadIdx.x);
     if (part == kPartSeed && blockIdx.y == 0) {
-        // a device-prepared instance whose input was refused walks no item
-        const unsigned long long c0 = (I.prep && I.prep->status != 0) ? (1ull << 62) : 0ull;
-        for (int c = tid; c < n_counters; c += kTableThreads) counters[c] = c0;
+        for (int c = tid; c < n_groups * kCounterWords; c += kTableThreads) counters[c] = 0;
     }
     if (part == kPartRows && I.bits) {   // no item has reported yet
         const uint64_t words = (I.n_items + 31) / 32;
@@ -563,10 +562,10 @@ hipError_t launch_prepare(const void *dQ, int n, int is_fp32, int32_t *d_T, Prep
 }
 
 hipError_t launch_tables(const Inst *d_insts, int n_inst, unsigned long long *d_counters,
-                         int n_counters, hipStream_t stream)
+                         int n_groups, hipStream_t stream)
 {
     hipLaunchKernelGGL(tables_kernel, dim3(kTableParts, n_inst), dim3(kTableThreads), 0, stream,
-                       d_insts, d_counters, n_counters);
+                       d_insts, d_counters, n_groups);
     return hipGetLastError();
 }
 
@@ -604,10 +603,11 @@ int walk_occupancy(int mcols, int vgpr_levels, int tier, int topk_k)
 }
 
 hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts, int n_inst,
-                       uint64_t total_items, unsigned long long *d_counter, const int32_t *d_k,
-                       int waves, hipStream_t stream, const TopkWalk *tk)
+                       uint64_t total_items, int max_L, unsigned long long *d_counter,
+                       const int32_t *d_k, int waves, hipStream_t stream, const TopkWalk *tk)
 {
-    const WalkLaunch w{tier, d_insts, n_inst, total_items, d_counter, d_k, waves, stream, tk};
+    const int others = max_L >= kStealSteps ? kQueues - 1 : 0;
+    const WalkLaunch w{tier, d_insts, n_inst, total_items, d_counter, others, d_k, waves, stream, tk};
     if (vgpr_levels == 6 || vgpr_levels == 5 || vgpr_levels == 4 || vgpr_levels == 3) {
         if (mcols != 16) return hipErrorInvalidValue;
         if (vgpr_levels == 6 || vgpr_levels == 4) return launch_walk_g6(vgpr_levels == 4, w);

@@ -396,13 +396,17 @@ static qubo_status_t plan_walk(const qubo_options_t *opt, Plan &P, std::string *
         }
     }
 
-    // Work items: 2^L consecutive Gray steps each.  Default 2^14 steps (the
-    // per-item set-up, about A*MC adds plus the prefix fields, stays below
-    // 0.3% of the item), the whole prefix range when it is smaller, and never
-    // more than 2^20 items per instance.  A lone instance instead keeps at
-    // least 2^13 items (two per resident wavefront) down to 2^9-step items,
-    // and at most 2^18 (longer items where there are plenty: fewer item
-    // records and set-ups; the autotuner measured this at n = 43 and 44).
+    // Work items: 2^L consecutive Gray steps each, never more than 2^20 items
+    // per instance.  A lone instance spreads over the whole grid: 2^13 items
+    // (two per resident wavefront) of at least one super-block, and of at
+    // most 2^10 steps, so that the waves end together (a SIMD favours its
+    // oldest wave, and the youngest one's last item is what the walk waits
+    // for), up to 2^18 items (fewer records and set-ups where there are
+    // plenty).  Measured, walk time at the old rule (at least 2^9 steps, 2^14
+    // where that leaves 2^13 items) and at this one: n = 24 49 -> 14 us,
+    // n = 30 53 -> 42 us, n = 33 181 -> 163 us, packed n = 36 639 -> 585 us,
+    // and 1092 -> 1088 us at n = 36, where the set-ups cost what the tail
+    // gains.
     int L;
     if (opt && opt->L) {
         L = opt->L;
@@ -423,7 +427,7 @@ static qubo_status_t plan_walk(const qubo_options_t *opt, Plan &P, std::string *
         // set-up (finding its instance among thousands, loading that
         // instance's rows, the state from scratch) outweighs its walk.
         if (many && P.A - L < 6) L = std::max(std::min(P.A, kManyMinL), P.A - 6);
-        if (!many && P.A - L < 13) L = P.A - 13 < 9 ? 9 : P.A - 13;
+        if (!many) L = std::min(std::max(P.A - 13, kSuper), kLoneMaxL);
         if (!many && P.A - L > 18) L = P.A - 18;
         if (L > P.A) L = P.A;
         if (P.A - L > 20) L = P.A - 20;

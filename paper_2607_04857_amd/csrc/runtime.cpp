@@ -96,7 +96,7 @@ static JobOffsets compute_offsets(const Job &job, size_t *stage_bytes, size_t *b
     }
     *stage_bytes = off;
     o.counter = off;
-    off = align_up(off + std::max<size_t>(1, job.groups.size()) * sizeof(unsigned long long), 256);
+    off = align_up(off + std::max<size_t>(1, job.groups.size()) * qk::kCounterWords * sizeof(unsigned long long), 256);
     for (size_t i = 0; i < ni; i++) {
         const qplan::Plan &P = job.plans[i];
         // words per chunk vector: 2^B, or 2^(B-1) packed (two columns a word)
@@ -186,6 +186,7 @@ qubo_status_t job_layout(Job *job, int waves_per_cu)
         WalkGroup &g = job->groups.back();
         g.count = int(i) + 1 - g.first;
         g.items += P.walk_items();
+        g.max_L = std::max(g.max_L, P.L);
         job->total_items += P.walk_items();
     }
     if (job->topk > 1 && (job->plans.size() != 1 ||
@@ -334,7 +335,7 @@ qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, hipEvent_t
     for (size_t k = 0; k < job.groups.size(); k++) {
         const WalkGroup &g = job.groups[k];
         QRT_HIP(qk::launch_walk(g.mcols, g.vgpr_levels, g.tier, job.d_insts + g.first, g.count,
-                                g.items, job.d_counter + k, job.d_k, g.waves, stream,
+                                g.items, g.max_L, job.d_counter + k * qk::kCounterWords, job.d_k, g.waves, stream,
                                 job.topk > 1 ? &job.tkb.walk : nullptr),
                 "walk kernel");
     }

@@ -31,11 +31,12 @@ struct DeviceInfo {
 qubo_status_t device_info(DeviceInfo *info);
 
 // Consecutive walked instances sharing one walk kernel variant: one
-// persistent launch with its own item numbering and counter.
+// persistent launch with its own item numbering and counters.
 struct WalkGroup {
     int first = 0, count = 0;            // instance range in the job
     int mcols = 0, vgpr_levels = 0, tier = 0;
     uint64_t items = 0;
+    int max_L = 0;                       // log2 of the longest item's steps
     int waves = 0;
 };
 
@@ -54,7 +55,7 @@ struct Job {
     size_t stage_bytes = 0;              // leading part of d_mem uploaded from the host
     std::vector<unsigned char> stage;    // insts | T... | Qf... (pinned copy in Batch)
     qk::Inst *d_insts = nullptr;
-    unsigned long long *d_counter = nullptr;   // one per group
+    unsigned long long *d_counter = nullptr;   // kCounterWords per group
     qk::ItemRes *d_res = nullptr;
     qk::FinalRes *d_out = nullptr;
     int32_t *d_k = nullptr;              // all K tables, instance i at i * kKTable

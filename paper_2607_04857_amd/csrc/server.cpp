@@ -38,7 +38,8 @@ using Clock = std::chrono::steady_clock;
 // Walk launches per tick are one per distinct walk kernel variant among the
 // active requests; this bounds the number of built variants (B x cache x tier).
 constexpr int kMaxTickLaunches = 32;
-constexpr int kServeL = 12;         // log2 Gray steps per work item of a served request
+constexpr int kServeL = 12;         // log2 Gray steps per work item of a served request, or
+constexpr int kServeItemsLog = 11;  // fewer where that leaves less than 2^11 items
 
 enum class RState { Queued, Active, Done, Failed };
 
@@ -258,7 +259,7 @@ qubo_status_t enqueue_tick(qubo_server *s, TickBuf &t, bool *launched)
         const qplan::Plan &a = walkers[x]->job.plans[0], &b = walkers[y]->job.plans[0];
         return std::make_tuple(a.mcols, a.vgpr_levels, a.tier) < std::make_tuple(b.mcols, b.vgpr_levels, b.tier);
     });
-    struct Launch { int first, count; uint64_t items; const qplan::Plan *P; };
+    struct Launch { int first, count; uint64_t items; int max_L; const qplan::Plan *P; };
     std::vector<Launch> launches;
     int nw = 0;
     uint64_t g = 0;
@@ -267,7 +268,7 @@ qubo_status_t enqueue_tick(qubo_server *s, TickBuf &t, bool *launched)
         const uint64_t c = share[k];
         const qplan::Plan &P = r->job.plans[0];
         if (launches.empty() || !qrt::same_variant(*launches.back().P, P)) {
-            launches.push_back({nw, 0, 0, &P});
+            launches.push_back({nw, 0, 0, 0, &P});
             g = 0;
         }
         qk::Inst I = r->base;
@@ -280,6 +281,7 @@ qubo_status_t enqueue_tick(qubo_server *s, TickBuf &t, bool *launched)
         g += c;
         launches.back().count++;
         launches.back().items += c;
+        launches.back().max_L = std::max(launches.back().max_L, P.L);
         r->next_item += c;
         if (r->next_item == P.items) finishers.push_back(r);
     }
@@ -287,14 +289,15 @@ qubo_status_t enqueue_tick(qubo_server *s, TickBuf &t, bool *launched)
         QRT_HIP(hipMemcpyAsync(t.d_walk, t.h_walk, size_t(nw) * sizeof(qk::Inst), hipMemcpyHostToDevice,
                                s->stream),
                 "hipMemcpyAsync tick");
-        QRT_HIP(hipMemsetAsync(s->d_counter, 0, launches.size() * sizeof(unsigned long long), s->stream),
+        QRT_HIP(hipMemsetAsync(s->d_counter, 0, 
+                               launches.size() * qk::kCounterWords * sizeof(unsigned long long), s->stream),
                 "hipMemsetAsync");
         for (size_t k = 0; k < launches.size(); k++) {
             const Launch &L = launches[k];
             const int occ = qk::walk_occupancy(L.P->mcols, L.P->vgpr_levels, L.P->tier);
             const int waves = int(std::min<uint64_t>(L.items, uint64_t(s->cus) * uint64_t(occ)));
             QRT_HIP(qk::launch_walk(L.P->mcols, L.P->vgpr_levels, L.P->tier, t.d_walk + L.first, L.count,
-                                    L.items, s->d_counter + k, s->d_karena, waves, s->stream),
+                                    L.items, L.max_L, s->d_counter + k * qk::kCounterWords, s->d_karena, waves, s->stream),
                     "walk kernel");
         }
     }
@@ -423,8 +426,9 @@ qubo_status_t server_init(qubo_server *s, size_t budget, int max_slots)
     QRT_HIP(hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking), "hipStreamCreate");
     QRT_HIP(hipMalloc(&s->d_karena, size_t(max_slots) * qk::kKTable * sizeof(int32_t)), "hipMalloc");
     QRT_HIP(hipMalloc(&s->d_setup, size_t(max_slots) * sizeof(qk::Inst)), "hipMalloc");
-    // one item counter per walk variant launched in a tick
-    QRT_HIP(hipMalloc(&s->d_counter, kMaxTickLaunches * sizeof(unsigned long long)), "hipMalloc");
+    // item counters of every walk variant launched in a tick
+    QRT_HIP(hipMalloc(&s->d_counter,
+                      kMaxTickLaunches * qk::kCounterWords * sizeof(unsigned long long)), "hipMalloc");
     for (int k = max_slots - 1; k >= 0; k--) s->free_kslots.push_back(k);
     for (TickBuf &t : s->ticks) {
         QRT_HIP(hipEventCreateWithFlags(&t.done, hipEventDisableTiming), "hipEventCreate");
@@ -497,7 +501,8 @@ qubo_status_t qubo_server_submit(qubo_server_t *s, const void *Q, int n, qubo_dt
         // items per instance still holds (L >= A - 20), so large requests
         // keep their item records (16 B each) and their finish bounded.
         qplan::Plan &P = r->job.plans[0];
-        const int serveL = std::max(kServeL, P.A - 20);
+        const int serveL = std::max(std::min(kServeL, std::max(P.A - kServeItemsLog, qplan::kSuper)),
+                                    P.A - 20);
         if (!P.direct && P.L > serveL) {
             P.L = serveL;
             P.items = uint64_t(1) << (P.A - P.L);

@@ -291,7 +291,8 @@ __device__ __noinline__ void tk_flush()
 template <int MC, int G, int TIER, bool LR = false>
 __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void walk_kernel(
     const Inst *__restrict__ insts, int n_inst, uint64_t total_items,
-    unsigned long long *__restrict__ counter, const int32_t *__restrict__ kall, TopkWalk tk)
+    unsigned long long *__restrict__ counter, int others, const int32_t *__restrict__ kall,
+    TopkWalk tk)
 {
     static_assert(TIER >= 1 && TIER <= 5, "tier");
     static_assert(G >= kLowLevels && G <= kMaxVgprLevels, "VGPR-resident levels");
@@ -318,7 +319,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
     int cur = -1;
     // the tables, addressed as global memory (uniform base + lane offset +
     // immediate), not through generic pointers
-    const gint32 *ML = nullptr, *EB = nullptr, *S = nullptr;
+    const gint32 *ML = nullptr, *S = nullptr;
     int kbase = 0;                // this instance's K table: kall[kbase ...] (scalar loads)
     // word j of this lane in M_int's (signed) row v: its lane part, one load
     // per lane, plus its column part, a scalar load
@@ -326,26 +327,31 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
     auto hrow = [&](int v) {
         return *reinterpret_cast<const ivec<MC> *>(kall + (kbase + kKHigh + v * MC));
     };
-    int A = 0, L = 0;
-    uint64_t item_begin = 0, item_local0 = 0;
+    int A = 0;
     int32_t R[G][MC];        // M_int rows of Gray levels 0..G-1 (variable A-1-t)
     int32_t Smid = 0;          // couplings of the middle-level variable, one lane each
     int32_t SmidL[kLowLevels];  // couplings of the middle-level variable with the low ones
-    const int32_t *Tm = nullptr;  // the instance's folded T (the diagonal is
-    int nT = 0;                   // re-read per item rather than held in a VGPR)
     int32_t CR[kPatterns];   // low-low coupling increments per pattern
-    int32_t *gbest = nullptr;     // the current instance's shared best
     int32_t best = kNoEnergy;     // tier 3: the current top-k threshold
     uint64_t bestRow = ~0ull;
 
     if constexpr (BT == 3) tk_init(tk);
 
-    for (;;) {
-        uint64_t g = 0;
-        if (lane == 0) g = atomicAdd(counter, 1ull);
-        g = sread64(g);
-        if (g >= total_items) break;
-
+    // the next item of this wave's queue (kQueues), or, where it is empty, of
+    // one of the next `others` queues
+    uint32_t queue = blockIdx.x % kQueues;
+    auto claim = [&]() {
+        for (int k = 0;; k++) {
+            uint64_t c = 0;
+            if (lane == 0) c = atomicAdd(counter + queue * kQueueStride, 1ull);
+            // a queue's first items are the waves' own
+            const uint64_t g = (sread64(c) + (gridDim.x + kQueues - 1 - queue) / kQueues) * kQueues +
+                               queue;
+            if (g < total_items || k >= others) return g;
+            queue = (queue + 1) % kQueues;
+        }
+    };
+    for (uint64_t g = blockIdx.x; g < total_items; g = claim()) {
         // instance owning item g: first k with item_end > g
         int lo = 0, hi = n_inst - 1;
         while (lo < hi) {
@@ -353,17 +359,17 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
             if (insts[mid].item_end > g) hi = mid;
             else lo = mid + 1;
         }
+        // (what only the item set-up and the rare paths use is read from the
+        // descriptor where it is used, not held in registers)
+        const Inst &I = insts[lo];
         if (lo != cur) {
             cur = lo;
-            const Inst &I = insts[lo];
+            // a device-prepared instance whose input was refused walks no item
+            if (I.prep && sread(I.prep->status) != 0) break;
             ML = to_global(I.ML);
-            EB = to_global(I.EB);
             S = to_global(I.S);
             kbase = I.kslot * kKTable;
             A = I.A;
-            L = I.L;
-            item_begin = I.item_begin;
-            item_local0 = I.item_local0;
             static_for<0, G>([&](auto tc) {
                 constexpr int t = decltype(tc)::value;
                 const bool have = t < A;
@@ -386,8 +392,6 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
                 constexpr int t = decltype(tc)::value;
                 SmidL[t] = kall[kbase + kKBound + (A - 1 - kLowLevels) * kLowLevels + t];
             });
-            Tm = I.T;
-            nT = I.n;
             // Sll(t,u): coupling of the low variables A-1-t and A-1-u
             int32_t Sll[kLowLevels][kLowLevels];
             static_for<0, kLowLevels>([&](auto tc) {
@@ -413,7 +417,6 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
             });
             best = kNoEnergy;
             bestRow = ~0ull;
-            if constexpr (BT != 3) gbest = I.gbest;
         }
 
         // Best energy found by any wave for this instance (published at the
@@ -422,7 +425,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         // recorded: bestRow restarts at the largest row whenever the shared
         // value lowers best.)
         if constexpr (BT != 3) {
-            const int32_t g0 = sread(__hip_atomic_load(gbest, __ATOMIC_RELAXED,
+            const int32_t g0 = sread(__hip_atomic_load(I.gbest, __ATOMIC_RELAXED,
                                                        __HIP_MEMORY_SCOPE_AGENT));
             if (g0 < best) {
                 best = g0;
@@ -431,10 +434,10 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         }
 
         // ---- item set-up: state g(i0) from scratch
-        const uint64_t qloc = g - item_begin + item_local0;   // the instance's item number
-        const uint64_t i0 = qloc << L;
+        const uint64_t qloc = g - I.item_begin + I.item_local0;   // the instance's item number
+        const uint64_t i0 = qloc << I.L;
         const uint64_t sb0 = i0 >> kSuperLog;
-        const uint64_t sbEnd = sb0 + (1ull << (L - kSuperLog));
+        const uint64_t sbEnd = sb0 + (1ull << (I.L - kSuperLog));
         const uint64_t row0 = i0 ^ (i0 >> 1);
 
         // (Loads are masked, not branched over, so that they are in flight
@@ -446,7 +449,8 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         // T[v][A+t].  Lane 16 q + t adds up the rows v = q (mod 4).
         int32_t h = 0;
         {
-            const gint32 *T = to_global(Tm);
+            const gint32 *T = to_global(I.T);
+            const int nT = I.n;
             const int t = lane & 15;
 #pragma unroll 4
             for (int v0 = 0; v0 < A; v0 += 4) {
@@ -475,6 +479,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
             // packed: both columns of a word, the high one with variable A set
             const uint32_t top = PK ? uint32_t(__builtin_amdgcn_readlane(h, 0)) << 16 : 0u;
             if constexpr (PK) lsum *= 0x10001u;
+            const gint32 *EB = to_global(I.EB);
             static_for<0, MC>([&](auto jc) {
                 constexpr int j = decltype(jc)::value;
                 const uint32_t hj = PK ? hsum[j] * 0x10001u + top : hsum[j];
@@ -486,7 +491,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         // lane per variable.  own: the part from the variables before it, so
         // that the energy E_nl of the non-low prefix bits is the sum of own
         // over the set ones (a partial sum of T at every point).
-        int32_t F = lane < A ? Tm[lane * nT + lane] : 0;   // T[l][l], lane l < A
+        int32_t F = lane < A ? to_global(I.T)[lane * I.n + lane] : 0;   // T[l][l], lane l < A
         int32_t own = F;
 #pragma unroll 4
         for (int w = 0; w <= A - 1 - kLowLevels; w++) {
@@ -500,7 +505,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         // the chunk energies carry the instance's shift c (packed: into the
         // 16-bit range; int32: non-negative), the prefix energy the opposite
         // one, so every sum is the true energy
-        Enl -= insts[cur].pack_shift;
+        Enl -= I.pack_shift;
         Enl = sread(Enl);
         int32_t H[kLowLevels];
         static_for<0, kLowLevels>([&](auto tc) {
@@ -849,13 +854,13 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
             r.E = itemE;
             r.found = 1;
             r.row = itemRow;
-            const uint64_t q = g - item_begin;
+            const uint64_t q = g - insts[cur].item_begin;
             insts[cur].res[q] = r;
             const uint64_t b = insts[cur].bit0 + q;
             atomicOr(insts[cur].bits + (b >> 5), 1u << (b & 31));
             // publish once per item: every wave starting an item of this
             // instance at once would otherwise contend on one address
-            atomicMin(gbest, itemE);
+            atomicMin(insts[cur].gbest, itemE);
         }
     }
     if constexpr (BT == 3) tk_flush();
@@ -874,27 +879,27 @@ static hipError_t launch_walk_g(const WalkLaunch &w)
     if (w.tier == 1) {
         hipLaunchKernelGGL((walk_kernel<MC, G, 1, LR>), dim3(w.waves), dim3(kWave),
                            (walk_lds_bytes<MC, G, LR>(1, 0)), w.stream, w.insts, w.n_inst,
-                           w.total_items, w.counter, w.k, none);
+                           w.total_items, w.counter, w.others, w.k, none);
     } else if (w.tier == 2) {
         hipLaunchKernelGGL((walk_kernel<MC, G, 2, LR>), dim3(w.waves), dim3(kWave),
                            (walk_lds_bytes<MC, G, LR>(2, 0)), w.stream, w.insts, w.n_inst,
-                           w.total_items, w.counter, w.k, none);
+                           w.total_items, w.counter, w.others, w.k, none);
     } else if (w.tier == 4 && MC >= 4) {
         if constexpr (MC >= 4)
             hipLaunchKernelGGL((walk_kernel<MC, G, 4, LR>), dim3(w.waves), dim3(kWave),
                                (walk_lds_bytes<MC, G, LR>(4, 0)), w.stream, w.insts, w.n_inst,
-                               w.total_items, w.counter, w.k, none);
+                               w.total_items, w.counter, w.others, w.k, none);
     } else if (w.tier == 3) {
         if (!w.tk || w.tk->k < 2 || w.n_inst != 1) return hipErrorInvalidValue;
         hipLaunchKernelGGL((walk_kernel<MC, G, 3, LR>), dim3(w.waves), dim3(kWave),
                            (walk_lds_bytes<MC, G, LR>(3, w.tk->k)), w.stream, w.insts, w.n_inst,
-                           w.total_items, w.counter, w.k, *w.tk);
+                           w.total_items, w.counter, w.others, w.k, *w.tk);
     } else if (w.tier == 5 && MC >= 4) {
         if (!w.tk || w.tk->k < 2 || w.n_inst != 1) return hipErrorInvalidValue;
         if constexpr (MC >= 4)
             hipLaunchKernelGGL((walk_kernel<MC, G, 5, LR>), dim3(w.waves), dim3(kWave),
                                (walk_lds_bytes<MC, G, LR>(5, w.tk->k)), w.stream, w.insts,
-                               w.n_inst, w.total_items, w.counter, w.k, *w.tk);
+                               w.n_inst, w.total_items, w.counter, w.others, w.k, *w.tk);
     } else {
         return hipErrorInvalidValue;
     }

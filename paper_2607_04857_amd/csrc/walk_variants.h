@@ -14,6 +14,7 @@ struct WalkLaunch {
     int n_inst;
     uint64_t total_items;
     unsigned long long *counter;
+    int others;          // queues a wave tries after its own (see kStealSteps)
     const int32_t *k;
     int waves;
     hipStream_t stream;
