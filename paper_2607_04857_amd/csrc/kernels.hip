@@ -401,62 +401,142 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
 
 // ---------------------------------------------------------------- finish
 
-// Lexicographic (E, index) minimum over the block: butterflies inside each
-// wave, then the wave results through LDS (sE, sI: one slot per wave).
-__device__ void block_lexmin(int64_t &bE, uint64_t &bI, int64_t *sE, uint64_t *sI)
+constexpr int kFinishThreads = 256;
+constexpr int kFinishWaves = kFinishThreads / kWave;
+constexpr int kDirectLow = 8;    // index bits of a direct instance held by the thread number
+constexpr int kDirectHigh = 14 - kDirectLow;
+static_assert((1 << kDirectLow) == kFinishThreads, "one low pattern per thread");
+
+__device__ __forceinline__ uint32_t wave_umin(uint32_t v)
 {
-#pragma unroll
-    for (int off = kWave / 2; off >= 1; off >>= 1) {
-        const int64_t e = __shfl_xor(bE, off, kWave);
-        const uint64_t i = __shfl_xor(bI, off, kWave);
-        lexmin(bE, bI, e, i);
-    }
-    const int w = int(threadIdx.x) / kWave, nw = int(blockDim.x) / kWave;
-    if (int(threadIdx.x) % kWave == 0) {
-        sE[w] = bE;
-        sI[w] = bI;
-    }
-    __syncthreads();
-    bE = INT64_MAX;
-    bI = ~0ull;
-    for (int k = 0; k < nw; k++) lexmin(bE, bI, sE[k], sI[k]);
-    __syncthreads();
+    return uint32_t(wave_min(int32_t(v ^ 0x80000000u))) ^ 0x80000000u;
 }
 
-constexpr int kFinishThreads = 1024;
+// Lexicographic (E, index) minimum over the block, the same in every thread:
+// DPP minima of the energy, then of the index words among the lanes that
+// hold it, and the wave results through LDS (sE, sI: one slot per wave).
+__device__ void block_lexmin(int32_t &E, uint64_t &I, int32_t *sE, uint64_t *sI)
+{
+    const int32_t m = wave_min(E);
+    const uint32_t hi = E == m ? uint32_t(I >> 32) : ~0u;
+    const uint32_t mh = wave_umin(hi);
+    const uint32_t ml = wave_umin(E == m && hi == mh ? uint32_t(I) : ~0u);
+    const int w = int(threadIdx.x) / kWave;
+    __syncthreads();   // the slots may still be read from the last call
+    if (int(threadIdx.x) % kWave == 0) {
+        sE[w] = m;
+        sI[w] = (uint64_t(mh) << 32) | ml;
+    }
+    __syncthreads();
+    E = sE[0];
+    I = sI[0];
+#pragma unroll
+    for (int k = 1; k < kFinishWaves; k++)
+        if (sE[k] < E || (sE[k] == E && sI[k] < I)) {
+            E = sE[k];
+            I = sI[k];
+        }
+}
 
+// One 256-thread block per instance.  What bounds it is the chain of short
+// dependent steps (descriptor, T and records, block minimum, suffix fields,
+// chunk minimum, check), so the steps are few, their loads are issued together
+// ahead of the first barrier, and sums and minima go through DPP; four waves a
+// block let eight blocks share a CU, which a batch needs.  Energies are
+// partial sums of T and fit int32 (sum |T| <= 2^30 - 1).
+// Measured, against 1024-thread blocks with the O(B^2) rescan per state and a
+// serial gather of the rescore: n = 12 direct 29 -> 6.6 us, lone walked int32
+// 17-21 -> 6.6-12 us, float32 31-50 -> 10-18 us; 1000 float32 instances 163 ->
+// 16 us, 4096 int32 ones 184 -> 21 us.
 __global__ __launch_bounds__(kFinishThreads) void finish_kernel(const Inst *__restrict__ insts,
                                                                 FinalRes *__restrict__ out)
 {
-    __shared__ int64_t sE[kFinishThreads / kWave];
-    __shared__ uint64_t sI[kFinishThreads / kWave];
-    __shared__ int64_t sC[kMaxVars];   // suffix fields of the winning chunk
-    __shared__ int64_t sEp;            // its prefix energy
-    // T (and the caller's float32 Q) staged in LDS: every energy below reads
-    // entries of T, and the float64 rescore runs on one thread in a fixed
-    // order, where global-memory latency would dominate
-    __shared__ int32_t sT[kMaxVars * kMaxVars];
-    __shared__ float sQ[kMaxVars * kMaxVars];
+    __shared__ int32_t sE[kFinishWaves];
+    __shared__ uint64_t sI[kFinishWaves];
+    __shared__ int32_t sH[16];                    // suffix fields of the winning chunk
+    __shared__ int32_t sFull[kFinishWaves];
+    __shared__ int32_t sVar[kWave];               // the answer's set variables, ascending
+    __shared__ int32_t sHigh[1 << kDirectHigh];   // direct: energies of the high patterns
+    // T made symmetric, and later the float32 entries the rescore adds up
+    __shared__ int32_t sS[kMaxVars * kMaxVars];
     const Inst I = insts[blockIdx.x];
-    const int n = I.n;
-    for (int e = int(threadIdx.x); e < n * n; e += int(blockDim.x)) {
-        sT[e] = I.T[e];
-        if (I.Qf) sQ[e] = I.Qf[e];
+    const int n = I.n, tid = int(threadIdx.x), w = tid / kWave, l = tid % kWave;
+    for (int e = tid; e < n * n; e += kFinishThreads) {
+        const int i = e / n, j = e % n;
+        if (i > j) continue;
+        const int32_t t = I.T[e];
+        sS[e] = t;
+        sS[j * n + i] = t;
     }
-    __syncthreads();
-    int64_t bE = INT64_MAX;
+    int32_t bE = INT32_MAX;
     uint64_t bI = ~0ull;
     int32_t status = 0;
     if (I.direct) {
-        const uint64_t N = 1ull << n;
-        for (uint64_t r = threadIdx.x; r < N; r += blockDim.x) lexmin(bE, bI, energy_int(sT, n, r), r);
+        __syncthreads();
+        // Every state r = (high pattern) 2^low + tid, low = min(n, 8): the
+        // energy of the low bits and their fields on the high variables once
+        // per thread, then the high patterns in Gray order, one add each, plus
+        // the pattern's own energy.  Bit b of r is variable n-1-b.
+        const int low = n < kDirectLow ? n : kDirectLow, nh = n - low;
+        auto S = [&](int b, int c) { return sS[(n - 1 - b) * n + n - 1 - c]; };
+        if (tid < (1 << nh)) {
+            int32_t e = 0;
+            for (int x = 0; x < nh; x++) {
+                int32_t row = S(low + x, low + x);
+                for (int y = 0; y < x; y++) row += -((tid >> y) & 1) & S(low + x, low + y);
+                e += -((tid >> x) & 1) & row;
+            }
+            sHigh[tid] = e;
+        }
+        int32_t base = 0, g[kDirectHigh];
+        for (int b = 0; b < low; b++) {
+            int32_t row = S(b, b);
+            for (int c = 0; c < b; c++) row += -((tid >> c) & 1) & S(b, c);
+            base += -((tid >> b) & 1) & row;
+        }
+#pragma unroll
+        for (int x = 0; x < kDirectHigh; x++) {
+            g[x] = 0;
+            if (x < nh)
+                for (int b = 0; b < low; b++) g[x] += -((tid >> b) & 1) & S(low + x, b);
+        }
+        __syncthreads();
+        uint32_t bR = ~0u;
+        if (tid < (1 << low)) {
+            bE = base;
+            bR = uint32_t(tid);
+            int32_t e = base;
+            static_for<1, (1 << kDirectHigh)>([&](auto pc) {
+                constexpr int p = decltype(pc)::value, x = cx_ctz(p), pat = p ^ (p >> 1);
+                if (p < (1 << nh)) {
+                    e += ((pat >> x) & 1) ? g[x] : -g[x];
+                    const int32_t E = e + sHigh[pat];
+                    const uint32_t r = (uint32_t(pat) << low) | uint32_t(tid);
+                    if (E < bE || (E == bE && r < bR)) {
+                        bE = E;
+                        bR = r;
+                    }
+                }
+            });
+        }
+        bI = bR;
         block_lexmin(bE, bI, sE, sI);
     } else {
+        const int A = I.A, B = I.B;
+        const int NS = 1 << B, NW = I.packed ? NS / 2 : NS;
+        // suffix energies of this thread's columns (words tid + 256 k)
+        constexpr int kWords = kMaxCols * kWave / kFinishThreads;
+        int32_t eb[kWords];
+#pragma unroll
+        for (int k = 0; k < kWords; k++) {
+            const int c = tid + kFinishThreads * k;
+            eb[k] = c < NW ? I.EB[c] : 0;
+        }
         // the records of items whose bit is set (the others were never
         // written); each thread takes four consecutive bitmap words at a
         // time, loaded together before any is examined
         const uint64_t words = (I.n_items + 31) / 32;
-        for (uint64_t w0 = uint64_t(threadIdx.x) * 4; w0 < words; w0 += uint64_t(blockDim.x) * 4) {
+        for (uint64_t w0 = uint64_t(tid) * 4; w0 < words; w0 += uint64_t(kFinishThreads) * 4) {
             uint32_t x[4];
 #pragma unroll
             for (int k = 0; k < 4; k++) x[k] = w0 + k < words ? I.bits[w0 + k] : 0u;
@@ -466,84 +546,105 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(const Inst *__re
                     const uint32_t b = uint32_t(__builtin_ctz(x[k]));
                     x[k] &= x[k] - 1u;
                     const ItemRes r = I.res[(w0 + k) * 32 + b];
-                    lexmin(bE, bI, r.E, r.row);
+                    if (r.E < bE || (r.E == bE && r.row < bI)) {
+                        bE = r.E;
+                        bI = r.row;
+                    }
                 }
             }
         }
-        block_lexmin(bE, bI, sE, sI);
-        const int64_t Estar = bE;
+        block_lexmin(bE, bI, sE, sI);   // (its barriers also cover sS)
+        const int32_t Estar = bE;
         const uint64_t rowstar = bI;
-        if (Estar == INT64_MAX) {
+        if (Estar == INT32_MAX) {
             status = 2;   // no item reported a candidate
         } else {
             // Argmin reconstruction (ConstructState of Alg. 2): the lowest
-            // suffix s of chunk rowstar whose energy equals E*, from T.  With
-            // the prefix fixed, E(row, s) = E_p(row) + sum_{t in s} c_t +
-            // sum_{t < u in s} T[A+t][A+u] (Sec. II-C), where c_t = T[A+t][A+t]
-            // + sum over the set prefix variables v of T[v][A+t].
-            const int A = I.A, B = I.B;
-            const int w = int(threadIdx.x) / kWave, l = int(threadIdx.x) % kWave;
-            auto set = [&](int v) { return ((rowstar >> (A - 1 - v)) & 1) != 0; };
-            // E_p(row*): the pairs i <= j < A of set prefix variables, spread
-            // over the block (a few per thread), one LDS add per wave
-            if (threadIdx.x == 0) sEp = 0;
-            __syncthreads();
-            int64_t part = 0;
-            for (int e = int(threadIdx.x); e < A * A; e += int(blockDim.x)) {
-                const int i = e / A, j = e % A;
-                if (j >= i && set(i) && set(j)) part += sT[i * n + j];
-            }
-            part = wave_sum64(part);
-            if (l == 0 && part != 0) atomicAdd(reinterpret_cast<unsigned long long *>(&sEp),
-                                               static_cast<unsigned long long>(part));
-            // c_t: wave t sums the couplings of suffix variable A+t with the
-            // set prefix variables, one lane per prefix variable (A < 64)
-            if (w < B) {
-                int64_t c = (l < A && set(l)) ? int64_t(sT[l * n + A + w]) : 0;
-                c = wave_sum64(c);
-                if (l == 0) sC[w] = c + sT[(A + w) * n + (A + w)];
+            // suffix s of the minima of chunk rowstar.  With the prefix fixed,
+            // E(row, s) = E_p(row) + E_s(s) + sum_{t in s} h_t (Sec. II-C),
+            // h_t = sum over the set prefix variables v of T[v][A+t], so the
+            // chunk's minima are those of E_s + sum h_t.  Wave w forms h_t for
+            // t = w, w + 4, ..., one lane per prefix variable (A < 64).
+            for (int t = w; t < B; t += kFinishWaves) {
+                const bool on = l < A && ((rowstar >> ((A - 1 - l) & 63)) & 1);
+                const int32_t h = wave_sum(on ? sS[(A + t) * n + l] : 0);
+                if (l == 0) sH[t] = h;
             }
             __syncthreads();
-            bE = INT64_MAX;
-            bI = ~0ull;
-            const uint32_t NS = 1u << B;
-            for (uint32_t s = threadIdx.x; s < NS; s += blockDim.x) {
-                int64_t e = sEp;
-                for (int t = 0; t < B; t++) {
-                    if (!((s >> (B - 1 - t)) & 1)) continue;
-                    e += sC[t];
-                    for (int u = t + 1; u < B; u++)
-                        if ((s >> (B - 1 - u)) & 1) e += sT[(A + t) * n + A + u];
+            int32_t lowsum = 0;   // column bits 0..5 and 6, 7: tid's
+#pragma unroll
+            for (int b = 0; b < 8; b++)
+                if (b < B) lowsum += -((tid >> b) & 1) & sH[B - 1 - b];
+            int32_t mF = INT32_MAX;
+            uint32_t mS = ~0u;
+            auto offer = [&](int32_t es, uint32_t s) {
+                int32_t f = es + lowsum;
+#pragma unroll
+                for (int b = 8; b < 11; b++)
+                    if (b < B) f += -int32_t((s >> b) & 1) & sH[B - 1 - b];
+                if (f < mF || (f == mF && s < mS)) {
+                    mF = f;
+                    mS = s;
                 }
-                if (e == Estar) lexmin(bE, bI, e, (rowstar << B) | s);
-            }
-            block_lexmin(bE, bI, sE, sI);
-            if (bE != Estar) {
-                status = 3;   // the walk claimed an energy the chunk lacks
-            } else {
-                // the winner evaluated in full from T must agree: its pairs
-                // i <= j < n spread over the block as above
-                if (threadIdx.x == 0) sEp = 0;
-                __syncthreads();
-                int64_t full = 0;
-                for (int e = int(threadIdx.x); e < n * n; e += int(blockDim.x)) {
-                    const int i = e / n, j = e % n;
-                    if (j >= i && ((bI >> (n - 1 - i)) & 1) && ((bI >> (n - 1 - j)) & 1))
-                        full += sT[i * n + j];
+            };
+#pragma unroll
+            for (int k = 0; k < kWords; k++) {
+                const int c = tid + kFinishThreads * k;
+                if (c >= NW) continue;
+                if (I.packed) {
+                    offer(eb[k] & 0xffff, uint32_t(c));
+                    offer(int32_t(uint32_t(eb[k]) >> 16), uint32_t(c + NW));
+                } else {
+                    offer(eb[k], uint32_t(c));
                 }
-                full = wave_sum64(full);
-                if (l == 0 && full != 0) atomicAdd(reinterpret_cast<unsigned long long *>(&sEp),
-                                                   static_cast<unsigned long long>(full));
-                __syncthreads();
-                if (sEp != Estar) status = 3;
             }
+            uint64_t s64 = mS;
+            block_lexmin(mF, s64, sE, sI);
+            bI = (rowstar << B) | s64;
+            // the winner evaluated in full from T must have the energy the
+            // walk claimed: lane l adds up variable l's row, each wave a
+            // quarter of it
+            const bool on = l < n && ((bI >> ((n - 1 - l) & 63)) & 1);
+            int32_t own = 0;
+            for (int j = w; j < n; j += kFinishWaves) {
+                const int32_t c = sS[j * n + (l < n ? l : 0)];
+                own += (j >= l && ((bI >> (n - 1 - j)) & 1)) ? c : 0;
+            }
+            own = wave_sum(on ? own : 0);
+            if (l == 0) sFull[w] = own;
+            __syncthreads();
+            int32_t full = 0;
+#pragma unroll
+            for (int k = 0; k < kFinishWaves; k++) full += sFull[k];
+            if (full != Estar) status = 3;   // the walk claimed an energy the chunk lacks
         }
     }
-    if (threadIdx.x == 0) {
+    double E64 = double(bE);
+    if (I.Qf && status == 0) {
+        // float64 rescore from the caller's matrix, summed i ascending then j
+        // ascending over the set variables: the entries are gathered side by
+        // side, in that order, and one thread adds them up
+        float *sQ = reinterpret_cast<float *>(sS);
+        const int m = __builtin_popcountll(bI);
+        // variable l is bit n-1-l: its rank counts the set bits above
+        if (tid < n && ((bI >> (n - 1 - tid)) & 1))
+            sVar[__builtin_popcountll((bI >> (n - 1 - tid)) >> 1)] = tid;
+        __syncthreads();   // (and sS is done with)
+        for (int e = w; e < m; e += kFinishWaves)
+            if (l < m) sQ[e * m + l] = I.Qf[sVar[e] * n + sVar[l]];
+        __syncthreads();
+        if (tid == 0) {
+            double s = 0.0;
+#pragma unroll 8
+            for (int e = 0; e < m * m; e++) s += double(sQ[e]);
+            E64 = s;
+        }
+    }
+    if (tid == 0) {
         FinalRes o;
         o.E = bE;
         o.index = bI;
-        o.E64 = (I.Qf && status == 0) ? energy_f64(sQ, n, bI) : double(bE);
+        o.E64 = E64;
         o.status = status;
         o.pad = 0;
         out[blockIdx.x] = o;

@@ -321,8 +321,9 @@ qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, hipEvent_t
         QRT_HIP(qk::launch_prepare(job.dq, job.plans[0].n, job.plans[0].dtype == QUBO_FP32 ? 1 : 0,
                                    job.d_T0, job.d_prep, job.d_insts, stream),
                 "prepare kernel");
-    QRT_HIP(qk::launch_tables(job.d_insts, ni, job.d_counter, int(job.groups.size()), stream),
-            "tables kernel");
+    if (!job.groups.empty())   // direct instances need no tables
+        QRT_HIP(qk::launch_tables(job.d_insts, ni, job.d_counter, int(job.groups.size()), stream),
+                "tables kernel");
     if (walk_begin) QRT_HIP(hipEventRecord(walk_begin, stream), "hipEventRecord");
     if (job.topk > 1) {
         // a bound of the k-th smallest chunk key from states near a local
