@@ -148,7 +148,7 @@ struct TopkWalk {
     int32_t *listCount;  // [waves] entries used (written by every wave on exit)
     int32_t *gthr;       // shared bound, kNoEnergy before the walk
     uint32_t *hist;      // [kTopkBins] keys entered into any list, by energy bin (zeroed)
-    int32_t *lowbin;     // lowest non-empty bin (kTopkBins before the walk)
+    int32_t *lowbin;     // [0]: lowest non-empty bin (kTopkBins before the walk), [1]: keys counted
     int64_t hist_lo;     // energy of bin 0's lower edge (-sum|T|)
     int hist_shift;      // bin = (E - hist_lo) >> hist_shift
     int k;

@@ -88,7 +88,7 @@ static JobOffsets compute_offsets(const Job &job, size_t *stage_bytes, size_t *b
         o.gthr = off;
         off = align_up(off + sizeof(int32_t), 256);
         o.lowbin = off;
-        off = align_up(off + sizeof(int32_t), 256);
+        off = align_up(off + 2 * sizeof(int32_t), 256);
         o.candN = off;
         off = align_up(off + sizeof(int32_t), 256);
         o.hist = off;

@@ -43,6 +43,7 @@ struct SelArgs {
     uint64_t *oR;
     int32_t *oCount;
     int32_t *clear;            // set to 0 when done (a later kernel's counter), or null
+    int32_t *status;           // likewise (the answer's status, raised by the final kernel)
 };
 
 __device__ __forceinline__ uint32_t ukey(int32_t e) { return uint32_t(e) ^ 0x80000000u; }
@@ -52,93 +53,140 @@ __device__ __forceinline__ bool key_less(int32_t ea, uint64_t ra, int32_t eb, ui
     return ea < eb || (ea == eb && ra < rb);
 }
 
-// Visit every candidate: f(E, R).
-template <typename F>
-__device__ __forceinline__ void for_valid(const SelArgs &a, uint32_t N, F &&f)
-{
-    for (uint32_t x = threadIdx.x; x < N; x += kSelThreads) f(a.E[x], a.R[x]);
-}
-
-// Bin of the histogram where the running count reaches `need`.
+// Bin of the histogram where the running count reaches `need` (need <= the
+// total), by the first wave: four bins a lane, one wave-wide prefix sum.  (One
+// thread's walk over the 256 bins had taken 10 us a digit.)
 __device__ void pick_bin(const uint32_t *hist, uint32_t need, uint32_t *bin, uint32_t *rest,
                          uint32_t *inbin)
 {
-    uint32_t cum = 0;
-    for (uint32_t b = 0; b < 256; b++) {
-        if (cum + hist[b] >= need) {
-            *bin = b;
-            *rest = need - cum;
-            *inbin = hist[b];
-            return;
-        }
-        cum += hist[b];
+    const int lane = int(threadIdx.x);
+    if (lane >= kWave) return;
+    uint32_t h[4], sum = 0;
+#pragma unroll
+    for (int x = 0; x < 4; x++) {
+        h[x] = hist[4 * lane + x];
+        sum += h[x];
     }
-    *bin = 255;      // unreachable when need <= total
-    *rest = 0;
-    *inbin = 0;
+    uint32_t cum = sum;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const uint32_t o = __shfl_up(cum, off, kWave);
+        if (lane >= off) cum += o;
+    }
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(cum >= need);
+    if (hit == 0 || lane != int(__builtin_ctzll(hit))) return;
+    cum -= sum;
+    int x = 0;
+    while (x < 3 && cum + h[x] < need) cum += h[x++];
+    *bin = uint32_t(4 * lane + x);
+    *rest = need - cum;
+    *inbin = h[x];
 }
+
+// One block.  The energies are taken from their minimum, so that only the
+// digits their spread occupies are counted, and up to kHeld entries a thread
+// are read from memory once.  What bounds it is the chain of digits and the
+// sort's 55 exchanges.  Measured: 4-5 us for a few
+// hundred candidates and 22 us for 2600 of them with k = 1024 (59 us, and 42 us
+// for a thousand, when one thread walked the histogram and every digit of the
+// key was counted).
+constexpr int kHeld = 4;
 
 __global__ __launch_bounds__(kSelThreads) void topk_select_kernel(SelArgs a)
 {
     __shared__ uint32_t hist[256];
-    __shared__ uint32_t sh_total, sh_pos, sh_bin, sh_rest, sh_in;
+    __shared__ uint32_t sh_pos, sh_bin, sh_rest, sh_in, sh_min, sh_max;
     __shared__ int32_t sE[kSelThreads];
     __shared__ uint64_t sR[kSelThreads];
     const uint32_t tid = threadIdx.x;
     const uint32_t k = uint32_t(a.k);
+    const uint32_t total = uint32_t(*a.count) * a.mult;
+    const bool held = total <= kHeld * kSelThreads;
 
+    int32_t hE[kHeld];
+    uint64_t hR[kHeld];
+#pragma unroll
+    for (int x = 0; x < kHeld; x++) {
+        const uint32_t i = tid + uint32_t(x) * kSelThreads;
+        const bool on = held && i < total;
+        hE[x] = on ? a.E[i] : INT32_MAX;
+        hR[x] = on ? a.R[i] : ~0ull;
+    }
     if (tid == 0) {
-        sh_total = uint32_t(*a.count) * a.mult;
         sh_pos = 0;
+        sh_min = ~0u;
+        sh_max = 0;
     }
     __syncthreads();
-    const uint32_t total = sh_total;
+    // visit every candidate: f(E, R)
+    auto for_valid = [&](auto &&f) {
+        if (held) {
+#pragma unroll
+            for (int x = 0; x < kHeld; x++)
+                if (tid + uint32_t(x) * kSelThreads < total) f(hE[x], hR[x]);
+        } else {
+            for (uint32_t i = tid; i < total; i += kSelThreads) f(a.E[i], a.R[i]);
+        }
+    };
 
     bool take_all = total <= k;
     uint32_t uk = 0xFFFFFFFFu;      // energy key of the k-th entry
     bool all_eq = true;             // take every entry whose key equals uk
     uint64_t rk = ~0ull;            // else those with R <= rk
     if (!take_all) {
+        int32_t mn = INT32_MAX, mx = INT32_MIN;
+        for_valid([&](int32_t e, uint64_t) {
+            mn = min(mn, e);
+            mx = max(mx, e);
+        });
+        mn = wave_min(mn);
+        mx = -1 - wave_min(-1 - mx);   // max: ~ reverses the order
+        if (tid % kWave == 0) {
+            atomicMin(&sh_min, ukey(mn));
+            atomicMax(&sh_max, ukey(mx));
+        }
+        __syncthreads();
+        const uint32_t u0 = sh_min, spread = sh_max - u0;
+        const int digits = spread ? (31 - __builtin_clz(spread)) / 8 : 0;
         uint32_t prefix = 0, mask = 0, need = k;
-        for (int shift = 24; shift >= 0; shift -= 8) {
+        for (int shift = 8 * digits; shift >= 0; shift -= 8) {
             for (uint32_t b = tid; b < 256; b += kSelThreads) hist[b] = 0;
             __syncthreads();
-            for_valid(a, total, [&](int32_t e, uint64_t) {
-                const uint32_t u = ukey(e);
+            for_valid([&](int32_t e, uint64_t) {
+                const uint32_t u = ukey(e) - u0;
                 if ((u & mask) == prefix) atomicAdd(&hist[(u >> shift) & 255u], 1u);
             });
             __syncthreads();
-            if (tid == 0) pick_bin(hist, need, &sh_bin, &sh_rest, &sh_in);
+            pick_bin(hist, need, &sh_bin, &sh_rest, &sh_in);
             __syncthreads();
             prefix |= sh_bin << shift;
             mask |= 255u << shift;
             need = sh_rest;
-            __syncthreads();
         }
-        uk = prefix;
+        uk = prefix + u0;
         all_eq = need == sh_in;     // every entry with energy key uk is kept
         if (!all_eq) {
             uint64_t rprefix = 0, rmask = 0;
             for (int shift = 56; shift >= 0; shift -= 8) {
+                __syncthreads();
                 for (uint32_t b = tid; b < 256; b += kSelThreads) hist[b] = 0;
                 __syncthreads();
-                for_valid(a, total, [&](int32_t e, uint64_t r) {
+                for_valid([&](int32_t e, uint64_t r) {
                     if (ukey(e) == uk && (r & rmask) == rprefix)
                         atomicAdd(&hist[uint32_t(r >> shift) & 255u], 1u);
                 });
                 __syncthreads();
-                if (tid == 0) pick_bin(hist, need, &sh_bin, &sh_rest, &sh_in);
+                pick_bin(hist, need, &sh_bin, &sh_rest, &sh_in);
                 __syncthreads();
                 rprefix |= uint64_t(sh_bin) << shift;
                 rmask |= uint64_t(255) << shift;
                 need = sh_rest;
-                __syncthreads();
             }
             rk = rprefix;
         }
     }
     // compaction into LDS (at most k entries)
-    for_valid(a, total, [&](int32_t e, uint64_t r) {
+    for_valid([&](int32_t e, uint64_t r) {
         const uint32_t u = ukey(e);
         if (take_all || u < uk || (u == uk && (all_eq || r <= rk))) {
             const uint32_t p = atomicAdd(&sh_pos, 1u);
@@ -183,6 +231,7 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_kernel(SelArgs a)
     if (tid == 0) {
         *a.oCount = int32_t(cnt);
         if (a.clear) *a.clear = 0;
+        if (a.status) *a.status = 0;
     }
 }
 
@@ -219,87 +268,108 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(const int32_t *__rest
     }
 }
 
-// Step 3: block b rescans chunk rows[b] (if b < *rowCount) and appends its
-// states with E <= the largest selected chunk key to (stE, stI), densely
-// (wave-aggregated slots counted in *stCount, zeroed by the chunk select).
-// With fewer than k chunks selected (the instance has fewer than k chunks)
-// the k-th smallest state may lie above every chunk minimum, so every state
-// of every chunk is kept: at most rc << B < k << B entries.
-__global__ __launch_bounds__(256) void topk_rescan_kernel(const Inst *__restrict__ inst,
-                                                          const uint64_t *__restrict__ rows,
-                                                          const int32_t *__restrict__ rowE,
-                                                          const int32_t *__restrict__ rowCount,
-                                                          int k,
-                                                          int32_t *__restrict__ stE,
-                                                          uint64_t *__restrict__ stI,
-                                                          int32_t *__restrict__ stCount)
+// Step 3: each wave rescans one chunk of rows[0 .. *rowCount) and its states
+// with E <= the largest selected chunk key go to (stE, stI), densely (slots
+// counted in *stCount, zeroed by the chunk select).  With fewer than k chunks
+// selected (the instance has fewer than k chunks) the k-th smallest state may
+// lie above every chunk minimum, so every state of every chunk is kept: at
+// most rc << B < k << B entries.
+// A chunk's states follow from its suffix fields h_t = sum over the set prefix
+// variables v of T[v][A+t]: E(row, s) = E_p + E_s(s) + sum_{t in s} h_t, E_s
+// read from the walk's table.  One atomic per block of kRescanWaves chunks
+// (they complete one per 12.4 ns).  Measured: 10 us for k = 1024
+// at n = 31 and 7 us for k = 16 at n = 21 (27 and 13 us with a block per chunk,
+// its rows summed one after another, and an atomic per wave and pass).
+constexpr int kRescanWaves = 8;
+
+__global__ __launch_bounds__(kRescanWaves *kWave) void topk_rescan_kernel(
+    const Inst *__restrict__ inst, const uint64_t *__restrict__ rows,
+    const int32_t *__restrict__ rowE, const int32_t *__restrict__ rowCount, int k,
+    int32_t *__restrict__ stE, uint64_t *__restrict__ stI, int32_t *__restrict__ stCount)
 {
-    __shared__ int64_t red[256];
+    __shared__ int32_t sT[kMaxVars * kMaxVars];
+    __shared__ int32_t sN[kRescanWaves], sBase;
     const Inst I = *inst;
     const int n = I.n, A = I.A, B = I.B;
-    const uint32_t NS = 1u << B;
-    const uint32_t b = blockIdx.x;
+    const int tid = int(threadIdx.x), lane = tid % kWave, w = tid / kWave;
     const int32_t rc = *rowCount;
-    if (int32_t(b) >= rc) return;
+    const int32_t b = int32_t(blockIdx.x) * kRescanWaves + w;
+    if (int32_t(blockIdx.x) * kRescanWaves >= rc) return;
+    for (int e = tid; e < n * n; e += kRescanWaves * kWave) sT[e] = I.T[e];
     // rows are sorted by (key, row)
     const int32_t bound = rc < k ? INT32_MAX : rowE[rc - 1];
-    const int lane = int(threadIdx.x) & (kWave - 1);
-    const uint64_t row = rows[b];
-    // E_p(row) = sum over set prefix bits i <= j of T[i][j]; prefix variable
-    // v is bit A-1-v of the U_A row.
-    int64_t part = 0;
-    for (int i = int(threadIdx.x); i < A; i += int(blockDim.x)) {
-        if (!((row >> (A - 1 - i)) & 1)) continue;
-        for (int j = i; j < A; j++)
-            if ((row >> (A - 1 - j)) & 1) part += I.T[i * n + j];
-    }
-    red[threadIdx.x] = part;
+    const bool mine = b < rc;
+    const uint64_t row = mine ? sread64(rows[b]) : 0;
+    const int NW = I.packed ? (1 << B) / 2 : 1 << B, MC = NW / kWave;
+    int32_t eb[kMaxCols];
+#pragma unroll
+    for (int j = 0; j < kMaxCols; j++) eb[j] = j < MC ? I.EB[j * kWave + lane] : 0;
     __syncthreads();
-    for (int off = 128; off > 0; off >>= 1) {
-        if (int(threadIdx.x) < off) red[threadIdx.x] += red[threadIdx.x + off];
-        __syncthreads();
+    auto set = [&](int v) { return ((row >> (A - 1 - v)) & 1) != 0; };
+    // E_p: lane l adds up column l of the set prefix variables v <= l
+    int32_t own = 0;
+    for (int v = 0; v < A; v++)
+        if (set(v)) own += (v <= lane && lane < A) ? sT[v * n + lane] : 0;
+    const int32_t Ep = wave_sum(lane < A && set(lane < A ? lane : 0) ? own : 0);
+    int32_t h = 0;   // lane t: h_t
+    for (int v = 0; v < A; v++)
+        if (set(v)) h += lane < B ? sT[v * n + A + lane] : 0;
+    int32_t low = Ep;   // the lane's six column bits
+#pragma unroll
+    for (int u = 0; u < 6; u++) low += -((lane >> u) & 1) & __builtin_amdgcn_readlane(h, B - 1 - u);
+    const int JB = I.packed ? B - 7 : B - 6;
+    const int32_t top = __builtin_amdgcn_readlane(h, 0);   // packed: the high column's variable A
+    // energies of the lane's words (packed: of both columns of a word)
+    int32_t E[kMaxCols], E2[kMaxCols];
+    int32_t kept = 0;
+#pragma unroll
+    for (int j = 0; j < kMaxCols; j++) {
+        int32_t hj = 0;   // the bits of j
+#pragma unroll
+        for (int u = 0; u < 4; u++)
+            if (u < JB && ((j >> u) & 1)) hj += __builtin_amdgcn_readlane(h, B - 7 - u);
+        if (I.packed) {
+            // E_s carries the walk's shift and the packed bias
+            const int32_t base = low + hj - kPackBias - I.pack_shift;
+            E[j] = base + (eb[j] & 0xffff);
+            E2[j] = base + top + int32_t(uint32_t(eb[j]) >> 16);
+        } else {
+            E[j] = low + hj + eb[j] - I.pack_shift;
+            E2[j] = 0;
+        }
+        if (mine && j < MC) {
+            kept += __builtin_popcountll(__builtin_amdgcn_ballot_w64(E[j] <= bound));
+            if (I.packed) kept += __builtin_popcountll(__builtin_amdgcn_ballot_w64(E2[j] <= bound));
+        }
     }
-    const int32_t Ep = int32_t(red[0]);
-    // state (row, s) of energy e: kept when at most the bound (the whole
-    // wave calls this together)
+    if (lane == 0) sN[w] = kept;
+    __syncthreads();
+    if (tid == 0) {
+        int32_t sum = 0;
+        for (int x = 0; x < kRescanWaves; x++) {
+            const int32_t c = sN[x];
+            sN[x] = sum;
+            sum += c;
+        }
+        sBase = sum ? atomicAdd(stCount, sum) : 0;
+    }
+    __syncthreads();
+    if (!mine) return;
+    int32_t at = sBase + sN[w];
     auto offer = [&](int32_t e, uint32_t s) {
-        const bool keep = e <= bound;
-        const uint64_t m = __builtin_amdgcn_ballot_w64(keep);
-        if (!m) return;
-        int base = 0;
-        if (lane == 0) base = atomicAdd(stCount, int(__builtin_popcountll(m)));
-        base = __builtin_amdgcn_readfirstlane(base);
-        if (keep) {
-            const int p = base + int(__builtin_popcountll(m & ((1ull << lane) - 1)));
+        const uint64_t m = __builtin_amdgcn_ballot_w64(e <= bound);
+        if (e <= bound) {
+            const int p = at + int(__builtin_popcountll(m & ((1ull << lane) - 1)));
             stE[p] = e;
             stI[p] = (row << B) | s;
         }
+        at += int(__builtin_popcountll(m));
     };
-    // word c of M_int's row v, NW words a row, from its lane and column parts
-    auto mrow = [&](int v, uint32_t c, uint32_t NW) {
-        return I.ML[uint32_t(v) * kWave + c % kWave] +
-               I.K[kKHigh + uint32_t(v) * (NW / kWave) + c / kWave];
-    };
-    // NS (and NS / 2) is a multiple of 64: every lane of a wave that enters
-    // runs each pass
-    if (I.packed) {
-        // the walk's own arithmetic: the packed words of the chunk summed mod
-        // 2^32, then both 16-bit halves decoded (columns c and c + NS / 2)
-        const uint32_t NW = NS / 2;
-        const int32_t off = kPackBias + I.pack_shift;
-        for (uint32_t c = threadIdx.x; c < NW; c += blockDim.x) {
-            uint32_t w = uint32_t(I.EB[c]);
-            for (int v = 0; v < A; v++)
-                if ((row >> (A - 1 - v)) & 1) w += uint32_t(mrow(v, c, NW));
-            offer(Ep + int32_t(w & 0xffffu) - off, c);
-            offer(Ep + int32_t(w >> 16) - off, c + NW);
-        }
-    } else {
-        for (uint32_t s = threadIdx.x; s < NS; s += blockDim.x) {
-            int32_t e = Ep - I.pack_shift + I.EB[s];   // E_s carries the walk's shift
-            for (int v = 0; v < A; v++)
-                if ((row >> (A - 1 - v)) & 1) e += mrow(v, s, NS);
-            offer(e, s);
+#pragma unroll
+    for (int j = 0; j < kMaxCols; j++) {
+        if (j < MC) {
+            offer(E[j], uint32_t(j * kWave + lane));
+            if (I.packed) offer(E2[j], uint32_t(NW + j * kWave + lane));
         }
     }
 }
@@ -319,79 +389,104 @@ __global__ __launch_bounds__(256) void topk_direct_kernel(const Inst *__restrict
     if (blockIdx.x == 0 && threadIdx.x == 0) segCount[0] = int32_t(N);
 }
 
-// Step 5: verify, rescore, order; one block of k (<= 1024) threads.
-__global__ __launch_bounds__(kSelThreads) void topk_final_kernel(
+// Step 5: one thread per state of the answer, one wave a block: its energy
+// from T must be the one the selection has, and float32 instances are rescored
+// in float64.  int32 answers are in their final order already (the last
+// select's), float32 ones are ordered by topk_order_kernel.  Measured: 17 us for
+// k = 1024 at n = 31, 10 us for k = 16 at n = 21 (54 and 21 us in one block).
+__global__ __launch_bounds__(kWave) void topk_final_kernel(
     const Inst *__restrict__ inst, const int32_t *__restrict__ selE,
     const uint64_t *__restrict__ selR, const int32_t *__restrict__ selCount, int k,
     TopkState *__restrict__ out, FinalRes *__restrict__ best)
 {
+    __shared__ int32_t sT[kMaxVars * kMaxVars];
+    __shared__ float sQ[kMaxVars * kMaxVars];
+    const Inst I = *inst;
+    const int n = I.n;
+    const int at = int(blockIdx.x) * kWave + int(threadIdx.x);
+    const int cnt = *selCount;
+    const uint64_t idx = at < cnt ? selR[at] : 0;
+    const int32_t e = at < cnt ? selE[at] : 0;
+    for (int x = int(threadIdx.x); x < n * n; x += kWave) {
+        sT[x] = I.T[x];
+        if (I.Qf) sQ[x] = I.Qf[x];
+    }
+    __syncthreads();
+    int32_t sum = 0;   // a partial sum of T: within the int32 bound
+    for (int i = 0; i < n; i++) {
+        int32_t row = 0;
+#pragma unroll 4
+        for (int j = i; j < n; j++) row += -int32_t((idx >> (n - 1 - j)) & 1) & sT[i * n + j];
+        sum += -int32_t((idx >> (n - 1 - i)) & 1) & row;
+    }
+    if (at < cnt && at < k) {
+        TopkState o;
+        o.E = e;
+        o.E64 = I.Qf ? energy_f64(sQ, n, idx) : double(e);
+        o.index = idx;
+        out[at] = o;
+    }
+    // (the last select cleared the status)
+    if (__builtin_amdgcn_ballot_w64(at < cnt && sum != e) && threadIdx.x == 0)
+        atomicMax(&best->status, 3);
+    if (at == 0) {
+        best->E = cnt > 0 ? e : 0;
+        best->index = idx;
+        best->E64 = cnt > 0 ? (I.Qf ? energy_f64(sQ, n, idx) : double(e)) : 0.0;
+        if (cnt < k) atomicMax(&best->status, 4);
+    }
+}
+
+// The integer order is exact for the scaled energies; float32 answers are
+// reported by their float64 energies, in their own (E64, index) order.
+__global__ __launch_bounds__(kSelThreads) void topk_order_kernel(
+    const int32_t *__restrict__ selCount, int k, TopkState *__restrict__ out,
+    FinalRes *__restrict__ best)
+{
     __shared__ double sF[kSelThreads];
     __shared__ uint64_t sI[kSelThreads];
     __shared__ int64_t sE[kSelThreads];
-    __shared__ int32_t sh_bad;
-    const Inst I = *inst;
     const uint32_t tid = threadIdx.x;
-    const int cnt = *selCount;
-    if (tid == 0) sh_bad = 0;
+    const int cnt = min(*selCount, k);
+    uint32_t P = 1;
+    while (P < uint32_t(cnt)) P <<= 1;
+    const bool on = int(tid) < cnt;
+    sF[tid] = on ? out[tid].E64 : __builtin_huge_val();
+    sI[tid] = on ? out[tid].index : ~0ull;
+    sE[tid] = on ? out[tid].E : 0;
     __syncthreads();
-    if (int(tid) < cnt) {
-        const uint64_t idx = selR[tid];
-        const int64_t e = selE[tid];
-        if (energy_int(I.T, I.n, idx) != e) atomicOr(&sh_bad, 1);
-        sE[tid] = e;
-        sI[tid] = idx;
-        sF[tid] = I.Qf ? energy_f64(I.Qf, I.n, idx) : double(e);
-    }
-    __syncthreads();
-    if (I.Qf) {
-        // the integer order is exact for the scaled energies; report the
-        // float64 energies in their own (E64, index) order
-        uint32_t P = 1;
-        while (P < uint32_t(cnt)) P <<= 1;
-        if (int(tid) >= cnt && tid < P) {
-            sF[tid] = __builtin_huge_val();
-            sI[tid] = ~0ull;
-            sE[tid] = 0;
-        }
-        __syncthreads();
-        for (uint32_t size = 2; size <= P; size <<= 1) {
-            for (uint32_t st = size >> 1; st > 0; st >>= 1) {
-                const uint32_t j = tid ^ st;
-                if (tid < P && j > tid) {
-                    const bool asc = (tid & size) == 0;
-                    const bool jl = sF[j] < sF[tid] || (sF[j] == sF[tid] && sI[j] < sI[tid]);
-                    if (jl == asc) {
-                        const double tf = sF[tid];
-                        const uint64_t ti = sI[tid];
-                        const int64_t te = sE[tid];
-                        sF[tid] = sF[j];
-                        sI[tid] = sI[j];
-                        sE[tid] = sE[j];
-                        sF[j] = tf;
-                        sI[j] = ti;
-                        sE[j] = te;
-                    }
+    for (uint32_t size = 2; size <= P; size <<= 1) {
+        for (uint32_t st = size >> 1; st > 0; st >>= 1) {
+            const uint32_t j = tid ^ st;
+            if (tid < P && j > tid) {
+                const bool asc = (tid & size) == 0;
+                const bool jl = sF[j] < sF[tid] || (sF[j] == sF[tid] && sI[j] < sI[tid]);
+                if (jl == asc) {
+                    const double tf = sF[tid];
+                    const uint64_t ti = sI[tid];
+                    const int64_t te = sE[tid];
+                    sF[tid] = sF[j];
+                    sI[tid] = sI[j];
+                    sE[tid] = sE[j];
+                    sF[j] = tf;
+                    sI[j] = ti;
+                    sE[j] = te;
                 }
-                __syncthreads();
             }
+            __syncthreads();
         }
     }
-    if (int(tid) < cnt && int(tid) < k) {
+    if (on) {
         TopkState o;
         o.E = sE[tid];
         o.E64 = sF[tid];
         o.index = sI[tid];
         out[tid] = o;
     }
-    if (tid == 0) {
-        FinalRes r;
-        const int32_t status = sh_bad ? 3 : (cnt < k ? 4 : 0);
-        r.E = cnt > 0 ? sE[0] : 0;
-        r.index = cnt > 0 ? sI[0] : 0;
-        r.E64 = cnt > 0 ? sF[0] : 0.0;
-        r.status = status;
-        r.pad = 0;
-        *best = r;
+    if (tid == 0 && cnt > 0) {
+        best->E = sE[0];
+        best->index = sI[0];
+        best->E64 = sF[0];
     }
 }
 
@@ -406,16 +501,15 @@ __global__ __launch_bounds__(kSelThreads) void topk_final_kernel(
 // each group in colex order).  Their energies follow from x*'s single-flip
 // changes d_i and the couplings: flipping the set F changes E by
 //   sum_{i in F} d_i + sum_{i<j in F} s_i s_j T_ij,   s_i = 1 - 2 x_i.
-constexpr int kSeedStates = 4096;
-constexpr int kSeedThreads = 256;
-
-__device__ __forceinline__ int64_t binom_small(int v, int r)   // C(v, r), r <= 4
-{
-    if (v < r) return 0;
-    int64_t c = 1;
-    for (int t = 0; t < r; t++) c = c * (v - t) / (t + 1);
-    return c;
-}
+// Each thread numbers its four states by binary search over the binomials and
+// keeps their energies in registers; the k-th smallest is found by bisection
+// on the value, its counts taken by ballots.  Measured: 25 us at n = 31, k =
+// 1024 and 14 us at n = 21 (506 and 78 us when every thread unranked by 64-bit
+// division and scanned all energies for their range).
+constexpr int kSeedThreads = 1024;
+constexpr int kSeedPer = 4;
+constexpr int kSeedStates = kSeedPer * kSeedThreads;
+constexpr int kSeedDescents = 8;
 
 __global__ __launch_bounds__(kSeedThreads) void topk_seed_kernel(const Inst *__restrict__ inst,
                                                                  int32_t *gthr, int k)
@@ -423,15 +517,14 @@ __global__ __launch_bounds__(kSeedThreads) void topk_seed_kernel(const Inst *__r
     const Inst &I = *inst;
     const int n = I.n, A = I.A;
     const int tid = int(threadIdx.x), lane = tid % kWave, wave = tid / kWave;
+    constexpr int kWaves = kSeedThreads / kWave;
     __shared__ int32_t T[kMaxVars * kMaxVars];   // T made symmetric
-    __shared__ int32_t wE[kSeedThreads / kWave];
-    __shared__ uint64_t wX[kSeedThreads / kWave];
+    __shared__ int32_t C[5][kWave];              // C[p][v] = binomial(v, p)
+    __shared__ int32_t wE[kSeedDescents];
+    __shared__ uint64_t wX[kSeedDescents];
     __shared__ int32_t d[kWave];
     __shared__ int32_t sg[kWave];
-    __shared__ int32_t Ec[kSeedStates];
-    __shared__ int64_t sBest;
-    __shared__ uint64_t sXm;
-    __shared__ uint32_t sCount;
+    __shared__ int32_t wLo[kWaves], wHi[kWaves], wN[kWaves];
 
     for (int e = tid; e < n * n; e += kSeedThreads) {
         const int i = e / n, j = e % n;
@@ -440,96 +533,108 @@ __global__ __launch_bounds__(kSeedThreads) void topk_seed_kernel(const Inst *__r
         T[e] = t;
         T[j * n + i] = t;
     }
+    if (tid < kWave) {   // v <= 60: within int32
+        const int v = tid;
+        C[0][v] = 1;
+        C[1][v] = v;
+        C[2][v] = v * (v - 1) / 2;
+        C[3][v] = v * (v - 1) / 2 * (v - 2) / 3;
+        C[4][v] = v < 4 ? 0 : v * (v - 1) / 2 * (v - 2) / 3 * (v - 3) / 4;
+    }
     __syncthreads();
-    // 1. the best local minimum of eight descents (two per wave)
-    int32_t bE = kNoEnergy;
-    uint64_t bX = 0;
-    for (int rep = 0; rep < 2; rep++) {
+    // 1. the best local minimum of eight descents
+    if (wave < kSeedDescents) {
         int32_t E;
         uint64_t xm;
-        greedy_descent(T, n, uint32_t(wave) * 2u + uint32_t(rep), E, xm);
-        if (E < bE || (E == bE && xm < bX)) {
-            bE = E;
-            bX = xm;
+        greedy_descent(T, n, uint32_t(wave), E, xm);
+        if (lane == 0) {
+            wE[wave] = E;
+            wX[wave] = xm;
         }
     }
-    if (lane == 0) {
-        wE[wave] = bE;
-        wX[wave] = bX;
-    }
     __syncthreads();
-    if (tid == 0) {
-        int32_t e = wE[0];
-        uint64_t x = wX[0];
-        for (int w = 1; w < kSeedThreads / kWave; w++)
-            if (wE[w] < e || (wE[w] == e && wX[w] < x)) {
-                e = wE[w];
-                x = wX[w];
-            }
-        sBest = e;
-        sXm = x;
-    }
-    __syncthreads();
-    const uint64_t xm = sXm;
+    int32_t bE = wE[0];
+    uint64_t xm = wX[0];
+    for (int w = 1; w < kSeedDescents; w++)
+        if (wE[w] < bE || (wE[w] == bE && wX[w] < xm)) {
+            bE = wE[w];
+            xm = wX[w];
+        }
     // 2. single-flip changes and signs at x*, one thread per variable
     if (tid < n) {
         const int xl = int((xm >> tid) & 1);
         int32_t f = T[tid * n + tid];
-        for (int j = 0; j < n; j++)
-            if (j != tid && ((xm >> j) & 1)) f += T[j * n + tid];
+        for (int j = 0; j < n; j++) f += (j != tid && ((xm >> j) & 1)) ? T[j * n + tid] : 0;
         d[tid] = xl ? -f : f;
         sg[tid] = xl ? -1 : 1;
     }
     // 3. the states with 0..4 prefix variables flipped
-    int64_t groups[5];
-    int64_t total = 0;
-    for (int p = 0; p <= 4; p++) {
-        groups[p] = binom_small(A, p);
-        total += groups[p];
-    }
-    const int M = int(total < kSeedStates ? total : kSeedStates);
+    int32_t total = 0;
+    for (int p = 0; p <= 4; p++) total += C[p][A];
+    const int M = min(total, kSeedStates);
     if (M < k) return;   // fewer distinct rows than k: no bound
     __syncthreads();
-    for (int c = tid; c < M; c += kSeedThreads) {
-        int p = 0;
-        int64_t rank = c;
-        while (rank >= groups[p]) rank -= groups[p++];
-        int v[4];
-        for (int r = p; r >= 1; r--) {   // colex unranking of the p-subset
-            int x = r - 1;
-            while (binom_small(x + 1, r) <= rank) x++;
-            rank -= binom_small(x, r);
-            v[r - 1] = x;
-        }
-        int64_t e = sBest;
-        for (int a = 0; a < p; a++) {
-            e += d[v[a]];
-            for (int b = 0; b < a; b++) {
-                const int i = v[b], j = v[a];   // i < j
-                e += int64_t(sg[i] * sg[j]) * T[i * n + j];
+    int32_t Ec[kSeedPer];
+    int32_t lo32 = INT32_MAX, hi32 = INT32_MIN;
+#pragma unroll
+    for (int q = 0; q < kSeedPer; q++) {
+        const int c = tid + q * kSeedThreads;
+        int32_t e = bE;
+        if (c < M) {
+            int p = 0, rank = c;
+            while (rank >= C[p][A]) rank -= C[p++][A];
+            // colex unranking: the largest x with C(x, r) <= rank, from r = p
+            int v[4] = {0, 0, 0, 0};
+#pragma unroll
+            for (int r = 4; r >= 1; r--) {
+                if (r > p) continue;
+                int x = 0;
+#pragma unroll
+                for (int bit = 32; bit >= 1; bit >>= 1)
+                    if (x + bit < A && C[r][x + bit] <= rank) x += bit;
+                rank -= C[r][x];
+                v[r - 1] = x;
             }
+#pragma unroll
+            for (int a = 0; a < 4; a++) {
+                if (a >= p) continue;
+                e += d[v[a]];
+#pragma unroll
+                for (int b = 0; b < a; b++) e += sg[v[b]] * sg[v[a]] * T[v[b] * n + v[a]];
+            }
+            lo32 = min(lo32, e);
+            hi32 = max(hi32, e);
         }
-        Ec[c] = int32_t(e);
+        Ec[q] = c < M ? e : INT32_MAX;
+    }
+    lo32 = wave_min(lo32);
+    hi32 = -1 - wave_min(-1 - hi32);
+    if (lane == 0) {
+        wLo[wave] = lo32;
+        wHi[wave] = hi32;
     }
     __syncthreads();
     // 4. the k-th smallest of the M energies: the least value v with at
-    //    least k energies <= v (bisection on v with block-wide counts)
-    int64_t lo = INT32_MAX, hi = INT32_MIN;
-    for (int c = 0; c < M; c++) {   // every thread the same bounds
-        lo = min(lo, int64_t(Ec[c]));
-        hi = max(hi, int64_t(Ec[c]));
+    //    least k energies <= v
+    int64_t lo = wLo[0], hi = wHi[0];
+    for (int w = 1; w < kWaves; w++) {
+        lo = min(lo, int64_t(wLo[w]));
+        hi = max(hi, int64_t(wHi[w]));
     }
     while (lo < hi) {
         const int64_t mid = lo + (hi - lo) / 2;
-        if (tid == 0) sCount = 0;
+        const int32_t m32 = int32_t(mid);
+        int cnt = 0;
+#pragma unroll
+        for (int q = 0; q < kSeedPer; q++)
+            cnt += int(__builtin_popcountll(__builtin_amdgcn_ballot_w64(Ec[q] <= m32)));
+        __syncthreads();   // the counts of the last round have been read
+        if (lane == 0) wN[wave] = cnt;
         __syncthreads();
-        uint32_t cnt = 0;
-        for (int c = tid; c < M; c += kSeedThreads) cnt += Ec[c] <= mid ? 1u : 0u;
-        atomicAdd(&sCount, cnt);
-        __syncthreads();
-        const uint32_t total_le = sCount;
-        __syncthreads();
-        if (total_le >= uint32_t(k)) hi = mid;
+        int sum = 0;
+#pragma unroll
+        for (int w = 0; w < kWaves; w++) sum += wN[w];
+        if (sum >= k) hi = mid;
         else lo = mid + 1;
     }
     if (tid == 0) atomicMin(gthr, int32_t(lo));
@@ -575,8 +680,9 @@ hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs
         ch.oCount = buf.chunkCount;
         ch.clear = buf.segCount;     // [0]: the rescan's state counter
         hipLaunchKernelGGL(topk_select_kernel, dim3(1), dim3(kSelThreads), 0, stream, ch);
-        hipLaunchKernelGGL(topk_rescan_kernel, dim3(k), dim3(256), 0, stream, d_inst, buf.chunkR,
-                           buf.chunkE, buf.chunkCount, k, buf.stE, buf.stI, buf.segCount);
+        hipLaunchKernelGGL(topk_rescan_kernel, dim3((k + kRescanWaves - 1) / kRescanWaves),
+                           dim3(kRescanWaves * kWave), 0, stream, d_inst, buf.chunkR, buf.chunkE,
+                           buf.chunkCount, k, buf.stE, buf.stI, buf.segCount);
         st.count = buf.segCount;     // states kept by the rescan, densely
         st.mult = 1;
     }
@@ -586,9 +692,13 @@ hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs
     st.oE = buf.selE;
     st.oR = buf.selR;
     st.oCount = buf.selCount;
+    st.status = &d_best->status;
     hipLaunchKernelGGL(topk_select_kernel, dim3(1), dim3(kSelThreads), 0, stream, st);
-    hipLaunchKernelGGL(topk_final_kernel, dim3(1), dim3(kSelThreads), 0, stream, d_inst, buf.selE,
-                       buf.selR, buf.selCount, k, buf.out, d_best);
+    hipLaunchKernelGGL(topk_final_kernel, dim3((k + kWave - 1) / kWave), dim3(kWave), 0, stream,
+                       d_inst, buf.selE, buf.selR, buf.selCount, k, buf.out, d_best);
+    if (hI.Qf)
+        hipLaunchKernelGGL(topk_order_kernel, dim3(1), dim3(kSelThreads), 0, stream, buf.selCount, k,
+                           buf.out, d_best);
     return hipGetLastError();
 }
 
