@@ -133,7 +133,7 @@ qubo_status_t batch_build(qubo_batch *b, int count, const void *const *Q, const 
     qubo_status_t cst = QUBO_OK;
     e = hipMemcpyAsync(b->d_mem, b->h_stage, b->job.stage_bytes, hipMemcpyHostToDevice, b->stream);
     if (e != hipSuccess) cst = qrt::device_error("capture H2D", e);
-    if (cst == QUBO_OK) cst = qrt::job_enqueue_kernels(b->job, b->stream, nullptr, nullptr);
+    if (cst == QUBO_OK) cst = qrt::job_enqueue_kernels(b->job, b->stream);
     if (cst == QUBO_OK) {
         e = hipMemcpyAsync(b->h_out, b->job.d_out, size_t(count) * sizeof(qk::FinalRes),
                            hipMemcpyDeviceToHost, b->stream);

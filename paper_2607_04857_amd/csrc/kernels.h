@@ -126,7 +126,7 @@ struct Inst {
     uint64_t n_items;      // item records of the instance (res[0 .. n_items), bitmap
                            // words bits[0 .. ceil(n_items / 32)))
     int32_t *gbest;        // best energy any wave has found for the instance
-                           // (kNoEnergy in the uploaded image)
+                           // (set by the table build)
     const PrepOut *prep;   // device-prepared instance: its preparation (an error
                            // makes the walk skip all items), else null
 };
@@ -189,7 +189,24 @@ struct FinalRes {
     double E64;        // float64 rescore from Qf (fp32 instances)
     int32_t status;    // 0 ok, nonzero: self-check failure
     int32_t pad;
+    uint64_t walk_ticks;   // lone solves: from the table build's end to the finish's
+                           // start (from before the top-k seed to its compaction), in
+                           // ticks of the device's constant clock
 };
+
+// Host image of a lone solve, read by the first kernel itself instead of by a
+// copy ahead of it (a 4 us copy and a 10 us gap): `copy_bytes` of the mapped
+// host block `src` go to `dst`, and the `zero_bytes` after them are cleared.
+// src null: the image is in place.
+struct Upload {
+    const unsigned char *src;
+    unsigned char *dst;
+    uint32_t copy_bytes, zero_from, zero_bytes;
+};
+
+// Word of a walk launch's counters that holds its start (and, top-k, the word
+// after it its end), in ticks of the device clock.
+constexpr int kClockWord = 1;
 
 // Fold, check and (float32) scale the caller's device matrix dQ (n x n,
 // row-major, int32 or float32) into the instance's upper-triangular int32 T
@@ -198,7 +215,7 @@ struct FinalRes {
 // descriptor's split A, B already set; int32 walk only).  On an input error
 // T is left zero and the status says why.
 hipError_t launch_prepare(const void *dQ, int n, int is_fp32, int32_t *d_T, PrepOut *d_prep,
-                          Inst *d_inst, hipStream_t stream);
+                          Inst *d_inst, const Upload &up, hipStream_t stream);
 
 // Item counters of one walk launch: kQueues of them, kQueueStride words apart.
 // Wave b walks item b first, without a claim, and then claims from queue b mod
@@ -216,10 +233,11 @@ constexpr int kCounterWords = kQueues * kQueueStride;
 constexpr int kStealSteps = 12;
 
 // Builds ML, EB, S, K for every instance, clears each instance's item bitmap,
-// lowers its shared best by greedy descents (over an uploaded kNoEnergy), and
-// zeroes the item counters of n_groups walk launches (kCounterWords each).
+// sets its shared best (to the energy of greedy descents), and zeroes the item
+// counters of n_groups walk launches (kCounterWords each).  With up.src (one
+// instance) the descriptor and T are read there.
 hipError_t launch_tables(const Inst *d_insts, int n_inst, unsigned long long *d_counters,
-                         int n_groups, hipStream_t stream);
+                         int n_groups, const Upload &up, hipStream_t stream);
 
 // Persistent Gray walk over all items (d_counter: the launch's kCounterWords
 // zeroed words, max_L: log2 of the longest item's steps); `waves` resident wavefronts.  d_k is
@@ -264,11 +282,16 @@ hipError_t launch_topk_seed(const Inst *d_inst, int32_t *d_gthr, int k, hipStrea
 // and write buf.out and *d_best (status 3: an energy did not verify; 4:
 // fewer than k states).
 hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs &buf, int k,
-                              FinalRes *d_best, hipStream_t stream);
+                              FinalRes *d_best, unsigned long long *d_counters,
+                              hipStream_t stream);
 
 // Per-instance reduction of item results (insts[i].res[0..n_items)), argmin
 // rescan (or direct evaluation for tiny n) and float64 rescoring; one
-// FinalRes per descriptor.
-hipError_t launch_finish(const Inst *d_insts, int n_inst, FinalRes *d_out, hipStream_t stream);
+// FinalRes per descriptor.  up.src (a direct instance, whose first kernel this
+// is): the descriptor, T and Q are read there.  d_counters: the walk's (its
+// start time), or null.  prep_out: receives the instance's preparation, or null.
+hipError_t launch_finish(const Inst *d_insts, int n_inst, FinalRes *d_out, const Upload &up,
+                         const unsigned long long *d_counters, PrepOut *prep_out,
+                         hipStream_t stream);
 
 }  // namespace qk

@@ -47,12 +47,12 @@ namespace qk {
 // ---------------------------------------------------------------- tables
 
 // Greedy single-flip descents from two starts per wave (the all-zero state
-// for wave 0's first start, hashed states otherwise), lowering the
-// instance's shared best to the energy of the local minima found.  Any
+// for wave 0's first start, hashed states otherwise); the block's least
+// energy becomes the instance's shared best.  Any
 // state's energy is a valid threshold for the walk (the state's own chunk
 // still passes it), and a local minimum of a dense QUBO is usually close to
 // the global one, so walk waves start with a near-final threshold.
-__device__ void seed_best(const int32_t *S, int n, int32_t *gbest, int wave)
+__device__ int32_t seed_best(const int32_t *S, int n, int wave)
 {
     int32_t bestE = kNoEnergy;
     for (int rep = 0; rep < 2; rep++) {
@@ -61,7 +61,18 @@ __device__ void seed_best(const int32_t *S, int n, int32_t *gbest, int wave)
         greedy_descent(S, n, uint32_t(wave) * 2u + uint32_t(rep), E, xm);
         bestE = min(bestE, E);
     }
-    if (int(threadIdx.x) % kWave == 0) atomicMin(gbest, bestE);
+    return bestE;
+}
+
+// The first kernel of a lone solve copies its host image (see Upload).
+__device__ void upload(const Upload &up, int tid, int threads)
+{
+    const uint4 *src = reinterpret_cast<const uint4 *>(up.src);
+    uint4 *dst = reinterpret_cast<uint4 *>(up.dst);
+    for (uint32_t x = uint32_t(tid); x < up.copy_bytes / 16; x += uint32_t(threads)) dst[x] = src[x];
+    uint4 *z = reinterpret_cast<uint4 *>(up.dst + up.zero_from);
+    for (uint32_t x = uint32_t(tid); x < up.zero_bytes / 16; x += uint32_t(threads))
+        z[x] = uint4{0, 0, 0, 0};
 }
 
 // One block per (instance, part of its tables), blockIdx.x naming the part.
@@ -72,16 +83,25 @@ __device__ void seed_best(const int32_t *S, int n, int32_t *gbest, int wave)
 // Measured: a lone build 9-16 us and 4096 batch instances 132 us; 60-92 us and
 // 950 us when 8 blocks per instance wrote the whole M_int (2A x 2^B words) and
 // reduced the bound constants over its columns.
-enum { kPartSeed = 0, kPartK, kPartEB, kPartRows, kTableParts };
+enum { kPartSeed = 0, kPartK, kPartEB, kPartRows, kTableParts, kPartUpload = kTableParts };
 constexpr int kTableThreads = 256;
 
 __global__ __launch_bounds__(kTableThreads) void tables_kernel(
-    const Inst *__restrict__ insts, unsigned long long *__restrict__ counters, int n_groups)
+    const Inst *__restrict__ insts, unsigned long long *__restrict__ counters, int n_groups,
+    Upload up)
 {
     __shared__ int32_t sS[kMaxVars * kMaxVars];   // T made symmetric
-    const Inst I = insts[blockIdx.y];
+    __shared__ int32_t sSeed;
     const int part = int(blockIdx.x);
     const int tid = int(threadIdx.x);
+    if (part == kPartUpload) {
+        upload(up, tid, kTableThreads);
+        return;
+    }
+    const Inst I = up.src ? *reinterpret_cast<const Inst *>(up.src) : insts[blockIdx.y];
+    const int32_t *T = up.src ? reinterpret_cast<const int32_t *>(
+                                    reinterpret_cast<const unsigned char *>(I.T) - up.dst + up.src)
+                              : I.T;
     if (part == kPartSeed && blockIdx.y == 0) {
         for (int c = tid; c < n_groups * kCounterWords; c += kTableThreads) counters[c] = 0;
     }
@@ -94,10 +114,11 @@ __global__ __launch_bounds__(kTableThreads) void tables_kernel(
     for (int e = tid; e < n * n; e += kTableThreads) {
         const int i = e / n, j = e % n;
         if (i > j) continue;
-        const int32_t t = I.T[e];
+        const int32_t t = T[e];
         sS[e] = t;
         sS[j * n + i] = t;
     }
+    if (tid == 0) sSeed = kNoEnergy;
     __syncthreads();
     const int MC = 1 << (I.packed ? B - 7 : B - 6);   // words per lane
     // Packed words: a part x shared by both columns is x in each half, and
@@ -107,8 +128,15 @@ __global__ __launch_bounds__(kTableThreads) void tables_kernel(
     if (part == kPartSeed) {
         // (only when the walk covers every state: a restricted item range must
         // not start from an energy found outside it)
-        if (I.gbest && I.item_local0 == 0 && I.n_items == (uint64_t(1) << (A - I.L)))
-            seed_best(sS, n, I.gbest, tid / kWave);
+        if (I.item_local0 == 0 && I.n_items == (uint64_t(1) << (A - I.L))) {
+            const int32_t E = seed_best(sS, n, tid / kWave);
+            if (tid % kWave == 0) atomicMin(&sSeed, E);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            *I.gbest = sSeed;
+            if (n_groups > 0 && blockIdx.y == 0) counters[kClockWord] = wall_clock64();
+        }
     } else if (part == kPartRows) {
         for (int e = tid; e < A * kWave; e += kTableThreads) {
             const int v = e / kWave, l = e % kWave;
@@ -255,7 +283,7 @@ __device__ __forceinline__ int prep_scale_exponent(double S)
 __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__restrict__ dQ, int n,
                                                                int is_fp32, int32_t *__restrict__ T,
                                                                PrepOut *__restrict__ out,
-                                                               Inst *__restrict__ inst)
+                                                               Inst *__restrict__ inst, Upload up)
 {
     __shared__ double sTd[kMaxVars * kMaxVars];   // folded float32 input in float64
     __shared__ int32_t sTi[kMaxVars * kMaxVars];  // the int32 T written to T
@@ -265,6 +293,9 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
     __shared__ int sNnz, sBad;
     __shared__ double sS;
     const int tid = int(threadIdx.x), nn = n * n;
+    const Inst &hI = up.src ? *reinterpret_cast<const Inst *>(up.src) : *inst;
+    const int A = hI.A, B = hI.B, direct = hI.direct;
+    if (up.src) upload(up, tid, kPrepThreads);
     if (tid == 0) {
         sSum = 0ull;
         sNnz = 0;
@@ -342,8 +373,7 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
     // E_sd(s, x_p) = E_s(s) + sum_v x_v M[v][s] is at least E_s(s) + the
     // negative M[v][s], so the least is the minimum of that over the 2^B
     // columns (the host planner's rule, with the same int32 bound).
-    const int A = inst->A, B = inst->B;
-    const bool walked = !inst->direct && status == 0;
+    const bool walked = !direct && status == 0;
     if (tid == 0) sLo = LLONG_MAX;
     __syncthreads();
     // M[v][s] as the table build forms it: the partial sums over the five
@@ -448,9 +478,11 @@ __device__ void block_lexmin(int32_t &E, uint64_t &I, int32_t *sE, uint64_t *sI)
 // serial gather of the rescore: n = 12 direct 29 -> 6.6 us, lone walked int32
 // 17-21 -> 6.6-12 us, float32 31-50 -> 10-18 us; 1000 float32 instances 163 ->
 // 16 us, 4096 int32 ones 184 -> 21 us.
-__global__ __launch_bounds__(kFinishThreads) void finish_kernel(const Inst *__restrict__ insts,
-                                                                FinalRes *__restrict__ out)
+__global__ __launch_bounds__(kFinishThreads) void finish_kernel(
+    const Inst *__restrict__ insts, FinalRes *__restrict__ out, Upload up,
+    const unsigned long long *__restrict__ counters, PrepOut *__restrict__ prep_out)
 {
+    const unsigned long long now = wall_clock64();
     __shared__ int32_t sE[kFinishWaves];
     __shared__ uint64_t sI[kFinishWaves];
     __shared__ int32_t sH[16];                    // suffix fields of the winning chunk
@@ -459,7 +491,14 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(const Inst *__re
     __shared__ int32_t sHigh[1 << kDirectHigh];   // direct: energies of the high patterns
     // T made symmetric, and later the float32 entries the rescore adds up
     __shared__ int32_t sS[kMaxVars * kMaxVars];
-    const Inst I = insts[blockIdx.x];
+    Inst I = up.src ? *reinterpret_cast<const Inst *>(up.src) : insts[blockIdx.x];
+    if (up.src) {   // T and Q of the host image
+        I.T = reinterpret_cast<const int32_t *>(reinterpret_cast<const unsigned char *>(I.T) - up.dst +
+                                                up.src);
+        if (I.Qf)
+            I.Qf = reinterpret_cast<const float *>(reinterpret_cast<const unsigned char *>(I.Qf) -
+                                                   up.dst + up.src);
+    }
     const int n = I.n, tid = int(threadIdx.x), w = tid / kWave, l = tid % kWave;
     for (int e = tid; e < n * n; e += kFinishThreads) {
         const int i = e / n, j = e % n;
@@ -647,26 +686,29 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(const Inst *__re
         o.E64 = E64;
         o.status = status;
         o.pad = 0;
+        o.walk_ticks = counters ? now - counters[kClockWord] : 0;
         out[blockIdx.x] = o;
+        if (prep_out) *prep_out = *I.prep;
     }
 }
 
 // ---------------------------------------------------------------- launchers
 
 hipError_t launch_prepare(const void *dQ, int n, int is_fp32, int32_t *d_T, PrepOut *d_prep,
-                          Inst *d_inst, hipStream_t stream)
+                          Inst *d_inst, const Upload &up, hipStream_t stream)
 {
     if (n < 1 || n > kMaxVars) return hipErrorInvalidValue;
     hipLaunchKernelGGL(prepare_kernel, dim3(1), dim3(kPrepThreads), 0, stream, dQ, n, is_fp32, d_T,
-                       d_prep, d_inst);
+                       d_prep, d_inst, up);
     return hipGetLastError();
 }
 
 hipError_t launch_tables(const Inst *d_insts, int n_inst, unsigned long long *d_counters,
-                         int n_groups, hipStream_t stream)
+                         int n_groups, const Upload &up, hipStream_t stream)
 {
-    hipLaunchKernelGGL(tables_kernel, dim3(kTableParts, n_inst), dim3(kTableThreads), 0, stream,
-                       d_insts, d_counters, n_groups);
+    if (up.src && n_inst != 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(tables_kernel, dim3(up.src ? kTableParts + 1 : kTableParts, n_inst),
+                       dim3(kTableThreads), 0, stream, d_insts, d_counters, n_groups, up);
     return hipGetLastError();
 }
 
@@ -719,9 +761,13 @@ hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts
     return mcols <= 4 ? launch_walk_g12(mcols, w) : launch_walk_g12w(mcols, w);
 }
 
-hipError_t launch_finish(const Inst *d_insts, int n_inst, FinalRes *d_out, hipStream_t stream)
+hipError_t launch_finish(const Inst *d_insts, int n_inst, FinalRes *d_out, const Upload &up,
+                         const unsigned long long *d_counters, PrepOut *prep_out,
+                         hipStream_t stream)
 {
-    hipLaunchKernelGGL(finish_kernel, dim3(n_inst), dim3(kFinishThreads), 0, stream, d_insts, d_out);
+    if (up.src && n_inst != 1) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(finish_kernel, dim3(n_inst), dim3(kFinishThreads), 0, stream, d_insts, d_out,
+                       up, d_counters, prep_out);
     return hipGetLastError();
 }
 

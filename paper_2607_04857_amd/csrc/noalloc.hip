@@ -27,7 +27,6 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 struct DeviceScratch {
     bool ready = false;
     void *ptr = nullptr;           // device address of `scratch` on this device
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;   // walk timing, made once per device
 };
 
 std::mutex g_mu;
@@ -49,8 +48,6 @@ qubo_status_t scratch_for_device(int dev, DeviceScratch **out)
             qrt::set_error("hipGetSymbolAddress(scratch) returned a null address");
             return QUBO_EDEVICE;
         }
-        QRT_HIP(hipEventCreate(&d.ev0), "hipEventCreate");
-        QRT_HIP(hipEventCreate(&d.ev1), "hipEventCreate");
         d.ptr = p;
         d.ready = true;
     }
@@ -99,7 +96,7 @@ qubo_status_t solve_noalloc(const void *Q, int n, qubo_dtype_t dtype, hipStream_
             st = qrt::device_error("hipMemcpyAsync H2D", e);
             break;
         }
-        if ((st = qrt::job_enqueue_kernels(job, stream, ds->ev0, ds->ev1)) != QUBO_OK) break;
+        if ((st = qrt::job_enqueue_kernels(job, stream)) != QUBO_OK) break;
         e = hipMemcpyAsync(&fr, job.d_out, sizeof(fr), hipMemcpyDeviceToHost, stream);
         if (e != hipSuccess) st = qrt::device_error("hipMemcpyAsync D2H", e);
     } while (false);
@@ -107,11 +104,9 @@ qubo_status_t solve_noalloc(const void *Q, int n, qubo_dtype_t dtype, hipStream_
     const hipError_t es = hipStreamSynchronize(stream);
     if (st != QUBO_OK) return st;
     if (es != hipSuccess) return qrt::device_error("hipStreamSynchronize", es);
-    float ms = 0.f;
-    (void)hipEventElapsedTime(&ms, ds->ev0, ds->ev1);
     st = qrt::job_result(job, 0, fr, out);
     if (st != QUBO_OK) return st;
-    out->kernel_ms = ms;
+    out->kernel_ms = qrt::walk_ms(fr.walk_ticks);
     out->total_ms = std::chrono::duration<double, std::milli>(clock::now() - t0).count();
     return QUBO_OK;
 }

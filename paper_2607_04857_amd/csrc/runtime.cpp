@@ -63,13 +63,22 @@ qubo_status_t device_info(DeviceInfo *info)
 // Layout helpers kept in one translation unit with the job code.
 namespace qrt {
 
-static JobOffsets compute_offsets(const Job &job, size_t *stage_bytes, size_t *bytes)
+// Sets the job's byte counts too.
+static JobOffsets compute_offsets(Job &job)
 {
     JobOffsets o;
     const size_t ni = job.plans.size();
+    const size_t k = size_t(job.topk);
     size_t off = 0;
     o.insts = off;
     off = align_up(off + ni * sizeof(qk::Inst), 256);
+    if (k > 1) {   // the shared top-k bound and lowest bin
+        o.gthr = off;
+        off = align_up(off + sizeof(int32_t), 256);
+        o.lowbin = off;
+        off = align_up(off + 2 * sizeof(int32_t), 256);
+    }
+    job.head_bytes = off;
     for (size_t i = 0; i < ni; i++) {
         const size_t nn = size_t(job.plans[i].n) * job.plans[i].n;
         o.T.push_back(off);
@@ -81,20 +90,16 @@ static JobOffsets compute_offsets(const Job &job, size_t *stage_bytes, size_t *b
             o.Qf.push_back(size_t(-1));
         }
     }
-    o.gbest = off;   // the shared bests start at kNoEnergy in the uploaded image
-    off = align_up(off + ni * sizeof(int32_t), 256);
-    const size_t k = size_t(job.topk);
-    if (k > 1) {   // the shared top-k bound and histogram start in the uploaded image
-        o.gthr = off;
-        off = align_up(off + sizeof(int32_t), 256);
-        o.lowbin = off;
-        off = align_up(off + 2 * sizeof(int32_t), 256);
+    job.stage_bytes = off;
+    if (k > 1) {
         o.candN = off;
         off = align_up(off + sizeof(int32_t), 256);
         o.hist = off;
         off = align_up(off + qk::kTopkBins * sizeof(uint32_t), 256);
     }
-    *stage_bytes = off;
+    job.zero_bytes = off - job.stage_bytes;
+    o.gbest = off;
+    off = align_up(off + ni * sizeof(int32_t), 256);
     o.counter = off;
     off = align_up(off + std::max<size_t>(1, job.groups.size()) * qk::kCounterWords * sizeof(unsigned long long), 256);
     for (size_t i = 0; i < ni; i++) {
@@ -126,6 +131,12 @@ static JobOffsets compute_offsets(const Job &job, size_t *stage_bytes, size_t *b
     o.prep = off;
     off = align_up(off + sizeof(qk::PrepOut), 256);
     if (k > 1) {
+        o.topk = off;
+        off = align_up(off + k * sizeof(qk::TopkState), 256);
+    }
+    job.result_from = o.out;
+    job.result_bytes = off - o.out;
+    if (k > 1) {
         const qplan::Plan &P = job.plans[0];
         const size_t W = job.groups.empty() ? 0 : size_t(job.groups[0].waves);
         const size_t nst = P.direct ? (size_t(1) << P.n) : (k << P.B);
@@ -147,9 +158,8 @@ static JobOffsets compute_offsets(const Job &job, size_t *stage_bytes, size_t *b
         put(&o.selE, k * sizeof(int32_t));
         put(&o.selR, k * sizeof(uint64_t));
         put(&o.selCount, sizeof(int32_t));
-        put(&o.topk, k * sizeof(qk::TopkState));
     }
-    *bytes = off;
+    job.bytes = off;
     return o;
 }
 
@@ -202,21 +212,17 @@ qubo_status_t job_layout(Job *job, int waves_per_cu)
         if (g.items < waves) waves = g.items;
         g.waves = int(waves);
     }
-    size_t sb = 0, b = 0;
-    (void)compute_offsets(*job, &sb, &b);
-    job->stage_bytes = sb;
-    job->bytes = b;
+    (void)compute_offsets(*job);
     return QUBO_OK;
 }
 
 // Fill the staging image and device pointers for allocation d_mem.
 qubo_status_t job_bind(Job *job, void *d_mem)
 {
-    size_t sb = 0, b = 0;
-    JobOffsets o = compute_offsets(*job, &sb, &b);
+    JobOffsets o = compute_offsets(*job);
     unsigned char *base = static_cast<unsigned char *>(d_mem);
     job->d_mem = d_mem;
-    job->stage.assign(sb, 0);
+    job->stage.assign(job->stage_bytes, 0);
     job->d_insts = reinterpret_cast<qk::Inst *>(base + o.insts);
     job->d_counter = reinterpret_cast<unsigned long long *>(base + o.counter);
     job->d_res = reinterpret_cast<qk::ItemRes *>(base + o.res);
@@ -273,8 +279,6 @@ qubo_status_t job_bind(Job *job, void *d_mem)
         if (job->qf[i]) std::memcpy(job->stage.data() + o.Qf[i], job->qf[i], nn * sizeof(float));
     }
     std::memcpy(job->stage.data() + o.insts, insts.data(), insts.size() * sizeof(qk::Inst));
-    std::fill_n(reinterpret_cast<int32_t *>(job->stage.data() + o.gbest), insts.size(),
-                qk::kNoEnergy);
     if (job->topk > 1) {
         const int32_t none = qk::kNoEnergy, nobin = qk::kTopkBins;
         std::memcpy(job->stage.data() + o.gthr, &none, sizeof(none));
@@ -313,18 +317,35 @@ qubo_status_t job_bind(Job *job, void *d_mem)
     return QUBO_OK;
 }
 
-qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, hipEvent_t walk_begin,
-                                  hipEvent_t walk_end)
+qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, const unsigned char *image,
+                                  LoneResults *results)
 {
     const int ni = int(job.plans.size());
-    if (job.dq)
+    const qk::Upload none{};
+    qk::Upload up{};
+    if (image) {
+        up.src = image;
+        up.dst = static_cast<unsigned char *>(job.d_mem);
+        // (a device-prepared instance's T is written by the preparation)
+        up.copy_bytes = uint32_t(job.dq ? job.head_bytes : job.stage_bytes);
+        up.zero_from = uint32_t(job.stage_bytes);
+        up.zero_bytes = uint32_t(job.zero_bytes);
+    }
+    const bool walks = !job.groups.empty();
+    unsigned long long *const counters = walks ? job.d_counter : nullptr;
+    if (job.dq) {
         QRT_HIP(qk::launch_prepare(job.dq, job.plans[0].n, job.plans[0].dtype == QUBO_FP32 ? 1 : 0,
-                                   job.d_T0, job.d_prep, job.d_insts, stream),
+                                   job.d_T0, job.d_prep, job.d_insts, up, stream),
                 "prepare kernel");
-    if (!job.groups.empty())   // direct instances need no tables
-        QRT_HIP(qk::launch_tables(job.d_insts, ni, job.d_counter, int(job.groups.size()), stream),
+        up = none;   // the image is in place
+    }
+    // direct instances need no tables; a direct k = 1 solve's only kernel is
+    // the finish, which then reads the image
+    if (walks || (up.src && job.topk > 1)) {
+        QRT_HIP(qk::launch_tables(job.d_insts, ni, job.d_counter, int(job.groups.size()), up, stream),
                 "tables kernel");
-    if (walk_begin) QRT_HIP(hipEventRecord(walk_begin, stream), "hipEventRecord");
+        up = none;
+    }
     if (job.topk > 1) {
         // a bound of the k-th smallest chunk key from states near a local
         // minimum, when the walk covers every chunk (timed with the walk)
@@ -336,17 +357,28 @@ qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, hipEvent_t
     for (size_t k = 0; k < job.groups.size(); k++) {
         const WalkGroup &g = job.groups[k];
         QRT_HIP(qk::launch_walk(g.mcols, g.vgpr_levels, g.tier, job.d_insts + g.first, g.count,
-                                g.items, g.max_L, job.d_counter + k * qk::kCounterWords, job.d_k, g.waves, stream,
-                                job.topk > 1 ? &job.tkb.walk : nullptr),
+                                g.items, g.max_L, job.d_counter + k * qk::kCounterWords, job.d_k,
+                                g.waves, stream, job.topk > 1 ? &job.tkb.walk : nullptr),
                 "walk kernel");
     }
-    if (walk_end) QRT_HIP(hipEventRecord(walk_end, stream), "hipEventRecord");
     if (job.topk > 1)
-        QRT_HIP(qk::launch_topk_finish(job.d_insts, job.h_inst0, job.tkb, job.topk, job.d_out, stream),
+        QRT_HIP(qk::launch_topk_finish(job.d_insts, job.h_inst0, job.tkb, job.topk, job.d_out, counters,
+                                       stream),
                 "top-k kernels");
     else
-        QRT_HIP(qk::launch_finish(job.d_insts, ni, job.d_out, stream), "finish kernel");
+        QRT_HIP(qk::launch_finish(job.d_insts, ni, results ? &results->best : job.d_out, up, counters,
+                                  results && job.dq ? &results->prep : nullptr, stream),
+                "finish kernel");
     return QUBO_OK;
+}
+
+double walk_ms(uint64_t ticks)
+{
+    int dev = 0, khz = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) != hipSuccess || khz <= 0)
+        khz = 100000;
+    return double(ticks) / khz;
 }
 
 qubo_status_t job_result(const Job &job, int i, const qk::FinalRes &fr, qubo_result_t *out)
@@ -399,62 +431,140 @@ hipStream_t thread_stream(qubo_status_t *st)
     return s;
 }
 
+namespace {
+
+// Device memory and a mapped host block that a thread keeps between its lone
+// solves (an allocation, its release and the runtime's trimming at each
+// synchronisation cost more than a small solve: 10 us, and milliseconds for
+// the 110 MB of a k = 1024 solve's lists).  A call has them to itself and is
+// synchronous, so the next one may use another stream.  At most kKeepBytes of
+// device memory are kept; larger jobs allocate their own.  Given back when
+// the thread ends, and when it goes on with another device.
+constexpr size_t kKeepBytes = size_t(128) << 20;
+
+struct Workspace {
+    int dev = -1;
+    unsigned char *mem = nullptr, *host = nullptr, *host_dev = nullptr;
+    size_t mem_bytes = 0, host_bytes = 0;
+
+    void release_mem()
+    {
+        if (mem) (void)hipFree(mem);
+        mem = nullptr;
+        mem_bytes = 0;
+    }
+    void release_host()
+    {
+        if (host) (void)hipHostFree(host);
+        host = host_dev = nullptr;
+        host_bytes = 0;
+    }
+    void release()
+    {
+        release_mem();
+        release_host();
+    }
+    // At least `need` bytes of device memory and of mapped host memory; either
+    // stays null where it cannot be had (the call then does without it).
+    void reserve(int device, size_t need, size_t host_need)
+    {
+        if (dev != device) release();
+        dev = device;
+        if (need <= mem_bytes && host_need <= host_bytes) return;
+        // allocation is legal while another stream of the thread captures
+        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+        if (need > mem_bytes && need <= kKeepBytes) {
+            release_mem();
+            const size_t b = align_up(need, size_t(1) << 20);
+            void *p = nullptr;
+            if (hipMalloc(&p, b) == hipSuccess) {
+                mem = static_cast<unsigned char *>(p);
+                mem_bytes = b;
+            } else {
+                (void)hipGetLastError();
+            }
+        }
+        if (host_need > host_bytes) {
+            release_host();
+            const size_t b = align_up(host_need, size_t(64) << 10);
+            void *p = nullptr, *d = nullptr;
+            if (hipHostMalloc(&p, b, hipHostMallocMapped) == hipSuccess) {
+                if (hipHostGetDevicePointer(&d, p, 0) == hipSuccess) {
+                    host = static_cast<unsigned char *>(p);
+                    host_dev = static_cast<unsigned char *>(d);
+                    host_bytes = b;
+                } else {
+                    (void)hipHostFree(p);
+                }
+            }
+            if (!host) (void)hipGetLastError();
+        }
+        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+    ~Workspace() { release(); }
+};
+
+thread_local Workspace g_workspace;
+
+}  // namespace
+
 qubo_status_t solve_planned(qrt::Job &job, hipStream_t stream, int waves_per_cu, qubo_result_t *out,
                             qubo_state_t *topk)
 {
     using clock = std::chrono::steady_clock;
     const auto t0 = clock::now();
+    static_assert(sizeof(qk::TopkState) == sizeof(qubo_state_t), "top-k state layout");
     qubo_status_t st = qrt::job_layout(&job, waves_per_cu);
     if (st != QUBO_OK) return st;
-    void *d_mem = nullptr;
-    QRT_HIP(hipMallocAsync(&d_mem, job.bytes, stream), "hipMallocAsync");
-    hipEvent_t ev0 = nullptr, ev1 = nullptr;
+    DeviceInfo di;
+    if ((st = device_info(&di)) != QUBO_OK) return st;
+    Workspace &ws = g_workspace;
+    ws.reserve(di.device, job.bytes, job.stage_bytes + job.result_bytes);
+    const bool kept = ws.mem_bytes >= job.bytes;
+    const bool mapped = ws.host_bytes >= job.stage_bytes + job.result_bytes;
+    std::vector<LoneResults> pageable(mapped ? 0 : job.result_bytes / sizeof(LoneResults) + 1);
+    unsigned char *const result = mapped ? ws.host + job.stage_bytes
+                                         : reinterpret_cast<unsigned char *>(pageable.data());
+    void *d_mem = ws.mem;
+    if (!kept) QRT_HIP(hipMallocAsync(&d_mem, job.bytes, stream), "hipMallocAsync");
     qubo_status_t rs = QUBO_OK;
-    qk::FinalRes fr{};
-    qk::PrepOut prep{};
-    std::vector<qk::TopkState> tk_host;
     do {
         if ((rs = qrt::job_bind(&job, d_mem)) != QUBO_OK) break;
         hipError_t e;
-        if ((e = hipEventCreate(&ev0)) != hipSuccess || (e = hipEventCreate(&ev1)) != hipSuccess) {
-            rs = qrt::device_error("hipEventCreate", e);
-            break;
-        }
-        if ((e = hipMemcpyAsync(d_mem, job.stage.data(), job.stage_bytes, hipMemcpyHostToDevice,
-                                stream)) != hipSuccess) {
-            rs = qrt::device_error("hipMemcpyAsync H2D", e);
-            break;
-        }
-        if ((rs = qrt::job_enqueue_kernels(job, stream, ev0, ev1)) != QUBO_OK) break;
-        if ((e = hipMemcpyAsync(&fr, job.d_out, sizeof(fr), hipMemcpyDeviceToHost, stream)) !=
-            hipSuccess) {
-            rs = qrt::device_error("hipMemcpyAsync D2H", e);
-            break;
-        }
-        if (job.dq && (e = hipMemcpyAsync(&prep, job.d_prep, sizeof(prep), hipMemcpyDeviceToHost,
-                                          stream)) != hipSuccess) {
-            rs = qrt::device_error("hipMemcpyAsync D2H preparation", e);
-            break;
-        }
-        if (job.topk > 1) {
-            static_assert(sizeof(qk::TopkState) == sizeof(qubo_state_t), "top-k state layout");
-            tk_host.resize(size_t(job.topk));
-            if ((e = hipMemcpyAsync(tk_host.data(), job.tkb.out, tk_host.size() * sizeof(qk::TopkState),
-                                    hipMemcpyDeviceToHost, stream)) != hipSuccess) {
-                rs = qrt::device_error("hipMemcpyAsync D2H top-k", e);
+        LoneResults *direct_out = nullptr;   // k = 1: the finish writes the host block itself
+        if (mapped) {
+            std::memcpy(ws.host, job.stage.data(), job.stage_bytes);
+            if (job.topk <= 1)
+                direct_out = reinterpret_cast<LoneResults *>(ws.host_dev + job.stage_bytes);
+        } else {
+            // the image by copies (the part that starts out zero with it)
+            job.stage.resize(job.stage_bytes + job.zero_bytes, 0);
+            if ((e = hipMemcpyAsync(d_mem, job.stage.data(), job.stage.size(), hipMemcpyHostToDevice,
+                                    stream)) != hipSuccess) {
+                rs = qrt::device_error("hipMemcpyAsync H2D", e);
                 break;
             }
         }
+        rs = qrt::job_enqueue_kernels(job, stream, mapped ? ws.host_dev : nullptr, direct_out);
+        if (rs != QUBO_OK) break;
+        if (!direct_out &&
+            (e = hipMemcpyAsync(result, static_cast<unsigned char *>(d_mem) + job.result_from,
+                                job.result_bytes, hipMemcpyDeviceToHost, stream)) != hipSuccess) {
+            rs = qrt::device_error("hipMemcpyAsync D2H", e);
+            break;
+        }
     } while (false);
-    hipError_t ef = hipFreeAsync(d_mem, stream);
+    hipError_t ef = kept ? hipSuccess : hipFreeAsync(d_mem, stream);
     hipError_t es = hipStreamSynchronize(stream);
-    float ms = 0.f;
-    if (rs == QUBO_OK && es == hipSuccess) (void)hipEventElapsedTime(&ms, ev0, ev1);
-    if (ev0) (void)hipEventDestroy(ev0);
-    if (ev1) (void)hipEventDestroy(ev1);
+    if (es != hipSuccess) ws.release();   // never reuse memory that work may still hold
     if (rs != QUBO_OK) return rs;
     if (es != hipSuccess) return qrt::device_error("hipStreamSynchronize", es);
     if (ef != hipSuccess) return qrt::device_error("hipFreeAsync", ef);
+    const LoneResults &lone = *reinterpret_cast<const LoneResults *>(result);
+    const qk::FinalRes &fr = lone.best;
+    const qk::PrepOut &prep = lone.prep;
+    const qk::TopkState *tk_host = lone.topk;
     if (job.dq) {
         // the device preparation's outcome for the input, as the host planner's
         switch (prep.status) {
@@ -479,12 +589,12 @@ qubo_status_t solve_planned(qrt::Job &job, hipStream_t stream, int waves_per_cu,
     if (job.topk > 1 && topk) {
         const bool fp = job.plans[0].dtype == QUBO_FP32;
         for (int i = 0; i < job.topk; i++) {
-            topk[i].energy_i = tk_host[size_t(i)].E;
-            topk[i].index = tk_host[size_t(i)].index;
-            topk[i].energy = fp ? tk_host[size_t(i)].E64 : double(tk_host[size_t(i)].E);
+            topk[i].energy_i = tk_host[i].E;
+            topk[i].index = tk_host[i].index;
+            topk[i].energy = fp ? tk_host[i].E64 : double(tk_host[i].E);
         }
     }
-    out->kernel_ms = ms;
+    out->kernel_ms = walk_ms(fr.walk_ticks);
     out->total_ms = std::chrono::duration<double, std::milli>(clock::now() - t0).count();
     return QUBO_OK;
 }

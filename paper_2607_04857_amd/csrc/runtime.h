@@ -53,6 +53,9 @@ struct Job {
     void *d_mem = nullptr;
     size_t bytes = 0;
     size_t stage_bytes = 0;              // leading part of d_mem uploaded from the host
+    size_t zero_bytes = 0;               // and the part after it that starts out zero
+    size_t head_bytes = 0;               // the image without the matrices (T, Q) at its end
+    size_t result_from = 0, result_bytes = 0;   // FinalRes, PrepOut and the top-k states
     std::vector<unsigned char> stage;    // insts | T... | Qf... (pinned copy in Batch)
     qk::Inst *d_insts = nullptr;
     unsigned long long *d_counter = nullptr;   // kCounterWords per group
@@ -79,11 +82,24 @@ qubo_status_t job_layout(Job *job, int waves_per_cu);
 // host staging image (instance descriptors, T and float32 Q).
 qubo_status_t job_bind(Job *job, void *d_mem);
 
+// Results of a lone solve as the device lays them out (from result_from on).
+struct LoneResults {
+    alignas(256) qk::FinalRes best;
+    alignas(256) qk::PrepOut prep;
+    alignas(256) qk::TopkState topk[1];   // as many as were asked for
+};
+
 // Enqueue tables -> walk (one launch per group) -> finish on `stream` (device
-// memory must exist and the staging image must already be uploaded).
-// Optional events bracket the walk launches.
-qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, hipEvent_t walk_begin,
-                                  hipEvent_t walk_end);
+// memory must exist).  image: device address of a mapped host block holding
+// the staging image, which the first kernel reads, or null once the image has
+// been copied into place.  results: device address of a mapped host block for
+// the results of a lone k = 1 solve, or null to leave them in device memory.
+qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream,
+                                  const unsigned char *image = nullptr,
+                                  LoneResults *results = nullptr);
+
+// Milliseconds of FinalRes::walk_ticks on the current device.
+double walk_ms(uint64_t ticks);
 
 // Whether two plans run the same walk kernel variant.
 bool same_variant(const qplan::Plan &a, const qplan::Plan &b);

@@ -210,7 +210,7 @@ qubo_status_t build_tables(qubo_server *s, const std::vector<Request *> &adm)
                                hipMemcpyDeviceToDevice, s->stream),
                 "hipMemcpyAsync descriptor");
     }
-    QRT_HIP(qk::launch_tables(s->d_setup, int(adm.size()), nullptr, 0, s->stream),
+    QRT_HIP(qk::launch_tables(s->d_setup, int(adm.size()), nullptr, 0, qk::Upload{}, s->stream),
             "tables kernel");
     return QUBO_OK;
 }
@@ -306,7 +306,9 @@ qubo_status_t enqueue_tick(qubo_server *s, TickBuf &t, bool *launched)
         QRT_HIP(hipMemcpyAsync(t.d_fin, t.h_fin, finishers.size() * sizeof(qk::Inst),
                                hipMemcpyHostToDevice, s->stream),
                 "hipMemcpyAsync finish");
-        QRT_HIP(qk::launch_finish(t.d_fin, int(finishers.size()), t.d_out, s->stream), "finish kernel");
+        QRT_HIP(qk::launch_finish(t.d_fin, int(finishers.size()), t.d_out, qk::Upload{}, nullptr, nullptr,
+                                  s->stream),
+                "finish kernel");
         QRT_HIP(hipMemcpyAsync(t.h_out, t.d_out, finishers.size() * sizeof(qk::FinalRes),
                                hipMemcpyDeviceToHost, s->stream),
                 "hipMemcpyAsync results");

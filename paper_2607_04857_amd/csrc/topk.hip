@@ -244,8 +244,10 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(const int32_t *__rest
                                                            const int32_t *__restrict__ bound,
                                                            int32_t *__restrict__ oE,
                                                            uint64_t *__restrict__ oR,
-                                                           int32_t *__restrict__ oN)
+                                                           int32_t *__restrict__ oN,
+                                                           unsigned long long *__restrict__ counters)
 {
+    if (counters && blockIdx.x == 0 && threadIdx.x == 0) counters[kClockWord + 1] = wall_clock64();
     const int lane = int(threadIdx.x) & (kWave - 1);
     const int list = int(blockIdx.x) * (256 / kWave) + int(threadIdx.x) / kWave;
     if (list >= nlists) return;
@@ -397,7 +399,8 @@ __global__ __launch_bounds__(256) void topk_direct_kernel(const Inst *__restrict
 __global__ __launch_bounds__(kWave) void topk_final_kernel(
     const Inst *__restrict__ inst, const int32_t *__restrict__ selE,
     const uint64_t *__restrict__ selR, const int32_t *__restrict__ selCount, int k,
-    TopkState *__restrict__ out, FinalRes *__restrict__ best)
+    TopkState *__restrict__ out, FinalRes *__restrict__ best,
+    const unsigned long long *__restrict__ counters)
 {
     __shared__ int32_t sT[kMaxVars * kMaxVars];
     __shared__ float sQ[kMaxVars * kMaxVars];
@@ -432,6 +435,7 @@ __global__ __launch_bounds__(kWave) void topk_final_kernel(
     if (at == 0) {
         best->E = cnt > 0 ? e : 0;
         best->index = idx;
+        best->walk_ticks = counters ? counters[kClockWord + 1] - counters[kClockWord] : 0;
         best->E64 = cnt > 0 ? (I.Qf ? energy_f64(sQ, n, idx) : double(e)) : 0.0;
         if (cnt < k) atomicMax(&best->status, 4);
     }
@@ -650,8 +654,10 @@ hipError_t launch_topk_seed(const Inst *d_inst, int32_t *d_gthr, int k, hipStrea
 }
 
 hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs &buf, int k,
-                              FinalRes *d_best, hipStream_t stream)
+                              FinalRes *d_best, unsigned long long *d_counters,
+                              hipStream_t stream)
 {
+    if (hI.direct) d_counters = nullptr;
     if (k < 2 || k > kSelThreads) return hipErrorInvalidValue;
     SelArgs st{};
     if (hI.direct) {
@@ -668,7 +674,7 @@ hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs
         if (blocks > 0)
             hipLaunchKernelGGL(topk_compact_kernel, dim3(blocks), dim3(256), 0, stream,
                                buf.walk.listE, buf.walk.listR, buf.walk.listCount, buf.waves, k,
-                               buf.walk.gthr, buf.candE, buf.candR, buf.candN);
+                               buf.walk.gthr, buf.candE, buf.candR, buf.candN, d_counters);
         SelArgs ch{};
         ch.E = buf.candE;
         ch.R = buf.candR;
@@ -695,7 +701,7 @@ hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs
     st.status = &d_best->status;
     hipLaunchKernelGGL(topk_select_kernel, dim3(1), dim3(kSelThreads), 0, stream, st);
     hipLaunchKernelGGL(topk_final_kernel, dim3((k + kWave - 1) / kWave), dim3(kWave), 0, stream,
-                       d_inst, buf.selE, buf.selR, buf.selCount, k, buf.out, d_best);
+                       d_inst, buf.selE, buf.selR, buf.selCount, k, buf.out, d_best, d_counters);
     if (hI.Qf)
         hipLaunchKernelGGL(topk_order_kernel, dim3(1), dim3(kSelThreads), 0, stream, buf.selCount, k,
                            buf.out, d_best);
