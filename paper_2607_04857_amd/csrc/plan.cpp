@@ -140,47 +140,73 @@ int64_t suffix_sum_abs(const Plan &P, int A)
     return s;
 }
 
-void chunk_energy_range(const Plan &P, int A, int64_t *lo, int64_t *hi)
+bool chunk_energy_range(const Plan &P, int A, int64_t *lo, int64_t *hi, int64_t most)
 {
+    // E_sd(s, x_p) = E_s(s) + sum_v x_v M[v][s]; over all prefixes x_p its
+    // extremes are E_s(s) + the sums of the negative / positive M[v][s], and
+    // the two sums add up to sum_v M[v][s].  Column s = 64 j + l: M[v][s] =
+    // ml[v][l] + mh[v][j], over the bits of l and of j (bit b <-> variable
+    // n-1-b).  Every value here is a partial sum of T, within 2^30: 32-bit
+    // arithmetic is exact and the loops over l run in vector registers (with
+    // 64-bit entries and an index per column a plan at n = 36 took 132 us,
+    // call and marshalling included, instead of 29).
+    constexpr size_t W = 64;
     const size_t nn = size_t(P.n);
     const int B = P.n - A;
-    const size_t NS = size_t(1) << B;
-    // E_sd(s, x_p) = E_s(s) + sum_v x_v M[v][s]; over all prefixes x_p its
-    // extremes are E_s(s) + the sums of the negative / positive M[v][s].
-    // Column s is a subset of the suffix variables (bit b <-> variable
-    // A + B-1-b); each array is filled from s with its lowest bit cleared.
-    std::vector<int64_t> es(NS, 0), neg(NS, 0), pos(NS, 0), m(NS, 0);
-    auto var = [&](size_t s) { return A + B - 1 - __builtin_ctzll(uint64_t(s)); };
-    for (size_t s = 1; s < NS; s++) {
-        const size_t r = s & (s - 1);
-        const size_t w = size_t(var(s));
-        int64_t e = es[r] + P.T[w * nn + w];
-        for (size_t q = r; q; q &= q - 1) {
-            const size_t u = size_t(var(q));
-            e += u < w ? P.T[u * nn + w] : P.T[w * nn + u];
+    const size_t NJ = size_t(1) << (B - 6);
+    auto T = [&](size_t i, size_t j) { return P.T[i * nn + j]; };   // i <= j
+    // out[x] = sum of row v's entries over the bits of x (bit b <-> n-1-b0-b)
+    auto subset = [&](size_t v, size_t b0, size_t bits, int32_t *out) {
+        out[0] = 0;
+        for (size_t b = 0; b < bits; b++) {
+            const int32_t t = T(v, nn - 1 - b0 - b);
+            for (size_t x = 0; x < (size_t(1) << b); x++) out[(size_t(1) << b) + x] = out[x] + t;
         }
-        es[s] = e;
+    };
+    std::vector<int32_t> ml(size_t(A) * W), mh(size_t(A) * NJ);
+    for (size_t v = 0; v < size_t(A); v++) {
+        subset(v, 0, 6, &ml[v * W]);
+        subset(v, 6, size_t(B - 6), &mh[v * NJ]);
     }
-    for (int v = 0; v < A; v++) {
-        m[0] = 0;
-        for (size_t s = 1; s < NS; s++) {
-            m[s] = m[s & (s - 1)] + P.T[size_t(v) * nn + size_t(var(s))];
-            (m[s] < 0 ? neg[s] : pos[s]) += m[s];
+    // E_s by its highest bit: that variable's diagonal plus its couplings with
+    // the lower bits (higher variables)
+    std::vector<int32_t> es(W * NJ, 0), c(W * NJ, 0);
+    for (size_t b = 0; b < size_t(B); b++) {
+        const size_t w = nn - 1 - b;
+        const int32_t d = T(w, w);
+        for (size_t u = 0; u < b; u++) {
+            const int32_t t = T(w, nn - 1 - u);
+            for (size_t x = 0; x < (size_t(1) << u); x++) c[(size_t(1) << u) + x] = c[x] + t;
         }
+        for (size_t x = 0; x < (size_t(1) << b); x++) es[(size_t(1) << b) + x] = es[x] + c[x] + d;
     }
-    int64_t l = INT64_MAX, h = INT64_MIN;
-    for (size_t s = 0; s < NS; s++) {
-        l = std::min(l, es[s] + neg[s]);
-        h = std::max(h, es[s] + pos[s]);
+    int32_t l = INT32_MAX, h = INT32_MIN;
+    for (size_t j = 0; j < NJ; j++) {
+        int32_t neg[W] = {}, sum[W] = {};
+        for (size_t v = 0; v < size_t(A); v++) {
+            const int32_t *m0 = &ml[v * W], mj = mh[v * NJ + j];
+            for (size_t x = 0; x < W; x++) {
+                const int32_t m = m0[x] + mj;
+                sum[x] += m;
+                neg[x] += m & (m >> 31);
+            }
+        }
+        for (size_t x = 0; x < W; x++) {
+            const int32_t e = es[j * W + x];
+            l = std::min(l, e + neg[x]);
+            h = std::max(h, e + (sum[x] - neg[x]));
+        }
+        if (int64_t(h) - l > most) return false;
     }
     *lo = l;
     *hi = h;
+    return true;
 }
 
 int32_t nonneg_shift(const Plan &P, int A)
 {
     int64_t lo = 0, hi = 0;
-    chunk_energy_range(P, A, &lo, &hi);
+    (void)chunk_energy_range(P, A, &lo, &hi, INT64_MAX);
     return P.sum_abs + (lo < 0 ? -lo : lo) <= kIntSumLimit ? int32_t(-lo) : 0;
 }
 
@@ -189,8 +215,7 @@ bool packed_shift(const Plan &P, int A, int32_t *shift)
     // the exact extremes decide (the suffix-column sum, a cheaper bound of
     // them, is not used: the shift below also wants the least value)
     int64_t lo = 0, hi = 0;
-    chunk_energy_range(P, A, &lo, &hi);
-    if (hi - lo > 2 * kPackSumLimit + 1) return false;
+    if (!chunk_energy_range(P, A, &lo, &hi, 2 * kPackSumLimit + 1)) return false;
     // shifted chunk energies E_sd + c span [-2^15, hi - lo - 2^15], so the
     // biased halves start at 0 and their upper bits flip as little as the
     // range allows (measured 5% on the packed n = 44 walk against c = 0)

@@ -93,8 +93,10 @@ qubo_status_t make_plan(const void *Q, int n, qubo_dtype_t dtype, const qubo_opt
 int64_t suffix_sum_abs(const Plan &P, int A);
 
 // Exact extremes, over every prefix and suffix column, of the chunk energies
-// E_sd of the split at A (P.T set).
-void chunk_energy_range(const Plan &P, int A, int64_t *lo, int64_t *hi);
+// E_sd of the split at A (P.T set, n - A >= 6).  False, with *lo and *hi
+// untouched, once they are found to lie more than `most` apart.
+bool chunk_energy_range(const Plan &P, int A, int64_t *lo, int64_t *hi,
+                        int64_t most = INT64_MAX);
 
 // Whether the split at A can run the packed tier, and its shift c: every
 // E_sd + c must be a signed 16-bit value, the least one -2^15 (from the
