@@ -749,8 +749,13 @@ hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts
                        uint64_t total_items, int max_L, unsigned long long *d_counter,
                        const int32_t *d_k, int waves, hipStream_t stream, const TopkWalk *tk)
 {
-    const int others = max_L >= kStealSteps ? kQueues - 1 : 0;
-    const WalkLaunch w{tier, d_insts, n_inst, total_items, d_counter, others, d_k, waves, stream, tk};
+    WalkClaims wc{total_items, 0, 0, max_L >= kStealSteps ? kQueues - 1 : 0};
+    if (n_inst == 1 && total_items >= kRunItems && max_L + kRunLog <= kRunMaxSteps) {
+        wc.run_log = kRunLog;
+        wc.runs = (total_items >> kRunLog) * 17 / 20;
+        wc.claims = wc.runs + (total_items - (wc.runs << kRunLog));
+    }
+    const WalkLaunch w{tier, d_insts, n_inst, wc, d_counter, d_k, waves, stream, tk};
     if (vgpr_levels == 6 || vgpr_levels == 5 || vgpr_levels == 4 || vgpr_levels == 3) {
         if (mcols != 16) return hipErrorInvalidValue;
         if (vgpr_levels == 6 || vgpr_levels == 4) return launch_walk_g6(vgpr_levels == 4, w);

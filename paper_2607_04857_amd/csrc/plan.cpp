@@ -422,16 +422,15 @@ static qubo_status_t plan_walk(const qubo_options_t *opt, Plan &P, std::string *
     }
 
     // Work items: 2^L consecutive Gray steps each, never more than 2^20 items
-    // per instance.  A lone instance spreads over the whole grid: 2^13 items
-    // (two per resident wavefront) of at least one super-block, and of at
-    // most 2^10 steps, so that the waves end together (a SIMD favours its
-    // oldest wave, and the youngest one's last item is what the walk waits
-    // for), up to 2^18 items (fewer records and set-ups where there are
-    // plenty).  Measured, walk time at the old rule (at least 2^9 steps, 2^14
-    // where that leaves 2^13 items) and at this one: n = 24 49 -> 14 us,
-    // n = 30 53 -> 42 us, n = 33 181 -> 163 us, packed n = 36 639 -> 585 us,
-    // and 1092 -> 1088 us at n = 36, where the set-ups cost what the tail
-    // gains.
+    // per instance.  A lone instance spreads over the whole grid, and its
+    // waves should end together (a SIMD favours its oldest wave, and the
+    // youngest one's last item is what the walk waits for): 2^13 items (two
+    // per resident wavefront) of at least one super-block, from 2^22 steps on
+    // 2^15 and from 2^24 on 2^16 items, most of them claimed in runs (see
+    // WalkClaims), and from 2^32 on 2^18.  Measured, walk time with 2^13 items
+    // of at least 2^9 steps and with this rule: n = 24 49 -> 14 us, n = 30 53
+    // -> 38 us, n = 33 181 -> 160 us, packed n = 36 639 -> 570 us, n = 36 1092
+    // -> 1068 us.
     int L;
     if (opt && opt->L) {
         L = opt->L;
@@ -452,8 +451,7 @@ static qubo_status_t plan_walk(const qubo_options_t *opt, Plan &P, std::string *
         // set-up (finding its instance among thousands, loading that
         // instance's rows, the state from scratch) outweighs its walk.
         if (many && P.A - L < 6) L = std::max(std::min(P.A, kManyMinL), P.A - 6);
-        if (!many) L = std::min(std::max(P.A - 13, kSuper), kLoneMaxL);
-        if (!many && P.A - L > 18) L = P.A - 18;
+        if (!many) L = std::max(P.A - (P.A < 22 ? 13 : P.A < 24 ? 15 : P.A < 32 ? 16 : 18), kSuper);
         if (L > P.A) L = P.A;
         if (P.A - L > 20) L = P.A - 20;
     }

@@ -310,9 +310,8 @@ __device__ __noinline__ void tk_flush()
 //         energy: the wave keeps the k smallest chunk keys it has met in LDS.
 template <int MC, int G, int TIER, bool LR = false>
 __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void walk_kernel(
-    const Inst *__restrict__ insts, int n_inst, uint64_t total_items,
-    unsigned long long *__restrict__ counter, int others, const int32_t *__restrict__ kall,
-    TopkWalk tk)
+    const Inst *__restrict__ insts, int n_inst, WalkClaims wc,
+    unsigned long long *__restrict__ counter, const int32_t *__restrict__ kall, TopkWalk tk)
 {
     static_assert(TIER >= 1 && TIER <= 5, "tier");
     static_assert(G >= kLowLevels && G <= kMaxVgprLevels, "VGPR-resident levels");
@@ -357,21 +356,24 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
 
     if constexpr (BT == 3) tk_init(tk);
 
-    // the next item of this wave's queue (kQueues), or, where it is empty, of
-    // one of the next `others` queues
+    // the next claim of this wave's queue (kQueues), or, where it is empty, of
+    // one of the next wc.others queues
     uint32_t queue = blockIdx.x % kQueues;
     auto claim = [&]() {
         for (int k = 0;; k++) {
             uint64_t c = 0;
             if (lane == 0) c = atomicAdd(counter + queue * kQueueStride, 1ull);
             // a queue's first items are the waves' own
-            const uint64_t g = (sread64(c) + (gridDim.x + kQueues - 1 - queue) / kQueues) * kQueues +
+            const uint64_t v = (sread64(c) + (gridDim.x + kQueues - 1 - queue) / kQueues) * kQueues +
                                queue;
-            if (g < total_items || k >= others) return g;
+            if (v < wc.claims || k >= wc.others) return v;
             queue = (queue + 1) % kQueues;
         }
     };
-    for (uint64_t g = blockIdx.x; g < total_items; g = claim()) {
+    for (uint64_t v = blockIdx.x; v < wc.claims; v = claim()) {
+        // items [g, g + 2^run): a run of them for the first wc.runs claims
+        const int run = v < wc.runs ? wc.run_log : 0;
+        const uint64_t g = v < wc.runs ? v << wc.run_log : v + ((wc.runs << wc.run_log) - wc.runs);
         // instance owning item g: first k with item_end > g
         int lo = 0, hi = n_inst - 1;
         while (lo < hi) {
@@ -440,49 +442,54 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         }
 
         // Best energy found by any wave for this instance (published at the
-        // end of each item): a chunk can improve the final answer only if its
-        // key is at most that.  (A chunk tying it with an unknown row is still
-        // recorded: bestRow restarts at the largest row whenever the shared
-        // value lowers best.)
-        if constexpr (BT != 3) {
-            const int32_t g0 = sread(__hip_atomic_load(I.gbest, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT));
-            if (g0 < best) {
-                best = g0;
-                bestRow = ~0ull;
-            }
-        }
+        // end of each item), read while the set-up's other loads are in flight.
+        int32_t g0 = kNoEnergy;
+        if constexpr (BT != 3)
+            g0 = __hip_atomic_load(I.gbest, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
         // ---- item set-up: state g(i0) from scratch
         const uint64_t qloc = g - I.item_begin + I.item_local0;   // the instance's item number
         const uint64_t i0 = qloc << I.L;
         const uint64_t sb0 = i0 >> kSuperLog;
-        const uint64_t sbEnd = sb0 + (1ull << (I.L - kSuperLog));
+        const uint64_t sbEnd = sb0 + (1ull << (I.L + run - kSuperLog));
         const uint64_t row0 = i0 ^ (i0 >> 1);
 
-        // (Loads are masked, not branched over, so that they are in flight
-        // together; reading the set bits' rows one after another had cost a
-        // dependent L2 round trip each: 274 -> 248 us for an n = 33 walk.)
+        // What bounds the set-up is latency: its loads are masked, not branched
+        // over, and issued in groups, so that most of them share one L2 round
+        // trip (one per set bit of the row had made an n = 33 walk 274 us
+        // instead of 248).
+        int32_t E[MC];
+        {
+            const gint32 *EB = to_global(I.EB);
+#pragma unroll
+            for (int j = 0; j < MC; j++) E[j] = EB[j * kWave + ulane];
+        }
         // Chunk vector E_s + x_p M_int: M_int[v][s] sums T[v][A+t] over the set
         // suffix bits t of s, so x_p M_int[s] sums, over the same bits, the
         // suffix fields h_t = sum over the set prefix variables v of
         // T[v][A+t].  Lane 16 q + t adds up the rows v = q (mod 4).
+        const gint32 *T = to_global(I.T);
+        const int nT = I.n;
+        int32_t F = T[min(lane, A - 1) * (nT + 1)];   // T[l][l], lane l < A
+        F = lane < A ? F : 0;
         int32_t h = 0;
-        {
-            const gint32 *T = to_global(I.T);
-            const int nT = I.n;
-            const int t = lane & 15;
-#pragma unroll 4
-            for (int v0 = 0; v0 < A; v0 += 4) {
-                const int v = v0 + (lane >> 4);
-                const bool on = t < B && v < A && ((row0 >> ((A - 1 - v) & 63)) & 1);
-                const int32_t x = T[on ? v * nT + A + t : 0];
-                h += on ? x : 0;
+        for (int v0 = 0; v0 < A; v0 += 32) {
+            int32_t x[8];
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const int v = v0 + 4 * k + (lane >> 4);
+                // (a lane without a row or a column reads another entry, masked below)
+                x[k] = T[min(v, A - 1) * nT + A + min(lane & 15, B - 1)];
             }
-            h += __shfl_xor(h, 16, kWave);
-            h += __shfl_xor(h, 32, kWave);
+#pragma unroll
+            for (int k = 0; k < 8; k++) {
+                const int v = v0 + 4 * k + (lane >> 4);
+                const uint32_t on = uint32_t(row0 >> ((A - 1 - v) & 63)) & uint32_t(v < A);
+                h += x[k] & -int32_t(on & 1u);
+            }
         }
-        int32_t E[MC];
+        h += __shfl_xor(h, 16, kWave);
+        h += __shfl_xor(h, 32, kWave);
         {
             uint32_t lsum = 0;   // over the six bits of the lane
             static_for<0, 6>([&](auto uc) {
@@ -499,11 +506,10 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
             // packed: both columns of a word, the high one with variable A set
             const uint32_t top = PK ? uint32_t(__builtin_amdgcn_readlane(h, 0)) << 16 : 0u;
             if constexpr (PK) lsum *= 0x10001u;
-            const gint32 *EB = to_global(I.EB);
             static_for<0, MC>([&](auto jc) {
                 constexpr int j = decltype(jc)::value;
                 const uint32_t hj = PK ? hsum[j] * 0x10001u + top : hsum[j];
-                E[j] = int32_t(uint32_t(EB[j * kWave + ulane]) + lsum + hj);
+                E[j] = int32_t(uint32_t(E[j]) + lsum + hj);
             });
         }
         // F: field of every prefix variable from the non-low ones (levels >=
@@ -511,14 +517,19 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         // lane per variable.  own: the part from the variables before it, so
         // that the energy E_nl of the non-low prefix bits is the sum of own
         // over the set ones (a partial sum of T at every point).
-        int32_t F = lane < A ? to_global(I.T)[lane * I.n + lane] : 0;   // T[l][l], lane l < A
         int32_t own = F;
-#pragma unroll 4
-        for (int w = 0; w <= A - 1 - kLowLevels; w++) {
-            const int32_t on = -int32_t((row0 >> (A - 1 - w)) & 1);
-            const int32_t c = S[w * kWave + ulane] & on;
-            F += c;
-            own += w < lane ? c : 0;
+        for (int w0 = 0; w0 <= A - 1 - kLowLevels; w0 += 16) {
+            int32_t c[16];
+#pragma unroll
+            for (int k = 0; k < 16; k++) c[k] = S[min(w0 + k, A - 1) * kWave + ulane];
+#pragma unroll
+            for (int k = 0; k < 16; k++) {
+                const int w = w0 + k;
+                const int32_t on =
+                    w <= A - 1 - kLowLevels ? -int32_t((row0 >> ((A - 1 - w) & 63)) & 1) : 0;
+                F += c[k] & on;
+                own += w < lane ? c[k] & on : 0;
+            }
         }
         const bool lbit = lane <= A - 1 - kLowLevels && ((row0 >> (A - 1 - lane)) & 1);
         int32_t Enl = wave_sum(lbit ? own : 0);
@@ -532,7 +543,19 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
             constexpr int t = decltype(tc)::value;
             H[t] = __builtin_amdgcn_readlane(F, A - 1 - t);
         });
-        if constexpr (BT == 3) best = tk_threshold();
+        if constexpr (BT == 3) {
+            best = tk_threshold();
+        } else {
+            // A chunk can improve the final answer only if its key is at most
+            // the shared best.  (A chunk tying it with an unknown row is still
+            // recorded: bestRow restarts at the largest row whenever the
+            // shared value lowers best.)
+            g0 = sread(g0);
+            if (g0 < best) {
+                best = g0;
+                bestRow = ~0ull;
+            }
+        }
 
         // TIER 1: THR[p] = best - E_p(low pattern p): the chunk holds a
         // candidate when its minimum E_sd is <= THR of the current pattern.
@@ -899,27 +922,27 @@ static hipError_t launch_walk_g(const WalkLaunch &w)
     if (w.tier == 1) {
         hipLaunchKernelGGL((walk_kernel<MC, G, 1, LR>), dim3(w.waves), dim3(kWave),
                            (walk_lds_bytes<MC, G, LR>(1, 0)), w.stream, w.insts, w.n_inst,
-                           w.total_items, w.counter, w.others, w.k, none);
+                           w.claims, w.counter, w.k, none);
     } else if (w.tier == 2) {
         hipLaunchKernelGGL((walk_kernel<MC, G, 2, LR>), dim3(w.waves), dim3(kWave),
                            (walk_lds_bytes<MC, G, LR>(2, 0)), w.stream, w.insts, w.n_inst,
-                           w.total_items, w.counter, w.others, w.k, none);
+                           w.claims, w.counter, w.k, none);
     } else if (w.tier == 4 && MC >= 4) {
         if constexpr (MC >= 4)
             hipLaunchKernelGGL((walk_kernel<MC, G, 4, LR>), dim3(w.waves), dim3(kWave),
                                (walk_lds_bytes<MC, G, LR>(4, 0)), w.stream, w.insts, w.n_inst,
-                               w.total_items, w.counter, w.others, w.k, none);
+                               w.claims, w.counter, w.k, none);
     } else if (w.tier == 3) {
         if (!w.tk || w.tk->k < 2 || w.n_inst != 1) return hipErrorInvalidValue;
         hipLaunchKernelGGL((walk_kernel<MC, G, 3, LR>), dim3(w.waves), dim3(kWave),
                            (walk_lds_bytes<MC, G, LR>(3, w.tk->k)), w.stream, w.insts, w.n_inst,
-                           w.total_items, w.counter, w.others, w.k, *w.tk);
+                           w.claims, w.counter, w.k, *w.tk);
     } else if (w.tier == 5 && MC >= 4) {
         if (!w.tk || w.tk->k < 2 || w.n_inst != 1) return hipErrorInvalidValue;
         if constexpr (MC >= 4)
             hipLaunchKernelGGL((walk_kernel<MC, G, 5, LR>), dim3(w.waves), dim3(kWave),
                                (walk_lds_bytes<MC, G, LR>(5, w.tk->k)), w.stream, w.insts,
-                               w.n_inst, w.total_items, w.counter, w.others, w.k, *w.tk);
+                               w.n_inst, w.claims, w.counter, w.k, *w.tk);
     } else {
         return hipErrorInvalidValue;
     }

@@ -12,9 +12,8 @@ struct WalkLaunch {
     int tier;
     const Inst *insts;
     int n_inst;
-    uint64_t total_items;
+    WalkClaims claims;
     unsigned long long *counter;
-    int others;          // queues a wave tries after its own (see kStealSteps)
     const int32_t *k;
     int waves;
     hipStream_t stream;
