@@ -59,7 +59,7 @@ PMC_FILE = os.path.join(ROOT, "profiles", "walk_n44_pmc.md")
 # sources of the walk kernel (its template, helpers, layout and the unit of
 # the headline variant); a PMC summary taken with other sources is stale
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2607_04857_amd", "csrc", f)
-               for f in ("kernels.h", "kcommon.h", "walk.h", "walk_g6.hip")]
+               for f in ("kernels.h", "kcommon.h", "walk.h", "walk_g4.hip")]
 
 
 def kernel_hash():
@@ -71,12 +71,15 @@ def kernel_hash():
 
 
 def kernel_name(r):
-    """Template instance of the walk kernel a plan runs (row caches "4" and
-    "3" are G = 6 and G = 5 with the rows of levels 3 and 4 in LDS)."""
+    """Template instance of the walk kernel a lone solve's plan runs (row cache
+    "4": levels 0-3 in VGPRs and the next ones in LDS, shared by a block; "3":
+    G = 5 with the rows of levels 3 and 4 in LDS per wave)."""
     mc = 2 ** (r.B - 7 if r.tier >= 4 else r.B - 6)    # words per lane
-    if r.vgpr_levels in (3, 4):
-        return "walk_kernel<%d,%d,%d,true>" % (mc, r.vgpr_levels + 2, r.tier)
-    return "walk_kernel<%d,%d,%d>" % (mc, r.vgpr_levels, r.tier)
+    if r.vgpr_levels == 4:
+        return "walk_kernel<%d,4,%d,2>" % (mc, r.tier)
+    if r.vgpr_levels == 3:
+        return "walk_kernel<%d,5,%d,1>" % (mc, r.tier)
+    return "walk_kernel<%d,%d,%d,0>" % (mc, r.vgpr_levels, r.tier)
 
 
 def traffic_from_profile():

@@ -125,7 +125,10 @@ typedef struct {
                             4 or 3 (B = 10); fewer levels free VGPRs for a third
                             or fourth wave per SIMD, the higher rows being read
                             from L2 when they flip.  4 keeps levels 0-2 and 5
-                            in VGPRs and levels 3-4 in LDS (8 KB per wave); 3
+                            in VGPRs and levels 3-4 in LDS (8 KB per wave), or,
+                            walking one instance alone for its best state,
+                            levels 0-3 in VGPRs and 4-8 in LDS (32 KB per
+                            block of four waves); 3
                             keeps levels 0-2 in VGPRs, levels 3-4 in LDS and
                             reads every level from 5 up from L2              */
     int item_first;

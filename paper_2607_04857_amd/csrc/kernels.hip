@@ -758,6 +758,7 @@ hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts
     const WalkLaunch w{tier, d_insts, n_inst, wc, d_counter, d_k, waves, stream, tk};
     if (vgpr_levels == 6 || vgpr_levels == 5 || vgpr_levels == 4 || vgpr_levels == 3) {
         if (mcols != 16) return hipErrorInvalidValue;
+        if (vgpr_levels == 4 && n_inst == 1 && (tier == 2 || tier == 4)) return launch_walk_g4(w);
         if (vgpr_levels == 6 || vgpr_levels == 4) return launch_walk_g6(vgpr_levels == 4, w);
         return launch_walk_g5(vgpr_levels == 3, w);
     }

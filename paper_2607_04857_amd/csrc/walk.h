@@ -41,15 +41,38 @@ __device__ __forceinline__ int32_t wave_min_bcast(int32_t v)
 //         incremental_update at 16-bit precision); only the lane minimum
 //         (packed 16-bit minima, then the unbiased smaller half) and the
 //         prefix energy's shift differ.
+// Where the rows of the frequent Gray levels live (levels below G are in
+// VGPRs, except where LDS holds them; RC):
+//  kRowsVgpr    VGPRs only
+//  kRowsWave    levels 3 and 4 in LDS, a copy per wave (2 x MC x 64 dwords),
+//               which leaves room for a fourth wave per SIMD
+//  kRowsBlock   G = 4: levels 4 to 8 in LDS, one copy for the four waves of a
+//               block, which all walk the launch's one instance (a copy per
+//               wave has room for two rows).  Rows 0 and 1 are levels 4 and 5,
+//               then come level 6's row and its negation, 7's and 8's: a
+//               boundary flip of either direction is one code path.  Nearly
+//               every flip then is one full-rate add per word: a row formed
+//               from its parts takes a three-operand add, which issues at half
+//               the rate (one on every boundary was 1.5% of the VALU work).
+//               Measured: n = 44 walk 255.9 -> 254.6 ms, n = 33 and 36 equal.
+enum { kRowsVgpr = 0, kRowsWave = 1, kRowsBlock = 2 };
+constexpr int kBlockLow = 4;      // first Gray level of the block's rows
+constexpr int kBlockTop = 8;      // last one
+constexpr int kBlockRows = 8;     // 32 KB at MC = 16: four blocks fit a CU's LDS
+constexpr int kBlockWaves = 4;
+
+template <int RC>
+constexpr int walk_block_waves()
+{
+    return RC == kRowsBlock ? kBlockWaves : 1;
+}
 // Resident waves per SIMD each variant is register-allocated for: the full
 // 12-level row cache fits 256 VGPRs (2 waves); the 8- and 6-level caches
 // leave room for a third (MC=16) or a fourth (MC=8) wave.
-// LR: the rows of Gray levels 3 and 4 live in LDS (2 x MC x 64 dwords per
-// wave) instead of VGPRs, which leaves room for a fourth wave per SIMD.
-template <int MC, int G, bool LR = false>
+template <int MC, int G, int RC = kRowsVgpr>
 constexpr int walk_waves_per_simd()
 {
-    return LR ? 4 : (G >= 12 ? (MC >= 16 ? 2 : (MC >= 8 ? 3 : 4)) : (G <= 5 ? 4 : (MC >= 16 ? 3 : 4)));
+    return RC != kRowsVgpr ? 4 : (G >= 12 ? (MC >= 16 ? 2 : (MC >= 8 ? 3 : 4)) : (G <= 5 ? 4 : (MC >= 16 ? 3 : 4)));
 }
 // (G = 6 and 8 with MC = 16 target 3 waves, G = 5 four; 8 and 5 spill a few
 // values outside the unrolled steps.)
@@ -61,10 +84,11 @@ __host__ __device__ inline size_t lds_rows_offset(int tier, int k)
     (void)k;
     return (tier == 3 || tier == 5) ? (topk_lds_bytes() + 15) & ~size_t(15) : 0;
 }
-template <int MC>
+template <int MC, int RC>
 constexpr size_t lds_rows_bytes()
 {
-    return size_t(2) * MC * kWave * sizeof(int32_t);
+    constexpr int rows = RC == kRowsBlock ? kBlockRows : RC == kRowsWave ? 2 : 0;
+    return size_t(rows) * MC * kWave * sizeof(int32_t);
 }
 
 // ---- tier-3 list (top-k).  One wave per workgroup.  The list's scalars
@@ -308,13 +332,18 @@ __device__ __noinline__ void tk_flush()
 
 // TIER 3: tier 2's bound test against a top-k threshold instead of the best
 //         energy: the wave keeps the k smallest chunk keys it has met in LDS.
-template <int MC, int G, int TIER, bool LR = false>
-__global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void walk_kernel(
+template <int MC, int G, int TIER, int RC = kRowsVgpr>
+__global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
+                             (walk_waves_per_simd<MC, G, RC>())) void walk_kernel(
     const Inst *__restrict__ insts, int n_inst, WalkClaims wc,
     unsigned long long *__restrict__ counter, const int32_t *__restrict__ kall, TopkWalk tk)
 {
     static_assert(TIER >= 1 && TIER <= 5, "tier");
-    static_assert(G >= kLowLevels && G <= kMaxVgprLevels, "VGPR-resident levels");
+    static_assert(RC == kRowsBlock ? G == kBlockLow : G >= kLowLevels && G <= kMaxVgprLevels,
+                  "VGPR-resident levels");
+    static_assert(RC != kRowsBlock || TIER == 2 || TIER == 4, "the top-k lists are per block");
+    constexpr bool LR = RC == kRowsWave, BR = RC == kRowsBlock;
+    constexpr int WPB = walk_block_waves<RC>();
     // packed layout (tiers 4 and 5) and the test it runs (2: best, 3: top-k)
     constexpr bool PK = TIER >= 4;
     constexpr int BT = PK ? TIER - 2 : TIER;
@@ -322,8 +351,9 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
     // exact path more often, where shorter segments and SGPR thresholds pay
     constexpr int SEG = BT == 3 ? kSegStepsTopk : kSegSteps;
     constexpr int NSEG = (1 << kSuperLog) / SEG;
-    const int lane = int(threadIdx.x);
-    const uint32_t ulane = threadIdx.x;
+    const int lane = int(threadIdx.x) % kWave;
+    const uint32_t ulane = threadIdx.x % kWave;
+    const int bwave = WPB > 1 ? sread(int(threadIdx.x) / kWave) : 0;   // this wave of the block
     // log2 of the words per lane, and the suffix bits of a chunk
     constexpr int JB = cx_ctz(MC), B = JB + (PK ? 7 : 6);
     // this lane's chunk minimum (packed: over both halves of every word)
@@ -331,7 +361,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         if constexpr (PK) return tree_min_packed<MC>(e);
         else return tree_min<MC>(e);
     };
-    // LR: rows of levels 3 and 4 after the (tier-3) list in dynamic LDS
+    // the rows in dynamic LDS, after the (tier-3) list
     int32_t *const ldsR = reinterpret_cast<int32_t *>(
         reinterpret_cast<char *>(tk_lds) + lds_rows_offset(TIER, tk.k));
 
@@ -364,18 +394,35 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
             uint64_t c = 0;
             if (lane == 0) c = atomicAdd(counter + queue * kQueueStride, 1ull);
             // a queue's first items are the waves' own
-            const uint64_t v = (sread64(c) + (gridDim.x + kQueues - 1 - queue) / kQueues) * kQueues +
-                               queue;
+            const uint64_t v =
+                (sread64(c) + (gridDim.x * WPB + kQueues - 1 - queue) / kQueues) * kQueues + queue;
             if (v < wc.claims || k >= wc.others) return v;
             queue = (queue + 1) % kQueues;
         }
     };
-    for (uint64_t v = blockIdx.x; v < wc.claims; v = claim()) {
+    if constexpr (BR) {
+        // the block's rows, a wave filling every fourth one
+        const Inst &I = insts[0];
+        A = I.A;
+        ML = to_global(I.ML);
+        kbase = I.kslot * kKTable;
+        for (int r = bwave; r < kBlockRows; r += WPB) {
+            const int t = r < 2 ? kBlockLow + r : kSuperLog + (r - 2) / 2;
+            const int row = (r >= 2 && r % 2 ? 2 * A : A) - 1 - t;   // M_int's or its negation's
+            if (t >= A) continue;
+            const int32_t ml = lrow(row);
+            const ivec<MC> mh = hrow(row);
+#pragma unroll
+            for (int j = 0; j < MC; j++) ldsR[(r * MC + j) * kWave + lane] = ml + mh[j];
+        }
+        __syncthreads();
+    }
+    for (uint64_t v = blockIdx.x * WPB + bwave; v < wc.claims; v = claim()) {
         // items [g, g + 2^run): a run of them for the first wc.runs claims
         const int run = v < wc.runs ? wc.run_log : 0;
         const uint64_t g = v < wc.runs ? v << wc.run_log : v + ((wc.runs << wc.run_log) - wc.runs);
         // instance owning item g: first k with item_end > g
-        int lo = 0, hi = n_inst - 1;
+        int lo = 0, hi = BR ? 0 : n_inst - 1;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
             if (insts[mid].item_end > g) hi = mid;
@@ -673,6 +720,12 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
                     const int32_t r = ldsR[(t - 3) * (MC * kWave) + j * kWave + lane];
                     E[j] = up ? E[j] + r : E[j] - r;
                 }
+            } else if constexpr (BR && t >= kBlockLow) {
+#pragma unroll
+                for (int j = 0; j < MC; j++) {
+                    const int32_t r = ldsR[((t - kBlockLow) * MC + j) * kWave + lane];
+                    E[j] = up ? E[j] + r : E[j] - r;
+                }
             } else {
 #pragma unroll
                 for (int j = 0; j < MC; j++) E[j] = up ? E[j] + R[t][j] : E[j] - R[t][j];
@@ -684,7 +737,18 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         auto middle_flip = [&](uint64_t sb) {
             const bool up = (sb & 1) == 0;
             constexpr int tm = kLowLevels;
-            if constexpr (G > tm) {
+            if constexpr (BR) {
+                int32_t r[MC];
+#pragma unroll
+                for (int j = 0; j < MC; j++) r[j] = ldsR[((tm - kBlockLow) * MC + j) * kWave + lane];
+                if (up) {
+#pragma unroll
+                    for (int j = 0; j < MC; j++) E[j] += r[j];
+                } else {
+#pragma unroll
+                    for (int j = 0; j < MC; j++) E[j] -= r[j];
+                }
+            } else if constexpr (G > tm) {
                 if (up) {
 #pragma unroll
                     for (int j = 0; j < MC; j++) E[j] += R[tm][j];
@@ -723,7 +787,7 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
             // (past the last super-block t can be A: any row will do there)
             b.w = max(A - 1 - t, 0);
             b.row = b.up ? b.w : b.w + A;
-            b.ml = lrow(b.row);
+            b.ml = BR ? 0 : lrow(b.row);
             b.sd = S[b.row * kWave + ulane];
             return b;
         };
@@ -742,7 +806,22 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
                     done = true;
                 }
             });
-            if (!done) {
+            if constexpr (BR) {
+                const int t = A - 1 - b.w;
+                if (__builtin_expect(t <= kBlockTop, 1)) {
+                    const int r0 = 2 + 2 * (t - kSuperLog) + (b.up ? 0 : 1);
+#pragma unroll
+                    for (int j = 0; j < MC; j++) E[j] += ldsR[(r0 * MC + j) * kWave + lane];
+                }
+                // (an if of its own: as the other branch's else the chunk vector is
+                // copied, 16 moves, where the two meet)
+                if (t > kBlockTop) {
+                    const int32_t ml = lrow(b.row);
+                    const ivec<MC> mh = hrow(b.row);
+#pragma unroll
+                    for (int j = 0; j < MC; j++) E[j] += ml + mh[j];
+                }
+            } else if (!done) {
                 const ivec<MC> mh = hrow(b.row);
 #pragma unroll
                 for (int j = 0; j < MC; j++) E[j] += b.ml + mh[j];
@@ -781,9 +860,13 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
         } else {
             // 32-bit trip count: a 64-bit compare would take the vector unit
             const uint32_t nsb = uint32_t(sbEnd - sb0);
+            Boundary next = boundary_load(sb0);
             for (uint32_t ks = 0; ks < nsb; ks++) {
                 const uint64_t sb = sb0 + ks;
-                const Boundary next = boundary_load(sb);
+                if (ks) {
+                    boundary_flip(next);
+                    next = boundary_load(sb);
+                }
                 lm0 = lane_min(E);
                 tab2 = 0;
                 // NSEG segments of SEG steps (tier 2: the two halves around
@@ -881,8 +964,6 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
                         constexpr int t = cx_ctz(o);
                         constexpr bool up = (((o ^ (o >> 1)) >> t) & 1) != 0;
                         low_flip(std::integral_constant<int, t>{}, std::integral_constant<bool, up>{});
-                    } else if (ks + 1 < nsb) {
-                        boundary_flip(next);
                     }
                 });
             }
@@ -909,71 +990,64 @@ __global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, LR>())) void wal
     if constexpr (BT == 3) tk_flush();
 }
 
-template <int MC, int G, bool LR = false>
+template <int MC, int G, int RC>
 static size_t walk_lds_bytes(int tier, int k)
 {
-    return lds_rows_offset(tier, k) + (LR ? lds_rows_bytes<MC>() : 0);
+    return lds_rows_offset(tier, k) + lds_rows_bytes<MC, RC>();
 }
 
-template <int MC, int G, bool LR = false>
-static hipError_t launch_walk_g(const WalkLaunch &w)
+template <int MC, int G, int TIER, int RC>
+static hipError_t launch_walk_tier(const WalkLaunch &w, const TopkWalk &tk)
 {
-    TopkWalk none{};
-    if (w.tier == 1) {
-        hipLaunchKernelGGL((walk_kernel<MC, G, 1, LR>), dim3(w.waves), dim3(kWave),
-                           (walk_lds_bytes<MC, G, LR>(1, 0)), w.stream, w.insts, w.n_inst,
-                           w.claims, w.counter, w.k, none);
-    } else if (w.tier == 2) {
-        hipLaunchKernelGGL((walk_kernel<MC, G, 2, LR>), dim3(w.waves), dim3(kWave),
-                           (walk_lds_bytes<MC, G, LR>(2, 0)), w.stream, w.insts, w.n_inst,
-                           w.claims, w.counter, w.k, none);
-    } else if (w.tier == 4 && MC >= 4) {
-        if constexpr (MC >= 4)
-            hipLaunchKernelGGL((walk_kernel<MC, G, 4, LR>), dim3(w.waves), dim3(kWave),
-                               (walk_lds_bytes<MC, G, LR>(4, 0)), w.stream, w.insts, w.n_inst,
-                               w.claims, w.counter, w.k, none);
-    } else if (w.tier == 3) {
-        if (!w.tk || w.tk->k < 2 || w.n_inst != 1) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((walk_kernel<MC, G, 3, LR>), dim3(w.waves), dim3(kWave),
-                           (walk_lds_bytes<MC, G, LR>(3, w.tk->k)), w.stream, w.insts, w.n_inst,
-                           w.claims, w.counter, w.k, *w.tk);
-    } else if (w.tier == 5 && MC >= 4) {
-        if (!w.tk || w.tk->k < 2 || w.n_inst != 1) return hipErrorInvalidValue;
-        if constexpr (MC >= 4)
-            hipLaunchKernelGGL((walk_kernel<MC, G, 5, LR>), dim3(w.waves), dim3(kWave),
-                               (walk_lds_bytes<MC, G, LR>(5, w.tk->k)), w.stream, w.insts,
-                               w.n_inst, w.claims, w.counter, w.k, *w.tk);
-    } else {
-        return hipErrorInvalidValue;
-    }
+    constexpr int WPB = walk_block_waves<RC>();
+    hipLaunchKernelGGL((walk_kernel<MC, G, TIER, RC>), dim3((w.waves + WPB - 1) / WPB),
+                       dim3(kWave * WPB), (walk_lds_bytes<MC, G, RC>(TIER, tk.k)), w.stream, w.insts,
+                       w.n_inst, w.claims, w.counter, w.k, tk);
     return hipGetLastError();
 }
 
-template <int MC, int G, bool LR = false>
+template <int MC, int G, int RC = kRowsVgpr>
+static hipError_t launch_walk_g(const WalkLaunch &w)
+{
+    const TopkWalk none{};
+    if constexpr (RC == kRowsBlock) {
+        if (w.n_inst != 1) return hipErrorInvalidValue;
+        if (w.tier == 2) return launch_walk_tier<MC, G, 2, RC>(w, none);
+        if (w.tier == 4) return launch_walk_tier<MC, G, 4, RC>(w, none);
+    } else {
+        if (w.tier == 1) return launch_walk_tier<MC, G, 1, RC>(w, none);
+        if (w.tier == 2) return launch_walk_tier<MC, G, 2, RC>(w, none);
+        if constexpr (MC >= 4)
+            if (w.tier == 4) return launch_walk_tier<MC, G, 4, RC>(w, none);
+        if (!w.tk || w.tk->k < 2 || w.n_inst != 1) return hipErrorInvalidValue;
+        if (w.tier == 3) return launch_walk_tier<MC, G, 3, RC>(w, *w.tk);
+        if constexpr (MC >= 4)
+            if (w.tier == 5) return launch_walk_tier<MC, G, 5, RC>(w, *w.tk);
+    }
+    return hipErrorInvalidValue;
+}
+
+// Resident waves per CU (>= 1).
+template <int MC, int G, int TIER, int RC>
+static int occupancy_tier(int k)
+{
+    constexpr int WPB = walk_block_waves<RC>();
+    int blocks = 0;
+    const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &blocks, walk_kernel<MC, G, TIER, RC>, kWave * WPB, walk_lds_bytes<MC, G, RC>(TIER, k));
+    return e != hipSuccess || blocks < 1 ? 1 : blocks * WPB;
+}
+
+template <int MC, int G, int RC = kRowsVgpr>
 static int occupancy_g(int tier, int topk_k)
 {
-    int blocks = 0;
-    hipError_t e = hipErrorInvalidValue;
-    if (tier == 3)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, walk_kernel<MC, G, 3, LR>, kWave,
-                                                         walk_lds_bytes<MC, G, LR>(3, topk_k));
-    else if (tier == 2)
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, walk_kernel<MC, G, 2, LR>, kWave,
-                                                         walk_lds_bytes<MC, G, LR>(2, 0));
-    else if (tier == 4 && MC >= 4) {
-        if constexpr (MC >= 4)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, walk_kernel<MC, G, 4, LR>, kWave,
-                                                             walk_lds_bytes<MC, G, LR>(4, 0));
-    } else if (tier == 5 && MC >= 4) {
-        if constexpr (MC >= 4)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, walk_kernel<MC, G, 5, LR>, kWave,
-                                                             walk_lds_bytes<MC, G, LR>(5, topk_k));
+    if (tier == 3) return occupancy_tier<MC, G, 3, RC>(topk_k);
+    if (tier == 2) return occupancy_tier<MC, G, 2, RC>(0);
+    if constexpr (MC >= 4) {
+        if (tier == 4) return occupancy_tier<MC, G, 4, RC>(0);
+        if (tier == 5) return occupancy_tier<MC, G, 5, RC>(topk_k);
     }
-    else
-        e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&blocks, walk_kernel<MC, G, 1, LR>, kWave,
-                                                         walk_lds_bytes<MC, G, LR>(1, 0));
-    if (e != hipSuccess || blocks < 1) return 1;
-    return blocks;
+    return occupancy_tier<MC, G, 1, RC>(0);
 }
 
 }  // namespace qk

@@ -5,12 +5,12 @@ namespace qk {
 
 hipError_t launch_walk_g6(bool lds, const WalkLaunch &w)
 {
-    return lds ? launch_walk_g<16, 6, true>(w) : launch_walk_g<16, 6>(w);
+    return lds ? launch_walk_g<16, 6, kRowsWave>(w) : launch_walk_g<16, 6>(w);
 }
 
 int occupancy_walk_g6(bool lds, int tier, int topk_k)
 {
-    return lds ? occupancy_g<16, 6, true>(tier, topk_k) : occupancy_g<16, 6>(tier, topk_k);
+    return lds ? occupancy_g<16, 6, kRowsWave>(tier, topk_k) : occupancy_g<16, 6>(tier, topk_k);
 }
 
 }  // namespace qk
