@@ -256,6 +256,13 @@ struct WalkClaims {
 hipError_t launch_tables(const Inst *d_insts, int n_inst, unsigned long long *d_counters,
                          int n_groups, const Upload &up, hipStream_t stream);
 
+// The same for n_inst instances whose host images ups[0 .. n_inst) (a mapped
+// array) the build puts in place.
+hipError_t launch_tables_upload(const Upload *ups, int n_inst, hipStream_t stream);
+
+// Puts one host image in place.
+hipError_t launch_upload(const Upload &up, hipStream_t stream);
+
 // Persistent Gray walk over all items (d_counter: the launch's kCounterWords
 // zeroed words, max_L: log2 of the longest item's steps); `waves` resident wavefronts.  d_k is
 // the contiguous array of K tables (instance i's at insts[i].kslot*kKTable).

@@ -75,6 +75,11 @@ __device__ void upload(const Upload &up, int tid, int threads)
         z[x] = uint4{0, 0, 0, 0};
 }
 
+__global__ __launch_bounds__(256) void upload_kernel(Upload up)
+{
+    upload(up, int(blockIdx.x * blockDim.x + threadIdx.x), int(gridDim.x * blockDim.x));
+}
+
 // One block per (instance, part of its tables), blockIdx.x naming the part.
 // Every part stages T in LDS first, as the symmetric matrix: everything below
 // is sums of a few entries, so what bounds the build is latency, and no part
@@ -88,8 +93,9 @@ constexpr int kTableThreads = 256;
 
 __global__ __launch_bounds__(kTableThreads) void tables_kernel(
     const Inst *__restrict__ insts, unsigned long long *__restrict__ counters, int n_groups,
-    Upload up)
+    Upload up, const Upload *__restrict__ ups)
 {
+    if (ups) up = ups[blockIdx.y];
     __shared__ int32_t sS[kMaxVars * kMaxVars];   // T made symmetric
     __shared__ int32_t sSeed;
     const int part = int(blockIdx.x);
@@ -708,7 +714,24 @@ hipError_t launch_tables(const Inst *d_insts, int n_inst, unsigned long long *d_
 {
     if (up.src && n_inst != 1) return hipErrorInvalidValue;
     hipLaunchKernelGGL(tables_kernel, dim3(up.src ? kTableParts + 1 : kTableParts, n_inst),
-                       dim3(kTableThreads), 0, stream, d_insts, d_counters, n_groups, up);
+                       dim3(kTableThreads), 0, stream, d_insts, d_counters, n_groups, up,
+                       static_cast<const Upload *>(nullptr));
+    return hipGetLastError();
+}
+
+hipError_t launch_tables_upload(const Upload *ups, int n_inst, hipStream_t stream)
+{
+    hipLaunchKernelGGL(tables_kernel, dim3(kTableParts + 1, n_inst), dim3(kTableThreads), 0, stream,
+                       static_cast<const Inst *>(nullptr), static_cast<unsigned long long *>(nullptr),
+                       0, Upload{}, ups);
+    return hipGetLastError();
+}
+
+hipError_t launch_upload(const Upload &up, hipStream_t stream)
+{
+    const uint32_t bytes = up.copy_bytes + up.zero_bytes;
+    const int blocks = int(bytes / 16384 < 63 ? bytes / 16384 + 1 : 64);
+    hipLaunchKernelGGL(upload_kernel, dim3(blocks), dim3(kTableThreads), 0, stream, up);
     return hipGetLastError();
 }
 

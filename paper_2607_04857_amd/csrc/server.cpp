@@ -11,8 +11,8 @@
 //      admitted request (water-filling: requests with few items left get all
 //      of them, the rest share the remaining per-tick item budget), so a
 //      request arriving while others are on the GPU joins the next tick;
-//   3. a finish launch for requests whose last items ran in this tick, and
-//      one small result download.
+//   3. a finish launch for requests whose last items ran in this tick, which
+//      writes the results to mapped host memory.
 // Ticks alternate between two buffer sets: tick k+1 is enqueued before the
 // host waits for tick k, so the GPU does not idle between ticks.  A request
 // is solved by the same kernels and the same integer arithmetic whether it
@@ -38,8 +38,18 @@ using Clock = std::chrono::steady_clock;
 // Walk launches per tick are one per distinct walk kernel variant among the
 // active requests; this bounds the number of built variants (B x cache x tier).
 constexpr int kMaxTickLaunches = 32;
-constexpr int kServeL = 12;         // log2 Gray steps per work item of a served request, or
-constexpr int kServeItemsLog = 11;  // fewer where that leaves less than 2^11 items
+constexpr int kUnitLog = 12;        // the tick budget counts units of 2^12 Gray steps
+// log2 Gray steps per work item of a served request: 2^11 items or more, of at
+// most 2^10 steps (a tick ends when its last wave does, and the youngest wave
+// of a SIMD takes several times an item's time: with items of 2^12 steps the
+// tail was most of a tick of mixed requests), and at most 2^18 items (records).
+constexpr int kServeL = 10;
+constexpr int kServeItemsLog = 11;
+constexpr int kServeMaxItemsLog = 18;
+constexpr int kMaxRound = 128;      // requests admitted in one round, at most: their host
+                                    // images share one mapped block per tick buffer
+// A request's image at most: its descriptor, T and float32 Q, each aligned.
+constexpr size_t kImageBytes = 1024 + 2 * (size_t(qplan::kMaxN) * qplan::kMaxN * 4 + 256);
 
 enum class RState { Queued, Active, Done, Failed };
 
@@ -60,9 +70,16 @@ struct Request {
 
 struct TickBuf {
     hipEvent_t done = nullptr;
-    qk::Inst *h_walk = nullptr, *d_walk = nullptr;   // walk descriptors (max_slots)
-    qk::Inst *h_fin = nullptr, *d_fin = nullptr;     // finish descriptors (max_slots)
-    qk::FinalRes *h_out = nullptr, *d_out = nullptr; // finish results (max_slots)
+    // Mapped host blocks, with their device addresses: the images of a round's
+    // requests and where they go, the tick's descriptors (walk, then finish:
+    // 2 max_slots), and the finish results (max_slots), which the finish
+    // writes there.  A copy each had cost about 10 us of the stream.
+    unsigned char *h_block = nullptr;   // all of them
+    unsigned char *h_images = nullptr, *hd_images = nullptr;
+    qk::Upload *h_ups = nullptr, *hd_ups = nullptr;
+    qk::Inst *h_descs = nullptr, *hd_descs = nullptr;
+    qk::FinalRes *h_out = nullptr, *hd_out = nullptr;
+    unsigned char *d_block = nullptr;   // the descriptors in place, then the item counters
     std::vector<Request *> finishing;
     bool inflight = false;
 };
@@ -77,8 +94,7 @@ struct qubo_server {
     uint64_t tick_items = 0;      // work items per tick (two per resident wave)
     hipStream_t stream = nullptr;
     int32_t *d_karena = nullptr;  // max_slots K tables
-    qk::Inst *d_setup = nullptr;  // descriptors of the requests admitted in one round
-    unsigned long long *d_counter = nullptr;
+    size_t counters_at = 0;       // offset of the item counters in TickBuf::d_block
     std::vector<int> free_kslots;
     TickBuf ticks[2];
     int cur = 0;
@@ -164,7 +180,8 @@ std::vector<Request *> take_admissions(qubo_server *s)
     const size_t free_slots = std::min(size_t(s->max_slots) - std::min(size_t(s->max_slots),
                                                                       s->active.size()),
                                        s->free_kslots.size());
-    size_t n_adm = qsched::admit_count(bytes, s->mem_used, s->budget, free_slots);
+    size_t n_adm = qsched::admit_count(bytes, s->mem_used, s->budget,
+                                       std::min(free_slots, size_t(kMaxRound)));
     for (; n_adm > 0; n_adm--) {
         Request *r = s->queue.front();
         s->queue.pop_front();
@@ -180,7 +197,9 @@ std::vector<Request *> take_admissions(qubo_server *s)
     return adm;
 }
 
-qubo_status_t setup_request(qubo_server *s, Request *r)
+// Device memory of the k-th request admitted in a round, and its image in the
+// tick buffer's mapped block.
+qubo_status_t setup_request(qubo_server *s, TickBuf &t, Request *r, size_t k)
 {
     QRT_HIP(hipMallocAsync(&r->d_mem, r->job.bytes, s->stream), "hipMallocAsync");
     qubo_status_t st = qrt::job_bind(&r->job, r->d_mem);
@@ -193,25 +212,25 @@ qubo_status_t setup_request(qubo_server *s, Request *r)
     I.kslot = r->kslot;
     std::memcpy(r->job.stage.data(), &I, sizeof(I));
     r->base = I;
-    QRT_HIP(hipMemcpyAsync(r->d_mem, r->job.stage.data(), r->job.stage_bytes, hipMemcpyHostToDevice,
-                           s->stream),
-            "hipMemcpyAsync H2D");
+    if (r->job.stage_bytes > kImageBytes) {
+        qrt::set_error("internal: request image larger than its share of the block");
+        return QUBO_EINTERNAL;
+    }
+    std::memcpy(t.h_images + k * kImageBytes, r->job.stage.data(), r->job.stage_bytes);
+    qk::Upload up{};
+    up.src = t.hd_images + k * kImageBytes;
+    up.dst = static_cast<unsigned char *>(r->d_mem);
+    up.copy_bytes = uint32_t(r->job.stage_bytes);
+    t.h_ups[k] = up;
     return QUBO_OK;
 }
 
-// One table-build launch for every request admitted in a round: their
-// descriptors are gathered device-to-device into one array, so the builds
-// run side by side instead of one small launch after another.
-qubo_status_t build_tables(qubo_server *s, const std::vector<Request *> &adm)
+// One table-build launch for every request admitted in a round, which also
+// puts their images in place.
+qubo_status_t build_tables(qubo_server *s, TickBuf &t, size_t n_adm)
 {
-    if (adm.empty()) return QUBO_OK;
-    for (size_t k = 0; k < adm.size(); k++) {
-        QRT_HIP(hipMemcpyAsync(s->d_setup + k, adm[k]->job.d_insts, sizeof(qk::Inst),
-                               hipMemcpyDeviceToDevice, s->stream),
-                "hipMemcpyAsync descriptor");
-    }
-    QRT_HIP(qk::launch_tables(s->d_setup, int(adm.size()), nullptr, 0, qk::Upload{}, s->stream),
-            "tables kernel");
+    if (n_adm == 0) return QUBO_OK;
+    QRT_HIP(qk::launch_tables_upload(t.hd_ups, int(n_adm), s->stream), "tables kernel");
     return QUBO_OK;
 }
 
@@ -238,17 +257,24 @@ qubo_status_t enqueue_tick(qubo_server *s, TickBuf &t, bool *launched)
         }
     }
     // water-filling over the per-tick item budget, fewest remaining first,
-    // then grouped by walk variant (one launch per variant group)
-    std::sort(walkers.begin(), walkers.end(), [](Request *a, Request *b) {
-        return a->job.plans[0].items - a->next_item < b->job.plans[0].items - b->next_item;
-    });
+    // then grouped by walk variant (one launch per variant group), in units of
+    // 2^kUnitLog steps: requests differ in the length of their items
+    auto unit_log = [](const Request *r) { return std::max(kUnitLog - r->job.plans[0].L, 0); };
+    auto units_left = [&](const Request *r) {
+        const int u = unit_log(r);
+        return (r->job.plans[0].items - r->next_item + (uint64_t(1) << u) - 1) >> u;
+    };
+    std::sort(walkers.begin(), walkers.end(),
+              [&](Request *a, Request *b) { return units_left(a) < units_left(b); });
     // Under a backlog the tick grows (qsched::tick_scale): fewer tick
     // boundaries (each costs a drain of the walk grid and a finish launch),
     // at no cost in latency since requests queue anyway.
     std::vector<uint64_t> left(walkers.size());
+    for (size_t k = 0; k < walkers.size(); k++) left[k] = units_left(walkers[k]);
+    std::vector<uint64_t> share = qsched::tick_shares(left, s->tick_items);
     for (size_t k = 0; k < walkers.size(); k++)
-        left[k] = walkers[k]->job.plans[0].items - walkers[k]->next_item;
-    const std::vector<uint64_t> share = qsched::tick_shares(left, s->tick_items);
+        share[k] = std::min(share[k] << unit_log(walkers[k]),
+                            walkers[k]->job.plans[0].items - walkers[k]->next_item);
     uint64_t total = 0;
     for (uint64_t c : share) total += c;
     if (total == 0 && finishers.empty()) return QUBO_OK;
@@ -277,7 +303,7 @@ qubo_status_t enqueue_tick(qubo_server *s, TickBuf &t, bool *launched)
         I.item_local0 = r->next_item;
         I.res = r->base.res + r->next_item;
         I.bit0 = r->next_item;          // I.bits: the request's whole bitmap
-        t.h_walk[nw++] = I;
+        t.h_descs[nw++] = I;
         g += c;
         launches.back().count++;
         launches.back().items += c;
@@ -285,34 +311,33 @@ qubo_status_t enqueue_tick(qubo_server *s, TickBuf &t, bool *launched)
         r->next_item += c;
         if (r->next_item == P.items) finishers.push_back(r);
     }
-    if (nw > 0) {
-        QRT_HIP(hipMemcpyAsync(t.d_walk, t.h_walk, size_t(nw) * sizeof(qk::Inst), hipMemcpyHostToDevice,
-                               s->stream),
-                "hipMemcpyAsync tick");
-        QRT_HIP(hipMemsetAsync(s->d_counter, 0, 
-                               launches.size() * qk::kCounterWords * sizeof(unsigned long long), s->stream),
-                "hipMemsetAsync");
-        for (size_t k = 0; k < launches.size(); k++) {
-            const Launch &L = launches[k];
-            const int occ = qk::walk_occupancy(L.P->mcols, L.P->vgpr_levels, L.P->tier);
-            const int waves = int(std::min<uint64_t>(L.items, uint64_t(s->cus) * uint64_t(occ)));
-            QRT_HIP(qk::launch_walk(L.P->mcols, L.P->vgpr_levels, L.P->tier, t.d_walk + L.first, L.count,
-                                    L.items, L.max_L, s->d_counter + k * qk::kCounterWords, s->d_karena, waves, s->stream),
-                    "walk kernel");
-        }
+    // one launch puts the descriptors (walk, then finish) in place and clears
+    // the item counters
+    for (size_t i = 0; i < finishers.size(); i++) t.h_descs[size_t(nw) + i] = finishers[i]->base;
+    qk::Upload up{};
+    up.src = reinterpret_cast<const unsigned char *>(t.hd_descs);
+    up.dst = t.d_block;
+    up.copy_bytes = uint32_t(((size_t(nw) + finishers.size()) * sizeof(qk::Inst) + 15) / 16 * 16);
+    up.zero_from = uint32_t(s->counters_at);
+    up.zero_bytes =
+        uint32_t(launches.size() * qk::kCounterWords * sizeof(unsigned long long));
+    QRT_HIP(qk::launch_upload(up, s->stream), "upload kernel");
+    const qk::Inst *d_descs = reinterpret_cast<const qk::Inst *>(t.d_block);
+    unsigned long long *counters =
+        reinterpret_cast<unsigned long long *>(t.d_block + s->counters_at);
+    for (size_t k = 0; k < launches.size(); k++) {
+        const Launch &L = launches[k];
+        const int occ = qk::walk_occupancy(L.P->mcols, L.P->vgpr_levels, L.P->tier);
+        const int waves = int(std::min<uint64_t>(L.items, uint64_t(s->cus) * uint64_t(occ)));
+        QRT_HIP(qk::launch_walk(L.P->mcols, L.P->vgpr_levels, L.P->tier, d_descs + L.first, L.count,
+                                L.items, L.max_L, counters + k * qk::kCounterWords, s->d_karena,
+                                waves, s->stream),
+                "walk kernel");
     }
-    if (!finishers.empty()) {
-        for (size_t i = 0; i < finishers.size(); i++) t.h_fin[i] = finishers[i]->base;
-        QRT_HIP(hipMemcpyAsync(t.d_fin, t.h_fin, finishers.size() * sizeof(qk::Inst),
-                               hipMemcpyHostToDevice, s->stream),
-                "hipMemcpyAsync finish");
-        QRT_HIP(qk::launch_finish(t.d_fin, int(finishers.size()), t.d_out, qk::Upload{}, nullptr, nullptr,
-                                  s->stream),
+    if (!finishers.empty())
+        QRT_HIP(qk::launch_finish(d_descs + nw, int(finishers.size()), t.hd_out, qk::Upload{}, nullptr,
+                                  nullptr, s->stream),
                 "finish kernel");
-        QRT_HIP(hipMemcpyAsync(t.h_out, t.d_out, finishers.size() * sizeof(qk::FinalRes),
-                               hipMemcpyDeviceToHost, s->stream),
-                "hipMemcpyAsync results");
-    }
     t.finishing = std::move(finishers);
     QRT_HIP(hipEventRecord(t.done, s->stream), "hipEventRecord");
     t.inflight = true;
@@ -343,17 +368,6 @@ void scheduler(qubo_server *s)
                 continue;
             }
         }
-        for (Request *r : adm) {
-            qubo_status_t st = setup_request(s, r);
-            if (st != QUBO_OK) {
-                fail_all(s, qrt::last_error_cstr());
-                return;
-            }
-        }
-        if (build_tables(s, adm) != QUBO_OK) {
-            fail_all(s, qrt::last_error_cstr());
-            return;
-        }
         TickBuf &t = s->ticks[s->cur];
         if (t.inflight) {
             // the buffer's previous tick was enqueued two ticks ago
@@ -362,6 +376,16 @@ void scheduler(qubo_server *s)
                 return;
             }
             complete_tick(s, t);
+        }
+        for (size_t k = 0; k < adm.size(); k++) {
+            if (setup_request(s, t, adm[k], k) != QUBO_OK) {
+                fail_all(s, qrt::last_error_cstr());
+                return;
+            }
+        }
+        if (build_tables(s, t, adm.size()) != QUBO_OK) {
+            fail_all(s, qrt::last_error_cstr());
+            return;
         }
         bool launched = false;
         if (enqueue_tick(s, t, &launched) != QUBO_OK) {
@@ -394,20 +418,14 @@ void server_free(qubo_server *s)
     if (s->stream) (void)hipStreamSynchronize(s->stream);
     for (TickBuf &t : s->ticks) {
         if (t.done) (void)hipEventDestroy(t.done);
-        if (t.h_walk) (void)hipHostFree(t.h_walk);
-        if (t.h_fin) (void)hipHostFree(t.h_fin);
-        if (t.h_out) (void)hipHostFree(t.h_out);
-        if (t.d_walk) (void)hipFree(t.d_walk);
-        if (t.d_fin) (void)hipFree(t.d_fin);
-        if (t.d_out) (void)hipFree(t.d_out);
+        if (t.h_block) (void)hipHostFree(t.h_block);
+        if (t.d_block) (void)hipFree(t.d_block);
     }
     for (auto &kv : s->reqs) {
         if (kv.second->d_mem) (void)hipFree(kv.second->d_mem);
         delete kv.second;
     }
     if (s->d_karena) (void)hipFree(s->d_karena);
-    if (s->d_setup) (void)hipFree(s->d_setup);
-    if (s->d_counter) (void)hipFree(s->d_counter);
     if (s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
 }
@@ -427,20 +445,35 @@ qubo_status_t server_init(qubo_server *s, size_t budget, int max_slots)
     s->tick_items = uint64_t(di.cus) * uint64_t(qk::walk_occupancy(16, 4, 2)) * 2;
     QRT_HIP(hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking), "hipStreamCreate");
     QRT_HIP(hipMalloc(&s->d_karena, size_t(max_slots) * qk::kKTable * sizeof(int32_t)), "hipMalloc");
-    QRT_HIP(hipMalloc(&s->d_setup, size_t(max_slots) * sizeof(qk::Inst)), "hipMalloc");
-    // item counters of every walk variant launched in a tick
-    QRT_HIP(hipMalloc(&s->d_counter,
-                      kMaxTickLaunches * qk::kCounterWords * sizeof(unsigned long long)), "hipMalloc");
     for (int k = max_slots - 1; k >= 0; k--) s->free_kslots.push_back(k);
     for (TickBuf &t : s->ticks) {
         QRT_HIP(hipEventCreateWithFlags(&t.done, hipEventDisableTiming), "hipEventCreate");
-        const size_t ib = size_t(max_slots) * sizeof(qk::Inst), ob = size_t(max_slots) * sizeof(qk::FinalRes);
-        QRT_HIP(hipHostMalloc(reinterpret_cast<void **>(&t.h_walk), ib, 0), "hipHostMalloc");
-        QRT_HIP(hipHostMalloc(reinterpret_cast<void **>(&t.h_fin), ib, 0), "hipHostMalloc");
-        QRT_HIP(hipHostMalloc(reinterpret_cast<void **>(&t.h_out), ob, 0), "hipHostMalloc");
-        QRT_HIP(hipMalloc(&t.d_walk, ib), "hipMalloc");
-        QRT_HIP(hipMalloc(&t.d_fin, ib), "hipMalloc");
-        QRT_HIP(hipMalloc(&t.d_out, ob), "hipMalloc");
+        const size_t slots = size_t(max_slots), round = std::min(slots, size_t(kMaxRound));
+        // (16 bytes past the descriptors: an image is copied in 16-byte words)
+        const size_t ib = 2 * slots * sizeof(qk::Inst) + 16;
+        s->counters_at = (ib + 255) / 256 * 256;
+        // images | where they go | descriptors | results
+        const size_t ups_at = round * kImageBytes;
+        const size_t descs_at = (ups_at + round * sizeof(qk::Upload) + 255) / 256 * 256;
+        const size_t out_at = descs_at + s->counters_at;
+        void *h = nullptr, *d = nullptr;
+        QRT_HIP(hipHostMalloc(&h, out_at + slots * sizeof(qk::FinalRes), hipHostMallocMapped),
+                "hipHostMalloc");
+        t.h_block = static_cast<unsigned char *>(h);
+        QRT_HIP(hipHostGetDevicePointer(&d, h, 0), "hipHostGetDevicePointer");
+        unsigned char *hd = static_cast<unsigned char *>(d);
+        t.h_images = t.h_block;
+        t.hd_images = hd;
+        t.h_ups = reinterpret_cast<qk::Upload *>(t.h_block + ups_at);
+        t.hd_ups = reinterpret_cast<qk::Upload *>(hd + ups_at);
+        t.h_descs = reinterpret_cast<qk::Inst *>(t.h_block + descs_at);
+        t.hd_descs = reinterpret_cast<qk::Inst *>(hd + descs_at);
+        t.h_out = reinterpret_cast<qk::FinalRes *>(t.h_block + out_at);
+        t.hd_out = reinterpret_cast<qk::FinalRes *>(hd + out_at);
+        // item counters of every walk variant launched in a tick
+        QRT_HIP(hipMalloc(&t.d_block, s->counters_at + kMaxTickLaunches * qk::kCounterWords *
+                                                           sizeof(unsigned long long)),
+                "hipMalloc");
     }
     return QUBO_OK;
 }
@@ -496,15 +529,9 @@ qubo_status_t qubo_server_submit(qubo_server_t *s, const void *Q, int n, qubo_dt
             qrt::set_error(msg);
             return st;
         }
-        // Served requests walk 2^12-step items (a quarter of a batch's): a
-        // tick then lasts about a millisecond at light load, which sets the
-        // latency of a request that arrives while one runs; under a backlog
-        // the ticks grow instead (enqueue_tick).  The planner's cap of 2^20
-        // items per instance still holds (L >= A - 20), so large requests
-        // keep their item records (16 B each) and their finish bounded.
         qplan::Plan &P = r->job.plans[0];
         const int serveL = std::max(std::min(kServeL, std::max(P.A - kServeItemsLog, qplan::kSuper)),
-                                    P.A - 20);
+                                    P.A - kServeMaxItemsLog);
         if (!P.direct && P.L > serveL) {
             P.L = serveL;
             P.items = uint64_t(1) << (P.A - P.L);
