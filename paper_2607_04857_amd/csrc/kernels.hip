@@ -46,22 +46,58 @@ namespace qk {
 
 // ---------------------------------------------------------------- tables
 
-// Greedy single-flip descents from two starts per wave (the all-zero state
-// for wave 0's first start, hashed states otherwise); the block's least
-// energy becomes the instance's shared best.  Any
+// Greedy single-flip descents, one per wave (from the all-zero state for wave
+// 0, from hashed states otherwise); the block's least energy becomes the
+// instance's shared best.  Any
 // state's energy is a valid threshold for the walk (the state's own chunk
 // still passes it), and a local minimum of a dense QUBO is usually close to
 // the global one, so walk waves start with a near-final threshold.
 __device__ int32_t seed_best(const int32_t *S, int n, int wave)
 {
-    int32_t bestE = kNoEnergy;
-    for (int rep = 0; rep < 2; rep++) {
-        int32_t E;
-        uint64_t xm;
-        greedy_descent(S, n, uint32_t(wave) * 2u + uint32_t(rep), E, xm);
-        bestE = min(bestE, E);
+    int32_t E;
+    uint64_t xm;
+    greedy_descent(S, n, uint32_t(wave), E, xm);
+    return E;
+}
+
+// The upper triangle of T (n x n) as a symmetric matrix in LDS, by the whole
+// block.  bus: T is a host image, read over the bus in 16-byte words (its
+// region is 256-byte aligned; n = 36 build 22 -> 13 us); one entry a lane is
+// faster from device memory, where the wide form's strided LDS writes weigh
+// more (100 builds 12 us against 21).
+__device__ void stage_symmetric(const int32_t *T, int n, int32_t *S, int tid, int threads, bool bus)
+{
+    const int nn = n * n;
+    if (!bus) {
+        for (int e = tid; e < nn; e += threads) {
+            const int i = e / n, j = e % n;
+            if (i > j) continue;
+            const int32_t t = T[e];
+            S[e] = t;
+            S[j * n + i] = t;
+        }
+        return;
     }
-    return bestE;
+    for (int e0 = 4 * tid; e0 < nn; e0 += 4 * threads) {
+        int32_t t[4] = {0, 0, 0, 0};
+        if (e0 + 4 <= nn) {
+            *reinterpret_cast<int4 *>(t) = *reinterpret_cast<const int4 *>(T + e0);
+        } else {
+            for (int x = 0; x < nn - e0; x++) t[x] = T[e0 + x];
+        }
+        int i = e0 / n, j = e0 - i * n;
+#pragma unroll
+        for (int x = 0; x < 4; x++) {
+            if (e0 + x < nn && i <= j) {
+                S[i * n + j] = t[x];
+                S[j * n + i] = t[x];
+            }
+            if (++j == n) {
+                j = 0;
+                i++;
+            }
+        }
+    }
 }
 
 // The first kernel of a lone solve copies its host image (see Upload).
@@ -89,7 +125,7 @@ __global__ __launch_bounds__(256) void upload_kernel(Upload up)
 // 950 us when 8 blocks per instance wrote the whole M_int (2A x 2^B words) and
 // reduced the bound constants over its columns.
 enum { kPartSeed = 0, kPartK, kPartEB, kPartRows, kTableParts, kPartUpload = kTableParts };
-constexpr int kTableThreads = 256;
+constexpr int kTableThreads = 512;   // eight descents at once
 
 __global__ __launch_bounds__(kTableThreads) void tables_kernel(
     const Inst *__restrict__ insts, unsigned long long *__restrict__ counters, int n_groups,
@@ -117,13 +153,7 @@ __global__ __launch_bounds__(kTableThreads) void tables_kernel(
     }
     if (I.direct) return;
     const int n = I.n, A = I.A, B = I.B;
-    for (int e = tid; e < n * n; e += kTableThreads) {
-        const int i = e / n, j = e % n;
-        if (i > j) continue;
-        const int32_t t = T[e];
-        sS[e] = t;
-        sS[j * n + i] = t;
-    }
+    stage_symmetric(T, n, sS, tid, kTableThreads, up.src != nullptr);
     if (tid == 0) sSeed = kNoEnergy;
     __syncthreads();
     const int MC = 1 << (I.packed ? B - 7 : B - 6);   // words per lane
@@ -161,9 +191,9 @@ __global__ __launch_bounds__(kTableThreads) void tables_kernel(
         }
     } else if (part == kPartEB) {
         // E_s(U_B)[s] = sum_{t <= u, both set} T[A+t][A+u] (Sec. III-A, step
-        // 2), s = tid + 256 hp: the low eight bits' energy and their fields
-        // on the (at most three) high variables once per thread, then one
-        // sum per high pattern hp.  Bit b of s is variable n-1-b.
+        // 2), s = (tid mod 256) + 256 hp: the low eight bits' energy and their
+        // fields on the (at most three) high variables once per thread, then
+        // one sum per high pattern hp.  Bit b of s is variable n-1-b.
         int32_t base = 0, h[3] = {0, 0, 0}, hh[3][3];
 #pragma unroll
         for (int b = 0; b < 8; b++) {
@@ -274,7 +304,13 @@ __global__ __launch_bounds__(kTableThreads) void tables_kernel(
 // finite, S = sum |T| in float64 accumulated i ascending then j ascending
 // (the host's order, so the same S), p = the largest exponent with
 // S 2^p <= 2^29, T~ = round-half-even(T 2^p).
+// One block.  What bounds it is latency, so nothing of size n^2 runs on one
+// thread: S's exponent comes from a parallel sum unless that is within its
+// rounding of a power of two (then one thread adds in the host's order), and
+// the least chunk energy from the column parts of M_int (as in the table
+// build).  Measured: n = 27 float32 37 -> 11 us, n = 44 28 -> 12 us.
 constexpr int kPrepThreads = 1024;
+constexpr int kPrepWaves = kPrepThreads / kWave;
 
 __device__ __forceinline__ int prep_scale_exponent(double S)
 {
@@ -293,8 +329,10 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
 {
     __shared__ double sTd[kMaxVars * kMaxVars];   // folded float32 input in float64
     __shared__ int32_t sTi[kMaxVars * kMaxVars];  // the int32 T written to T
-    __shared__ int32_t sPart[kMaxPrefixRows][64]; // M_int partial sums (see below)
-    __shared__ long long sLo;
+    __shared__ int32_t sML[kMaxPrefixRows][kWave];      // M_int's lane parts (see ML)
+    __shared__ int32_t sMH[kMaxPrefixRows][kMaxCols];   // and column parts
+    __shared__ double sW[kPrepWaves];
+    __shared__ int sLo;
     __shared__ unsigned long long sSum;
     __shared__ int sNnz, sBad;
     __shared__ double sS;
@@ -306,10 +344,12 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
         sSum = 0ull;
         sNnz = 0;
         sBad = 0;
+        sLo = INT32_MAX;
     }
     __syncthreads();
     uint64_t mySum = 0;
     int myNnz = 0, myBad = 0;
+    double myAbs = 0.0;
     if (!is_fp32) {
         const int32_t *q = static_cast<const int32_t *>(dQ);
         for (int e = tid; e < nn; e += kPrepThreads) {
@@ -333,13 +373,23 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
                 if (!isfinite(a) || !isfinite(b)) myBad = 1;
                 t = a + b;
                 if (t != 0.0) myNnz++;
+                myAbs += fabs(t);
             }
             sTd[e] = t;
         }
     }
-    atomicAdd(&sSum, (unsigned long long)mySum);
-    atomicAdd(&sNnz, myNnz);
-    atomicOr(&sBad, myBad);
+    // wave sums first: one LDS atomic per wave
+    mySum = uint64_t(wave_sum64(int64_t(mySum)));
+    myNnz = wave_sum(myNnz);
+    const bool anyBad = __builtin_amdgcn_ballot_w64(myBad != 0) != 0;
+#pragma unroll
+    for (int off = kWave / 2; off >= 1; off >>= 1) myAbs += __shfl_xor(myAbs, off, kWave);
+    if (tid % kWave == 0) {
+        if (mySum) atomicAdd(&sSum, (unsigned long long)mySum);
+        if (myNnz) atomicAdd(&sNnz, myNnz);
+        if (anyBad) atomicOr(&sBad, 1);
+        sW[tid / kWave] = myAbs;
+    }
     __syncthreads();
     int32_t status = 0;
     int p = 0;
@@ -351,15 +401,24 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
     } else if (sBad) {
         status = kPrepNonFinite;
     } else {
-        if (tid == 0) {
-            double S = 0.0;
-            for (int i = 0; i < n; i++)
-                for (int j = i; j < n; j++) S += fabs(sTd[i * n + j]);
-            sS = S;
-            sSum = 0ull;
+        // S by a tree: any order of at most 1830 non-negative terms is within
+        // 2^-41 of the exact sum, and so of the host's.  The exponents agree
+        // unless a power of two lies between.
+        double S = 0.0;
+#pragma unroll
+        for (int w = 0; w < kPrepWaves; w++) S += sW[w];
+        p = prep_scale_exponent(S);
+        const double off = ldexp(S, -40);
+        if (prep_scale_exponent(S - off) != p || prep_scale_exponent(S + off) != p) {
+            if (tid == 0) {
+                double s = 0.0;
+                for (int i = 0; i < n; i++)
+                    for (int j = i; j < n; j++) s += fabs(sTd[i * n + j]);
+                sS = s;
+            }
+            __syncthreads();
+            p = prep_scale_exponent(sS);
         }
-        __syncthreads();
-        p = prep_scale_exponent(sS);
         uint64_t s2 = 0;
         for (int e = tid; e < nn; e += kPrepThreads) {
             const int64_t t = int64_t(rint(ldexp(sTd[e], p)));   // ties to even
@@ -367,7 +426,8 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
             T[e] = int32_t(t);
             sTi[e] = int32_t(t);
         }
-        atomicAdd(&sSum, (unsigned long long)s2);
+        s2 = uint64_t(wave_sum64(int64_t(s2)));
+        if (tid % kWave == 0 && s2) atomicAdd(&sSum, (unsigned long long)s2);
         __syncthreads();
         sum = int64_t(sSum);
         if (sum > kExactSumLimit) status = kPrepInternal;
@@ -378,49 +438,50 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
     // The int32 walk's shift c = -(least chunk energy of the split): every
     // E_sd(s, x_p) = E_s(s) + sum_v x_v M[v][s] is at least E_s(s) + the
     // negative M[v][s], so the least is the minimum of that over the 2^B
-    // columns (the host planner's rule, with the same int32 bound).
+    // columns s = j*64 + l (the host planner's rule; B <= 10 here).  All are
+    // partial sums of T: int32.
     const bool walked = !direct && status == 0;
-    if (tid == 0) sLo = LLONG_MAX;
-    __syncthreads();
-    // M[v][s] as the table build forms it: the partial sums over the five
-    // lowest bits of s and over the others (B <= 10 here: 32 + 32 entries)
-    if (walked)
-        for (int e = tid; e < A * 64; e += kPrepThreads) {
-            const int v = e / 64, x = e % 64;
-            int32_t acc = 0;
-            if (x < 32) {
-                for (int u = 0; u < 5 && u < B; u++)
-                    if ((x >> u) & 1) acc += sTi[v * n + A + B - 1 - u];
-            } else {
-                for (int u = 0; u < B - 5; u++)
-                    if (((x - 32) >> u) & 1) acc += sTi[v * n + A + B - 6 - u];
-            }
-            sPart[v][x] = acc;
+    const int JB = B - 6;
+    if (walked) {
+        for (int e = tid; e < A * kWave; e += kPrepThreads) {
+            const int v = e / kWave, l = e % kWave;
+            int32_t m = 0;
+#pragma unroll
+            for (int u = 0; u < 6; u++) m += -((l >> u) & 1) & sTi[v * n + n - 1 - u];
+            sML[v][l] = m;
         }
+        for (int e = tid; e < A * kMaxCols; e += kPrepThreads) {
+            const int v = e / kMaxCols, j = e % kMaxCols;
+            int32_t m = 0;
+            for (int u = 0; u < JB; u++) m += -((j >> u) & 1) & sTi[v * n + n - 7 - u];
+            sMH[v][j] = m;
+        }
+    }
     __syncthreads();
     if (walked) {
-        long long lo = LLONG_MAX;
-        for (uint32_t c = uint32_t(tid); c < (1u << B); c += kPrepThreads) {
-            int64_t e = 0;
-            for (int t = 0; t < B; t++) {
-                if (!((c >> (B - 1 - t)) & 1u)) continue;
-                for (int u = t; u < B; u++)
-                    if ((c >> (B - 1 - u)) & 1u) e += sTi[(A + t) * n + A + u];
+        // thread (j, l): column j*64 + l
+        int32_t lo = INT32_MAX;
+        const int l = tid % kWave, j = tid / kWave;
+        if (j < (1 << JB)) {
+            const int s = tid;
+            int32_t e = 0;
+            for (int b = 0; b < B; b++) {
+                const int r = (n - 1 - b) * n;
+                int32_t row = sTi[r + n - 1 - b];
+                for (int c = 0; c < b; c++) row += -((s >> c) & 1) & sTi[r + n - 1 - c];
+                e += -((s >> b) & 1) & row;
             }
-            for (int v = 0; v < A; v++) {
-                const int32_t m = sPart[v][c & 31u] + sPart[v][32u + (c >> 5)];
-                if (m < 0) e += m;
-            }
-            lo = e < lo ? e : lo;
+#pragma unroll 4
+            for (int v = 0; v < A; v++) e += min(0, sML[v][l] + sMH[v][j]);
+            lo = e;
         }
-        atomicMin(&sLo, lo);
+        lo = wave_min(lo);
+        if (tid % kWave == 0) atomicMin(&sLo, lo);
     }
     __syncthreads();
     if (tid == 0) {
         const int64_t lo = walked ? int64_t(sLo) : 0;
         inst->pack_shift = sum + (lo < 0 ? -lo : lo) <= kExactSumLimit ? int32_t(-lo) : 0;
-    }
-    if (tid == 0) {
         PrepOut o;
         o.status = status;
         o.p = status ? 0 : p;
@@ -506,13 +567,7 @@ __global__ __launch_bounds__(kFinishThreads) void finish_kernel(
                                                    up.dst + up.src);
     }
     const int n = I.n, tid = int(threadIdx.x), w = tid / kWave, l = tid % kWave;
-    for (int e = tid; e < n * n; e += kFinishThreads) {
-        const int i = e / n, j = e % n;
-        if (i > j) continue;
-        const int32_t t = I.T[e];
-        sS[e] = t;
-        sS[j * n + i] = t;
-    }
+    stage_symmetric(I.T, n, sS, tid, kFinishThreads, false);
     int32_t bE = INT32_MAX;
     uint64_t bI = ~0ull;
     int32_t status = 0;
@@ -731,7 +786,7 @@ hipError_t launch_upload(const Upload &up, hipStream_t stream)
 {
     const uint32_t bytes = up.copy_bytes + up.zero_bytes;
     const int blocks = int(bytes / 16384 < 63 ? bytes / 16384 + 1 : 64);
-    hipLaunchKernelGGL(upload_kernel, dim3(blocks), dim3(kTableThreads), 0, stream, up);
+    hipLaunchKernelGGL(upload_kernel, dim3(blocks), dim3(256), 0, stream, up);
     return hipGetLastError();
 }
 
