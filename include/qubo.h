@@ -198,7 +198,7 @@ size_t qubo_noalloc_scratch_bytes(void);
 
 /* Solve `count` independent instances (host memory) in one persistent walk
  * launch.  Q[i] is n[i] x n[i] of dtype[i].  out[i] receives instance i's
- * result (best state only).  The whole sequence is replayed from a HIP graph. */
+ * result (best state only). */
 qubo_status_t qubo_solve_batch(int count, const void *const *Q, const int *n,
                                const qubo_dtype_t *dtype, qubo_result_t *out);
 

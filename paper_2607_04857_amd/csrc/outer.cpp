@@ -120,15 +120,9 @@ qubo_status_t qubo_solve_outer(const void *Q, int n, qubo_dtype_t dtype, int k, 
             }
             ptrs[x] = Qr;
         }
-        qubo_batch_t *b = nullptr;
-        qubo_status_t st = qubo_batch_create(int(count), ptrs.data(), ns.data(), dts.data(), nullptr, &b);
-        if (st != QUBO_OK) return st;
         std::vector<qubo_result_t> res(count);
-        double states = 0.0, kms = 0.0;
-        st = qubo_batch_run(b, nullptr);
-        if (st == QUBO_OK) st = qubo_batch_results(b, res.data());
-        if (st == QUBO_OK) st = qubo_batch_stats(b, &states, &kms);
-        qubo_batch_destroy(b);
+        const qubo_status_t st =
+            qubo_solve_batch(int(count), ptrs.data(), ns.data(), dts.data(), res.data());
         if (st != QUBO_OK) return st;
         // lexicographic minimum of (E, index); x_f are the index's top bits
         size_t best = 0;
@@ -148,7 +142,7 @@ qubo_status_t qubo_solve_outer(const void *Q, int n, qubo_dtype_t dtype, int k, 
         out->best.energy = double(bestE);
         out->best.index = bestI;
         out->states = n >= 64 ? ~0ull : (1ull << n);
-        out->kernel_ms = kms;
+        out->kernel_ms = res[0].kernel_ms;   // the batch's walk
         out->total_ms = std::chrono::duration<double, std::milli>(clock::now() - t0).count();
         return QUBO_OK;
     } catch (const std::bad_alloc &) {

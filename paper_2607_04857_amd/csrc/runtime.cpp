@@ -438,9 +438,11 @@ namespace {
 // synchronisation cost more than a small solve: 10 us, and milliseconds for
 // the 110 MB of a k = 1024 solve's lists).  A call has them to itself and is
 // synchronous, so the next one may use another stream.  At most kKeepBytes of
-// device memory are kept; larger jobs allocate their own.  Given back when
-// the thread ends, and when it goes on with another device.
+// device memory and kKeepHostBytes of host memory are kept; larger jobs
+// allocate their own device memory and copy from pageable memory.  Given back
+// when the thread ends, and when it goes on with another device.
 constexpr size_t kKeepBytes = size_t(128) << 20;
+constexpr size_t kKeepHostBytes = size_t(4) << 20;
 
 struct Workspace {
     int dev = -1;
@@ -485,7 +487,7 @@ struct Workspace {
                 (void)hipGetLastError();
             }
         }
-        if (host_need > host_bytes) {
+        if (host_need > host_bytes && host_need <= kKeepHostBytes) {
             release_host();
             const size_t b = align_up(host_need, size_t(64) << 10);
             void *p = nullptr, *d = nullptr;
@@ -508,6 +510,58 @@ struct Workspace {
 thread_local Workspace g_workspace;
 
 }  // namespace
+
+qubo_status_t run_once(Job &job, hipStream_t stream, std::vector<qk::FinalRes> *out)
+{
+    const size_t ni = job.plans.size(), out_bytes = ni * sizeof(qk::FinalRes);
+    out->resize(ni);
+    DeviceInfo di;
+    qubo_status_t rs = device_info(&di);
+    if (rs != QUBO_OK) return rs;
+    Workspace &ws = g_workspace;
+    ws.reserve(di.device, job.bytes, job.stage_bytes + out_bytes);
+    const bool kept = ws.mem_bytes >= job.bytes;
+    const bool mapped = ws.host_bytes >= job.stage_bytes + out_bytes;
+    void *d_mem = ws.mem;
+    if (!kept && hipMallocAsync(&d_mem, job.bytes, stream) != hipSuccess) {
+        (void)hipGetLastError();
+        set_error("device allocation of " + std::to_string(job.bytes) + " bytes failed");
+        return QUBO_ENOMEM;
+    }
+    do {
+        if ((rs = job_bind(&job, d_mem)) != QUBO_OK) break;
+        hipError_t e;
+        LoneResults *results = nullptr;
+        if (mapped) {
+            std::memcpy(ws.host, job.stage.data(), job.stage_bytes);
+            qk::Upload up{};
+            up.src = ws.host_dev;
+            up.dst = static_cast<unsigned char *>(d_mem);
+            up.copy_bytes = uint32_t(job.stage_bytes);
+            if ((e = qk::launch_upload(up, stream)) != hipSuccess) {
+                rs = device_error("upload kernel", e);
+                break;
+            }
+            results = reinterpret_cast<LoneResults *>(ws.host_dev + job.stage_bytes);
+        } else if ((e = hipMemcpyAsync(d_mem, job.stage.data(), job.stage_bytes,
+                                       hipMemcpyHostToDevice, stream)) != hipSuccess) {
+            rs = device_error("hipMemcpyAsync H2D", e);
+            break;
+        }
+        if ((rs = job_enqueue_kernels(job, stream, nullptr, results)) != QUBO_OK) break;
+        if (!mapped && (e = hipMemcpyAsync(out->data(), job.d_out, out_bytes, hipMemcpyDeviceToHost,
+                                           stream)) != hipSuccess)
+            rs = device_error("hipMemcpyAsync D2H", e);
+    } while (false);
+    const hipError_t ef = kept ? hipSuccess : hipFreeAsync(d_mem, stream);
+    const hipError_t es = hipStreamSynchronize(stream);
+    if (es != hipSuccess) ws.release();   // never reuse memory that work may still hold
+    if (rs != QUBO_OK) return rs;
+    if (es != hipSuccess) return device_error("hipStreamSynchronize", es);
+    if (ef != hipSuccess) return device_error("hipFreeAsync", ef);
+    if (mapped) std::memcpy(out->data(), ws.host + job.stage_bytes, out_bytes);
+    return QUBO_OK;
+}
 
 qubo_status_t solve_planned(qrt::Job &job, hipStream_t stream, int waves_per_cu, qubo_result_t *out,
                             qubo_state_t *topk)

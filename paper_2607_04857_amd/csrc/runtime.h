@@ -93,10 +93,15 @@ struct LoneResults {
 // memory must exist).  image: device address of a mapped host block holding
 // the staging image, which the first kernel reads, or null once the image has
 // been copied into place.  results: device address of a mapped host block for
-// the results of a lone k = 1 solve, or null to leave them in device memory.
+// the results of a lone k = 1 solve (or, from its start on, the FinalRes of a
+// best-state job's instances), or null to leave them in device memory.
 qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream,
                                   const unsigned char *image = nullptr,
                                   LoneResults *results = nullptr);
+
+// Run a laid-out best-state job once on `stream` (synchronous, no graph) and
+// read back its results, in the thread's kept memory where that has room.
+qubo_status_t run_once(Job &job, hipStream_t stream, std::vector<qk::FinalRes> *out);
 
 // Milliseconds of FinalRes::walk_ticks on the current device.
 double walk_ms(uint64_t ticks);
