@@ -149,6 +149,30 @@ __device__ __forceinline__ int32_t wave_sum(int32_t v)
            __builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48);
 }
 
+// Three chunk energies, or three entries of a row, as a wide word (mod 2^64).
+__device__ __forceinline__ uint64_t wide_word(int32_t a, int32_t b, int32_t c)
+{
+    return uint64_t(int64_t(a)) + (uint64_t(int64_t(b)) << kWideBits) +
+           (uint64_t(int64_t(c)) << (2 * kWideBits));
+}
+
+// Minimum of the 16 energies in five wide words and a plain one.  The fields
+// are compared where each stands highest in a 32-bit word, with the bits of
+// the field below it as junk under it.
+__device__ __forceinline__ int32_t wide_min(const uint64_t *w, int32_t x)
+{
+    uint32_t m0 = ~0u, m1 = ~0u, m2 = ~0u;
+#pragma unroll
+    for (int k = 0; k < kWideWords; k++) {
+        const uint32_t lo = uint32_t(w[k]), hi = uint32_t(w[k] >> 32);
+        m0 = min(m0, lo << (32 - kWideBits));
+        m1 = min(m1, __builtin_amdgcn_alignbit(hi, lo, 2 * kWideBits - 32));
+        m2 = min(m2, hi);
+    }
+    return min(min(int32_t(m0 >> (32 - kWideBits)), int32_t(m1 >> (32 - kWideBits))),
+               min(int32_t(m2 >> (2 * kWideBits - 32)), x));
+}
+
 __device__ __forceinline__ int64_t wave_sum64(int64_t v)
 {
 #pragma unroll

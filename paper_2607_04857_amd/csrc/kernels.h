@@ -78,6 +78,15 @@ constexpr int kKTable = kKHigh + 2 * kMaxPrefixRows * kMaxCols;
 constexpr int32_t kPackBias = 1 << 15;
 constexpr int64_t kPackSumLimit = (int64_t(1) << 15) - 1;
 
+// Wide words (a lone tier-2 walk): three shifted chunk energies, each in [0,
+// 2^kWideBits), in a 64-bit word, whose add issues at half the rate of a 32-bit
+// one: 3 energies in the time of 2.  The 16 columns of a lane are five such
+// words and one plain one.  As with the packed words the map is additive mod
+// 2^64, so a word decodes exactly whenever its energies lie in range, which
+// their exact extremes prove.
+constexpr int kWideBits = 21;
+constexpr int kWideWords = 5;
+
 struct ItemRes;
 
 // An instance whose Q is prepared on the device (lone solve of a device
@@ -120,6 +129,9 @@ struct Inst {
                            // E_sd + c a signed 16-bit value, the int32 walk
                            // makes it non-negative (written by prepare_kernel
                            // for a device-prepared instance)
+    int wide;              // 1: the lone walk runs on wide words (device-prepared: set
+                           // in the image where the shape allows it, and cleared by
+                           // prepare_kernel where the energies do not)
     uint64_t item_begin;   // this launch's walk-item range [item_begin, item_end)
     uint64_t item_end;
     uint64_t item_local0;  // the instance's own item number of launch item item_begin
@@ -270,11 +282,13 @@ hipError_t launch_upload(const Upload &up, hipStream_t stream);
 // tiers 4 and 5), the M_int rows of Gray levels below vgpr_levels cached in
 // VGPRs (higher ones from L2), tier.
 // Tiers 3 and 5 (top-k lists) need `tk` and exactly one instance; tiers 1,
-// 2 and 4 ignore it (may be null).
+// 2 and 4 ignore it (may be null).  wide (one instance): 1 walks it on wide
+// words, 2 leaves that to its descriptor (both kernels are launched, and the
+// one it does not name returns at once).
 hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts, int n_inst,
                        uint64_t total_items, int max_L, unsigned long long *d_counter,
                        const int32_t *d_k,
-                       int waves, hipStream_t stream, const TopkWalk *tk = nullptr);
+                       int waves, hipStream_t stream, const TopkWalk *tk = nullptr, int wide = 0);
 
 // Whether a (mcols, vgpr_levels) walk variant is compiled in, and whether
 // its packed form (tiers 4 and 5: 2 mcols 64 suffix columns) is.

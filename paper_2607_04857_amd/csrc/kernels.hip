@@ -332,19 +332,20 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
     __shared__ int32_t sML[kMaxPrefixRows][kWave];      // M_int's lane parts (see ML)
     __shared__ int32_t sMH[kMaxPrefixRows][kMaxCols];   // and column parts
     __shared__ double sW[kPrepWaves];
-    __shared__ int sLo;
+    __shared__ int sLo, sHi;
     __shared__ unsigned long long sSum;
     __shared__ int sNnz, sBad;
     __shared__ double sS;
     const int tid = int(threadIdx.x), nn = n * n;
     const Inst &hI = up.src ? *reinterpret_cast<const Inst *>(up.src) : *inst;
-    const int A = hI.A, B = hI.B, direct = hI.direct;
+    const int A = hI.A, B = hI.B, direct = hI.direct, wide = hI.wide;
     if (up.src) upload(up, tid, kPrepThreads);
     if (tid == 0) {
         sSum = 0ull;
         sNnz = 0;
         sBad = 0;
         sLo = INT32_MAX;
+        sHi = INT32_MIN;
     }
     __syncthreads();
     uint64_t mySum = 0;
@@ -438,8 +439,9 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
     // The int32 walk's shift c = -(least chunk energy of the split): every
     // E_sd(s, x_p) = E_s(s) + sum_v x_v M[v][s] is at least E_s(s) + the
     // negative M[v][s], so the least is the minimum of that over the 2^B
-    // columns s = j*64 + l (the host planner's rule; B <= 10 here).  All are
-    // partial sums of T: int32.
+    // columns s = j*64 + l (the host planner's rule; B <= 10 here); the largest
+    // one decides whether the walk may use wide words.  All are partial sums of
+    // T: int32.
     const bool walked = !direct && status == 0;
     const int JB = B - 6;
     if (walked) {
@@ -460,7 +462,7 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
     __syncthreads();
     if (walked) {
         // thread (j, l): column j*64 + l
-        int32_t lo = INT32_MAX;
+        int32_t lo = INT32_MAX, hi = INT32_MIN;
         const int l = tid % kWave, j = tid / kWave;
         if (j < (1 << JB)) {
             const int s = tid;
@@ -471,17 +473,27 @@ __global__ __launch_bounds__(kPrepThreads) void prepare_kernel(const void *__res
                 for (int c = 0; c < b; c++) row += -((s >> c) & 1) & sTi[r + n - 1 - c];
                 e += -((s >> b) & 1) & row;
             }
+            lo = hi = e;
 #pragma unroll 4
-            for (int v = 0; v < A; v++) e += min(0, sML[v][l] + sMH[v][j]);
-            lo = e;
+            for (int v = 0; v < A; v++) {
+                const int32_t m = sML[v][l] + sMH[v][j];
+                lo += min(0, m);
+                hi += max(0, m);
+            }
         }
         lo = wave_min(lo);
-        if (tid % kWave == 0) atomicMin(&sLo, lo);
+        hi = -1 - wave_min(-1 - hi);
+        if (tid % kWave == 0) {
+            atomicMin(&sLo, lo);
+            atomicMax(&sHi, hi);
+        }
     }
     __syncthreads();
     if (tid == 0) {
         const int64_t lo = walked ? int64_t(sLo) : 0;
-        inst->pack_shift = sum + (lo < 0 ? -lo : lo) <= kExactSumLimit ? int32_t(-lo) : 0;
+        const bool fits = sum + (lo < 0 ? -lo : lo) <= kExactSumLimit;
+        inst->pack_shift = fits ? int32_t(-lo) : 0;
+        inst->wide = wide && walked && fits && int64_t(sHi) - lo < (int64_t(1) << kWideBits) ? 1 : 0;
         PrepOut o;
         o.status = status;
         o.p = status ? 0 : p;
@@ -825,7 +837,8 @@ int walk_occupancy(int mcols, int vgpr_levels, int tier, int topk_k)
 
 hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts, int n_inst,
                        uint64_t total_items, int max_L, unsigned long long *d_counter,
-                       const int32_t *d_k, int waves, hipStream_t stream, const TopkWalk *tk)
+                       const int32_t *d_k, int waves, hipStream_t stream, const TopkWalk *tk,
+                       int wide)
 {
     WalkClaims wc{total_items, 0, 0, max_L >= kStealSteps ? kQueues - 1 : 0};
     if (n_inst == 1 && total_items >= kRunItems && max_L + kRunLog <= kRunMaxSteps) {
@@ -836,7 +849,12 @@ hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts
     const WalkLaunch w{tier, d_insts, n_inst, wc, d_counter, d_k, waves, stream, tk};
     if (vgpr_levels == 6 || vgpr_levels == 5 || vgpr_levels == 4 || vgpr_levels == 3) {
         if (mcols != 16) return hipErrorInvalidValue;
-        if (vgpr_levels == 4 && n_inst == 1 && (tier == 2 || tier == 4)) return launch_walk_g4(w);
+        if (vgpr_levels == 4 && n_inst == 1 && (tier == 2 || tier == 4)) {
+            if (wide && tier != 2) return hipErrorInvalidValue;
+            const hipError_t e = wide ? launch_walk_wide(w) : hipSuccess;
+            return e != hipSuccess || wide == 1 ? e : launch_walk_g4(w);
+        }
+        if (wide) return hipErrorInvalidValue;
         if (vgpr_levels == 6 || vgpr_levels == 4) return launch_walk_g6(vgpr_levels == 4, w);
         return launch_walk_g5(vgpr_levels == 3, w);
     }

@@ -203,11 +203,19 @@ bool chunk_energy_range(const Plan &P, int A, int64_t *lo, int64_t *hi, int64_t 
     return true;
 }
 
-int32_t nonneg_shift(const Plan &P, int A)
+int32_t nonneg_shift(const Plan &P, int A, int64_t *span)
 {
     int64_t lo = 0, hi = 0;
     (void)chunk_energy_range(P, A, &lo, &hi, INT64_MAX);
-    return P.sum_abs + (lo < 0 ? -lo : lo) <= kIntSumLimit ? int32_t(-lo) : 0;
+    const bool fits = P.sum_abs + (lo < 0 ? -lo : lo) <= kIntSumLimit;
+    if (span) *span = fits ? hi - lo : INT64_MAX;
+    return fits ? int32_t(-lo) : 0;
+}
+
+bool wide_shape(const Plan &P)
+{
+    return !P.direct && P.dtype == QUBO_INT32 && P.tier == 2 && P.mcols == 16 &&
+           P.vgpr_levels == 4 && P.A >= kWideMinA;
 }
 
 bool packed_shift(const Plan &P, int A, int32_t *shift)
@@ -417,7 +425,9 @@ static qubo_status_t plan_walk(const qubo_options_t *opt, Plan &P, std::string *
             P.tier = 4;
             P.pack_shift = shift;
         } else if (!P.T.empty()) {
-            P.pack_shift = nonneg_shift(P, P.A);
+            int64_t span = 0;
+            P.pack_shift = nonneg_shift(P, P.A, &span);
+            P.wide = !many && span < kWideSpan && wide_shape(P);
         }
     }
 

@@ -20,6 +20,10 @@ constexpr int kSuper = 6;          // log2 of the unrolled Gray super-block (64 
 constexpr int kManyMinL = 10;      // log2 of the shortest item of an instance in a batch or
                                    // the server (4096 copies of n = 22: 4.0 ms per replay
                                    // with 2^6-step items, 1.3 ms with 2^10-step ones)
+constexpr int64_t kWideSpan = int64_t(1) << 21;   // values of a field of a wide word
+constexpr int kWideMinA = 20;   // whole call, host and device Q, int32 -> wide words: A = 19
+                                // 62.4 -> 61.7 and 68.3 -> 70.1 us, A = 20 74.2 -> 70.4 and
+                                // 80.3 -> 77.1, A = 21 92.2 -> 80.7 and 97.4 -> 87.5
 constexpr int kMaxN = 60;
 constexpr int kDirectMaxN = 14;    // n at or below this: direct evaluation, no walk
 constexpr int64_t kIntSumLimit = (int64_t(1) << 30) - 1;   // sum |T| bound, int32 input
@@ -42,6 +46,8 @@ struct Plan {
                               // from every prefix energy): tiers 4, 5 centre
                               // them in 16 bits, the int32 walk starts them
                               // at 0 (fewer result bits toggle per add)
+    bool wide = false;        // a lone walk may hold three chunk energies in a
+                              // 64-bit word: shifted, all lie in [0, kWideSpan)
     int p = 0;             // fixed-point exponent (fp32)
     double eps_q = 0.0;    // per-state quantisation bound (fp32)
     int64_t sum_abs = 0;   // sum |T| over i <= j (of the int32 matrix solved)
@@ -107,7 +113,15 @@ bool packed_shift(const Plan &P, int A, int32_t *shift);
 // flipping with the sign, which draws less power per add and lets the chip
 // hold a higher clock; measured 5% on the n = 44 walk), or 0 where P.sum_abs
 // + |c| would leave the int32 bound.
-int32_t nonneg_shift(const Plan &P, int A);
+// *span (may be null) receives the shifted energies' largest value, or
+// INT64_MAX where the shift is 0 for that reason.
+int32_t nonneg_shift(const Plan &P, int A, int64_t *span = nullptr);
+
+// Whether a lone plan of this shape (split, tier and row cache set) has a walk
+// on wide words, from kWideMinA prefix bits on (below, the walk gains less than
+// its longer set-up and, for a device-resident Q, the second launch cost).
+// int32 only: float32 entries are scaled until their sum fills 30 bits.
+bool wide_shape(const Plan &P);
 
 // The walk plan of an instance whose values are not on the host (a lone
 // solve of a device-resident Q): as make_plan, except that T, p, eps_q and

@@ -10,6 +10,7 @@
 static_assert(qk::kMaxVars == qplan::kMaxN, "finish kernel LDS sized for the largest n");
 static_assert(qk::kExactSumLimit == qplan::kIntSumLimit, "one int32 exactness bound");
 static_assert(qk::kPackSumLimit == qplan::kPackSumLimit, "one packed-tier bound");
+static_assert((int64_t(1) << qk::kWideBits) == qplan::kWideSpan, "one wide-word bound");
 
 namespace qrt {
 
@@ -261,6 +262,7 @@ qubo_status_t job_bind(Job *job, void *d_mem)
         I.kslot = int(i);
         I.packed = (P.tier == 4 || P.tier == 5) ? 1 : 0;
         I.pack_shift = P.direct ? 0 : P.pack_shift;   // device-prepared: set by prepare_kernel
+        I.wide = (job->dq ? qplan::wide_shape(P) : P.wide) ? 1 : 0;
         I.item_begin = group_base[i];
         I.item_end = group_base[i] + (P.direct ? 0 : P.walk_items());
         item += P.direct ? 0 : P.walk_items();
@@ -358,7 +360,10 @@ qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, const unsi
         const WalkGroup &g = job.groups[k];
         QRT_HIP(qk::launch_walk(g.mcols, g.vgpr_levels, g.tier, job.d_insts + g.first, g.count,
                                 g.items, g.max_L, job.d_counter + k * qk::kCounterWords, job.d_k,
-                                g.waves, stream, job.topk > 1 ? &job.tkb.walk : nullptr),
+                                g.waves, stream, job.topk > 1 ? &job.tkb.walk : nullptr,
+                                g.count != 1 || job.topk > 1 ? 0
+                                : job.dq ? (qplan::wide_shape(job.plans[size_t(g.first)]) ? 2 : 0)
+                                         : (job.plans[size_t(g.first)].wide ? 1 : 0)),
                 "walk kernel");
     }
     if (job.topk > 1)

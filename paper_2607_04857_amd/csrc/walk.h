@@ -55,7 +55,24 @@ __device__ __forceinline__ int32_t wave_min_bcast(int32_t v)
 //               from its parts takes a three-operand add, which issues at half
 //               the rate (one on every boundary was 1.5% of the VALU work).
 //               Measured: n = 44 walk 255.9 -> 254.6 ms, n = 33 and 36 equal.
-enum { kRowsVgpr = 0, kRowsWave = 1, kRowsBlock = 2 };
+//  kRowsWide    the chunk vector in wide words (kWideBits): the walk is bound
+//               by its adds, and five 64-bit ones and one of 32 bits take 11
+//               issue slots where 16 of 32 bits take 16.  As kRowsBlock, with
+//               levels 0-2 in VGPRs and 3-8 in LDS, and every row as well as
+//               its negation, since no 64-bit add subtracts: 128 VGPRs, none
+//               spilled.  A boundary above level 8 forms its row from its parts
+//               (1 in 8 of the boundaries).  Measured against kRowsBlock on the
+//               same instances: n = 44 walk 254.6 -> 192.5 ms (169 ms at the
+//               adds' full rate; 194 with level 9 in LDS and the plain words'
+//               rows apart, which takes a second address register), n = 40
+//               16.4 -> 12.4, n = 36 1.07 -> 0.85, n = 33 0.160 -> 0.139.
+enum { kRowsVgpr = 0, kRowsWave = 1, kRowsBlock = 2, kRowsWide = 3 };
+constexpr int kWideLow = 3;       // first Gray level of the wide rows in LDS
+constexpr int kWideTop = 8;       // last one
+constexpr int kWideRows = 2 * (kWideTop - kWideLow + 1);
+// a row: its words, then the plain one in a slot of the same size (one address
+// register for all): 36 KB in all, four blocks a CU
+constexpr size_t kWideRowBytes = kWave * (kWideWords + 1) * sizeof(uint64_t);
 constexpr int kBlockLow = 4;      // first Gray level of the block's rows
 constexpr int kBlockTop = 8;      // last one
 constexpr int kBlockRows = 8;     // 32 KB at MC = 16: four blocks fit a CU's LDS
@@ -64,7 +81,7 @@ constexpr int kBlockWaves = 4;
 template <int RC>
 constexpr int walk_block_waves()
 {
-    return RC == kRowsBlock ? kBlockWaves : 1;
+    return RC == kRowsBlock || RC == kRowsWide ? kBlockWaves : 1;
 }
 // Resident waves per SIMD each variant is register-allocated for: the full
 // 12-level row cache fits 256 VGPRs (2 waves); the 8- and 6-level caches
@@ -88,6 +105,7 @@ template <int MC, int RC>
 constexpr size_t lds_rows_bytes()
 {
     constexpr int rows = RC == kRowsBlock ? kBlockRows : RC == kRowsWave ? 2 : 0;
+    if (RC == kRowsWide) return kWideRows * kWideRowBytes;
     return size_t(rows) * MC * kWave * sizeof(int32_t);
 }
 
@@ -339,10 +357,13 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
     unsigned long long *__restrict__ counter, const int32_t *__restrict__ kall, TopkWalk tk)
 {
     static_assert(TIER >= 1 && TIER <= 5, "tier");
-    static_assert(RC == kRowsBlock ? G == kBlockLow : G >= kLowLevels && G <= kMaxVgprLevels,
+    static_assert(RC == kRowsBlock  ? G == kBlockLow
+                  : RC == kRowsWide ? G == kWideLow && MC == 3 * kWideWords + 1 && TIER == 2
+                                    : G >= kLowLevels && G <= kMaxVgprLevels,
                   "VGPR-resident levels");
     static_assert(RC != kRowsBlock || TIER == 2 || TIER == 4, "the top-k lists are per block");
-    constexpr bool LR = RC == kRowsWave, BR = RC == kRowsBlock;
+    constexpr bool LR = RC == kRowsWave, BR = RC == kRowsBlock, WD = RC == kRowsWide;
+    constexpr bool LONE = BR || WD;   // blocks of four waves over one instance
     constexpr int WPB = walk_block_waves<RC>();
     // packed layout (tiers 4 and 5) and the test it runs (2: best, 3: top-k)
     constexpr bool PK = TIER >= 4;
@@ -356,9 +377,19 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
     const int bwave = WPB > 1 ? sread(int(threadIdx.x) / kWave) : 0;   // this wave of the block
     // log2 of the words per lane, and the suffix bits of a chunk
     constexpr int JB = cx_ctz(MC), B = JB + (PK ? 7 : 6);
+    // wide words: the chunk vector W, X and the rows of levels 0-2, both signs
+    // (X's rows need one), in place of E and R
+    uint64_t W[kWideWords], RW[WD ? kWideLow : 1][2][kWideWords];
+    int32_t X = 0, RX[WD ? kWideLow : 1];
+    auto pin_wide = [&]() {
+#pragma unroll
+        for (int k = 0; k < kWideWords; k++) asm("" : "+v"(W[k]));
+        asm("" : "+v"(X));
+    };
     // this lane's chunk minimum (packed: over both halves of every word)
-    auto lane_min = [](const int32_t(&e)[MC]) {
-        if constexpr (PK) return tree_min_packed<MC>(e);
+    auto lane_min = [&](const int32_t(&e)[MC]) {
+        if constexpr (WD) return wide_min(W, X);
+        else if constexpr (PK) return tree_min_packed<MC>(e);
         else return tree_min<MC>(e);
     };
     // the rows in dynamic LDS, after the (tier-3) list
@@ -400,9 +431,54 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
             queue = (queue + 1) % kQueues;
         }
     };
+    // wide words: add signed row `row` of the LDS rows to the chunk vector
+    auto add_wide = [&](int row) {
+        const uint64_t *r = reinterpret_cast<const uint64_t *>(
+                                reinterpret_cast<const char *>(ldsR) + size_t(row) * kWideRowBytes) +
+                            lane;
+#pragma unroll
+        for (int k = 0; k < kWideWords; k++) W[k] += r[k * kWave];
+        X += int32_t(uint32_t(r[kWideWords * kWave]));
+    };
+    if constexpr (WD) {
+        const Inst &I = insts[0];
+        if (I.wide == 0) return;
+        A = I.A;
+        ML = to_global(I.ML);
+        kbase = I.kslot * kKTable;
+        auto words = [&](int row, uint64_t *w, int32_t *x) {
+            const int32_t ml = lrow(row);
+            const ivec<MC> mh = hrow(row);
+#pragma unroll
+            for (int k = 0; k < kWideWords; k++)
+                w[k] = wide_word(ml + mh[3 * k], ml + mh[3 * k + 1], ml + mh[3 * k + 2]);
+            *x = ml + mh[MC - 1];
+        };
+        for (int r = bwave; r < kWideRows; r += WPB) {
+            const int t = kWideLow + r / 2;
+            if (t >= A) continue;
+            uint64_t w[kWideWords];
+            int32_t x;
+            words((r % 2 ? 2 * A : A) - 1 - t, w, &x);
+            uint64_t *p = reinterpret_cast<uint64_t *>(reinterpret_cast<char *>(ldsR) +
+                                                       size_t(r) * kWideRowBytes) +
+                          lane;
+#pragma unroll
+            for (int k = 0; k < kWideWords; k++) p[k * kWave] = w[k];
+            p[kWideWords * kWave] = uint32_t(x);
+        }
+        static_for<0, kWideLow>([&](auto tc) {
+            constexpr int t = decltype(tc)::value;
+            words(A - 1 - t, RW[t][0], &RX[t]);
+            int32_t x;
+            words(2 * A - 1 - t, RW[t][1], &x);
+        });
+        __syncthreads();
+    }
     if constexpr (BR) {
         // the block's rows, a wave filling every fourth one
         const Inst &I = insts[0];
+        if (I.wide != 0) return;
         A = I.A;
         ML = to_global(I.ML);
         kbase = I.kslot * kKTable;
@@ -422,7 +498,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
         const int run = v < wc.runs ? wc.run_log : 0;
         const uint64_t g = v < wc.runs ? v << wc.run_log : v + ((wc.runs << wc.run_log) - wc.runs);
         // instance owning item g: first k with item_end > g
-        int lo = 0, hi = BR ? 0 : n_inst - 1;
+        int lo = 0, hi = LONE ? 0 : n_inst - 1;
         while (lo < hi) {
             const int mid = (lo + hi) >> 1;
             if (insts[mid].item_end > g) hi = mid;
@@ -439,7 +515,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
             S = to_global(I.S);
             kbase = I.kslot * kKTable;
             A = I.A;
-            static_for<0, G>([&](auto tc) {
+            static_for<0, WD ? 0 : G>([&](auto tc) {
                 constexpr int t = decltype(tc)::value;
                 const bool have = t < A;
                 const int v = have ? A - 1 - t : 0;
@@ -564,6 +640,11 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
         // lane per variable.  own: the part from the variables before it, so
         // that the energy E_nl of the non-low prefix bits is the sum of own
         // over the set ones (a partial sum of T at every point).
+        if constexpr (WD) {
+#pragma unroll
+            for (int k = 0; k < kWideWords; k++) W[k] = wide_word(E[3 * k], E[3 * k + 1], E[3 * k + 2]);
+            X = E[MC - 1];
+        }
         int32_t own = F;
         for (int w0 = 0; w0 <= A - 1 - kLowLevels; w0 += 16) {
             int32_t c[16];
@@ -714,7 +795,16 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
         auto low_flip = [&](auto tc, auto upc) {
             constexpr int t = decltype(tc)::value;
             constexpr bool up = decltype(upc)::value;
-            if constexpr (LR && (t == 3 || t == 4)) {
+            if constexpr (WD) {
+                if constexpr (t < kWideLow) {
+#pragma unroll
+                    for (int k = 0; k < kWideWords; k++) W[k] += RW[t][up ? 0 : 1][k];
+                    X = up ? X + RX[t] : X - RX[t];
+                } else {
+                    add_wide(2 * (t - kWideLow) + (up ? 0 : 1));
+                }
+                pin_wide();
+            } else if constexpr (LR && (t == 3 || t == 4)) {
 #pragma unroll
                 for (int j = 0; j < MC; j++) {
                     const int32_t r = ldsR[(t - 3) * (MC * kWave) + j * kWave + lane];
@@ -730,14 +820,17 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
 #pragma unroll
                 for (int j = 0; j < MC; j++) E[j] = up ? E[j] + R[t][j] : E[j] - R[t][j];
             }
-            pin_vec<MC>(E);
+            if constexpr (!WD) pin_vec<MC>(E);
         };
         // Flip of level kLowLevels in the middle of super-block sb (its
         // direction alternates between super-blocks).
         auto middle_flip = [&](uint64_t sb) {
             const bool up = (sb & 1) == 0;
             constexpr int tm = kLowLevels;
-            if constexpr (BR) {
+            if constexpr (WD) {
+                add_wide(2 * (tm - kWideLow) + (up ? 0 : 1));
+                pin_wide();
+            } else if constexpr (BR) {
                 int32_t r[MC];
 #pragma unroll
                 for (int j = 0; j < MC; j++) r[j] = ldsR[((tm - kBlockLow) * MC + j) * kWave + lane];
@@ -787,7 +880,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
             // (past the last super-block t can be A: any row will do there)
             b.w = max(A - 1 - t, 0);
             b.row = b.up ? b.w : b.w + A;
-            b.ml = BR ? 0 : lrow(b.row);
+            b.ml = LONE ? 0 : lrow(b.row);
             b.sd = S[b.row * kWave + ulane];
             return b;
         };
@@ -806,7 +899,19 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
                     done = true;
                 }
             });
-            if constexpr (BR) {
+            if constexpr (WD) {
+                const int t = A - 1 - b.w;
+                if (__builtin_expect(t <= kWideTop, 1)) add_wide(2 * (t - kWideLow) + (b.up ? 0 : 1));
+                if (t > kWideTop) {
+                    const int32_t ml = lrow(b.row);
+                    const ivec<MC> mh = hrow(b.row);
+#pragma unroll
+                    for (int k = 0; k < kWideWords; k++)
+                        W[k] += wide_word(ml + mh[3 * k], ml + mh[3 * k + 1], ml + mh[3 * k + 2]);
+                    X += ml + mh[MC - 1];
+                }
+                pin_wide();
+            } else if constexpr (BR) {
                 const int t = A - 1 - b.w;
                 if (__builtin_expect(t <= kBlockTop, 1)) {
                     const int r0 = 2 + 2 * (t - kSuperLog) + (b.up ? 0 : 1);

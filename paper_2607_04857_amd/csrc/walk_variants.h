@@ -1,6 +1,6 @@
 // walk_variants.h -- the walk variants' launch and occupancy entry points,
 // one pair per translation unit (walk_g12.hip, walk_g12w.hip, walk_g8.hip,
-// walk_g6.hip, walk_g5.hip, walk_g4.hip), so that the variants compile in
+// walk_g6.hip, walk_g5.hip, walk_g4.hip, walk_wide.hip), so that the variants compile in
 // parallel.
 #pragma once
 
@@ -44,5 +44,7 @@ int occupancy_walk_g5(bool lds, int tier, int topk_k);
 // row cache "4" of a lone instance, tiers 2 and 4 (the same four waves per
 // SIMD): levels 0-3 in VGPRs, 4-12 in LDS shared by a block of four waves
 hipError_t launch_walk_g4(const WalkLaunch &w);
+// the same for tier 2 on wide words
+hipError_t launch_walk_wide(const WalkLaunch &w);
 
 }  // namespace qk

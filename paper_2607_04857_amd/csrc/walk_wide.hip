@@ -1,0 +1,12 @@
+// walk_wide.hip -- walk kernel of a lone instance on wide words: 16 columns per lane, three to a 64-bit word.
+#include "walk.h"
+
+namespace qk {
+
+hipError_t launch_walk_wide(const WalkLaunch &w)
+{
+    if (w.tier != 2 || w.n_inst != 1) return hipErrorInvalidValue;
+    return launch_walk_tier<16, kWideLow, 2, kRowsWide>(w, TopkWalk{});
+}
+
+}  // namespace qk
