@@ -19,7 +19,7 @@
 //                     one 32-bit add moves both energies (see kPackSumLimit)
 //   S   [A][64]       S[w][l] = T[min(l,w)][max(l,w)] for l != w < A, else 0:
 //                     the prefix couplings, one lane per variable
-//   K   [6][32]+[12]  (all instances' K tables are contiguous) tier-2 bound
+//   K   [6][32]+[16]  (all instances' K tables are contiguous) tier-2 bound
 //                     constants per 64-step super-block offset o and table
 //                     (0: o < 32; 1: o >= 32, level-5 bit rising; 2: o >= 32,
 //                     falling), entry o mod 32: rows 0..2 hold C2 = ELOW + D,
@@ -27,8 +27,7 @@
 //                     columns of E_sd(o) - E_sd(super-block start) and ELOW
 //                     the low-low coupling energy of the low pattern at o;
 //                     then the minima of C2 over each bound-test segment
-//                     (kc2min_slot: per table for 32-step segments, per
-//                     table half for 16-step ones; 12 entries); then
+//                     (one a table; the other entries unused); then
 //                     SL[64][5]: SL[w][t] = coupling of prefix variable w
 //                     with the low variable A-1-t (0 when equal), so a flip
 //                     of w moves the low fields by scalar loads only; then
@@ -46,18 +45,13 @@ constexpr int kWave = 64;
 constexpr int kSuperLog = 6;          // unrolled super-block: 64 Gray steps
 constexpr int kLowLevels = 5;         // Gray levels with static patterns in a super-block
 constexpr int kPatterns = 1 << kLowLevels;
-constexpr int kSegSteps = 32;         // steps per tier-2 bound-test segment (measured
+constexpr int kBlockWaves = 4;        // waves of a block that walks one instance alone
+constexpr int kSegSteps = 32;         // steps per bound-test segment (measured
                                       // 3.7% faster than 16 at n = 44)
-constexpr int kSegStepsTopk = 16;     // tier 3, whose looser threshold passes more often
-static_assert(kPatterns == 32, "bound-test segments of 32 (a table) or 16 steps");
+static_assert(kPatterns == kSegSteps, "a segment is a table of K");
 constexpr int kKC2Min = 6 * kPatterns;   // min of C2 per (table, segment)
-constexpr int kKBound = kKC2Min + 12;    // bound constants at the head of a K table
-// Slot of the minimum of C2 over segment h of table tab: 32-step segments
-// (a whole table) at kKC2Min + tab, 16-step ones at kKC2Min + 3 + 2 tab + h % 2.
-__host__ __device__ constexpr int kc2min_slot(int seg_steps, int tab, int h)
-{
-    return seg_steps == 32 ? kKC2Min + tab : kKC2Min + 3 + 2 * tab + (h & 1);
-}
+constexpr int kKBound = kKC2Min + 16;    // bound constants at the head of a K table (and
+                                         // padding: a row of MH is a 64-byte line)
 constexpr int kMaxCols = 16;          // words per lane (MC) of the widest variant
 constexpr int kMaxVgprLevels = 12;    // at most Gray levels 0..11 keep their M_int row in VGPRs
 constexpr int32_t kNoEnergy = 1 << 30;  // above every energy the walk can meet
@@ -159,8 +153,8 @@ struct TopkWalk {
     uint64_t *listR;     // [waves][k] prefix rows of those chunks
     int32_t *listCount;  // [waves] entries used (written by every wave on exit)
     int32_t *gthr;       // shared bound, kNoEnergy before the walk
-    uint32_t *hist;      // [kTopkBins] keys entered into any list, by energy bin (zeroed)
-    int32_t *lowbin;     // [0]: lowest non-empty bin (kTopkBins before the walk), [1]: keys counted
+    uint32_t *hist;      // [kTopkBins] keys entered into any list, by energy bin, then
+                         // [kWave] by kTopkFine bins (zeroed)
     int64_t hist_lo;     // energy of bin 0's lower edge (-sum|T|)
     int hist_shift;      // bin = (E - hist_lo) >> hist_shift
     int k;
@@ -168,6 +162,8 @@ struct TopkWalk {
                          // from here instead (null otherwise)
 };
 constexpr int kTopkBins = 16384;
+constexpr int kTopkFine = kTopkBins / kWave;
+constexpr int kTopkLook = 8;   // entered keys of a wave per look at the counts
 
 // One state of a top-k answer; the same layout as qubo_state_t.
 struct TopkState {
@@ -296,13 +292,12 @@ bool walk_variant_exists(int mcols, int vgpr_levels);
 bool walk_packed_exists(int mcols, int vgpr_levels);
 
 // Resident walk wavefronts per CU for a variant (occupancy query, >= 1);
-// topk_k > 1 accounts for tier 3's LDS list.
-int walk_occupancy(int mcols, int vgpr_levels, int tier, int topk_k = 0);
+int walk_occupancy(int mcols, int vgpr_levels, int tier);
 
 // LDS bytes of one tier-3 wave's list scalars (its k entries are in listE /
 // listR in global memory).
-constexpr int kTopkMetaWords = 13;  // 64-bit words of list scalars
-__host__ __device__ inline size_t topk_lds_bytes()
+constexpr int kTopkMetaWords = 12 + kWave + kWave / 2;  // 64-bit words: scalars, queued keys
+__host__ __device__ constexpr size_t topk_lds_bytes()
 {
     return size_t(kTopkMetaWords) * 8;
 }

@@ -284,14 +284,11 @@ __global__ __launch_bounds__(kTableThreads) void tables_kernel(
             c2s[q] = elow + d;
         }
         __syncthreads();
-        if (tid < 9) {   // min of C2 over each bound-test segment (kc2min_slot)
-            const int tab = tid < 3 ? tid : (tid - 3) / 2;
-            const int lo = tid < 3 ? 0 : ((tid - 3) % 2) * 16, hi = tid < 3 ? kPatterns : lo + 16;
+        if (tid < 3) {   // min of C2 over each bound-test segment
             int32_t m = INT32_MAX;
-            for (int oo = lo; oo < hi; oo++) m = min(m, c2s[tab * kPatterns + oo]);
+            for (int oo = 0; oo < kPatterns; oo++) m = min(m, c2s[tid * kPatterns + oo]);
             I.K[kKC2Min + tid] = m;
         }
-        if (tid >= 9 && tid < 12) I.K[kKC2Min + tid] = 0;
     }
 }
 
@@ -821,17 +818,16 @@ bool walk_variant_exists(int mcols, int vgpr_levels)
     return false;
 }
 
-int walk_occupancy(int mcols, int vgpr_levels, int tier, int topk_k)
+int walk_occupancy(int mcols, int vgpr_levels, int tier)
 {
     switch (vgpr_levels) {
-    case 4: return occupancy_walk_g6(true, tier, topk_k);
-    case 3: return occupancy_walk_g5(true, tier, topk_k);
-    case 6: return occupancy_walk_g6(false, tier, topk_k);
-    case 5: return occupancy_walk_g5(false, tier, topk_k);
-    case 8: return occupancy_walk_g8(mcols, tier, topk_k);
+    case 4: return tier == 3 || tier == 5 ? occupancy_walk_g4(tier) : occupancy_walk_g6(true, tier);
+    case 3: return occupancy_walk_g5(true, tier);
+    case 6: return occupancy_walk_g6(false, tier);
+    case 5: return occupancy_walk_g5(false, tier);
+    case 8: return occupancy_walk_g8(mcols, tier);
     default:
-        return mcols <= 4 ? occupancy_walk_g12(mcols, tier, topk_k)
-                          : occupancy_walk_g12w(mcols, tier, topk_k);
+        return mcols <= 4 ? occupancy_walk_g12(mcols, tier) : occupancy_walk_g12w(mcols, tier);
     }
 }
 
@@ -849,8 +845,8 @@ hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts
     const WalkLaunch w{tier, d_insts, n_inst, wc, d_counter, d_k, waves, stream, tk};
     if (vgpr_levels == 6 || vgpr_levels == 5 || vgpr_levels == 4 || vgpr_levels == 3) {
         if (mcols != 16) return hipErrorInvalidValue;
-        if (vgpr_levels == 4 && n_inst == 1 && (tier == 2 || tier == 4)) {
-            if (wide && tier != 2) return hipErrorInvalidValue;
+        if (vgpr_levels == 4 && n_inst == 1 && tier >= 2) {
+            if (wide && tier != 2 && tier != 3) return hipErrorInvalidValue;
             const hipError_t e = wide ? launch_walk_wide(w) : hipSuccess;
             return e != hipSuccess || wide == 1 ? e : launch_walk_g4(w);
         }

@@ -214,7 +214,7 @@ int32_t nonneg_shift(const Plan &P, int A, int64_t *span)
 
 bool wide_shape(const Plan &P)
 {
-    return !P.direct && P.dtype == QUBO_INT32 && P.tier == 2 && P.mcols == 16 &&
+    return !P.direct && P.dtype == QUBO_INT32 && (P.tier == 2 || P.tier == 3) && P.mcols == 16 &&
            P.vgpr_levels == 4 && P.A >= kWideMinA;
 }
 

@@ -23,7 +23,7 @@ struct JobOffsets {
     size_t insts = 0, counter = 0, res = 0, out = 0, K = 0, gbest = 0, prep = 0;
     std::vector<size_t> T, Qf, ML, EB, S, bits;
     // top-k (k > 1, one instance)
-    size_t gthr = 0, hist = 0, lowbin = 0, candN = 0, candE = 0, candR = 0, listE = 0, listR = 0, listCount = 0, chunkE = 0, chunkR = 0, chunkCount = 0,
+    size_t gthr = 0, hist = 0, candN = 0, candE = 0, candR = 0, listE = 0, listR = 0, listCount = 0, chunkE = 0, chunkR = 0, chunkCount = 0,
            stE = 0, stI = 0, segCount = 0, selE = 0, selR = 0, selCount = 0, topk = 0;
 };
 
@@ -73,11 +73,9 @@ static JobOffsets compute_offsets(Job &job)
     size_t off = 0;
     o.insts = off;
     off = align_up(off + ni * sizeof(qk::Inst), 256);
-    if (k > 1) {   // the shared top-k bound and lowest bin
+    if (k > 1) {   // the shared top-k bound
         o.gthr = off;
         off = align_up(off + sizeof(int32_t), 256);
-        o.lowbin = off;
-        off = align_up(off + 2 * sizeof(int32_t), 256);
     }
     job.head_bytes = off;
     for (size_t i = 0; i < ni; i++) {
@@ -96,7 +94,7 @@ static JobOffsets compute_offsets(Job &job)
         o.candN = off;
         off = align_up(off + sizeof(int32_t), 256);
         o.hist = off;
-        off = align_up(off + qk::kTopkBins * sizeof(uint32_t), 256);
+        off = align_up(off + (qk::kTopkBins + qk::kWave) * sizeof(uint32_t), 256);
     }
     job.zero_bytes = off - job.stage_bytes;
     o.gbest = off;
@@ -207,10 +205,12 @@ qubo_status_t job_layout(Job *job, int waves_per_cu)
     }
     for (WalkGroup &g : job->groups) {
         int wpc = waves_per_cu > 0 ? waves_per_cu
-                                   : qk::walk_occupancy(g.mcols, g.vgpr_levels, g.tier, job->topk);
+                                   : qk::walk_occupancy(g.mcols, g.vgpr_levels, g.tier);
         if (wpc <= 0) wpc = 1;
         uint64_t waves = uint64_t(di.cus) * uint64_t(wpc);
         if (g.items < waves) waves = g.items;
+        // every wave of a block has a top-k list
+        if (job->topk > 1) waves = align_up(size_t(waves), size_t(qk::kBlockWaves));
         g.waves = int(waves);
     }
     (void)compute_offsets(*job);
@@ -282,16 +282,14 @@ qubo_status_t job_bind(Job *job, void *d_mem)
     }
     std::memcpy(job->stage.data() + o.insts, insts.data(), insts.size() * sizeof(qk::Inst));
     if (job->topk > 1) {
-        const int32_t none = qk::kNoEnergy, nobin = qk::kTopkBins;
+        const int32_t none = qk::kNoEnergy;
         std::memcpy(job->stage.data() + o.gthr, &none, sizeof(none));
-        std::memcpy(job->stage.data() + o.lowbin, &nobin, sizeof(nobin));
         qk::TopkBufs &t = job->tkb;
         t.walk.listE = reinterpret_cast<int32_t *>(base + o.listE);
         t.walk.listR = reinterpret_cast<uint64_t *>(base + o.listR);
         t.walk.listCount = reinterpret_cast<int32_t *>(base + o.listCount);
         t.walk.gthr = reinterpret_cast<int32_t *>(base + o.gthr);
         t.walk.hist = reinterpret_cast<uint32_t *>(base + o.hist);
-        t.walk.lowbin = reinterpret_cast<int32_t *>(base + o.lowbin);
         // bins of (E + sum|T|) over [0, 2 sum|T|]
         const int64_t span = 2 * job->plans[0].sum_abs;
         int shift = 0;
@@ -361,7 +359,7 @@ qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, const unsi
         QRT_HIP(qk::launch_walk(g.mcols, g.vgpr_levels, g.tier, job.d_insts + g.first, g.count,
                                 g.items, g.max_L, job.d_counter + k * qk::kCounterWords, job.d_k,
                                 g.waves, stream, job.topk > 1 ? &job.tkb.walk : nullptr,
-                                g.count != 1 || job.topk > 1 ? 0
+                                g.count != 1 ? 0
                                 : job.dq ? (qplan::wide_shape(job.plans[size_t(g.first)]) ? 2 : 0)
                                          : (job.plans[size_t(g.first)].wide ? 1 : 0)),
                 "walk kernel");
@@ -693,15 +691,15 @@ void plan_topk(qrt::Job &job, int k, const qubo_options_t *opt)
     if (P.direct) return;
     P.tier = P.tier == 4 ? 5 : 3;
     const int t = P.tier;
-    // The list entries live in global memory and only their scalars in LDS,
-    // so the LDS row caches keep four waves per SIMD for any k.  With the
-    // seeded bound the default one ("4") is the fastest top-k walk (its one
-    // spilled register is reloaded once per super-block); "3" is next, and
-    // the VGPR row cache (three waves) is taken should neither fit four waves.
+    // The list entries live in global memory and only their scalars and a
+    // super-block's keys in LDS, so the LDS row caches keep four waves per SIMD
+    // for any k, and "4" (a block's rows, or wide words) is the fastest; "3" and
+    // then the VGPR row cache (three waves) are taken should it not fit.
     if ((P.vgpr_levels == 4 || P.vgpr_levels == 3) && !(opt && opt->vgpr_levels)) {
-        if (qk::walk_occupancy(P.mcols, 4, t, k) >= 4 * 4) P.vgpr_levels = 4;
-        else P.vgpr_levels = qk::walk_occupancy(P.mcols, 3, t, k) >= 4 * 4 ? 3 : 6;
+        if (qk::walk_occupancy(P.mcols, 4, t) >= 4 * 4) P.vgpr_levels = 4;
+        else P.vgpr_levels = qk::walk_occupancy(P.mcols, 3, t) >= 4 * 4 ? 3 : 6;
     }
+    P.wide = P.wide && qplan::wide_shape(P);
 }
 
 qubo_status_t solve_host(const void *Q, int n, qubo_dtype_t dtype, int k, const qubo_options_t *opt,

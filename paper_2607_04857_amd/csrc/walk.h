@@ -76,7 +76,6 @@ constexpr size_t kWideRowBytes = kWave * (kWideWords + 1) * sizeof(uint64_t);
 constexpr int kBlockLow = 4;      // first Gray level of the block's rows
 constexpr int kBlockTop = 8;      // last one
 constexpr int kBlockRows = 8;     // 32 KB at MC = 16: four blocks fit a CU's LDS
-constexpr int kBlockWaves = 4;
 
 template <int RC>
 constexpr int walk_block_waves()
@@ -94,12 +93,11 @@ constexpr int walk_waves_per_simd()
 // (G = 6 and 8 with MC = 16 target 3 waves, G = 5 four; 8 and 5 spill a few
 // values outside the unrolled steps.)
 
-// Bytes of dynamic LDS ahead of the LDS rows (the tier-3 / tier-5 list),
-// 16-aligned.
-__host__ __device__ inline size_t lds_rows_offset(int tier, int k)
+// Bytes of dynamic LDS ahead of the LDS rows (the lists of the block's waves,
+// tiers 3 and 5), 16-aligned.
+__host__ __device__ constexpr size_t lds_rows_offset(int tier, int waves)
 {
-    (void)k;
-    return (tier == 3 || tier == 5) ? (topk_lds_bytes() + 15) & ~size_t(15) : 0;
+    return (tier == 3 || tier == 5) ? (size_t(waves) * topk_lds_bytes() + 15) & ~size_t(15) : 0;
 }
 template <int MC, int RC>
 constexpr size_t lds_rows_bytes()
@@ -109,52 +107,72 @@ constexpr size_t lds_rows_bytes()
     return size_t(rows) * MC * kWave * sizeof(int32_t);
 }
 
-// ---- tier-3 list (top-k).  One wave per workgroup.  The list's scalars
-// live in dynamic LDS (kTopkMetaWords 64-bit words); its k entries (E and
-// prefix row) live in global memory, at listE / listR + blockIdx.x * k, and
-// entry p is written and read only by lane p % 64, so each lane reads its own
-// earlier writes in program order and no fence is needed.  Only the rare
-// candidate path touches the entries (from L2), and the LDS stays free for
-// the row cache, so tier 3 runs the LDS row-cache variants at four waves per
-// SIMD whatever k is.  No list state is held in registers and the list code
-// sits in functions that are not inlined: the walk's registers stay those of
-// tier 2.
+// ---- tier-3 list (top-k), one a wave.  Its scalars and the keys met in the
+// current super-block live in dynamic LDS (kTopkMetaWords 64-bit words); its k
+// entries (E and prefix row) live in global memory, at listE / listR + the
+// wave's number * k, and entry p is written and read only by lane p % 64, so
+// each lane reads its own earlier writes in program order and no fence is
+// needed.  Only the rare candidate path touches the entries (from L2), and the
+// LDS stays free for the row cache, so tier 3 runs the LDS row-cache variants
+// at four waves per SIMD whatever k is.  No list state is held in registers,
+// and the list code sits in functions that are not inlined, called at one
+// place of the walk.
 //   M[0] entries used  M[1] slot of the largest key  M[2] its E (kNoEnergy
 //   until the list is full)  M[3] lowest shared bound seen  M[4] k
-//   M[5] histogram bin shift
+//   M[5] histogram bin shift  M[6] keys since the last look at the
+//   counts  M[7] the list's number
 //   P[0] the largest key's row  P[1] gthr  P[2] listE  P[3] listR
-//   P[4] listCount  P[5] hist  P[6] lowbin  P[7] hist_lo
-//   (M = words 0..3 as int32, P = words 4..12)
+//   P[4] listCount  P[5] hist  P[6] hist_lo
+//   (M = words 0..3 as int32, P = words 4..11, then the queue of keys met)
 //
 // Shared bound.  Every key that enters any wave's list is also counted in a
 // device-wide histogram by energy bin.  Keys entered belong to distinct
 // chunks (each chunk is walked once), so if the bins up to b hold at least k
 // of them, at least k chunks have a key <= the upper edge of bin b, which
 // therefore bounds the instance's k-th smallest chunk key: no chunk above it
-// can be among the k smallest.  Each insertion recomputes that edge and
-// lowers gthr; every wave's threshold is min(its own list's largest E when
-// full, gthr).
+// can be among the k smallest.  A wave that has entered kTopkLook keys
+// recomputes that edge and lowers gthr; every wave's threshold is min(its own
+// list's largest E when full, gthr as the wave last saw it).
 extern __shared__ uint64_t tk_lds[];
 
-__device__ __forceinline__ int32_t *tk_M() { return reinterpret_cast<int32_t *>(tk_lds); }
-__device__ __forceinline__ uint64_t *tk_P() { return tk_lds + 4; }
+__device__ __forceinline__ int tk_lane() { return int(threadIdx.x) % kWave; }
+__device__ __forceinline__ uint64_t *tk_meta()
+{
+    return tk_lds + sread(int(threadIdx.x) / kWave) * kTopkMetaWords;
+}
+__device__ __forceinline__ int32_t *tk_M() { return reinterpret_cast<int32_t *>(tk_meta()); }
+__device__ __forceinline__ uint64_t *tk_P() { return tk_meta() + 4; }
+// the keys the wave has met in its current super-block: at most one a step
+__device__ __forceinline__ uint64_t *tk_queueR() { return tk_meta() + 12; }
+__device__ __forceinline__ int32_t *tk_queueE()
+{
+    return reinterpret_cast<int32_t *>(tk_queueR() + kWave);
+}
+// The wave's LDS accesses before this are done before those after it (they
+// complete in order: this holds the compiler's order).
+__device__ __forceinline__ void tk_sync()
+{
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
 // this wave's k list entries in global memory
 __device__ __forceinline__ int32_t *tk_E(int k)
 {
-    return reinterpret_cast<int32_t *>(sread64(tk_P()[2])) + size_t(blockIdx.x) * size_t(k);
+    return reinterpret_cast<int32_t *>(sread64(tk_P()[2])) + size_t(sread(tk_M()[7])) * size_t(k);
 }
 __device__ __forceinline__ uint64_t *tk_R(int k)
 {
-    return reinterpret_cast<uint64_t *>(sread64(tk_P()[3])) + size_t(blockIdx.x) * size_t(k);
+    return reinterpret_cast<uint64_t *>(sread64(tk_P()[3])) + size_t(sread(tk_M()[7])) * size_t(k);
 }
 __device__ __forceinline__ int32_t *tk_gthr()
 {
     return reinterpret_cast<int32_t *>(sread64(tk_P()[1]));
 }
 
-__device__ __forceinline__ void tk_init(const TopkWalk &tk)
+// list: the wave's number in the grid
+__device__ __forceinline__ void tk_init(const TopkWalk &tk, int list)
 {
-    if (threadIdx.x == 0) {
+    if (tk_lane() == 0) {
         int32_t *M = tk_M();
         uint64_t *P = tk_P();
         M[0] = 0;
@@ -163,16 +181,17 @@ __device__ __forceinline__ void tk_init(const TopkWalk &tk)
         M[3] = kNoEnergy;
         M[4] = tk.k;
         M[5] = tk.prep ? tk.prep->hist_shift : tk.hist_shift;
+        M[6] = 0;
+        M[7] = list;
         P[0] = 0;
         P[1] = reinterpret_cast<uint64_t>(tk.gthr);
         P[2] = reinterpret_cast<uint64_t>(tk.listE);
         P[3] = reinterpret_cast<uint64_t>(tk.listR);
         P[4] = reinterpret_cast<uint64_t>(tk.listCount);
         P[5] = reinterpret_cast<uint64_t>(tk.hist);
-        P[6] = reinterpret_cast<uint64_t>(tk.lowbin);
-        P[7] = uint64_t(tk.prep ? tk.prep->hist_lo : tk.hist_lo);
+        P[6] = uint64_t(tk.prep ? tk.prep->hist_lo : tk.hist_lo);
     }
-    __syncthreads();
+    tk_sync();
 }
 
 // Threshold at an item start: min(largest E of the full list, shared bound).
@@ -182,9 +201,9 @@ __device__ __noinline__ int32_t tk_threshold()
     const int32_t g = sread(__hip_atomic_load(tk_gthr(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
     const int32_t gm = min(sread(M[3]), g);
     const int32_t t = min(sread(M[2]), gm);
-    __syncthreads();
-    if (threadIdx.x == 0) M[3] = gm;
-    __syncthreads();
+    tk_sync();
+    if (tk_lane() == 0) M[3] = gm;
+    tk_sync();
     return t;
 }
 
@@ -192,8 +211,8 @@ __device__ __noinline__ int32_t tk_threshold()
 // E to the shared bound; returns that E.
 __device__ int32_t tk_rescan(int k)
 {
-    __syncthreads();              // lane 0's LDS scalar stores are visible to the wave
-    const int lane = int(threadIdx.x);
+    tk_sync();              // lane 0's LDS scalar stores are visible to the wave
+    const int lane = tk_lane();
     const int32_t *E = tk_E(k);
     const uint64_t *R = tk_R(k);
     int32_t mE = INT32_MIN;
@@ -232,120 +251,151 @@ __device__ int32_t tk_rescan(int k)
     return mE;
 }
 
-// Count key energy Ec in the shared histogram and lower gthr to the upper
-// edge of the first bin where the running count reaches k.  Atomics on one
-// address complete one per 12.4 ns and thousands of keys may enter, so what
-// need not be exact is read first and written only where it changes: the
-// lowest bin, the bound, and (before any bound is known) the count of keys.
-// Only bins up to gthr's own can lower it, so the scan is short; with a bound
-// known and k large, every eighth key of a bin makes it.  (Three atomics and
-// a scan to the last of the 16384 bins per key had made the n = 31, k = 1024
-// walk 520 us and an n = 21, k = 16 one 970 us; now 126 and 33 us.)
-__device__ void tk_count(int32_t Ec, int k)
+// Count this lane's key energy Ec in the shared histogram: two atomics that
+// nothing waits for (at two levels, so that a look at the counts takes two
+// loads).
+__device__ __forceinline__ int tk_bin(int32_t E)
 {
-    const uint64_t *P = tk_P();
-    uint32_t *hist = reinterpret_cast<uint32_t *>(sread64(P[5]));
-    int32_t *lowbin = reinterpret_cast<int32_t *>(sread64(P[6]));   // [1]: keys counted
-    const int64_t lo = int64_t(sread64(P[7]));
-    const int shift = sread(tk_M()[5]);
-    const int lane = int(threadIdx.x);
-    auto bin_of = [&](int32_t E) {
-        const int64_t b = (int64_t(E) - lo) >> shift;
-        return int(b < 0 ? 0 : (b >= kTopkBins ? kTopkBins - 1 : b));
+    const int64_t b = (int64_t(E) - int64_t(sread64(tk_P()[6]))) >> sread(tk_M()[5]);
+    return int(b < 0 ? 0 : (b >= kTopkBins ? kTopkBins - 1 : b));
+}
+__device__ __forceinline__ void tk_count(int32_t Ec)
+{
+    uint32_t *hist = reinterpret_cast<uint32_t *>(sread64(tk_P()[5]));
+    const int b = tk_bin(Ec);
+    atomicAdd(&hist[b], 1u);
+    atomicAdd(&hist[kTopkBins + b / kTopkFine], 1u);
+}
+
+// The shared bound from the counts: the upper edge of the first bin where the
+// running count reaches k, by lanes over the coarse bins and then over the
+// coarse bin's own (counts that are not there yet only leave it higher).
+// Lowers gthr to it; returns gthr.
+__device__ int32_t tk_bound(int k)
+{
+    uint32_t *hist = reinterpret_cast<uint32_t *>(sread64(tk_P()[5]));
+    const int lane = tk_lane();
+    auto count = [&](int at) {
+        return __hip_atomic_load(&hist[at], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    auto load = [](const int32_t *p) {
-        return sread(__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    };
-    const int b = bin_of(Ec);
-    const int32_t gthr = load(tk_gthr());
-    int base = load(lowbin);
-    int32_t inbin = 0, counted = 0;
-    if (lane == 0) {
-        inbin = int32_t(atomicAdd(&hist[b], 1u)) + 1;
-        if (b < base) atomicMin(lowbin, b);
-        if (gthr == kNoEnergy) counted = atomicAdd(lowbin + 1, 1) + 1;
-    }
-    if (gthr == kNoEnergy ? sread(counted) < k : (k >= 64 && sread(inbin) % 8 != 0)) return;
-    __threadfence();
-    base = min(base, b);
-    const int last = bin_of(gthr);
-    uint32_t cum = 0;
-    for (; base <= last; base += kWave) {
-        const int bin = base + lane;
-        uint32_t c = bin < kTopkBins
-                         ? __hip_atomic_load(&hist[bin], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                         : 0u;
-        // inclusive prefix sum over the wave
+    // inclusive prefix sum over the wave
+    auto prefix = [&](uint32_t c) {
 #pragma unroll
         for (int off = 1; off < kWave; off <<= 1) {
             const uint32_t o = __shfl_up(c, off, kWave);
             if (lane >= off) c += o;
         }
-        const uint32_t total = uint32_t(__builtin_amdgcn_readlane(int32_t(c), kWave - 1));
-        if (cum + total >= uint32_t(k)) {
-            const uint64_t hit = __builtin_amdgcn_ballot_w64(cum + c >= uint32_t(k));
-            const int bstar = base + int(__builtin_ctzll(hit));
-            const int64_t edge = lo + (int64_t(bstar + 1) << shift) - 1;
-            const int32_t T = edge > int64_t(kNoEnergy) ? kNoEnergy : int32_t(edge);
-            if (lane == 0 && T < gthr) atomicMin(tk_gthr(), T);
-            return;
-        }
-        cum += total;
+        return c;
+    };
+    const int32_t gv = __hip_atomic_load(tk_gthr(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t c0 = count(kTopkBins + lane);
+    const int32_t g = sread(gv);
+    const uint32_t cum = prefix(c0);
+    const uint64_t hit = __builtin_amdgcn_ballot_w64(cum >= uint32_t(k));
+    if (hit == 0) return g;
+    const int cb = int(__builtin_ctzll(hit));
+    const uint32_t need = uint32_t(k) - uint32_t(__builtin_amdgcn_readlane(int32_t(cum - c0), cb));
+    constexpr int kPer = kTopkFine / kWave;
+    uint32_t f[kPer], sum = 0;
+#pragma unroll
+    for (int x = 0; x < kPer; x++) f[x] = count(cb * kTopkFine + kPer * lane + x);
+#pragma unroll
+    for (int x = 0; x < kPer; x++) f[x] = sum += f[x];
+    const uint32_t before = prefix(sum) - sum;
+    int past = 0;   // this lane's bins whose running count is below need
+#pragma unroll
+    for (int x = 0; x < kPer; x++) past += before + f[x] < need ? 1 : 0;
+    const uint64_t fhit = __builtin_amdgcn_ballot_w64(past < kPer);
+    int bin = (cb + 1) * kTopkFine - 1;
+    if (fhit) {
+        const int fl = int(__builtin_ctzll(fhit));
+        bin = cb * kTopkFine + kPer * fl + __builtin_amdgcn_readlane(past, fl);
     }
+    const int64_t edge =
+        int64_t(sread64(tk_P()[6])) + (int64_t(bin + 1) << sread(tk_M()[5])) - 1;
+    const int32_t T = edge > int64_t(kNoEnergy) ? kNoEnergy : int32_t(edge);
+    if (lane == 0 && T < g) atomicMin(tk_gthr(), T);
+    return min(T, g);
 }
 
-// Offer chunk key (Ec, rc), Ec <= the current threshold: append while the
-// list has room, else replace the largest key if (Ec, rc) is smaller.
-// Returns the new threshold.
-__device__ __noinline__ int32_t tk_insert(int32_t Ec, uint64_t rc)
+// Offer chunk key (Ec, rc) to the wave's list: append while it has room, else
+// replace the largest key if (Ec, rc) is smaller.
+__device__ void tk_insert(int32_t Ec, uint64_t rc)
 {
-    Ec = sread(Ec);
-    rc = sread64(rc);
     int32_t *M = tk_M();
-    __syncthreads();
     const int cnt = sread(M[0]);
     const int k = sread(M[4]);
-    int32_t lkth = sread(M[2]);
-    bool entered = false;
-    if (cnt < k) {
-        __syncthreads();
-        if (int(threadIdx.x) == cnt % kWave) {   // the lane that owns entry cnt
-            tk_E(k)[cnt] = Ec;
-            tk_R(k)[cnt] = rc;
-        }
-        if (threadIdx.x == 0) M[0] = cnt + 1;
-        entered = true;
-        if (cnt + 1 == k) lkth = tk_rescan(k);
-    } else {
+    int pos = cnt;
+    if (cnt >= k) {
+        const int32_t lkth = sread(M[2]);
         const uint64_t lkR = sread64(tk_P()[0]);
-        if (Ec < lkth || (Ec == lkth && rc < lkR)) {
-            const int pos = sread(M[1]);
-            __syncthreads();
-            if (int(threadIdx.x) == pos % kWave) {   // the lane that owns entry pos
-                tk_E(k)[pos] = Ec;
-                tk_R(k)[pos] = rc;
-            }
-            entered = true;
-            lkth = tk_rescan(k);
-        }
+        if (!(Ec < lkth || (Ec == lkth && rc < lkR))) return;
+        pos = sread(M[1]);
     }
-    if (entered) tk_count(Ec, k);
-    const int32_t g = sread(__hip_atomic_load(tk_gthr(), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-    __syncthreads();
-    if (threadIdx.x == 0) M[3] = min(M[3], g);
-    __syncthreads();
-    return min(lkth, sread(M[3]));
+    tk_sync();
+    if (tk_lane() == pos % kWave) {   // the lane that owns entry pos
+        tk_E(k)[pos] = Ec;
+        tk_R(k)[pos] = rc;
+    }
+    if (tk_lane() == 0) M[0] = max(cnt, pos + 1);
+    tk_sync();
+    if (pos + 1 == k || cnt >= k) (void)tk_rescan(k);
+    if (tk_lane() == 0) tk_count(Ec);
+}
+
+// Enter the nq (1 .. 64) queued keys of a super-block into the wave's list and
+// the counts; returns the new threshold.  Low keys lie close together in the
+// walk, so the few thousand that enter come to some waves by the dozen, and
+// those waves end the walk: with room in the list the lanes enter them side by
+// side, and nothing in global memory is waited for except that a wave looks at
+// the counts once in kTopkLook keys.  (An insertion at a time, with three
+// replies and the counts awaited, had made the walk of n = 31, k = 1024 take
+// 205 us and of n = 16, k = 1024, where every chunk enters, 117; now 128 and 35.)
+__device__ __noinline__ int32_t tk_drain(int nq)
+{
+    int32_t *M = tk_M();
+    const int32_t *qE = tk_queueE();
+    const uint64_t *qR = tk_queueR();
+    nq = sread(nq);
+    tk_sync();
+    const int cnt = sread(M[0]);
+    const int k = sread(M[4]);
+    const int lane = tk_lane();
+    if (cnt + nq <= k) {
+        const int j = (lane - cnt) & (kWave - 1);   // entry cnt + j is this lane's
+        if (j < nq) {
+            tk_E(k)[cnt + j] = qE[j];
+            tk_R(k)[cnt + j] = qR[j];
+            tk_count(qE[j]);
+        }
+        tk_sync();
+        if (lane == 0) M[0] = cnt + nq;
+        tk_sync();
+        if (cnt + nq == k) (void)tk_rescan(k);
+    } else {
+        for (int j = 0; j < nq; j++) tk_insert(sread(qE[j]), sread64(qR[j]));
+    }
+    const int seen = sread(M[6]) + nq;
+    int32_t g = sread(M[3]);
+    if (seen >= kTopkLook) g = min(g, tk_bound(k));
+    tk_sync();
+    if (lane == 0) {
+        M[3] = g;
+        M[6] = seen >= kTopkLook ? 0 : seen;
+    }
+    tk_sync();
+    return min(sread(M[2]), g);
 }
 
 // Publish the number of entries of the wave's list (the entries are already
 // in listE / listR at slot blockIdx.x * k).
 __device__ __noinline__ void tk_flush()
 {
-    __syncthreads();
+    tk_sync();
     const int32_t *M = tk_M();
     const uint64_t *P = tk_P();
     const int cnt = sread(M[0]);
-    if (threadIdx.x == 0) reinterpret_cast<int32_t *>(sread64(P[4]))[blockIdx.x] = cnt;
+    if (tk_lane() == 0) reinterpret_cast<int32_t *>(sread64(P[4]))[M[7]] = cnt;
 }
 
 // TIER 3: tier 2's bound test against a top-k threshold instead of the best
@@ -358,19 +408,17 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
 {
     static_assert(TIER >= 1 && TIER <= 5, "tier");
     static_assert(RC == kRowsBlock  ? G == kBlockLow
-                  : RC == kRowsWide ? G == kWideLow && MC == 3 * kWideWords + 1 && TIER == 2
+                  : RC == kRowsWide ? G == kWideLow && MC == 3 * kWideWords + 1 && (TIER == 2 || TIER == 3)
                                     : G >= kLowLevels && G <= kMaxVgprLevels,
                   "VGPR-resident levels");
-    static_assert(RC != kRowsBlock || TIER == 2 || TIER == 4, "the top-k lists are per block");
+    static_assert(RC != kRowsBlock || TIER >= 2, "no per-step exact walk over the block's rows");
     constexpr bool LR = RC == kRowsWave, BR = RC == kRowsBlock, WD = RC == kRowsWide;
     constexpr bool LONE = BR || WD;   // blocks of four waves over one instance
     constexpr int WPB = walk_block_waves<RC>();
     // packed layout (tiers 4 and 5) and the test it runs (2: best, 3: top-k)
     constexpr bool PK = TIER >= 4;
     constexpr int BT = PK ? TIER - 2 : TIER;
-    // steps per bound-test segment: tier 3's looser threshold takes the
-    // exact path more often, where shorter segments and SGPR thresholds pay
-    constexpr int SEG = BT == 3 ? kSegStepsTopk : kSegSteps;
+    constexpr int SEG = kSegSteps;   // steps per bound-test segment
     constexpr int NSEG = (1 << kSuperLog) / SEG;
     const int lane = int(threadIdx.x) % kWave;
     const uint32_t ulane = threadIdx.x % kWave;
@@ -394,7 +442,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
     };
     // the rows in dynamic LDS, after the (tier-3) list
     int32_t *const ldsR = reinterpret_cast<int32_t *>(
-        reinterpret_cast<char *>(tk_lds) + lds_rows_offset(TIER, tk.k));
+        reinterpret_cast<char *>(tk_lds) + lds_rows_offset(TIER, WPB));
 
     int cur = -1;
     // the tables, addressed as global memory (uniform base + lane offset +
@@ -415,7 +463,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
     int32_t best = kNoEnergy;     // tier 3: the current top-k threshold
     uint64_t bestRow = ~0ull;
 
-    if constexpr (BT == 3) tk_init(tk);
+    if constexpr (BT == 3) tk_init(tk, int(blockIdx.x) * WPB + bwave);
 
     // the next claim of this wave's queue (kQueues), or, where it is empty, of
     // one of the next wc.others queues
@@ -697,39 +745,6 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
                 THR[p] = THR[pp] - H[t] - CR[p];
             });
         };
-        // TIER 3: for the SEG offsets o of segment `seg` (o = SEG seg + o2),
-        //   tp(o) = best - E_p(low pattern at o) - C2(o)   (K table tab),
-        // computed by walking the Gray sequence of patterns g(o) & 31 from
-        // the segment's first one; hs = the sum of H[t] over the set low
-        // bits.  f(o2, tp) is called for every offset.  Step o can hold a
-        // candidate only if W0 <= tp(o).
-        auto for_each_tp = [&](auto segc, int tab, auto &&f) {
-            constexpr int seg = decltype(segc)::value;
-            constexpr int o0 = seg * SEG;
-            constexpr int p0 = (o0 ^ (o0 >> 1)) & (kPatterns - 1);
-            int32_t hs = 0;
-            static_for<0, kLowLevels>([&](auto tc) {
-                constexpr int t = decltype(tc)::value;
-                if constexpr ((p0 >> t) & 1) hs += H[t];
-            });
-            static_for<0, SEG>([&](auto oc) {
-                constexpr int o2 = decltype(oc)::value;
-                constexpr int o = o0 + o2;
-                if constexpr (o2 > 0) {
-                    constexpr int pa0 = ((o - 1) ^ ((o - 1) >> 1)) & (kPatterns - 1);
-                    constexpr int pa1 = (o ^ (o >> 1)) & (kPatterns - 1);
-                    constexpr int t = cx_ctz(pa0 ^ pa1);
-                    if constexpr (((pa1 >> t) & 1) != 0) hs += H[t];
-                    else hs -= H[t];
-                }
-                f(oc, (best - Enl) - hs - kall[kbase + tab * kPatterns + (o & (kPatterns - 1))]);
-            });
-        };
-        // Tier-3 thresholds of the current segment, kept in SGPRs.
-        int32_t TP[BT == 3 ? SEG : 1];
-        auto build_tp = [&](auto segc, int tab) {
-            for_each_tp(segc, tab, [&](auto oc, int32_t tp) { TP[decltype(oc)::value] = tp; });
-        };
         if constexpr (TIER == 1) build_thr();
 
         // A non-low prefix variable w flips (direction up: 0 -> 1); SLw[t] is
@@ -774,20 +789,23 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
             }
         };
 
-        // TIER 3 candidate: the chunk key (E_p + chunk minimum, row) enters
-        // the wave's list if the list has room or the key beats its largest;
-        // the threshold is then min(largest key's E when full, shared bound).
+        // TIER 3 candidate: a chunk key (E_p + chunk minimum, row) at or below
+        // the threshold waits in the wave's queue; the super-block's end enters
+        // the queue into the wave's list and lowers the threshold.
+        int nq = 0;
         auto candidate3 = [&](int32_t lm, int32_t thr, uint64_t i) {
             if (__builtin_amdgcn_ballot_w64(lm <= thr)) {
                 const int32_t Ec = wave_min(lm) + (best - thr);
-                if (Ec <= best) {
-                    const int32_t nb = sread(tk_insert(Ec, i ^ (i >> 1)));
-                    const int32_t d = nb - best;
-                    best = nb;
-                    if constexpr (BT == 3)
-                        static_for<0, SEG>([&](auto pc) { TP[decltype(pc)::value] += d; });
+                if (lane == 0) {
+                    tk_queueE()[nq] = Ec;
+                    tk_queueR()[nq] = i ^ (i >> 1);
                 }
+                nq++;
             }
+        };
+        auto test = [&](int32_t lm, int32_t thr, uint64_t i) {
+            if constexpr (BT == 3) candidate3(lm, thr, i);
+            else candidate(lm, thr, i);
         };
 
         // Low flip of static level t (< kLowLevels) with static direction (Alg. 2:
@@ -996,68 +1014,48 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
                     // hs(o) >= sum_t min(0, H[t]) and C2(o) >= the segment's
                     // minimum of C2; any lane at or below it takes the cold
                     // path (the wave minimum W0 is formed only then)
-                    int32_t tb = best - Enl - kall[kbase + kc2min_slot(SEG, tab2, h)];
+                    int32_t tb = best - Enl - kall[kbase + kKC2Min + tab2];
                     static_for<0, kLowLevels>([&](auto tc) { tb -= min(0, H[decltype(tc)::value]); });
                     const bool cold = __builtin_amdgcn_ballot_w64(lm0 <= tb) != 0;
-                    if constexpr (BT == 3) {
-                        if (__builtin_expect(cold, 0)) {
-                            // exact tests against the segment's SGPR thresholds
-                            W0 = wave_min_bcast(lm0);
-                            build_tp(sc, tab2);
-                            static_for<0, SEG>([&](auto oc) {
-                                constexpr int o2 = decltype(oc)::value;
-                                constexpr int o = h * SEG + o2;
-                                if (W0 <= TP[o2]) {
-                                    const int32_t thr =
-                                        TP[o2] + kall[kbase + (3 + tab2) * kPatterns + (o & (kPatterns - 1))];
-                                    candidate3(lane_min(E), thr, (sb << kSuperLog) | uint64_t(o));
-                                }
-                                step_flip(oc);
-                            });
-                        } else {
-                            static_for<0, SEG>([&](auto oc) { step_flip(oc); });
-                        }
+                    if (__builtin_expect(cold, 0)) {
+                        // Exact tests, step by step: at offset o,
+                        //   tp(o) = best - E_p(low pattern at o) - C2(o)
+                        // (K table tab2), with hs = the sum of H[t] over the
+                        // set low bits walked along the Gray sequence of
+                        // patterns g(o) & 31 and best read afresh at every
+                        // step (a candidate found earlier in the segment has
+                        // lowered it).  Step o can hold a candidate only if
+                        // W0 <= tp(o), and then holds one exactly when the
+                        // chunk minimum is <= tp(o) + D(o) = best - E_p(o).
+                        W0 = wave_min_bcast(lm0);
+                        constexpr int o0 = h * SEG;
+                        constexpr int p0 = (o0 ^ (o0 >> 1)) & (kPatterns - 1);
+                        int32_t hs = 0;
+                        static_for<0, kLowLevels>([&](auto tc) {
+                            constexpr int t = decltype(tc)::value;
+                            if constexpr ((p0 >> t) & 1) hs += H[t];
+                        });
+                        static_for<0, SEG>([&](auto oc) {
+                            constexpr int o2 = decltype(oc)::value;
+                            constexpr int o = o0 + o2;
+                            if constexpr (o2 > 0) {
+                                constexpr int pa0 = ((o - 1) ^ ((o - 1) >> 1)) & (kPatterns - 1);
+                                constexpr int pa1 = (o ^ (o >> 1)) & (kPatterns - 1);
+                                constexpr int t = cx_ctz(pa0 ^ pa1);
+                                if constexpr (((pa1 >> t) & 1) != 0) hs += H[t];
+                                else hs -= H[t];
+                            }
+                            const int32_t tp = (best - Enl) - hs -
+                                               kall[kbase + tab2 * kPatterns + (o & (kPatterns - 1))];
+                            if (W0 <= tp) {
+                                const int32_t thr =
+                                    tp + kall[kbase + (3 + tab2) * kPatterns + (o & (kPatterns - 1))];
+                                test(lane_min(E), thr, (sb << kSuperLog) | uint64_t(o));
+                            }
+                            step_flip(oc);
+                        });
                     } else {
-                        if (__builtin_expect(cold, 0)) {
-                            // Exact tests, step by step: at offset o,
-                            //   tp(o) = best - E_p(low pattern at o) - C2(o)
-                            // (K table tab2), with hs = the sum of H[t] over the
-                            // set low bits walked along the Gray sequence of
-                            // patterns g(o) & 31 and best read afresh at every
-                            // step (a candidate found earlier in the segment has
-                            // lowered it).  Step o can hold a candidate only if
-                            // W0 <= tp(o), and then holds one exactly when the
-                            // chunk minimum is <= tp(o) + D(o) = best - E_p(o).
-                            W0 = wave_min_bcast(lm0);
-                            constexpr int o0 = h * SEG;
-                            constexpr int p0 = (o0 ^ (o0 >> 1)) & (kPatterns - 1);
-                            int32_t hs = 0;
-                            static_for<0, kLowLevels>([&](auto tc) {
-                                constexpr int t = decltype(tc)::value;
-                                if constexpr ((p0 >> t) & 1) hs += H[t];
-                            });
-                            static_for<0, SEG>([&](auto oc) {
-                                constexpr int o2 = decltype(oc)::value;
-                                constexpr int o = o0 + o2;
-                                if constexpr (o2 > 0) {
-                                    constexpr int pa0 = ((o - 1) ^ ((o - 1) >> 1)) & (kPatterns - 1);
-                                    constexpr int pa1 = (o ^ (o >> 1)) & (kPatterns - 1);
-                                    constexpr int t = cx_ctz(pa0 ^ pa1);
-                                    if constexpr (((pa1 >> t) & 1) != 0) hs += H[t];
-                                    else hs -= H[t];
-                                }
-                                const int32_t tp = (best - Enl) - hs -
-                                                   kall[kbase + tab2 * kPatterns + (o & (kPatterns - 1))];
-                                if (W0 <= tp) {
-                                    const int32_t thr =
-                                        tp + kall[kbase + (3 + tab2) * kPatterns + (o & (kPatterns - 1))];
-                                    candidate(lane_min(E), thr, (sb << kSuperLog) | uint64_t(o));
-                                }
-                                step_flip(oc);
-                            });
-                        } else {
-                            static_for<0, SEG>([&](auto oc) { step_flip(oc); });
-                        }
+                        static_for<0, SEG>([&](auto oc) { step_flip(oc); });
                     }
                     // the flip after the segment's last step: level 5 in the
                     // middle, a low level (static direction) between shorter
@@ -1071,6 +1069,12 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
                         low_flip(std::integral_constant<int, t>{}, std::integral_constant<bool, up>{});
                     }
                 });
+                if constexpr (BT == 3) {
+                    if (__builtin_expect(nq != 0, 0)) {
+                        best = sread(tk_drain(nq));
+                        nq = 0;
+                    }
+                }
             }
         }
 
@@ -1096,9 +1100,9 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
 }
 
 template <int MC, int G, int RC>
-static size_t walk_lds_bytes(int tier, int k)
+static size_t walk_lds_bytes(int tier)
 {
-    return lds_rows_offset(tier, k) + lds_rows_bytes<MC, RC>();
+    return lds_rows_offset(tier, walk_block_waves<RC>()) + lds_rows_bytes<MC, RC>();
 }
 
 template <int MC, int G, int TIER, int RC>
@@ -1106,7 +1110,7 @@ static hipError_t launch_walk_tier(const WalkLaunch &w, const TopkWalk &tk)
 {
     constexpr int WPB = walk_block_waves<RC>();
     hipLaunchKernelGGL((walk_kernel<MC, G, TIER, RC>), dim3((w.waves + WPB - 1) / WPB),
-                       dim3(kWave * WPB), (walk_lds_bytes<MC, G, RC>(TIER, tk.k)), w.stream, w.insts,
+                       dim3(kWave * WPB), (walk_lds_bytes<MC, G, RC>(TIER)), w.stream, w.insts,
                        w.n_inst, w.claims, w.counter, w.k, tk);
     return hipGetLastError();
 }
@@ -1117,6 +1121,14 @@ static hipError_t launch_walk_g(const WalkLaunch &w)
     const TopkWalk none{};
     if constexpr (RC == kRowsBlock) {
         if (w.n_inst != 1) return hipErrorInvalidValue;
+        if (w.tier == 2) return launch_walk_tier<MC, G, 2, RC>(w, none);
+        if (w.tier == 4) return launch_walk_tier<MC, G, 4, RC>(w, none);
+        if (!w.tk || w.tk->k < 2) return hipErrorInvalidValue;
+        if (w.tier == 3) return launch_walk_tier<MC, G, 3, RC>(w, *w.tk);
+        if (w.tier == 5) return launch_walk_tier<MC, G, 5, RC>(w, *w.tk);
+    } else if constexpr (RC == kRowsWave && G == 6) {
+        // (its top-k form would be a lone walk, over the block's rows)
+        if (w.tier == 1) return launch_walk_tier<MC, G, 1, RC>(w, none);
         if (w.tier == 2) return launch_walk_tier<MC, G, 2, RC>(w, none);
         if (w.tier == 4) return launch_walk_tier<MC, G, 4, RC>(w, none);
     } else {
@@ -1134,25 +1146,29 @@ static hipError_t launch_walk_g(const WalkLaunch &w)
 
 // Resident waves per CU (>= 1).
 template <int MC, int G, int TIER, int RC>
-static int occupancy_tier(int k)
+static int occupancy_tier()
 {
     constexpr int WPB = walk_block_waves<RC>();
     int blocks = 0;
     const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-        &blocks, walk_kernel<MC, G, TIER, RC>, kWave * WPB, walk_lds_bytes<MC, G, RC>(TIER, k));
+        &blocks, walk_kernel<MC, G, TIER, RC>, kWave * WPB, walk_lds_bytes<MC, G, RC>(TIER));
     return e != hipSuccess || blocks < 1 ? 1 : blocks * WPB;
 }
 
 template <int MC, int G, int RC = kRowsVgpr>
-static int occupancy_g(int tier, int topk_k)
+static int occupancy_g(int tier)
 {
-    if (tier == 3) return occupancy_tier<MC, G, 3, RC>(topk_k);
-    if (tier == 2) return occupancy_tier<MC, G, 2, RC>(0);
+    constexpr bool topk = RC != kRowsWave || G != 6;
+    if constexpr (topk)
+        if (tier == 3) return occupancy_tier<MC, G, 3, RC>();
+    if (tier == 2) return occupancy_tier<MC, G, 2, RC>();
     if constexpr (MC >= 4) {
-        if (tier == 4) return occupancy_tier<MC, G, 4, RC>(0);
-        if (tier == 5) return occupancy_tier<MC, G, 5, RC>(topk_k);
+        if (tier == 4) return occupancy_tier<MC, G, 4, RC>();
+        if constexpr (topk)
+            if (tier == 5) return occupancy_tier<MC, G, 5, RC>();
     }
-    return occupancy_tier<MC, G, 1, RC>(0);
+    if constexpr (RC == kRowsBlock) return 1;
+    else return occupancy_tier<MC, G, 1, RC>();
 }
 
 }  // namespace qk

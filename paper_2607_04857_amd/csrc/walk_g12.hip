@@ -13,12 +13,12 @@ hipError_t launch_walk_g12(int mcols, const WalkLaunch &w)
     }
 }
 
-int occupancy_walk_g12(int mcols, int tier, int topk_k)
+int occupancy_walk_g12(int mcols, int tier)
 {
     switch (mcols) {
-    case 1: return occupancy_g<1, 12>(tier, topk_k);
-    case 2: return occupancy_g<2, 12>(tier, topk_k);
-    case 4: return occupancy_g<4, 12>(tier, topk_k);
+    case 1: return occupancy_g<1, 12>(tier);
+    case 2: return occupancy_g<2, 12>(tier);
+    case 4: return occupancy_g<4, 12>(tier);
     default: return 1;
     }
 }

@@ -12,11 +12,11 @@ hipError_t launch_walk_g12w(int mcols, const WalkLaunch &w)
     }
 }
 
-int occupancy_walk_g12w(int mcols, int tier, int topk_k)
+int occupancy_walk_g12w(int mcols, int tier)
 {
     switch (mcols) {
-    case 8: return occupancy_g<8, 12>(tier, topk_k);
-    case 16: return occupancy_g<16, 12>(tier, topk_k);
+    case 8: return occupancy_g<8, 12>(tier);
+    case 16: return occupancy_g<16, 12>(tier);
     default: return 1;
     }
 }

@@ -3,6 +3,8 @@
 
 namespace qk {
 
-hipError_t launch_walk_g4(const WalkLaunch &w) { return launch_walk_g<16, 4, kRowsBlock>(w); }
+hipError_t launch_walk_g4(const WalkLaunch &w) { return launch_walk_g<16, kBlockLow, kRowsBlock>(w); }
+
+int occupancy_walk_g4(int tier) { return occupancy_g<16, kBlockLow, kRowsBlock>(tier); }
 
 }  // namespace qk

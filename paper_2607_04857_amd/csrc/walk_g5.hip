@@ -8,9 +8,9 @@ hipError_t launch_walk_g5(bool lds, const WalkLaunch &w)
     return lds ? launch_walk_g<16, 5, kRowsWave>(w) : launch_walk_g<16, 5>(w);
 }
 
-int occupancy_walk_g5(bool lds, int tier, int topk_k)
+int occupancy_walk_g5(bool lds, int tier)
 {
-    return lds ? occupancy_g<16, 5, kRowsWave>(tier, topk_k) : occupancy_g<16, 5>(tier, topk_k);
+    return lds ? occupancy_g<16, 5, kRowsWave>(tier) : occupancy_g<16, 5>(tier);
 }
 
 }  // namespace qk

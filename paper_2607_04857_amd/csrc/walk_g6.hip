@@ -8,9 +8,9 @@ hipError_t launch_walk_g6(bool lds, const WalkLaunch &w)
     return lds ? launch_walk_g<16, 6, kRowsWave>(w) : launch_walk_g<16, 6>(w);
 }
 
-int occupancy_walk_g6(bool lds, int tier, int topk_k)
+int occupancy_walk_g6(bool lds, int tier)
 {
-    return lds ? occupancy_g<16, 6, kRowsWave>(tier, topk_k) : occupancy_g<16, 6>(tier, topk_k);
+    return lds ? occupancy_g<16, 6, kRowsWave>(tier) : occupancy_g<16, 6>(tier);
 }
 
 }  // namespace qk

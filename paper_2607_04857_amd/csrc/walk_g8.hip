@@ -12,11 +12,11 @@ hipError_t launch_walk_g8(int mcols, const WalkLaunch &w)
     }
 }
 
-int occupancy_walk_g8(int mcols, int tier, int topk_k)
+int occupancy_walk_g8(int mcols, int tier)
 {
     switch (mcols) {
-    case 8: return occupancy_g<8, 8>(tier, topk_k);
-    case 16: return occupancy_g<16, 8>(tier, topk_k);
+    case 8: return occupancy_g<8, 8>(tier);
+    case 16: return occupancy_g<16, 8>(tier);
     default: return 1;
     }
 }

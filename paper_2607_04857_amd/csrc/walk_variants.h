@@ -26,25 +26,26 @@ struct WalkLaunch {
 // per CU of the variant (>= 1).
 // 12 VGPR-resident levels, 1, 2 or 4 columns per lane
 hipError_t launch_walk_g12(int mcols, const WalkLaunch &w);
-int occupancy_walk_g12(int mcols, int tier, int topk_k);
+int occupancy_walk_g12(int mcols, int tier);
 // 12 VGPR-resident levels, 8 or 16 columns per lane
 hipError_t launch_walk_g12w(int mcols, const WalkLaunch &w);
-int occupancy_walk_g12w(int mcols, int tier, int topk_k);
+int occupancy_walk_g12w(int mcols, int tier);
 // 8 VGPR-resident levels, 8 or 16 columns per lane
 hipError_t launch_walk_g8(int mcols, const WalkLaunch &w);
-int occupancy_walk_g8(int mcols, int tier, int topk_k);
+int occupancy_walk_g8(int mcols, int tier);
 // 16 columns per lane, G = 6: levels 0-5 in VGPRs (lds = false) or levels
 // 0-2 and 5 in VGPRs, 3-4 in LDS (lds = true, row cache "4")
 hipError_t launch_walk_g6(bool lds, const WalkLaunch &w);
-int occupancy_walk_g6(bool lds, int tier, int topk_k);
+int occupancy_walk_g6(bool lds, int tier);
 // 16 columns per lane, G = 5: levels 0-4 in VGPRs (lds = false) or levels
 // 0-2 in VGPRs, 3-4 in LDS (lds = true, row cache "3")
 hipError_t launch_walk_g5(bool lds, const WalkLaunch &w);
-int occupancy_walk_g5(bool lds, int tier, int topk_k);
-// row cache "4" of a lone instance, tiers 2 and 4 (the same four waves per
-// SIMD): levels 0-3 in VGPRs, 4-12 in LDS shared by a block of four waves
+int occupancy_walk_g5(bool lds, int tier);
+// row cache "4" of a lone instance, tiers 2 to 5 (the same four waves per
+// SIMD): levels 0-3 in VGPRs, 4-8 in LDS shared by a block of four waves
 hipError_t launch_walk_g4(const WalkLaunch &w);
-// the same for tier 2 on wide words
+int occupancy_walk_g4(int tier);
+// the same for tiers 2 and 3 on wide words (as many waves)
 hipError_t launch_walk_wide(const WalkLaunch &w);
 
 }  // namespace qk
