@@ -13,9 +13,13 @@ roofline         = the walk kernel (dominant kernel) against the int32 VALU
                    = 78.64 T int32 lane-ops/s (the published 157.3 TFLOP/s fp32
                    vector rate counts an FMA lane-op as 2 flops; v_add_u32
                    issues a wave64 in 2 cycles, as the VALU probe confirms);
-                   algorithmic work = 1 int32 add per state (the Gray update of
-                   Sec. III-B); duration = HIP events around the walk kernel on
-                   its own stream.
+                   algorithmic work = 1 add per state (the Gray update of
+                   Sec. III-B).  An instance whose chunk energies span less
+                   than 2^21 values, as the headline's do, walks on wide words
+                   (three states per 64-bit add, which issues at half the
+                   rate): 16 states in 11 issue slots, so its peak is 16/11 of
+                   the int32 one (114.4 T states/s).  Duration = the walk
+                   kernel's own start and end, by the device clock.
 cpu_baseline     = the CPU oracle (direct evaluation) timed on this host over a
                    bounded contiguous index range of the same instance.
 batched          = 4096 instances, n ~ U{20..34}, int32 U[-100,100] (seed 5):
@@ -59,7 +63,7 @@ PMC_FILE = os.path.join(ROOT, "profiles", "walk_n44_pmc.md")
 # sources of the walk kernel (its template, helpers, layout and the unit of
 # the headline variant); a PMC summary taken with other sources is stale
 KERNEL_SRCS = [os.path.join(ROOT, "paper_2607_04857_amd", "csrc", f)
-               for f in ("kernels.h", "kcommon.h", "walk.h", "walk_g4.hip")]
+               for f in ("kernels.h", "kcommon.h", "walk.h", "walk_wide.hip")]
 
 
 def kernel_hash():
@@ -70,11 +74,26 @@ def kernel_hash():
     return h.hexdigest()[:16]
 
 
-def kernel_name(r):
+def chunk_span(Q, B):
+    """Largest minus smallest chunk energy E_sd(s, x_p) = E_s(s) + sum_v x_v M[v][s]
+    over every prefix x_p and suffix column s of the split."""
+    import numpy as np
+    T = np.triu(Q) + np.tril(Q, -1).T
+    A = Q.shape[0] - B
+    s = (np.arange(1 << B)[:, None] >> np.arange(B - 1, -1, -1)) & 1
+    E = ((s @ T[A:, A:]) * s).sum(1)
+    M = s @ T[:A, A:].T
+    return int((E + np.maximum(M, 0).sum(1)).max() - (E + np.minimum(M, 0).sum(1)).min())
+
+
+def kernel_name(r, wide=False):
     """Template instance of the walk kernel a lone solve's plan runs (row cache
-    "4": levels 0-3 in VGPRs and the next ones in LDS, shared by a block; "3":
-    G = 5 with the rows of levels 3 and 4 in LDS per wave)."""
+    "4": levels 0-3 in VGPRs and the next ones in LDS, shared by a block, and 0-2
+    in VGPRs on wide words; "3": G = 5 with the rows of levels 3 and 4 in LDS
+    per wave)."""
     mc = 2 ** (r.B - 7 if r.tier >= 4 else r.B - 6)    # words per lane
+    if wide and r.vgpr_levels == 4:
+        return "walk_kernel<%d,3,%d,3>" % (mc, r.tier)
     if r.vgpr_levels == 4:
         return "walk_kernel<%d,4,%d,2>" % (mc, r.tier)
     if r.vgpr_levels == 3:
@@ -394,7 +413,9 @@ def main():
     states = float(2 ** n) * args.steps
     value = states / dt
     walk_ms = sum(kms) / len(kms)
-    achieved = (2.0 ** n) / (walk_ms / 1e3)          # int32 adds per second in the walk
+    achieved = (2.0 ** n) / (walk_ms / 1e3)          # state updates per second in the walk
+    wide = chunk_span(Q, r.B) < 2 ** 21
+    slots = 11 / 16 if wide else 1.0                 # issue slots of an int32 add, per state
     line = {
         "metric": METRIC,
         "value": value,
@@ -412,17 +433,18 @@ def main():
                                "U[-10000,10000], seed 4", "n": n, "states_per_step": 2 ** n,
                    "tier": r.tier, "A": r.A, "B": r.B, "L": r.L, "vgpr_levels": r.vgpr_levels},
         "result": {"energy": r.energy_i, "index": r.index},
-        "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": VALU_PEAK_OPS / 1e12,
-                     "unit": "TOP/s", "frac": achieved / VALU_PEAK_OPS,
+        "roofline": {"bound": "alu", "achieved": achieved / 1e12,
+                     "peak": VALU_PEAK_OPS / slots / 1e12,
+                     "unit": "TOP/s", "frac": achieved * slots / VALU_PEAK_OPS,
                      "traffic": traffic_from_profile(),
-                     "kernel": kernel_name(r),
+                     "kernel": kernel_name(r, wide), "states_per_issue_slot": 1 / slots,
                      "walk_ms": walk_ms},
         "paper_context": {"states_per_s": 7.42e12, "hardware": "NVIDIA H100 80GB",
                           "precision": "int16", "n": 44},
     }
     probe, _ = q.probe_valu("add", 8, 2048)
     line["roofline"]["probe_peak"] = probe / 1e12       # measured v_add_u32 lane-ops/s
-    line["roofline"]["frac_of_probe"] = achieved / probe
+    line["roofline"]["frac_of_probe"] = achieved * slots / probe
     if not args.no_packed:
         line["single_packed"] = single_packed(q)
     if not args.no_batch:
