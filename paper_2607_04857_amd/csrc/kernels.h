@@ -179,17 +179,18 @@ struct TopkBufs {
     int32_t *candE;      // [waves * k] list entries <= the final bound, dense ...
     uint64_t *candR;
     int32_t *candN;      // [1] their number (zero before the finish)
-    int32_t *chunkE;     // [k] the k smallest chunk keys ...
+    int32_t *chunkE;     // [k] the k smallest chunk keys, in no order ...
     uint64_t *chunkR;    // [k] ... and their prefix rows
-    int32_t *chunkCount; // [1] chunks selected (min(k, chunks met))
+    int32_t *chunkCount; // [0] chunks selected (min(k, chunks met)), [1] their largest key
     int32_t *stE;        // [k << B] (or [2^n] direct) candidate state energies
     uint64_t *stI;       // same, U_N rows
     int32_t *segCount;   // [0]: states kept by the rescan (2^n when direct)
-    int32_t *selE;       // [k] the k smallest states, sorted by (E, index)
+    int32_t *selE;       // [k] the k smallest states, in no order
     uint64_t *selR;
-    int32_t *selCount;   // [1]
-    TopkState *out;      // [k] answer (fp32: sorted by (E64, index))
+    int32_t *selCount;   // [0] states selected, [1] their largest energy
+    TopkState *out;      // [k] the states in order of (E, index)
 };
+
 
 struct FinalRes {
     int64_t E;         // exact integer energy of the answer
@@ -201,6 +202,14 @@ struct FinalRes {
                            // start (from before the top-k seed to its compaction), in
                            // ticks of the device's constant clock
 };
+
+// Where a top-k finish leaves its results: device or mapped host memory.
+struct TopkResults {
+    FinalRes *best;
+    PrepOut *prep;       // the preparation's outcome, or null
+    TopkState *topk;     // [k] answer (fp32: sorted by (E64, index))
+};
+constexpr int64_t kTopkBadState = INT64_MIN;   // E of a state whose energy did not verify
 
 // Host image of a lone solve, read by the first kernel itself instead of by a
 // copy ahead of it (a 4 us copy and a 10 us gap): `copy_bytes` of the mapped
@@ -312,10 +321,9 @@ hipError_t launch_topk_seed(const Inst *d_inst, int32_t *d_gthr, int k, hipStrea
 // Top-k finish of one instance (descriptor d_inst, host copy hI): select the
 // k smallest chunks of the walk lists, rescan them (or, direct, evaluate all
 // 2^n states), select and sort the k smallest states, verify their energies
-// and write buf.out and *d_best (status 3: an energy did not verify; 4:
-// fewer than k states).
+// and write the results (best's status 4: fewer than k states).
 hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs &buf, int k,
-                              FinalRes *d_best, unsigned long long *d_counters,
+                              const TopkResults &to, unsigned long long *d_counters,
                               hipStream_t stream);
 
 // Per-instance reduction of item results (insts[i].res[0..n_items)), argmin

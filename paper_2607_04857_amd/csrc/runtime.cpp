@@ -150,13 +150,13 @@ static JobOffsets compute_offsets(Job &job)
         put(&o.candR, W * k * sizeof(uint64_t));
         put(&o.chunkE, k * sizeof(int32_t));
         put(&o.chunkR, k * sizeof(uint64_t));
-        put(&o.chunkCount, sizeof(int32_t));
+        put(&o.chunkCount, 2 * sizeof(int32_t));
         put(&o.stE, nst * sizeof(int32_t));
         put(&o.stI, nst * sizeof(uint64_t));
         put(&o.segCount, k * sizeof(int32_t));
         put(&o.selE, k * sizeof(int32_t));
         put(&o.selR, k * sizeof(uint64_t));
-        put(&o.selCount, sizeof(int32_t));
+        put(&o.selCount, 2 * sizeof(int32_t));
     }
     job.bytes = off;
     return o;
@@ -365,8 +365,12 @@ qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream, const unsi
                 "walk kernel");
     }
     if (job.topk > 1)
-        QRT_HIP(qk::launch_topk_finish(job.d_insts, job.h_inst0, job.tkb, job.topk, job.d_out, counters,
-                                       stream),
+        QRT_HIP(qk::launch_topk_finish(
+                    job.d_insts, job.h_inst0, job.tkb, job.topk,
+                    results ? qk::TopkResults{&results->best, job.dq ? &results->prep : nullptr,
+                                              results->topk}
+                            : qk::TopkResults{job.d_out, nullptr, job.tkb.out},
+                    counters, stream),
                 "top-k kernels");
     else
         QRT_HIP(qk::launch_finish(job.d_insts, ni, results ? &results->best : job.d_out, up, counters,
@@ -589,11 +593,10 @@ qubo_status_t solve_planned(qrt::Job &job, hipStream_t stream, int waves_per_cu,
     do {
         if ((rs = qrt::job_bind(&job, d_mem)) != QUBO_OK) break;
         hipError_t e;
-        LoneResults *direct_out = nullptr;   // k = 1: the finish writes the host block itself
+        LoneResults *direct_out = nullptr;   // the finish writes the host block itself
         if (mapped) {
             std::memcpy(ws.host, job.stage.data(), job.stage_bytes);
-            if (job.topk <= 1)
-                direct_out = reinterpret_cast<LoneResults *>(ws.host_dev + job.stage_bytes);
+            direct_out = reinterpret_cast<LoneResults *>(ws.host_dev + job.stage_bytes);
         } else {
             // the image by copies (the part that starts out zero with it)
             job.stage.resize(job.stage_bytes + job.zero_bytes, 0);
@@ -640,6 +643,12 @@ qubo_status_t solve_planned(qrt::Job &job, hipStream_t stream, int waves_per_cu,
         P.p = prep.p;
         P.eps_q = prep.eps_q;
         P.sum_abs = prep.sum_abs;
+    }
+    for (int i = 0; job.topk > 1 && fr.status == 0 && i < job.topk; i++) {
+        if (tk_host[i].E == qk::kTopkBadState) {
+            qrt::set_error("internal self-check failed (status 3)");
+            return QUBO_EINTERNAL;
+        }
     }
     st = qrt::job_result(job, 0, fr, out);
     if (st != QUBO_OK) return st;

@@ -93,7 +93,7 @@ struct LoneResults {
 // memory must exist).  image: device address of a mapped host block holding
 // the staging image, which the first kernel reads, or null once the image has
 // been copied into place.  results: device address of a mapped host block for
-// the results of a lone k = 1 solve (or, from its start on, the FinalRes of a
+// the results of a lone solve (or, from its start on, the FinalRes of a
 // best-state job's instances), or null to leave them in device memory.
 qubo_status_t job_enqueue_kernels(const Job &job, hipStream_t stream,
                                   const unsigned char *image = nullptr,

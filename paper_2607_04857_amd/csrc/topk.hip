@@ -14,11 +14,12 @@
 //   3. rescan those chunks: every state's energy from the tables,
 //      E = E_p(row) + E_s(s) + x_p M_int[:, s] (Sec. II-C), keeping the
 //      states at or below the largest selected chunk key (the k chunk minima
-//      are k states at or below it, so the k-th smallest energy is too);
-//      an instance with fewer than k chunks keeps all of its states;
-//   4. select the k smallest (E, index) among them, sorted;
-//   5. verify each energy from T, rescore fp32 instances in float64 and sort
-//      those by (E64, index).
+//      are k states at or below it, so the k-th smallest energy is too), or,
+//      with fewer than k chunks, those at or below a bound that each block
+//      finds for its own;
+//   4. select the k smallest (E, index) among them;
+//   5. put them in order, verify each energy from T, rescore fp32 instances
+//      in float64 and sort those by (E64, index).
 // Selection is an exact radix select on the energy (order-preserving
 // unsigned key) and, where the k-th energy is tied, on the row/index among
 // the tied entries; keys are unique (a row is walked once, an index occurs
@@ -39,11 +40,10 @@ struct SelArgs {
     const int32_t *count;
     uint32_t mult;
     int k;
-    int32_t *oE;               // [k] output, sorted by (E, R)
+    int32_t *oE;               // [k] output, in no order
     uint64_t *oR;
-    int32_t *oCount;
+    int32_t *oCount;           // [0] entries selected, [1] their largest energy
     int32_t *clear;            // set to 0 when done (a later kernel's counter), or null
-    int32_t *status;           // likewise (the answer's status, raised by the final kernel)
 };
 
 __device__ __forceinline__ uint32_t ukey(int32_t e) { return uint32_t(e) ^ 0x80000000u; }
@@ -85,19 +85,16 @@ __device__ void pick_bin(const uint32_t *hist, uint32_t need, uint32_t *bin, uin
 
 // One block.  The energies are taken from their minimum, so that only the
 // digits their spread occupies are counted, and up to kHeld entries a thread
-// are read from memory once.  What bounds it is the chain of digits and the
-// sort's 55 exchanges.  Measured: 4-5 us for a few
-// hundred candidates and 22 us for 2600 of them with k = 1024 (59 us, and 42 us
-// for a thousand, when one thread walked the histogram and every digit of the
-// key was counted).
+// are read from memory once.  What bounds it is the chain of digits.  Nothing
+// here needs the selected entries in order (the final kernel ranks them, on
+// many blocks): with the 55 exchanges of a sort at the end, 2600 candidates
+// with k = 1024 had taken 24 us, now 8, and a few hundred 6, now 5.
 constexpr int kHeld = 4;
 
 __global__ __launch_bounds__(kSelThreads) void topk_select_kernel(SelArgs a)
 {
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sh_pos, sh_bin, sh_rest, sh_in, sh_min, sh_max;
-    __shared__ int32_t sE[kSelThreads];
-    __shared__ uint64_t sR[kSelThreads];
     const uint32_t tid = threadIdx.x;
     const uint32_t k = uint32_t(a.k);
     const uint32_t total = uint32_t(*a.count) * a.mult;
@@ -129,23 +126,23 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_kernel(SelArgs a)
         }
     };
 
-    bool take_all = total <= k;
+    const bool take_all = total <= k;
     uint32_t uk = 0xFFFFFFFFu;      // energy key of the k-th entry
     bool all_eq = true;             // take every entry whose key equals uk
     uint64_t rk = ~0ull;            // else those with R <= rk
+    int32_t mn = INT32_MAX, mx = INT32_MIN;
+    for_valid([&](int32_t e, uint64_t) {
+        mn = min(mn, e);
+        mx = max(mx, e);
+    });
+    mn = wave_min(mn);
+    mx = -1 - wave_min(-1 - mx);   // max: ~ reverses the order
+    if (tid % kWave == 0) {
+        atomicMin(&sh_min, ukey(mn));
+        atomicMax(&sh_max, ukey(mx));
+    }
+    __syncthreads();
     if (!take_all) {
-        int32_t mn = INT32_MAX, mx = INT32_MIN;
-        for_valid([&](int32_t e, uint64_t) {
-            mn = min(mn, e);
-            mx = max(mx, e);
-        });
-        mn = wave_min(mn);
-        mx = -1 - wave_min(-1 - mx);   // max: ~ reverses the order
-        if (tid % kWave == 0) {
-            atomicMin(&sh_min, ukey(mn));
-            atomicMax(&sh_max, ukey(mx));
-        }
-        __syncthreads();
         const uint32_t u0 = sh_min, spread = sh_max - u0;
         const int digits = spread ? (31 - __builtin_clz(spread)) / 8 : 0;
         uint32_t prefix = 0, mask = 0, need = k;
@@ -185,53 +182,22 @@ __global__ __launch_bounds__(kSelThreads) void topk_select_kernel(SelArgs a)
             rk = rprefix;
         }
     }
-    // compaction into LDS (at most k entries)
+    // at most k entries
     for_valid([&](int32_t e, uint64_t r) {
         const uint32_t u = ukey(e);
         if (take_all || u < uk || (u == uk && (all_eq || r <= rk))) {
             const uint32_t p = atomicAdd(&sh_pos, 1u);
             if (p < k) {
-                sE[p] = e;
-                sR[p] = r;
+                a.oE[p] = e;
+                a.oR[p] = r;
             }
         }
     });
     __syncthreads();
-    const uint32_t cnt = min(sh_pos, k);
-    // bitonic sort of the kept entries by (E, R), padded to a power of two
-    uint32_t P = 1;
-    while (P < cnt) P <<= 1;
-    if (tid >= cnt && tid < P) {
-        sE[tid] = INT32_MAX;
-        sR[tid] = ~0ull;
-    }
-    __syncthreads();
-    for (uint32_t size = 2; size <= P; size <<= 1) {
-        for (uint32_t st = size >> 1; st > 0; st >>= 1) {
-            const uint32_t j = tid ^ st;
-            if (tid < P && j > tid) {
-                const bool asc = (tid & size) == 0;
-                const bool jl = key_less(sE[j], sR[j], sE[tid], sR[tid]);
-                if (jl == asc) {
-                    const int32_t te = sE[tid];
-                    const uint64_t tr = sR[tid];
-                    sE[tid] = sE[j];
-                    sR[tid] = sR[j];
-                    sE[j] = te;
-                    sR[j] = tr;
-                }
-            }
-            __syncthreads();
-        }
-    }
-    if (tid < cnt) {
-        a.oE[tid] = sE[tid];
-        a.oR[tid] = sR[tid];
-    }
     if (tid == 0) {
-        *a.oCount = int32_t(cnt);
+        a.oCount[0] = int32_t(min(sh_pos, k));
+        a.oCount[1] = int32_t((take_all ? sh_max : uk) ^ 0x80000000u);
         if (a.clear) *a.clear = 0;
-        if (a.status) *a.status = 0;
     }
 }
 
@@ -274,8 +240,10 @@ __global__ __launch_bounds__(256) void topk_compact_kernel(const int32_t *__rest
 // with E <= the largest selected chunk key go to (stE, stI), densely (slots
 // counted in *stCount, zeroed by the chunk select).  With fewer than k chunks
 // selected (the instance has fewer than k chunks) the k-th smallest state may
-// lie above every chunk minimum, so every state of every chunk is kept: at
-// most rc << B < k << B entries.
+// lie above every chunk minimum: each block then finds, by bisection on the
+// value, the least bound with k of its own states (which bounds the instance's
+// k-th smallest), so that hundreds of states of a chunk reach the select and not
+// all (n = 18, k = 700: whole call 570 -> 167 us).  At most rc << B < k << B entries.
 // A chunk's states follow from its suffix fields h_t = sum over the set prefix
 // variables v of T[v][A+t]: E(row, s) = E_p + E_s(s) + sum_{t in s} h_t, E_s
 // read from the walk's table.  One atomic per block of kRescanWaves chunks
@@ -286,11 +254,11 @@ constexpr int kRescanWaves = 8;
 
 __global__ __launch_bounds__(kRescanWaves *kWave) void topk_rescan_kernel(
     const Inst *__restrict__ inst, const uint64_t *__restrict__ rows,
-    const int32_t *__restrict__ rowE, const int32_t *__restrict__ rowCount, int k,
+    const int32_t *__restrict__ rowCount, int k,
     int32_t *__restrict__ stE, uint64_t *__restrict__ stI, int32_t *__restrict__ stCount)
 {
     __shared__ int32_t sT[kMaxVars * kMaxVars];
-    __shared__ int32_t sN[kRescanWaves], sBase;
+    __shared__ int32_t sN[kRescanWaves], sLo[kRescanWaves], sHi[kRescanWaves], sBase;
     const Inst I = *inst;
     const int n = I.n, A = I.A, B = I.B;
     const int tid = int(threadIdx.x), lane = tid % kWave, w = tid / kWave;
@@ -298,8 +266,7 @@ __global__ __launch_bounds__(kRescanWaves *kWave) void topk_rescan_kernel(
     const int32_t b = int32_t(blockIdx.x) * kRescanWaves + w;
     if (int32_t(blockIdx.x) * kRescanWaves >= rc) return;
     for (int e = tid; e < n * n; e += kRescanWaves * kWave) sT[e] = I.T[e];
-    // rows are sorted by (key, row)
-    const int32_t bound = rc < k ? INT32_MAX : rowE[rc - 1];
+    int32_t bound = rowCount[1];   // the largest selected key
     const bool mine = b < rc;
     const uint64_t row = mine ? sread64(rows[b]) : 0;
     const int NW = I.packed ? (1 << B) / 2 : 1 << B, MC = NW / kWave;
@@ -323,7 +290,6 @@ __global__ __launch_bounds__(kRescanWaves *kWave) void topk_rescan_kernel(
     const int32_t top = __builtin_amdgcn_readlane(h, 0);   // packed: the high column's variable A
     // energies of the lane's words (packed: of both columns of a word)
     int32_t E[kMaxCols], E2[kMaxCols];
-    int32_t kept = 0;
 #pragma unroll
     for (int j = 0; j < kMaxCols; j++) {
         int32_t hj = 0;   // the bits of j
@@ -339,11 +305,55 @@ __global__ __launch_bounds__(kRescanWaves *kWave) void topk_rescan_kernel(
             E[j] = low + hj + eb[j] - I.pack_shift;
             E2[j] = 0;
         }
-        if (mine && j < MC) {
-            kept += __builtin_popcountll(__builtin_amdgcn_ballot_w64(E[j] <= bound));
-            if (I.packed) kept += __builtin_popcountll(__builtin_amdgcn_ballot_w64(E2[j] <= bound));
-        }
     }
+    // this wave's states at or below e
+    auto at_most = [&](int32_t e) {
+        int32_t c = 0;
+#pragma unroll
+        for (int j = 0; j < kMaxCols; j++) {
+            if (!mine || j >= MC) continue;
+            c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(E[j] <= e));
+            if (I.packed) c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(E2[j] <= e));
+        }
+        return c;
+    };
+    if (rc < k) {
+        int32_t mn = INT32_MAX, mx = INT32_MIN;
+#pragma unroll
+        for (int j = 0; j < kMaxCols; j++) {
+            if (!mine || j >= MC) continue;
+            mn = min(mn, I.packed ? min(E[j], E2[j]) : E[j]);
+            mx = max(mx, I.packed ? max(E[j], E2[j]) : E[j]);
+        }
+        mn = wave_min(mn);
+        mx = -1 - wave_min(-1 - mx);
+        if (lane == 0) {
+            sLo[w] = mn;
+            sHi[w] = mx;
+        }
+        __syncthreads();
+        int64_t lo = INT32_MAX, hi = INT32_MIN;
+        for (int x = 0; x < kRescanWaves; x++) {
+            lo = min(lo, int64_t(sLo[x]));
+            hi = max(hi, int64_t(sHi[x]));
+        }
+        // (a block with fewer than k states ends at its largest)
+        while (lo < hi) {
+            const int64_t mid = lo + (hi - lo) / 2;
+            const int32_t c = at_most(int32_t(mid));
+            __syncthreads();   // the last round's counts have been read
+            if (lane == 0) sN[w] = c;
+            __syncthreads();
+            int32_t sum = 0;
+#pragma unroll
+            for (int x = 0; x < kRescanWaves; x++) sum += sN[x];
+            if (sum >= k) hi = mid;
+            else lo = mid + 1;
+        }
+        bound = int32_t(hi);
+        __syncthreads();
+    }
+    const int32_t kept = at_most(bound);
     if (lane == 0) sN[w] = kept;
     __syncthreads();
     if (tid == 0) {
@@ -391,61 +401,86 @@ __global__ __launch_bounds__(256) void topk_direct_kernel(const Inst *__restrict
     if (blockIdx.x == 0 && threadIdx.x == 0) segCount[0] = int32_t(N);
 }
 
-// Step 5: one thread per state of the answer, one wave a block: its energy
-// from T must be the one the selection has, and float32 instances are rescored
-// in float64.  int32 answers are in their final order already (the last
-// select's), float32 ones are ordered by topk_order_kernel.  Measured: 17 us for
-// k = 1024 at n = 31, 10 us for k = 16 at n = 21 (54 and 21 us in one block).
-__global__ __launch_bounds__(kWave) void topk_final_kernel(
+// Step 5: a block of sixteen waves per 64 states of the answer, a lane each in
+// every wave.  A state's place is the number of selected keys below its own
+// (each wave counts a sixteenth of them, broadcast from LDS), and its energy
+// from T, a sixteenth of the rows a wave, must be the one the selection has.
+// float32 instances are rescored in float64 and ordered by topk_order_kernel.
+// A state whose energy differs goes out as kTopkBadState: out and best may be
+// mapped host memory, where no atomic could raise a status (a copy of the
+// results had cost 10-12 us).  Measured, with the selection left unordered: 8 us
+// for k = 1024 at n = 31 and 3 us for k = 16 at n = 21 (16 and 9 us at one thread
+// a state, of states that the selection had sorted).
+constexpr int kFinalWaves = 16;
+
+__global__ __launch_bounds__(kFinalWaves *kWave) void topk_final_kernel(
     const Inst *__restrict__ inst, const int32_t *__restrict__ selE,
     const uint64_t *__restrict__ selR, const int32_t *__restrict__ selCount, int k,
     TopkState *__restrict__ out, FinalRes *__restrict__ best,
-    const unsigned long long *__restrict__ counters)
+    const unsigned long long *__restrict__ counters, const PrepOut *__restrict__ prep,
+    PrepOut *__restrict__ prep_out)
 {
     __shared__ int32_t sT[kMaxVars * kMaxVars];
     __shared__ float sQ[kMaxVars * kMaxVars];
+    __shared__ int32_t sE[kSelThreads], sPlace[kWave], sSum[kWave];
+    __shared__ uint64_t sR[kSelThreads];
     const Inst I = *inst;
     const int n = I.n;
-    const int at = int(blockIdx.x) * kWave + int(threadIdx.x);
-    const int cnt = *selCount;
-    const uint64_t idx = at < cnt ? selR[at] : 0;
-    const int32_t e = at < cnt ? selE[at] : 0;
-    for (int x = int(threadIdx.x); x < n * n; x += kWave) {
+    const int tid = int(threadIdx.x), lane = tid % kWave, w = tid / kWave;
+    const int cnt = min(*selCount, k);
+    for (int x = tid; x < cnt; x += kFinalWaves * kWave) {
+        sE[x] = selE[x];
+        sR[x] = selR[x];
+    }
+    for (int x = tid; x < n * n; x += kFinalWaves * kWave) {
         sT[x] = I.T[x];
         if (I.Qf) sQ[x] = I.Qf[x];
     }
+    if (tid < kWave) sPlace[tid] = sSum[tid] = 0;
     __syncthreads();
+    const int at = int(blockIdx.x) * kWave + lane;
+    const bool on = at < cnt;
+    const uint64_t idx = on ? sR[at] : 0;
+    const int32_t e = on ? sE[at] : 0;
+    int32_t place = 0;
+    for (int x = w; x < cnt; x += kFinalWaves) place += key_less(sE[x], sR[x], e, idx) ? 1 : 0;
     int32_t sum = 0;   // a partial sum of T: within the int32 bound
-    for (int i = 0; i < n; i++) {
+    for (int i = w; i < n; i += kFinalWaves) {
         int32_t row = 0;
 #pragma unroll 4
         for (int j = i; j < n; j++) row += -int32_t((idx >> (n - 1 - j)) & 1) & sT[i * n + j];
         sum += -int32_t((idx >> (n - 1 - i)) & 1) & row;
     }
-    if (at < cnt && at < k) {
+    if (on) {
+        atomicAdd(&sPlace[lane], place);
+        atomicAdd(&sSum[lane], sum);
+    }
+    __syncthreads();
+    if (w != 0) return;
+    if (on) {
         TopkState o;
-        o.E = e;
+        o.E = sSum[lane] == e ? int64_t(e) : kTopkBadState;
         o.E64 = I.Qf ? energy_f64(sQ, n, idx) : double(e);
         o.index = idx;
-        out[at] = o;
+        out[sPlace[lane]] = o;
+        if (sPlace[lane] == 0) {
+            best->E = o.E;
+            best->index = idx;
+            best->E64 = o.E64;
+        }
     }
-    // (the last select cleared the status)
-    if (__builtin_amdgcn_ballot_w64(at < cnt && sum != e) && threadIdx.x == 0)
-        atomicMax(&best->status, 3);
     if (at == 0) {
-        best->E = cnt > 0 ? e : 0;
-        best->index = idx;
         best->walk_ticks = counters ? counters[kClockWord + 1] - counters[kClockWord] : 0;
-        best->E64 = cnt > 0 ? (I.Qf ? energy_f64(sQ, n, idx) : double(e)) : 0.0;
-        if (cnt < k) atomicMax(&best->status, 4);
+        best->status = cnt < k ? 4 : 0;
+        if (prep_out) *prep_out = *prep;
     }
 }
 
 // The integer order is exact for the scaled energies; float32 answers are
 // reported by their float64 energies, in their own (E64, index) order.
 __global__ __launch_bounds__(kSelThreads) void topk_order_kernel(
-    const int32_t *__restrict__ selCount, int k, TopkState *__restrict__ out,
-    FinalRes *__restrict__ best)
+    const int32_t *__restrict__ selCount, int k, const TopkState *__restrict__ in,
+    TopkState *__restrict__ out, FinalRes *__restrict__ best)
 {
     __shared__ double sF[kSelThreads];
     __shared__ uint64_t sI[kSelThreads];
@@ -455,9 +490,9 @@ __global__ __launch_bounds__(kSelThreads) void topk_order_kernel(
     uint32_t P = 1;
     while (P < uint32_t(cnt)) P <<= 1;
     const bool on = int(tid) < cnt;
-    sF[tid] = on ? out[tid].E64 : __builtin_huge_val();
-    sI[tid] = on ? out[tid].index : ~0ull;
-    sE[tid] = on ? out[tid].E : 0;
+    sF[tid] = on ? in[tid].E64 : __builtin_huge_val();
+    sI[tid] = on ? in[tid].index : ~0ull;
+    sE[tid] = on ? in[tid].E : 0;
     __syncthreads();
     for (uint32_t size = 2; size <= P; size <<= 1) {
         for (uint32_t st = size >> 1; st > 0; st >>= 1) {
@@ -654,7 +689,7 @@ hipError_t launch_topk_seed(const Inst *d_inst, int32_t *d_gthr, int k, hipStrea
 }
 
 hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs &buf, int k,
-                              FinalRes *d_best, unsigned long long *d_counters,
+                              const TopkResults &to, unsigned long long *d_counters,
                               hipStream_t stream)
 {
     if (hI.direct) d_counters = nullptr;
@@ -687,8 +722,8 @@ hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs
         ch.clear = buf.segCount;     // [0]: the rescan's state counter
         hipLaunchKernelGGL(topk_select_kernel, dim3(1), dim3(kSelThreads), 0, stream, ch);
         hipLaunchKernelGGL(topk_rescan_kernel, dim3((k + kRescanWaves - 1) / kRescanWaves),
-                           dim3(kRescanWaves * kWave), 0, stream, d_inst, buf.chunkR, buf.chunkE,
-                           buf.chunkCount, k, buf.stE, buf.stI, buf.segCount);
+                           dim3(kRescanWaves * kWave), 0, stream, d_inst, buf.chunkR, buf.chunkCount,
+                            k, buf.stE, buf.stI, buf.segCount);
         st.count = buf.segCount;     // states kept by the rescan, densely
         st.mult = 1;
     }
@@ -698,13 +733,13 @@ hipError_t launch_topk_finish(const Inst *d_inst, const Inst &hI, const TopkBufs
     st.oE = buf.selE;
     st.oR = buf.selR;
     st.oCount = buf.selCount;
-    st.status = &d_best->status;
     hipLaunchKernelGGL(topk_select_kernel, dim3(1), dim3(kSelThreads), 0, stream, st);
-    hipLaunchKernelGGL(topk_final_kernel, dim3((k + kWave - 1) / kWave), dim3(kWave), 0, stream,
-                       d_inst, buf.selE, buf.selR, buf.selCount, k, buf.out, d_best, d_counters);
+    hipLaunchKernelGGL(topk_final_kernel, dim3((k + kWave - 1) / kWave),
+                       dim3(kFinalWaves * kWave), 0, stream, d_inst, buf.selE, buf.selR, buf.selCount, k, hI.Qf ? buf.out : to.topk,
+                       to.best, d_counters, buf.walk.prep, to.prep);
     if (hI.Qf)
         hipLaunchKernelGGL(topk_order_kernel, dim3(1), dim3(kSelThreads), 0, stream, buf.selCount, k,
-                           buf.out, d_best);
+                           buf.out, to.topk, to.best);
     return hipGetLastError();
 }
 
