@@ -4,9 +4,10 @@
 // thread owns the device stream and runs ticks:
 //   1. admission: queued requests enter device slots, first come first
 //      served, while a slot is free and the device-memory budget allows;
-//      each admitted request gets one allocation (its tables, per-item
-//      results) and a table-build launch; the tables stay resident until it
-//      finishes;
+//      each admitted request gets one block of device memory (its tables,
+//      per-item results), a finished request's where one of that size is kept,
+//      and a round's requests one table-build launch; the tables stay
+//      resident until the request finishes;
 //   2. one persistent walk launch over a slice of work items from EVERY
 //      admitted request (water-filling: requests with few items left get all
 //      of them, the rest share the remaining per-tick item budget), so a
@@ -98,6 +99,11 @@ struct qubo_server {
     std::vector<int> free_kslots;
     TickBuf ticks[2];
     int cur = 0;
+    // Device memory of finished requests, by size, for the next ones (the
+    // scheduler thread's, on its stream): with what the active requests hold,
+    // within the budget, and given back whenever the server idles.
+    std::unordered_map<size_t, std::vector<void *>> kept;
+    size_t kept_bytes = 0;
 
     std::mutex mu;
     std::condition_variable cv_work, cv_done;
@@ -138,7 +144,37 @@ void fail_all(qubo_server *s, const std::string &msg)
     s->cv_done.notify_all();
 }
 
-// Called with the tick's event complete: publish results, release memory.
+void give_back(qubo_server *s)
+{
+    for (auto &kv : s->kept)
+        for (void *p : kv.second) (void)hipFreeAsync(p, s->stream);
+    s->kept.clear();
+    s->kept_bytes = 0;
+}
+
+// Device memory of a request about to be set up (counted in mem_used already).
+hipError_t take_memory(qubo_server *s, size_t bytes, void **p)
+{
+    auto it = s->kept.find(bytes);
+    if (it != s->kept.end() && !it->second.empty()) {
+        *p = it->second.back();
+        it->second.pop_back();
+        s->kept_bytes -= bytes;
+        return hipSuccess;
+    }
+    if (s->kept_bytes + s->mem_used > s->budget) give_back(s);
+    hipError_t e = hipMallocAsync(p, bytes, s->stream);
+    if (e != hipSuccess && s->kept_bytes) {
+        (void)hipGetLastError();
+        give_back(s);
+        e = hipMallocAsync(p, bytes, s->stream);
+    }
+    return e;
+}
+
+// Called with the tick's event complete: publish results, keep the memory for
+// other requests (a hipFreeAsync each, about 10 us, had held back the results
+// of a tick of 25 requests by 250 us, and the next tick as long).
 void complete_tick(qubo_server *s, TickBuf &t)
 {
     std::vector<Request *> done = std::move(t.finishing);
@@ -160,9 +196,14 @@ void complete_tick(qubo_server *s, TickBuf &t)
         }
         s->lat_ms.push_back(lat);
         s->states_done += std::ldexp(1.0, r->job.plans[0].n);
-        (void)hipFreeAsync(r->d_mem, s->stream);
-        r->d_mem = nullptr;
         s->mem_used -= r->job.bytes;
+        if (s->kept_bytes + r->job.bytes + s->mem_used <= s->budget) {
+            s->kept[r->job.bytes].push_back(r->d_mem);
+            s->kept_bytes += r->job.bytes;
+        } else {
+            (void)hipFreeAsync(r->d_mem, s->stream);
+        }
+        r->d_mem = nullptr;
         s->free_kslots.push_back(r->kslot);
         s->active.erase(std::find(s->active.begin(), s->active.end(), r));
     }
@@ -201,7 +242,7 @@ std::vector<Request *> take_admissions(qubo_server *s)
 // tick buffer's mapped block.
 qubo_status_t setup_request(qubo_server *s, TickBuf &t, Request *r, size_t k)
 {
-    QRT_HIP(hipMallocAsync(&r->d_mem, r->job.bytes, s->stream), "hipMallocAsync");
+    QRT_HIP(take_memory(s, r->job.bytes, &r->d_mem), "hipMallocAsync");
     qubo_status_t st = qrt::job_bind(&r->job, r->d_mem);
     if (st != QUBO_OK) return st;
     // The K table lives in the server's arena so one walk launch sees every
@@ -364,7 +405,8 @@ void scheduler(qubo_server *s)
                               !s->ticks[1].inflight;
             if (idle) {
                 if (s->stop && s->queue.empty()) break;
-                s->cv_work.wait_for(lk, std::chrono::milliseconds(20));
+                if (s->cv_work.wait_for(lk, std::chrono::milliseconds(20)) == std::cv_status::timeout)
+                    give_back(s);
                 continue;
             }
         }
@@ -425,6 +467,8 @@ void server_free(qubo_server *s)
         if (kv.second->d_mem) (void)hipFree(kv.second->d_mem);
         delete kv.second;
     }
+    for (auto &kv : s->kept)
+        for (void *m : kv.second) (void)hipFree(m);
     if (s->d_karena) (void)hipFree(s->d_karena);
     if (s->stream) (void)hipStreamDestroy(s->stream);
     delete s;
