@@ -16,16 +16,19 @@
 //    split, Sec. III-C.2, at lane granularity);
 //  * the rows M_int[k] of the most frequently flipped Gray levels stay on
 //    chip: by default levels 0-2 and 5 in VGPRs and 3-4 in LDS (8 KB per
-//    wave), which fits 128 VGPRs and so four waves per SIMD; other variants
-//    keep 5, 6, 8 or 12 levels in VGPRs; higher levels are formed when they
+//    wave), or, walking one instance alone, 0-3 in VGPRs and 4-8 in LDS (32 KB
+//    per block of four waves), which fits 128 VGPRs and so four waves per
+//    SIMD; other variants keep 5, 6, 8 or 12 levels in VGPRs; a lone instance
+//    whose energies allow it walks three columns to a 64-bit word (kWideBits);
+//    higher levels are formed when they
 //    flip (level 6 once per 128 steps; level 5, in the 5-level variants, once
 //    per 64) from the row's two parts: column j*64 + lane of a row is a sum
 //    over the lane's bits plus a sum over the bits of j, so a row is one load
 //    per lane, 2^B / 64 scalars and a three-operand add per word;
 //  * wavefronts take work items (2^L consecutive Gray steps of the prefix,
 //    the "straightforward" split of Sec. III-C.1 along the Gray index), the
-//    first by its own number and the others from atomic counters, one at a
-//    time; the grid is persistent;
+//    first by its own number and the others from eight atomic counters, singly
+//    or in runs (WalkClaims); the grid is persistent;
 //  * the scalar unit keeps the prefix self-energy E_p: the walk is unrolled
 //    over 64-step super-blocks in which the five lowest Gray levels follow a
 //    static pattern and level 5 flips once, in the middle, so the flip
@@ -821,7 +824,7 @@ bool walk_variant_exists(int mcols, int vgpr_levels)
 int walk_occupancy(int mcols, int vgpr_levels, int tier)
 {
     switch (vgpr_levels) {
-    case 4: return tier == 3 || tier == 5 ? occupancy_walk_g4(tier) : occupancy_walk_g6(true, tier);
+    case 4: return tier == 3 || tier == 5 ? occupancy_walk_g4_topk(tier) : occupancy_walk_g6(true, tier);
     case 3: return occupancy_walk_g5(true, tier);
     case 6: return occupancy_walk_g6(false, tier);
     case 5: return occupancy_walk_g5(false, tier);

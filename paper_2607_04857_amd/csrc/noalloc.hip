@@ -1,8 +1,8 @@
 // noalloc.hip -- the allocation-free single solve (qubo_solve_noalloc).
 //
 // Same plan, kernels and result as qubo_solve with k = 1, but the job's
-// device image (descriptors, folded T, float32 Q, M_int / E_s / couplings,
-// bound tables, item records, results) lives in one file-scope device
+// device image (descriptors, folded T, float32 Q, M_int's lane parts, E_s,
+// couplings, bound tables, item records, results) lives in one file-scope device
 // array instead of a per-call allocation.  Each device holds its own copy of
 // the array at its own address, found once per device with
 // hipGetSymbolAddress; host code passes that address, never the array's

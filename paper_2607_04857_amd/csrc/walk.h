@@ -55,6 +55,11 @@ __device__ __forceinline__ int32_t wave_min_bcast(int32_t v)
 //               from its parts takes a three-operand add, which issues at half
 //               the rate (one on every boundary was 1.5% of the VALU work).
 //               Measured: n = 44 walk 255.9 -> 254.6 ms, n = 33 and 36 equal.
+//               A top-k walk holds what survives the list's call across the
+//               super-block; with G = 4 that spilled 9 registers that each
+//               half reloads, so its rows start at level 3 (n = 36 packed,
+//               k = 100 walk 795 -> 725 us, n = 33 float32, k = 1024 320 -> 280,
+//               n = 30, k = 4 57 -> 52).
 //  kRowsWide    the chunk vector in wide words (kWideBits): the walk is bound
 //               by its adds, and five 64-bit ones and one of 32 bits take 11
 //               issue slots where 16 of 32 bits take 16.  As kRowsBlock, with
@@ -73,9 +78,12 @@ constexpr int kWideRows = 2 * (kWideTop - kWideLow + 1);
 // a row: its words, then the plain one in a slot of the same size (one address
 // register for all): 36 KB in all, four blocks a CU
 constexpr size_t kWideRowBytes = kWave * (kWideWords + 1) * sizeof(uint64_t);
-constexpr int kBlockLow = 4;      // first Gray level of the block's rows
+constexpr int kBlockLow = 4;      // first Gray level of the block's rows,
+constexpr int kBlockLowTopk = 3;  // of a top-k walk, which needs the VGPRs
 constexpr int kBlockTop = 8;      // last one
-constexpr int kBlockRows = 8;     // 32 KB at MC = 16: four blocks fit a CU's LDS
+// rows for first level G (plain up to level 5, then signed): 32 KB at MC = 16
+// and G = 4, 36 KB at G = 3, four blocks a CU
+constexpr int block_rows(int G) { return (kSuperLog - G) + 2 * (kBlockTop - kSuperLog + 1); }
 
 template <int RC>
 constexpr int walk_block_waves()
@@ -99,10 +107,10 @@ __host__ __device__ constexpr size_t lds_rows_offset(int tier, int waves)
 {
     return (tier == 3 || tier == 5) ? (size_t(waves) * topk_lds_bytes() + 15) & ~size_t(15) : 0;
 }
-template <int MC, int RC>
+template <int MC, int G, int RC>
 constexpr size_t lds_rows_bytes()
 {
-    constexpr int rows = RC == kRowsBlock ? kBlockRows : RC == kRowsWave ? 2 : 0;
+    constexpr int rows = RC == kRowsBlock ? block_rows(G) : RC == kRowsWave ? 2 : 0;
     if (RC == kRowsWide) return kWideRows * kWideRowBytes;
     return size_t(rows) * MC * kWave * sizeof(int32_t);
 }
@@ -407,7 +415,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
     unsigned long long *__restrict__ counter, const int32_t *__restrict__ kall, TopkWalk tk)
 {
     static_assert(TIER >= 1 && TIER <= 5, "tier");
-    static_assert(RC == kRowsBlock  ? G == kBlockLow
+    static_assert(RC == kRowsBlock  ? G == kBlockLow || G == kBlockLowTopk
                   : RC == kRowsWide ? G == kWideLow && MC == 3 * kWideWords + 1 && (TIER == 2 || TIER == 3)
                                     : G >= kLowLevels && G <= kMaxVgprLevels,
                   "VGPR-resident levels");
@@ -530,9 +538,11 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
         A = I.A;
         ML = to_global(I.ML);
         kbase = I.kslot * kKTable;
-        for (int r = bwave; r < kBlockRows; r += WPB) {
-            const int t = r < 2 ? kBlockLow + r : kSuperLog + (r - 2) / 2;
-            const int row = (r >= 2 && r % 2 ? 2 * A : A) - 1 - t;   // M_int's or its negation's
+        for (int r = bwave; r < block_rows(G); r += WPB) {
+            constexpr int plain = kSuperLog - G;
+            const int t = r < plain ? G + r : kSuperLog + (r - plain) / 2;
+            // M_int's or its negation's
+            const int row = (r >= plain && (r - plain) % 2 ? 2 * A : A) - 1 - t;
             if (t >= A) continue;
             const int32_t ml = lrow(row);
             const ivec<MC> mh = hrow(row);
@@ -828,10 +838,10 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
                     const int32_t r = ldsR[(t - 3) * (MC * kWave) + j * kWave + lane];
                     E[j] = up ? E[j] + r : E[j] - r;
                 }
-            } else if constexpr (BR && t >= kBlockLow) {
+            } else if constexpr (BR && t >= G) {
 #pragma unroll
                 for (int j = 0; j < MC; j++) {
-                    const int32_t r = ldsR[((t - kBlockLow) * MC + j) * kWave + lane];
+                    const int32_t r = ldsR[((t - G) * MC + j) * kWave + lane];
                     E[j] = up ? E[j] + r : E[j] - r;
                 }
             } else {
@@ -851,7 +861,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
             } else if constexpr (BR) {
                 int32_t r[MC];
 #pragma unroll
-                for (int j = 0; j < MC; j++) r[j] = ldsR[((tm - kBlockLow) * MC + j) * kWave + lane];
+                for (int j = 0; j < MC; j++) r[j] = ldsR[((tm - G) * MC + j) * kWave + lane];
                 if (up) {
 #pragma unroll
                     for (int j = 0; j < MC; j++) E[j] += r[j];
@@ -932,7 +942,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
             } else if constexpr (BR) {
                 const int t = A - 1 - b.w;
                 if (__builtin_expect(t <= kBlockTop, 1)) {
-                    const int r0 = 2 + 2 * (t - kSuperLog) + (b.up ? 0 : 1);
+                    const int r0 = kSuperLog - G + 2 * (t - kSuperLog) + (b.up ? 0 : 1);
 #pragma unroll
                     for (int j = 0; j < MC; j++) E[j] += ldsR[(r0 * MC + j) * kWave + lane];
                 }
@@ -1102,7 +1112,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
 template <int MC, int G, int RC>
 static size_t walk_lds_bytes(int tier)
 {
-    return lds_rows_offset(tier, walk_block_waves<RC>()) + lds_rows_bytes<MC, RC>();
+    return lds_rows_offset(tier, walk_block_waves<RC>()) + lds_rows_bytes<MC, G, RC>();
 }
 
 template <int MC, int G, int TIER, int RC>
@@ -1124,8 +1134,8 @@ static hipError_t launch_walk_g(const WalkLaunch &w)
         if (w.tier == 2) return launch_walk_tier<MC, G, 2, RC>(w, none);
         if (w.tier == 4) return launch_walk_tier<MC, G, 4, RC>(w, none);
         if (!w.tk || w.tk->k < 2) return hipErrorInvalidValue;
-        if (w.tier == 3) return launch_walk_tier<MC, G, 3, RC>(w, *w.tk);
-        if (w.tier == 5) return launch_walk_tier<MC, G, 5, RC>(w, *w.tk);
+        if (w.tier == 3) return launch_walk_tier<MC, kBlockLowTopk, 3, RC>(w, *w.tk);
+        if (w.tier == 5) return launch_walk_tier<MC, kBlockLowTopk, 5, RC>(w, *w.tk);
     } else if constexpr (RC == kRowsWave && G == 6) {
         // (its top-k form would be a lone walk, over the block's rows)
         if (w.tier == 1) return launch_walk_tier<MC, G, 1, RC>(w, none);
@@ -1167,8 +1177,7 @@ static int occupancy_g(int tier)
         if constexpr (topk)
             if (tier == 5) return occupancy_tier<MC, G, 5, RC>();
     }
-    if constexpr (RC == kRowsBlock) return 1;
-    else return occupancy_tier<MC, G, 1, RC>();
+    return occupancy_tier<MC, G, 1, RC>();
 }
 
 }  // namespace qk

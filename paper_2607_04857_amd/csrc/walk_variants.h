@@ -42,9 +42,10 @@ int occupancy_walk_g6(bool lds, int tier);
 hipError_t launch_walk_g5(bool lds, const WalkLaunch &w);
 int occupancy_walk_g5(bool lds, int tier);
 // row cache "4" of a lone instance, tiers 2 to 5 (the same four waves per
-// SIMD): levels 0-3 in VGPRs, 4-8 in LDS shared by a block of four waves
+// SIMD): levels 0-3 (top-k: 0-2) in VGPRs, the next ones to 8 in LDS shared by
+// a block of four waves
 hipError_t launch_walk_g4(const WalkLaunch &w);
-int occupancy_walk_g4(int tier);
+int occupancy_walk_g4_topk(int tier);
 // the same for tiers 2 and 3 on wide words (as many waves)
 hipError_t launch_walk_wide(const WalkLaunch &w);
 
