@@ -295,6 +295,18 @@ hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts
                        const int32_t *d_k,
                        int waves, hipStream_t stream, const TopkWalk *tk = nullptr, int wide = 0);
 
+// Two groups of one launch_walk each, on 16 columns and row cache "4", of tiers 2
+// and 4, as one launch.
+struct WalkPart {
+    const Inst *d_insts;
+    int n_inst;
+    uint64_t total_items;
+    int max_L;
+    unsigned long long *d_counter;
+};
+hipError_t launch_walk_pair(const WalkPart &tier2, const WalkPart &tier4, const int32_t *d_k,
+                            int waves, hipStream_t stream);
+
 // Whether a (mcols, vgpr_levels) walk variant is compiled in, and whether
 // its packed form (tiers 4 and 5: 2 mcols 64 suffix columns) is.
 bool walk_variant_exists(int mcols, int vgpr_levels);

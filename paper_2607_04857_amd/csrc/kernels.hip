@@ -834,6 +834,16 @@ int walk_occupancy(int mcols, int vgpr_levels, int tier)
     }
 }
 
+hipError_t launch_walk_pair(const WalkPart &tier2, const WalkPart &tier4, const int32_t *d_k,
+                            int waves, hipStream_t stream)
+{
+    auto part = [&](int tier, const WalkPart &p) {
+        const WalkClaims wc{p.total_items, 0, 0, p.max_L >= kStealSteps ? kQueues - 1 : 0};
+        return WalkLaunch{tier, p.d_insts, p.n_inst, wc, p.d_counter, d_k, waves, stream, nullptr};
+    };
+    return launch_walk_pair(part(2, tier2), part(4, tier4));
+}
+
 hipError_t launch_walk(int mcols, int vgpr_levels, int tier, const Inst *d_insts, int n_inst,
                        uint64_t total_items, int max_L, unsigned long long *d_counter,
                        const int32_t *d_k, int waves, hipStream_t stream, const TopkWalk *tk,

@@ -366,8 +366,25 @@ qubo_status_t enqueue_tick(qubo_server *s, TickBuf &t, bool *launched)
     const qk::Inst *d_descs = reinterpret_cast<const qk::Inst *>(t.d_block);
     unsigned long long *counters =
         reinterpret_cast<unsigned long long *>(t.d_block + s->counters_at);
+    // the two default variants in one launch (grouped in order of tier)
+    for (size_t k = 0; k + 1 < launches.size(); k++) {
+        Launch &a = launches[k], &b = launches[k + 1];
+        if (a.P->mcols != 16 || a.P->vgpr_levels != 4 || a.P->tier != 2 || b.P->mcols != 16 ||
+            b.P->vgpr_levels != 4 || b.P->tier != 4)
+            continue;
+        const int occ = qk::walk_occupancy(16, 4, 2);
+        const int waves = int(std::min<uint64_t>(a.items + b.items, uint64_t(s->cus) * uint64_t(occ)));
+        QRT_HIP(qk::launch_walk_pair(
+                    {d_descs + a.first, a.count, a.items, a.max_L, counters + k * qk::kCounterWords},
+                    {d_descs + b.first, b.count, b.items, b.max_L,
+                     counters + (k + 1) * qk::kCounterWords},
+                    s->d_karena, waves, s->stream),
+                "walk kernel");
+        a.items = b.items = 0;
+    }
     for (size_t k = 0; k < launches.size(); k++) {
         const Launch &L = launches[k];
+        if (L.items == 0) continue;
         const int occ = qk::walk_occupancy(L.P->mcols, L.P->vgpr_levels, L.P->tier);
         const int waves = int(std::min<uint64_t>(L.items, uint64_t(s->cus) * uint64_t(occ)));
         QRT_HIP(qk::launch_walk(L.P->mcols, L.P->vgpr_levels, L.P->tier, d_descs + L.first, L.count,

@@ -408,11 +408,15 @@ __device__ __noinline__ void tk_flush()
 
 // TIER 3: tier 2's bound test against a top-k threshold instead of the best
 //         energy: the wave keeps the k smallest chunk keys it has met in LDS.
-template <int MC, int G, int TIER, int RC = kRowsVgpr>
-__global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
-                             (walk_waves_per_simd<MC, G, RC>())) void walk_kernel(
-    const Inst *__restrict__ insts, int n_inst, WalkClaims wc,
-    unsigned long long *__restrict__ counter, const int32_t *__restrict__ kall, TopkWalk tk)
+// own: a wave's first claim is its own number's, and the queues' start past
+// those (see claim).
+template <int MC, int G, int TIER, int RC>
+// (No __restrict__ here: on an inlined function's parameters it cost the lone
+// kernels some forty SGPRs.)
+__device__ __forceinline__ void walk_items(const Inst *insts, int n_inst, WalkClaims wc,
+                                           unsigned long long *counter,
+                                           const int32_t *kall, TopkWalk tk,
+                                           bool own)
 {
     static_assert(TIER >= 1 && TIER <= 5, "tier");
     static_assert(RC == kRowsBlock  ? G == kBlockLow || G == kBlockLowTopk
@@ -481,8 +485,8 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
             uint64_t c = 0;
             if (lane == 0) c = atomicAdd(counter + queue * kQueueStride, 1ull);
             // a queue's first items are the waves' own
-            const uint64_t v =
-                (sread64(c) + (gridDim.x * WPB + kQueues - 1 - queue) / kQueues) * kQueues + queue;
+            const uint64_t first = own ? (gridDim.x * WPB + kQueues - 1 - queue) / kQueues : 0;
+            const uint64_t v = (sread64(c) + first) * kQueues + queue;
             if (v < wc.claims || k >= wc.others) return v;
             queue = (queue + 1) % kQueues;
         }
@@ -551,7 +555,7 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
         }
         __syncthreads();
     }
-    for (uint64_t v = blockIdx.x * WPB + bwave; v < wc.claims; v = claim()) {
+    for (uint64_t v = own ? blockIdx.x * WPB + bwave : claim(); v < wc.claims; v = claim()) {
         // items [g, g + 2^run): a run of them for the first wc.runs claims
         const int run = v < wc.runs ? wc.run_log : 0;
         const uint64_t g = v < wc.runs ? v << wc.run_log : v + ((wc.runs << wc.run_log) - wc.runs);
@@ -1107,6 +1111,30 @@ __global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
         }
     }
     if constexpr (BT == 3) tk_flush();
+}
+
+template <int MC, int G, int TIER, int RC = kRowsVgpr>
+__global__ __launch_bounds__(kWave *walk_block_waves<RC>(),
+                             (walk_waves_per_simd<MC, G, RC>())) void walk_kernel(
+    const Inst *__restrict__ insts, int n_inst, WalkClaims wc,
+    unsigned long long *__restrict__ counter, const int32_t *__restrict__ kall, TopkWalk tk)
+{
+    walk_items<MC, G, TIER, RC>(insts, n_inst, wc, counter, kall, tk, true);
+}
+
+// The instances of tier 2 and then those of tier 4 in one launch: a wave that
+// finds the first queues empty goes on to the second ones, so that the tail of
+// the one (the time of an item, four waves to a SIMD) is filled by the other.
+// 64 requests of n = 16..34, 13 of them float32, submitted at once: 1961 -> 1905 us.
+template <int MC, int G, int RC>
+__global__ __launch_bounds__(kWave, (walk_waves_per_simd<MC, G, RC>())) void walk_pair_kernel(
+    const Inst *__restrict__ insts2, int n2, WalkClaims wc2, unsigned long long *__restrict__ counter2,
+    const Inst *__restrict__ insts4, int n4, WalkClaims wc4, unsigned long long *__restrict__ counter4,
+    const int32_t *__restrict__ kall)
+{
+    const TopkWalk none{};
+    walk_items<MC, G, 2, RC>(insts2, n2, wc2, counter2, kall, none, true);
+    walk_items<MC, G, 4, RC>(insts4, n4, wc4, counter4, kall, none, false);
 }
 
 template <int MC, int G, int RC>

@@ -13,4 +13,13 @@ int occupancy_walk_g6(bool lds, int tier)
     return lds ? occupancy_g<16, 6, kRowsWave>(tier) : occupancy_g<16, 6>(tier);
 }
 
+hipError_t launch_walk_pair(const WalkLaunch &a, const WalkLaunch &b)
+{
+    if (a.tier != 2 || b.tier != 4) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((walk_pair_kernel<16, 6, kRowsWave>), dim3(a.waves), dim3(kWave),
+                       (walk_lds_bytes<16, 6, kRowsWave>(4)), a.stream, a.insts, a.n_inst, a.claims,
+                       a.counter, b.insts, b.n_inst, b.claims, b.counter, a.k);
+    return hipGetLastError();
+}
+
 }  // namespace qk

@@ -37,6 +37,8 @@ int occupancy_walk_g8(int mcols, int tier);
 // 0-2 and 5 in VGPRs, 3-4 in LDS (lds = true, row cache "4")
 hipError_t launch_walk_g6(bool lds, const WalkLaunch &w);
 int occupancy_walk_g6(bool lds, int tier);
+// row cache "4", the instances of tier 2 (a) and then of tier 4 (b) on a's waves
+hipError_t launch_walk_pair(const WalkLaunch &a, const WalkLaunch &b);
 // 16 columns per lane, G = 5: levels 0-4 in VGPRs (lds = false) or levels
 // 0-2 in VGPRs, 3-4 in LDS (lds = true, row cache "3")
 hipError_t launch_walk_g5(bool lds, const WalkLaunch &w);
