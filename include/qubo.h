@@ -87,7 +87,7 @@ typedef struct {
                             on the packed layout (k > 1)                   */
     int vgpr_levels;     /* Gray levels with VGPR-resident rows (0 when direct)    */
     uint64_t states;     /* states evaluated = 2^n                                 */
-    double kernel_ms;    /* GPU time of the walk kernel (HIP events)               */
+    double kernel_ms;    /* GPU time of the walk (device clock)                    */
     double total_ms;     /* host wall time of the whole call                       */
 } qubo_result_t;
 
@@ -128,7 +128,11 @@ typedef struct {
                             in VGPRs and levels 3-4 in LDS (8 KB per wave), or,
                             walking one instance alone for its best state,
                             levels 0-3 in VGPRs and 4-8 in LDS (32 KB per
-                            block of four waves); 3
+                            block of four waves), or, where int32 chunk
+                            energies span less than 2^21 values (exactly
+                            proven) and A >= 20, three of them to a 64-bit
+                            word with levels 0-2 in VGPRs and 3-8 in LDS,
+                            with the same results; 3
                             keeps levels 0-2 in VGPRs, levels 3-4 in LDS and
                             reads every level from 5 up from L2              */
     int item_first;

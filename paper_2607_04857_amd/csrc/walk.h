@@ -64,8 +64,8 @@ __device__ __forceinline__ int32_t wave_min_bcast(int32_t v)
 //               by its adds, and five 64-bit ones and one of 32 bits take 11
 //               issue slots where 16 of 32 bits take 16.  As kRowsBlock, with
 //               levels 0-2 in VGPRs and 3-8 in LDS, and every row as well as
-//               its negation, since no 64-bit add subtracts: 128 VGPRs, none
-//               spilled.  A boundary above level 8 forms its row from its parts
+//               its negation, since no 64-bit add subtracts: 128 VGPRs, and no
+//               spill in the loop.  A boundary above level 8 forms its row from its parts
 //               (1 in 8 of the boundaries).  Measured against kRowsBlock on the
 //               same instances: n = 44 walk 254.6 -> 192.5 ms (169 ms at the
 //               adds' full rate; 194 with level 9 in LDS and the plain words'
@@ -407,7 +407,7 @@ __device__ __noinline__ void tk_flush()
 }
 
 // TIER 3: tier 2's bound test against a top-k threshold instead of the best
-//         energy: the wave keeps the k smallest chunk keys it has met in LDS.
+//         energy: the wave keeps the k smallest chunk keys it has met (above).
 // own: a wave's first claim is its own number's, and the queues' start past
 // those (see claim).
 template <int MC, int G, int TIER, int RC>
