@@ -1,5 +1,6 @@
 // runtime.cpp -- device jobs and the single-instance C ABI.
 #include "runtime.h"
+#include "workspace.h"
 
 #include <chrono>
 #include <cmath>
@@ -438,86 +439,6 @@ hipStream_t thread_stream(qubo_status_t *st)
     return s;
 }
 
-namespace {
-
-// Device memory and a mapped host block that a thread keeps between its lone
-// solves (an allocation, its release and the runtime's trimming at each
-// synchronisation cost more than a small solve: 10 us, and milliseconds for
-// the 110 MB of a k = 1024 solve's lists).  A call has them to itself and is
-// synchronous, so the next one may use another stream.  At most kKeepBytes of
-// device memory and kKeepHostBytes of host memory are kept; larger jobs
-// allocate their own device memory and copy from pageable memory.  Given back
-// when the thread ends, and when it goes on with another device.
-constexpr size_t kKeepBytes = size_t(128) << 20;
-constexpr size_t kKeepHostBytes = size_t(4) << 20;
-
-struct Workspace {
-    int dev = -1;
-    unsigned char *mem = nullptr, *host = nullptr, *host_dev = nullptr;
-    size_t mem_bytes = 0, host_bytes = 0;
-
-    void release_mem()
-    {
-        if (mem) (void)hipFree(mem);
-        mem = nullptr;
-        mem_bytes = 0;
-    }
-    void release_host()
-    {
-        if (host) (void)hipHostFree(host);
-        host = host_dev = nullptr;
-        host_bytes = 0;
-    }
-    void release()
-    {
-        release_mem();
-        release_host();
-    }
-    // At least `need` bytes of device memory and of mapped host memory; either
-    // stays null where it cannot be had (the call then does without it).
-    void reserve(int device, size_t need, size_t host_need)
-    {
-        if (dev != device) release();
-        dev = device;
-        if (need <= mem_bytes && host_need <= host_bytes) return;
-        // allocation is legal while another stream of the thread captures
-        hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-        const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
-        if (need > mem_bytes && need <= kKeepBytes) {
-            release_mem();
-            const size_t b = align_up(need, size_t(1) << 20);
-            void *p = nullptr;
-            if (hipMalloc(&p, b) == hipSuccess) {
-                mem = static_cast<unsigned char *>(p);
-                mem_bytes = b;
-            } else {
-                (void)hipGetLastError();
-            }
-        }
-        if (host_need > host_bytes && host_need <= kKeepHostBytes) {
-            release_host();
-            const size_t b = align_up(host_need, size_t(64) << 10);
-            void *p = nullptr, *d = nullptr;
-            if (hipHostMalloc(&p, b, hipHostMallocMapped) == hipSuccess) {
-                if (hipHostGetDevicePointer(&d, p, 0) == hipSuccess) {
-                    host = static_cast<unsigned char *>(p);
-                    host_dev = static_cast<unsigned char *>(d);
-                    host_bytes = b;
-                } else {
-                    (void)hipHostFree(p);
-                }
-            }
-            if (!host) (void)hipGetLastError();
-        }
-        if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
-    }
-    ~Workspace() { release(); }
-};
-
-thread_local Workspace g_workspace;
-
-}  // namespace
-
 qubo_status_t run_once(Job &job, hipStream_t stream, std::vector<qk::FinalRes> *out)
 {
     const size_t ni = job.plans.size(), out_bytes = ni * sizeof(qk::FinalRes);
@@ -525,7 +446,7 @@ qubo_status_t run_once(Job &job, hipStream_t stream, std::vector<qk::FinalRes> *
     DeviceInfo di;
     qubo_status_t rs = device_info(&di);
     if (rs != QUBO_OK) return rs;
-    Workspace &ws = g_workspace;
+    Workspace &ws = workspace();
     ws.reserve(di.device, job.bytes, job.stage_bytes + out_bytes);
     const bool kept = ws.mem_bytes >= job.bytes;
     const bool mapped = ws.host_bytes >= job.stage_bytes + out_bytes;
@@ -580,7 +501,7 @@ qubo_status_t solve_planned(qrt::Job &job, hipStream_t stream, int waves_per_cu,
     if (st != QUBO_OK) return st;
     DeviceInfo di;
     if ((st = device_info(&di)) != QUBO_OK) return st;
-    Workspace &ws = g_workspace;
+    Workspace &ws = workspace();
     ws.reserve(di.device, job.bytes, job.stage_bytes + job.result_bytes);
     const bool kept = ws.mem_bytes >= job.bytes;
     const bool mapped = ws.host_bytes >= job.stage_bytes + job.result_bytes;
