@@ -446,8 +446,8 @@ qubo_status_t run_once(Job &job, hipStream_t stream, std::vector<qk::FinalRes> *
     DeviceInfo di;
     qubo_status_t rs = device_info(&di);
     if (rs != QUBO_OK) return rs;
-    Workspace &ws = workspace();
-    ws.reserve(di.device, job.bytes, job.stage_bytes + out_bytes);
+    Workspace &ws = workspace(di.device);
+    ws.reserve(job.bytes, job.stage_bytes + out_bytes);
     const bool kept = ws.mem_bytes >= job.bytes;
     const bool mapped = ws.host_bytes >= job.stage_bytes + out_bytes;
     void *d_mem = ws.mem;
@@ -501,8 +501,8 @@ qubo_status_t solve_planned(qrt::Job &job, hipStream_t stream, int waves_per_cu,
     if (st != QUBO_OK) return st;
     DeviceInfo di;
     if ((st = device_info(&di)) != QUBO_OK) return st;
-    Workspace &ws = workspace();
-    ws.reserve(di.device, job.bytes, job.stage_bytes + job.result_bytes);
+    Workspace &ws = workspace(di.device);
+    ws.reserve(job.bytes, job.stage_bytes + job.result_bytes);
     const bool kept = ws.mem_bytes >= job.bytes;
     const bool mapped = ws.host_bytes >= job.stage_bytes + job.result_bytes;
     std::vector<LoneResults> pageable(mapped ? 0 : job.result_bytes / sizeof(LoneResults) + 1);

@@ -1,6 +1,8 @@
 // workspace.cpp -- memory that a thread keeps between its lone solves.
 #include "workspace.h"
 
+#include <map>
+
 namespace qrt {
 
 namespace {
@@ -43,10 +45,8 @@ void Workspace::release()
     release_host();
 }
 
-void Workspace::reserve(int device, size_t need, size_t host_need)
+void Workspace::reserve(size_t need, size_t host_need)
 {
-    if (dev != device) release();
-    dev = device;
     if (need <= mem_bytes && host_need <= host_bytes) return;
     RelaxedCapture relaxed;
     if (need > mem_bytes && need <= kKeepBytes) {
@@ -77,10 +77,10 @@ void Workspace::reserve(int device, size_t need, size_t host_need)
     }
 }
 
-Workspace &workspace()
+Workspace &workspace(int device)
 {
-    thread_local Workspace w;
-    return w;
+    thread_local std::map<int, Workspace> of_device;
+    return of_device[device];
 }
 
 }  // namespace qrt

@@ -4,6 +4,8 @@
 //
 //   workspace_checks capture  -- no release outside the relaxed capture mode:
 //                                it would end another thread's capture
+//   workspace_checks devices  -- a thread that goes from device to device keeps
+//                                its memory on each
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -39,7 +41,7 @@ std::mutex mu;
 std::map<void *, Block> live;
 int refused = 0;        // calls that a capture in the global mode forbids
 int waits = 0;          // releases that wait for all of the device's work
-size_t most = 0;        // largest sum of live device bytes
+int taken = 0;          // allocations
 thread_local int dev = 0;
 thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 
@@ -57,7 +59,7 @@ hipError_t take(void **p, size_t b, bool host, bool async)
     if (mode != hipStreamCaptureModeRelaxed && !async) refused++;
     *p = std::malloc(host ? b : 16);
     live[*p] = {dev, b, host, async};
-    if (bytes(false) > most) most = bytes(false);
+    taken++;
     return hipSuccess;
 }
 
@@ -126,7 +128,7 @@ hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 static void reserve(int dev, size_t need, size_t host_need)
 {
     fake::dev = dev;
-    qrt::workspace().reserve(dev, need, host_need);
+    qrt::workspace(dev).reserve(need, host_need);
 }
 
 static int run_capture()
@@ -136,7 +138,7 @@ static int run_capture()
         reserve(0, 1 << 20, 1 << 16);
         reserve(0, 8 << 20, 1 << 18);
         CHECK(fake::refused == 0);
-        qrt::workspace().release();
+        qrt::workspace(0).release();
         CHECK(fake::refused == 0);
         reserve(0, 1 << 20, 1 << 16);
         CHECK(fake::mode == hipStreamCaptureModeGlobal);
@@ -153,10 +155,31 @@ static int run_capture()
     return 0;
 }
 
+static int run_devices()
+{
+    std::thread([] {
+        reserve(0, 3 << 20, 1 << 16);
+        reserve(1, 1 << 20, 1 << 17);
+        const int taken = fake::taken;
+        for (int k = 0; k < 6; k++) {
+            qrt::Workspace &w = qrt::workspace(k % 2);
+            unsigned char *const mem = w.mem, *const host = w.host;
+            reserve(k % 2, 1 << 20, 1 << 16);
+            CHECK(w.mem == mem && w.host == host);
+            CHECK(fake::live[w.mem].dev == k % 2);
+        }
+        CHECK(fake::taken == taken);
+        CHECK(fake::bytes(false, 0) == 3 << 20 && fake::bytes(false, 1) == 1 << 20);
+    }).join();
+    CHECK(fake::bytes(false) == 0);
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "capture") run_capture();
+    else if (what == "devices") run_devices();
     else return 2;
     std::printf("%s: %s\n", what.c_str(), g_fail ? "FAILED" : "ok");
     return g_fail ? 1 : 0;
