@@ -170,8 +170,9 @@ qubo_status_t qubo_solve_ex(const void *Q, int n, qubo_dtype_t dtype, int k,
  * arithmetic (and so the same T, p and answer) as qubo_solve on a host copy.
  * The plan is made from n and dtype alone, before any value is read, so it
  * is qubo_solve's except that it never takes the packed tier (4), whose
- * eligibility depends on the values.  Returns after the result has been copied back (the stream is
- * synchronised once, at the end); input errors (QUBO_EOVERFLOW,
+ * eligibility depends on the values.  Returns after the result has been copied
+ * back (the stream is synchronised once, at the end: QUBO_EDEVICE, with
+ * nothing recorded, on a stream that is capturing); input errors (QUBO_EOVERFLOW,
  * QUBO_ENONFINITE) are detected on the device and reported then, after a
  * walk that skips every item. */
 qubo_status_t qubo_solve_device(const void *dQ, int n, qubo_dtype_t dtype, int k,

@@ -702,6 +702,15 @@ qubo_status_t qubo_solve_device(const void *dQ, int n, qubo_dtype_t dtype, int k
             return QUBO_EINVAL;
         }
         hipStream_t s = static_cast<hipStream_t>(hip_stream);
+        // A call waits for its stream, which a capture forbids: refused before
+        // anything is recorded, so that no node holds the thread's kept memory
+        // and the caller's capture goes on.
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (s && hipStreamIsCapturing(s, &cap) != hipSuccess) (void)hipGetLastError();
+        if (cap != hipStreamCaptureStatusNone) {
+            qrt::set_error("the stream is capturing: qubo_solve_device waits for its stream");
+            return QUBO_EDEVICE;
+        }
         // The plan depends on n, dtype and the tuning table only; the fold,
         // the exactness proof and the float32 scaling run on the device, in
         // stream order after whatever wrote dQ, and their outcome comes back
