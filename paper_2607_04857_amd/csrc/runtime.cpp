@@ -419,21 +419,19 @@ namespace qrt {
 
 hipStream_t thread_stream(qubo_status_t *st)
 {
-    thread_local hipStream_t s = nullptr;
-    thread_local int dev = -1;
     int cur = 0;
     if (hipGetDevice(&cur) != hipSuccess) {
         *st = qrt::device_error("hipGetDevice", hipErrorNoDevice);
         return nullptr;
     }
-    if (!s || dev != cur) {
+    hipStream_t &s = workspace(cur).stream;
+    if (!s) {
         hipError_t e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
         if (e != hipSuccess) {
             *st = qrt::device_error("hipStreamCreate", e);
             s = nullptr;
             return nullptr;
         }
-        dev = cur;
     }
     *st = QUBO_OK;
     return s;
@@ -447,7 +445,7 @@ qubo_status_t run_once(Job &job, hipStream_t stream, std::vector<qk::FinalRes> *
     qubo_status_t rs = device_info(&di);
     if (rs != QUBO_OK) return rs;
     Workspace &ws = workspace(di.device);
-    ws.reserve(job.bytes, job.stage_bytes + out_bytes);
+    ws.reserve(job.bytes, job.stage_bytes + out_bytes, stream);
     const bool kept = ws.mem_bytes >= job.bytes;
     const bool mapped = ws.host_bytes >= job.stage_bytes + out_bytes;
     void *d_mem = ws.mem;
@@ -483,7 +481,7 @@ qubo_status_t run_once(Job &job, hipStream_t stream, std::vector<qk::FinalRes> *
     } while (false);
     const hipError_t ef = kept ? hipSuccess : hipFreeAsync(d_mem, stream);
     const hipError_t es = hipStreamSynchronize(stream);
-    if (es != hipSuccess) ws.release();   // never reuse memory that work may still hold
+    if (es != hipSuccess) ws.drop(stream);   // never reuse memory that work may still hold
     if (rs != QUBO_OK) return rs;
     if (es != hipSuccess) return device_error("hipStreamSynchronize", es);
     if (ef != hipSuccess) return device_error("hipFreeAsync", ef);
@@ -502,7 +500,7 @@ qubo_status_t solve_planned(qrt::Job &job, hipStream_t stream, int waves_per_cu,
     DeviceInfo di;
     if ((st = device_info(&di)) != QUBO_OK) return st;
     Workspace &ws = workspace(di.device);
-    ws.reserve(job.bytes, job.stage_bytes + job.result_bytes);
+    ws.reserve(job.bytes, job.stage_bytes + job.result_bytes, stream);
     const bool kept = ws.mem_bytes >= job.bytes;
     const bool mapped = ws.host_bytes >= job.stage_bytes + job.result_bytes;
     std::vector<LoneResults> pageable(mapped ? 0 : job.result_bytes / sizeof(LoneResults) + 1);
@@ -538,7 +536,7 @@ qubo_status_t solve_planned(qrt::Job &job, hipStream_t stream, int waves_per_cu,
     } while (false);
     hipError_t ef = kept ? hipSuccess : hipFreeAsync(d_mem, stream);
     hipError_t es = hipStreamSynchronize(stream);
-    if (es != hipSuccess) ws.release();   // never reuse memory that work may still hold
+    if (es != hipSuccess) ws.drop(stream);   // never reuse memory that work may still hold
     if (rs != QUBO_OK) return rs;
     if (es != hipSuccess) return qrt::device_error("hipStreamSynchronize", es);
     if (ef != hipSuccess) return qrt::device_error("hipFreeAsync", ef);

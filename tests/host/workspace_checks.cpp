@@ -6,6 +6,9 @@
 //                                it would end another thread's capture
 //   workspace_checks devices  -- a thread that goes from device to device keeps
 //                                its memory on each
+//   workspace_checks waits    -- no call that waits for all of a device's work,
+//                                in growth or at a thread's end, and bounds
+#include <atomic>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -13,6 +16,7 @@
 #include <mutex>
 #include <string>
 #include <thread>
+#include <vector>
 
 #include "workspace.h"
 
@@ -63,13 +67,14 @@ hipError_t take(void **p, size_t b, bool host, bool async)
     return hipSuccess;
 }
 
-hipError_t give(void *p, bool host, bool async)
+hipError_t give(void *p, bool host, bool async, int on = -1)
 {
     std::lock_guard<std::mutex> lk(mu);
     auto it = live.find(p);
     CHECK(it != live.end());
     if (it == live.end()) return hipErrorOutOfMemory;
     CHECK(it->second.host == host && it->second.async == async);
+    CHECK(on < 0 || on == it->second.dev);
     if (!async) {
         waits++;
         if (mode != hipStreamCaptureModeRelaxed) refused++;
@@ -102,8 +107,7 @@ hipError_t hipFree(void *p) { return fake::give(p, false, false); }
 hipError_t hipMallocAsync(void **p, size_t b, hipStream_t) { return fake::take(p, b, false, true); }
 hipError_t hipFreeAsync(void *p, hipStream_t s)
 {
-    CHECK(!s || s->dev == fake::live[p].dev);
-    return fake::give(p, false, true);
+    return fake::give(p, false, true, s ? s->dev : -1);
 }
 hipError_t hipHostMalloc(void **p, size_t b, unsigned) { return fake::take(p, b, true, false); }
 hipError_t hipHostFree(void *p) { return fake::give(p, true, false); }
@@ -128,7 +132,7 @@ hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 static void reserve(int dev, size_t need, size_t host_need)
 {
     fake::dev = dev;
-    qrt::workspace(dev).reserve(need, host_need);
+    qrt::workspace(dev).reserve(need, host_need, nullptr);
 }
 
 static int run_capture()
@@ -138,7 +142,7 @@ static int run_capture()
         reserve(0, 1 << 20, 1 << 16);
         reserve(0, 8 << 20, 1 << 18);
         CHECK(fake::refused == 0);
-        qrt::workspace(0).release();
+        qrt::workspace(0).drop(nullptr);
         CHECK(fake::refused == 0);
         reserve(0, 1 << 20, 1 << 16);
         CHECK(fake::mode == hipStreamCaptureModeGlobal);
@@ -175,11 +179,61 @@ static int run_devices()
     return 0;
 }
 
+static int run_waits()
+{
+    const size_t MB = 1 << 20;
+    // growth in steps, and the thread's end, with and without its own stream
+    for (int own = 0; own < 2; own++)
+        std::thread([own] {
+            if (own) (void)hipStreamCreateWithFlags(&qrt::workspace(0).stream, hipStreamNonBlocking);
+            size_t host_before = 0;
+            for (size_t mb = 1; mb <= 64; mb *= 2) {
+                reserve(0, mb * MB, mb << 16);
+                qrt::Workspace &w = qrt::workspace(0);
+                CHECK(w.mem && w.mem_bytes >= mb * MB && w.host_bytes >= mb << 16);
+                CHECK(w.host_bytes >= host_before);
+                host_before = w.host_bytes;
+                CHECK(fake::bytes(false) == w.mem_bytes);
+            }
+            // more than is kept: what is there stays
+            reserve(0, qrt::kKeepBytes + 1, qrt::kKeepHostBytes + 1);
+            CHECK(qrt::workspace(0).mem_bytes == 64 * MB && qrt::workspace(0).host_bytes == 4 * MB);
+        }).join();
+    CHECK(fake::waits == 0);
+    CHECK(fake::bytes(false) == 0);
+    // the second thread took the first one's host blocks
+    CHECK(fake::bytes(true) < 8 * MB);
+    // many threads at once that end: device memory is given back, and host
+    // blocks up to the bound
+    std::atomic<int> have{0};
+    std::vector<std::thread> th;
+    for (int k = 0; k < 12; k++)
+        th.emplace_back([&] {
+            reserve(0, MB, 4 * MB);
+            have++;
+            while (have < 12) std::this_thread::yield();
+        });
+    for (std::thread &t : th) t.join();
+    CHECK(fake::bytes(false) == 0);
+    CHECK(fake::bytes(true) <= qrt::kSpareHostBytes);
+    // a block of one device is not given to a thread on another
+    std::thread([] {
+        reserve(1, 1 << 20, 1 << 16);
+        CHECK(fake::live[qrt::workspace(1).host].dev == 1);
+        // after a wait that failed no other thread gets the block
+        unsigned char *const host = qrt::workspace(1).host;
+        qrt::workspace(1).drop(nullptr);
+        CHECK(!qrt::workspace(1).host && !qrt::workspace(1).mem && !fake::live.count(host));
+    }).join();
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "capture") run_capture();
     else if (what == "devices") run_devices();
+    else if (what == "waits") run_waits();
     else return 2;
     std::printf("%s: %s\n", what.c_str(), g_fail ? "FAILED" : "ok");
     return g_fail ? 1 : 0;
