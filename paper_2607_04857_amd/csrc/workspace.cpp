@@ -141,7 +141,8 @@ void Workspace::reserve(size_t need, size_t host_need, hipStream_t s)
 
 Workspace::~Workspace()
 {
-    if (!mem && !host) return;
+    // (in a child forked since, the runtime and its memory are the parent's)
+    if ((!mem && !host) || pid != getpid()) return;
     RelaxedCapture relaxed;
     release_host();
     if (!mem) return;

@@ -1,6 +1,9 @@
 // workspace.h -- memory that a thread keeps between its lone solves.
 #pragma once
 
+#include <sys/types.h>
+#include <unistd.h>
+
 #include <cstddef>
 
 #include <hip/hip_runtime.h>
@@ -33,6 +36,7 @@ struct HostBlock {
 
 struct Workspace {
     const int dev;
+    const pid_t pid = getpid();     // (a forked child gives nothing back)
     hipStream_t stream = nullptr;   // the thread's own on the device (thread_stream)
     unsigned char *mem = nullptr, *host = nullptr, *host_dev = nullptr;
     size_t mem_bytes = 0, host_bytes = 0;

@@ -8,6 +8,10 @@
 //                                its memory on each
 //   workspace_checks waits    -- no call that waits for all of a device's work,
 //                                in growth or at a thread's end, and bounds
+//   workspace_checks fork     -- a forked child that exits calls no HIP function
+#include <sys/wait.h>
+#include <unistd.h>
+
 #include <atomic>
 #include <cstdio>
 #include <cstdlib>
@@ -46,6 +50,7 @@ std::map<void *, Block> live;
 int refused = 0;        // calls that a capture in the global mode forbids
 int waits = 0;          // releases that wait for all of the device's work
 int taken = 0;          // allocations
+bool forked = false;    // a child after fork: no call may come
 thread_local int dev = 0;
 thread_local hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
 
@@ -69,6 +74,7 @@ hipError_t take(void **p, size_t b, bool host, bool async)
 
 hipError_t give(void *p, bool host, bool async, int on = -1)
 {
+    if (forked) _exit(3);
     std::lock_guard<std::mutex> lk(mu);
     auto it = live.find(p);
     CHECK(it != live.end());
@@ -99,6 +105,7 @@ hipError_t hipSetDevice(int d)
 }
 hipError_t hipThreadExchangeStreamCaptureMode(hipStreamCaptureMode *m)
 {
+    if (fake::forked) _exit(3);
     std::swap(*m, fake::mode);
     return hipSuccess;
 }
@@ -228,12 +235,28 @@ static int run_waits()
     return 0;
 }
 
+static int run_fork()
+{
+    reserve(0, 1 << 20, 1 << 16);
+    std::fflush(nullptr);
+    const pid_t child = fork();
+    if (child == 0) {
+        fake::forked = true;
+        std::exit(0);   // runs the destructors of this thread's objects
+    }
+    int status = -1;
+    CHECK(waitpid(child, &status, 0) == child);
+    CHECK(WIFEXITED(status) && WEXITSTATUS(status) == 0);
+    return 0;
+}
+
 int main(int argc, char **argv)
 {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "capture") run_capture();
     else if (what == "devices") run_devices();
     else if (what == "waits") run_waits();
+    else if (what == "fork") run_fork();
     else return 2;
     std::printf("%s: %s\n", what.c_str(), g_fail ? "FAILED" : "ok");
     return g_fail ? 1 : 0;

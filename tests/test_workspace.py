@@ -23,7 +23,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("what", ["capture", "devices", "waits"])
+@pytest.mark.parametrize("what", ["capture", "devices", "waits", "fork"])
 def test_workspace(exe, what):
     p = subprocess.run([exe, what], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout + p.stderr
