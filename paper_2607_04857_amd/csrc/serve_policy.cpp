@@ -5,6 +5,15 @@
 
 namespace qsched {
 
+int item_log(int A)
+{
+    constexpr int kLongest = 10, kItemsLog = 11, kShortest = 6;
+    constexpr int kMaxItemsLog = 18, kMaxItemsLogLong = 20, kMaxLong = 12;
+    const int L = std::min(kLongest, std::max(A - kItemsLog, kShortest));
+    const int records = std::min(A - kMaxItemsLog, std::max(kMaxLong, A - kMaxItemsLogLong));
+    return std::min(std::max(L, records), A);
+}
+
 size_t admit_count(const std::vector<size_t> &queued_bytes, size_t mem_used, size_t budget,
                    size_t free_slots)
 {

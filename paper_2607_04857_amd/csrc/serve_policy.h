@@ -1,6 +1,7 @@
 // serve_policy.h -- scheduling policy of the serving loop (host only, no HIP).
 //
-// Two decisions, taken on every scheduler tick of the server:
+// The length of a request's work items (item_log), and two decisions, taken on
+// every scheduler tick of the server:
 //   * admission: requests enter device slots in arrival order while a slot
 //     is free and the device-memory budget allows; the first request that
 //     does not fit stops admission (no later request overtakes it);
@@ -17,6 +18,15 @@
 #include <vector>
 
 namespace qsched {
+
+// log2 Gray steps per work item of a served request with A prefix bits: 2^11
+// items, of 2^6 steps at least (A < 17: fewer items) and 2^10 at most (a tick
+// ends when its last wave does, and the youngest wave of a SIMD takes several
+// times an item's time: with items of 2^12 steps the tail was most of a tick of
+// mixed requests).  From A = 29 on items are longer, so that there are at most
+// 2^18 (records), but of at most 2^12 steps (a request that arrives waits for
+// the items that run), until from A = 33 on 2^20 items are too few for that.
+int item_log(int A);
 
 // How many requests at the head of the queue to admit now.  queued_bytes:
 // device bytes of the queued requests, head first; mem_used: bytes held by

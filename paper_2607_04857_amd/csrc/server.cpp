@@ -39,14 +39,8 @@ using Clock = std::chrono::steady_clock;
 // Walk launches per tick are one per distinct walk kernel variant among the
 // active requests; this bounds the number of built variants (B x cache x tier).
 constexpr int kMaxTickLaunches = 32;
-constexpr int kUnitLog = 12;        // the tick budget counts units of 2^12 Gray steps
-// log2 Gray steps per work item of a served request: 2^11 items or more, of at
-// most 2^10 steps (a tick ends when its last wave does, and the youngest wave
-// of a SIMD takes several times an item's time: with items of 2^12 steps the
-// tail was most of a tick of mixed requests), and at most 2^18 items (records).
-constexpr int kServeL = 10;
-constexpr int kServeItemsLog = 11;
-constexpr int kServeMaxItemsLog = 18;
+constexpr int kUnitLog = 12;        // the tick budget counts units of 2^12 Gray steps, or
+                                    // items where these are longer (A > 32)
 constexpr int kMaxRound = 128;      // requests admitted in one round, at most: their host
                                     // images share one mapped block per tick buffer
 // A request's image at most: its descriptor, T and float32 Q, each aligned.
@@ -591,10 +585,8 @@ qubo_status_t qubo_server_submit(qubo_server_t *s, const void *Q, int n, qubo_dt
             return st;
         }
         qplan::Plan &P = r->job.plans[0];
-        const int serveL = std::max(std::min(kServeL, std::max(P.A - kServeItemsLog, qplan::kSuper)),
-                                    P.A - kServeMaxItemsLog);
-        if (!P.direct && P.L > serveL) {
-            P.L = serveL;
+        if (!P.direct && P.L > qsched::item_log(P.A)) {
+            P.L = qsched::item_log(P.A);
             P.items = uint64_t(1) << (P.A - P.L);
         }
         if (dtype == QUBO_FP32) {
