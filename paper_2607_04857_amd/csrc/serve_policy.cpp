@@ -8,10 +8,15 @@ namespace qsched {
 int item_log(int A)
 {
     constexpr int kLongest = 10, kItemsLog = 11, kShortest = 6;
-    constexpr int kMaxItemsLog = 18, kMaxItemsLogLong = 20, kMaxLong = 12;
+    constexpr int kMaxItemsLog = 18;
     const int L = std::min(kLongest, std::max(A - kItemsLog, kShortest));
-    const int records = std::min(A - kMaxItemsLog, std::max(kMaxLong, A - kMaxItemsLogLong));
-    return std::min(std::max(L, records), A);
+    return std::max(std::min(L, A), std::min(A - kMaxItemsLog, longest_item_log(A)));
+}
+
+int longest_item_log(int A)
+{
+    constexpr int kLongest = 12, kMaxItemsLog = 20;
+    return std::min(std::max(kLongest, A - kMaxItemsLog), A);
 }
 
 size_t admit_count(const std::vector<size_t> &queued_bytes, size_t mem_used, size_t budget,

@@ -28,6 +28,10 @@ namespace qsched {
 // the items that run), until from A = 33 on 2^20 items are too few for that.
 int item_log(int A);
 
+// The longest items that a request may have, where the records of shorter ones
+// would not fit the server's memory budget (item_log(A) or more).
+int longest_item_log(int A);
+
 // How many requests at the head of the queue to admit now.  queued_bytes:
 // device bytes of the queued requests, head first; mem_used: bytes held by
 // admitted requests; budget: the server's device-memory budget; free_slots:

@@ -585,10 +585,6 @@ qubo_status_t qubo_server_submit(qubo_server_t *s, const void *Q, int n, qubo_dt
             return st;
         }
         qplan::Plan &P = r->job.plans[0];
-        if (!P.direct && P.L > qsched::item_log(P.A)) {
-            P.L = qsched::item_log(P.A);
-            P.items = uint64_t(1) << (P.A - P.L);
-        }
         if (dtype == QUBO_FP32) {
             const float *q = static_cast<const float *>(Q);
             r->qf.assign(q, q + size_t(n) * n);
@@ -596,10 +592,20 @@ qubo_status_t qubo_server_submit(qubo_server_t *s, const void *Q, int n, qubo_dt
         } else {
             r->job.qf.push_back(nullptr);
         }
-        st = qrt::job_layout(&r->job, 0);
-        if (st != QUBO_OK) {
-            delete r;
-            return st;
+        // Shorter items than the plan's; longer ones of these where the budget
+        // does not hold so many records.
+        const int planned = P.L, longest = std::min(planned, qsched::longest_item_log(P.A));
+        for (int L = std::min(planned, qsched::item_log(P.A));; L++) {
+            if (!P.direct) {
+                P.L = L;
+                P.items = uint64_t(1) << (P.A - L);
+            }
+            st = qrt::job_layout(&r->job, 0);
+            if (st != QUBO_OK) {
+                delete r;
+                return st;
+            }
+            if (P.direct || L >= longest || r->job.bytes <= s->budget) break;
         }
         std::lock_guard<std::mutex> lk(s->mu);
         if (!s->fatal.empty()) {

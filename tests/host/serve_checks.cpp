@@ -28,6 +28,8 @@ static int run_items()
         CHECK(A - L <= 20);
         if (A <= 28) CHECK(L <= 10);
         if (A >= 17) CHECK(A - L >= 11);
+        CHECK(qsched::longest_item_log(A) >= L);
+        CHECK(qsched::longest_item_log(A) <= 12 || A - qsched::longest_item_log(A) == 20);
     }
     return 0;
 }

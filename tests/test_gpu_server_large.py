@@ -31,3 +31,19 @@ def test_large_beside_small(q, n, span):
             assert (got.energy_i, got.energy, got.index) == (exp.energy_i, exp.energy, exp.index)
     finally:
         s.close()
+
+
+@pytest.mark.parametrize("n,span,budget", [(38, 10000, 3 << 19), (36, 100, 1 << 20), (26, 100, 6 << 15)])
+def test_small_budget(q, n, span, budget):
+    """A request whose records fit the budget only on longer items is taken, and
+    one that fits on none is refused."""
+    Q = inputs.uniform_int(n, -span, span, n)
+    s = q.Server(mem_budget_bytes=budget, max_slots=4)
+    try:
+        got, exp = s.wait(s.submit(Q)), q.solve(Q)
+        assert (got.energy_i, got.index) == (exp.energy_i, exp.index)
+        assert s.info()["mem_peak"] <= budget
+        with pytest.raises(q.QuboError, match="QUBO_ENOMEM"):
+            s.submit(inputs.uniform_int(44, -10000, 10000, 1))
+    finally:
+        s.close()
