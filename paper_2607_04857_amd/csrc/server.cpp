@@ -168,40 +168,45 @@ hipError_t take_memory(qubo_server *s, size_t bytes, void **p)
 
 // Called with the tick's event complete: publish results, keep the memory for
 // other requests (a hipFreeAsync each, about 10 us, had held back the results
-// of a tick of 25 requests by 250 us, and the next tick as long).
+// of a tick of 25 requests by 250 us, and the next tick as long).  What the
+// budget has no room for is freed after the results are out.
 void complete_tick(qubo_server *s, TickBuf &t)
 {
     std::vector<Request *> done = std::move(t.finishing);
+    std::vector<void *> freed;
     t.finishing.clear();
     t.inflight = false;
-    std::lock_guard<std::mutex> lk(s->mu);
-    for (size_t i = 0; i < done.size(); i++) {
-        Request *r = done[i];
-        qubo_status_t st = qrt::job_result(r->job, 0, t.h_out[i], &r->result);
-        const double lat = ms_since(r->arrival);
-        if (st != QUBO_OK) {
-            r->status = st;
-            r->error = qrt::last_error_cstr();
-            r->state = RState::Failed;
-        } else {
-            r->result.total_ms = lat;
-            r->result.kernel_ms = 0.0;
-            r->state = RState::Done;
+    {
+        std::lock_guard<std::mutex> lk(s->mu);
+        for (size_t i = 0; i < done.size(); i++) {
+            Request *r = done[i];
+            qubo_status_t st = qrt::job_result(r->job, 0, t.h_out[i], &r->result);
+            const double lat = ms_since(r->arrival);
+            if (st != QUBO_OK) {
+                r->status = st;
+                r->error = qrt::last_error_cstr();
+                r->state = RState::Failed;
+            } else {
+                r->result.total_ms = lat;
+                r->result.kernel_ms = 0.0;
+                r->state = RState::Done;
+            }
+            s->lat_ms.push_back(lat);
+            s->states_done += std::ldexp(1.0, r->job.plans[0].n);
+            s->mem_used -= r->job.bytes;
+            if (s->kept_bytes + r->job.bytes + s->mem_used <= s->budget) {
+                s->kept[r->job.bytes].push_back(r->d_mem);
+                s->kept_bytes += r->job.bytes;
+            } else {
+                freed.push_back(r->d_mem);
+            }
+            r->d_mem = nullptr;
+            s->free_kslots.push_back(r->kslot);
+            s->active.erase(std::find(s->active.begin(), s->active.end(), r));
         }
-        s->lat_ms.push_back(lat);
-        s->states_done += std::ldexp(1.0, r->job.plans[0].n);
-        s->mem_used -= r->job.bytes;
-        if (s->kept_bytes + r->job.bytes + s->mem_used <= s->budget) {
-            s->kept[r->job.bytes].push_back(r->d_mem);
-            s->kept_bytes += r->job.bytes;
-        } else {
-            (void)hipFreeAsync(r->d_mem, s->stream);
-        }
-        r->d_mem = nullptr;
-        s->free_kslots.push_back(r->kslot);
-        s->active.erase(std::find(s->active.begin(), s->active.end(), r));
     }
     s->cv_done.notify_all();
+    for (void *p : freed) (void)hipFreeAsync(p, s->stream);
 }
 
 // Admit queued requests (policy: qsched::admit_count); returns the newly
@@ -416,8 +421,11 @@ void scheduler(qubo_server *s)
                               !s->ticks[1].inflight;
             if (idle) {
                 if (s->stop && s->queue.empty()) break;
-                if (s->cv_work.wait_for(lk, std::chrono::milliseconds(20)) == std::cv_status::timeout)
+                if (s->cv_work.wait_for(lk, std::chrono::milliseconds(20)) ==
+                    std::cv_status::timeout) {
+                    lk.unlock();   // (`kept` is this thread's)
                     give_back(s);
+                }
                 continue;
             }
         }
