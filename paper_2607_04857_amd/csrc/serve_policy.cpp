@@ -30,6 +30,23 @@ size_t admit_count(const std::vector<size_t> &queued_bytes, size_t mem_used, siz
     return k;
 }
 
+std::vector<size_t> blocks_to_free(const std::vector<size_t> &sizes, size_t need)
+{
+    std::vector<size_t> out;
+    size_t end = sizes.size();   // the largest ones, from here on, are taken
+    while (need > 0 && end > 0) {
+        const size_t k = size_t(std::lower_bound(sizes.begin(), sizes.begin() + long(end), need) -
+                                sizes.begin());
+        if (k < end) {
+            out.push_back(k);
+            break;
+        }
+        out.push_back(--end);
+        need -= sizes[end];
+    }
+    return out;
+}
+
 uint64_t tick_scale(uint64_t backlog_items, uint64_t tick_items)
 {
     uint64_t scale = 1;

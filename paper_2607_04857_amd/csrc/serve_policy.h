@@ -1,7 +1,8 @@
 // serve_policy.h -- scheduling policy of the serving loop (host only, no HIP).
 //
-// The length of a request's work items (item_log), and two decisions, taken on
-// every scheduler tick of the server:
+// The length of a request's work items (item_log), which of the finished
+// requests' memory blocks to give back (blocks_to_free), and two decisions, taken
+// on every scheduler tick of the server:
 //   * admission: requests enter device slots in arrival order while a slot
 //     is free and the device-memory budget allows; the first request that
 //     does not fit stops admission (no later request overtakes it);
@@ -38,6 +39,11 @@ int longest_item_log(int A);
 // free device slots.
 size_t admit_count(const std::vector<size_t> &queued_bytes, size_t mem_used, size_t budget,
                    size_t free_slots);
+
+// Which kept blocks of device memory to give back so that they are `need` bytes
+// fewer: the positions in `sizes` (ascending) of as few blocks as will do, the
+// smallest one that does last; all of them where they are fewer than `need`.
+std::vector<size_t> blocks_to_free(const std::vector<size_t> &sizes, size_t need);
 
 // Largest tick budget multiplier: at 64 a tick gives each resident wave
 // about 128 items, so the drain at the tick's end (at most one item per

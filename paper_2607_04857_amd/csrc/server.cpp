@@ -24,6 +24,7 @@
 #include <condition_variable>
 #include <cstring>
 #include <deque>
+#include <map>
 #include <mutex>
 #include <thread>
 #include <tuple>
@@ -96,7 +97,7 @@ struct qubo_server {
     // Device memory of finished requests, by size, for the next ones (the
     // scheduler thread's, on its stream): with what the active requests hold,
     // within the budget, and given back whenever the server idles.
-    std::unordered_map<size_t, std::vector<void *>> kept;
+    std::map<size_t, std::vector<void *>> kept;
     size_t kept_bytes = 0;
 
     std::mutex mu;
@@ -138,29 +139,41 @@ void fail_all(qubo_server *s, const std::string &msg)
     s->cv_done.notify_all();
 }
 
-void give_back(qubo_server *s)
+// Give back at least `need` bytes of the kept blocks (all where they are fewer).
+void give_back(qubo_server *s, size_t need)
 {
-    for (auto &kv : s->kept)
-        for (void *p : kv.second) (void)hipFreeAsync(p, s->stream);
-    s->kept.clear();
-    s->kept_bytes = 0;
+    std::vector<size_t> sizes;
+    for (const auto &kv : s->kept) sizes.insert(sizes.end(), kv.second.size(), kv.first);
+    for (size_t k : qsched::blocks_to_free(sizes, need)) {
+        auto it = s->kept.find(sizes[k]);
+        (void)hipFreeAsync(it->second.back(), s->stream);
+        s->kept_bytes -= sizes[k];
+        it->second.pop_back();
+        if (it->second.empty()) s->kept.erase(it);
+    }
 }
 
-// Device memory of a request about to be set up (counted in mem_used already).
-hipError_t take_memory(qubo_server *s, size_t bytes, void **p)
+// A kept block of exactly that size, or null.
+void *take_kept(qubo_server *s, size_t bytes)
 {
     auto it = s->kept.find(bytes);
-    if (it != s->kept.end() && !it->second.empty()) {
-        *p = it->second.back();
-        it->second.pop_back();
-        s->kept_bytes -= bytes;
-        return hipSuccess;
-    }
-    if (s->kept_bytes + s->mem_used > s->budget) give_back(s);
+    if (it == s->kept.end()) return nullptr;
+    void *p = it->second.back();
+    s->kept_bytes -= bytes;
+    it->second.pop_back();
+    if (it->second.empty()) s->kept.erase(it);
+    return p;
+}
+
+// New device memory for a request about to be set up (counted in mem_used already).
+hipError_t take_memory(qubo_server *s, size_t bytes, void **p)
+{
+    const size_t held = s->kept_bytes + s->mem_used;
+    if (held > s->budget) give_back(s, held - s->budget);
     hipError_t e = hipMallocAsync(p, bytes, s->stream);
     if (e != hipSuccess && s->kept_bytes) {
         (void)hipGetLastError();
-        give_back(s);
+        give_back(s, s->kept_bytes);
         e = hipMallocAsync(p, bytes, s->stream);
     }
     return e;
@@ -241,7 +254,7 @@ std::vector<Request *> take_admissions(qubo_server *s)
 // tick buffer's mapped block.
 qubo_status_t setup_request(qubo_server *s, TickBuf &t, Request *r, size_t k)
 {
-    QRT_HIP(take_memory(s, r->job.bytes, &r->d_mem), "hipMallocAsync");
+    if (!r->d_mem) QRT_HIP(take_memory(s, r->job.bytes, &r->d_mem), "hipMallocAsync");
     qubo_status_t st = qrt::job_bind(&r->job, r->d_mem);
     if (st != QUBO_OK) return st;
     // The K table lives in the server's arena so one walk launch sees every
@@ -424,7 +437,11 @@ void scheduler(qubo_server *s)
                 if (s->cv_work.wait_for(lk, std::chrono::milliseconds(20)) ==
                     std::cv_status::timeout) {
                     lk.unlock();   // (`kept` is this thread's)
+<<<<<<< Updated upstream
                     give_back(s);
+=======
+                    give_back(s, s->kept_bytes);
+>>>>>>> Stashed changes
                 }
                 continue;
             }
@@ -438,6 +455,9 @@ void scheduler(qubo_server *s)
             }
             complete_tick(s, t);
         }
+        // the whole round's kept blocks first: a new block makes room by giving
+        // back others
+        for (Request *r : adm) r->d_mem = take_kept(s, r->job.bytes);
         for (size_t k = 0; k < adm.size(); k++) {
             if (setup_request(s, t, adm[k], k) != QUBO_OK) {
                 fail_all(s, qrt::last_error_cstr());

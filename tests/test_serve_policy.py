@@ -21,7 +21,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("what", ["items"])
+@pytest.mark.parametrize("what", ["items", "blocks"])
 def test_serve_policy(exe, what):
     p = subprocess.run([exe, what], capture_output=True, text=True, timeout=60)
     assert p.returncode == 0, p.stdout + p.stderr
