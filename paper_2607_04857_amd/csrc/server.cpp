@@ -437,11 +437,7 @@ void scheduler(qubo_server *s)
                 if (s->cv_work.wait_for(lk, std::chrono::milliseconds(20)) ==
                     std::cv_status::timeout) {
                     lk.unlock();   // (`kept` is this thread's)
-<<<<<<< Updated upstream
-                    give_back(s);
-=======
                     give_back(s, s->kept_bytes);
->>>>>>> Stashed changes
                 }
                 continue;
             }
