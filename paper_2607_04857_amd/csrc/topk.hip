@@ -477,10 +477,12 @@ __global__ __launch_bounds__(kFinalWaves *kWave) void topk_final_kernel(
 }
 
 // The integer order is exact for the scaled energies; float32 answers are
-// reported by their float64 energies, in their own (E64, index) order.
+// reported by their float64 energies, in their own (E64, index) order.  (in and
+// out are the same where the results stay in device memory: all of in is read
+// before the first barrier.)
 __global__ __launch_bounds__(kSelThreads) void topk_order_kernel(
-    const int32_t *__restrict__ selCount, int k, const TopkState *__restrict__ in,
-    TopkState *__restrict__ out, FinalRes *__restrict__ best)
+    const int32_t *__restrict__ selCount, int k, const TopkState *in, TopkState *out,
+    FinalRes *__restrict__ best)
 {
     __shared__ double sF[kSelThreads];
     __shared__ uint64_t sI[kSelThreads];
