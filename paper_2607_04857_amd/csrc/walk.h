@@ -396,7 +396,7 @@ __device__ __noinline__ int32_t tk_drain(int nq)
 }
 
 // Publish the number of entries of the wave's list (the entries are already
-// in listE / listR at slot blockIdx.x * k).
+// in listE / listR, at the wave's number * k).
 __device__ __noinline__ void tk_flush()
 {
     tk_sync();
@@ -699,15 +699,15 @@ __device__ __forceinline__ void walk_items(const Inst *insts, int n_inst, WalkCl
         }
         // F: field of every prefix variable from the non-low ones (levels >=
         // kLowLevels, variables 0..A-1-kLowLevels), plus its diagonal; one
-        // lane per variable.  own: the part from the variables before it, so
-        // that the energy E_nl of the non-low prefix bits is the sum of own
+        // lane per variable.  Fb: the part from the variables before it, so
+        // that the energy E_nl of the non-low prefix bits is the sum of Fb
         // over the set ones (a partial sum of T at every point).
         if constexpr (WD) {
 #pragma unroll
             for (int k = 0; k < kWideWords; k++) W[k] = wide_word(E[3 * k], E[3 * k + 1], E[3 * k + 2]);
             X = E[MC - 1];
         }
-        int32_t own = F;
+        int32_t Fb = F;
         for (int w0 = 0; w0 <= A - 1 - kLowLevels; w0 += 16) {
             int32_t c[16];
 #pragma unroll
@@ -718,11 +718,11 @@ __device__ __forceinline__ void walk_items(const Inst *insts, int n_inst, WalkCl
                 const int32_t on =
                     w <= A - 1 - kLowLevels ? -int32_t((row0 >> ((A - 1 - w) & 63)) & 1) : 0;
                 F += c[k] & on;
-                own += w < lane ? c[k] & on : 0;
+                Fb += w < lane ? c[k] & on : 0;
             }
         }
         const bool lbit = lane <= A - 1 - kLowLevels && ((row0 >> (A - 1 - lane)) & 1);
-        int32_t Enl = wave_sum(lbit ? own : 0);
+        int32_t Enl = wave_sum(lbit ? Fb : 0);
         // the chunk energies carry the instance's shift c (packed: into the
         // 16-bit range; int32: non-negative), the prefix energy the opposite
         // one, so every sum is the true energy
