@@ -18,8 +18,15 @@ roofline         = the walk kernel (dominant kernel) against the int32 VALU
                    than 2^21 values, as the headline's do, walks on wide words
                    (three states per 64-bit add, which issues at half the
                    rate): 16 states in 11 issue slots, so its peak is 16/11 of
-                   the int32 one (114.4 T states/s).  Duration = the walk
-                   kernel's own start and end, by the device clock.
+                   the int32 one (114.4 T states/s).  Duration = kernel_ms, by
+                   the device clock: from the end of the table build's descents
+                   to the finish's start, so the walk with its launch.
+walk_words       = what the headline's walk holds its chunk energies in: 21-bit
+                   fields of 64-bit words (their range is proven from the exact
+                   extremes of the instance, so every sum is the int32 one), or
+                   int32 words.
+int32_words      = the same instance, from host memory, on int32 words only
+                   (row cache "3", which has no wide form).
 cpu_baseline     = the CPU oracle (direct evaluation) timed on this host over a
                    bounded contiguous index range of the same instance.
 batched          = 4096 instances, n ~ U{20..34}, int32 U[-100,100] (seed 5):
@@ -224,6 +231,22 @@ def single_packed(q, steps=3):
             "frac": walk_rate / (2 * VALU_PEAK_OPS)}
 
 
+def int32_words(q, Q, steps=2):
+    """Lone solves of the headline instance with one int32 word per chunk energy."""
+    r = q.solve(Q, tier=2, vgpr_levels=3)     # warm-up
+    kms = []
+    t0 = time.perf_counter()
+    for _ in range(steps):
+        r = q.solve(Q, tier=2, vgpr_levels=3)
+        kms.append(r.kernel_ms)
+    dt = (time.perf_counter() - t0) / steps
+    walk_ms = sum(kms) / len(kms)
+    n = Q.shape[0]
+    return {"kernel": kernel_name(r), "result": [r.energy_i, r.index], "ms_per_solve": dt * 1e3,
+            "states_per_s": 2.0 ** n / dt, "walk_ms": walk_ms,
+            "frac": 2.0 ** n / (walk_ms / 1e3) / VALU_PEAK_OPS}
+
+
 def topk(q, torch, n=40, k=1024, steps=2):
     from paper_2607_04857_amd import inputs
     Q = inputs.uniform_int(n, -10000, 10000, 3)
@@ -330,7 +353,8 @@ def main():
     ap.add_argument("--no-batch", action="store_true")
     ap.add_argument("--no-serve", action="store_true")
     ap.add_argument("--no-topk", action="store_true")
-    ap.add_argument("--no-packed", action="store_true")
+    ap.add_argument("--no-packed", action="store_true",
+                    help="skip the lone packed and int32-word legs")
     ap.add_argument("--only-packed", action="store_true",
                     help="only the packed n=44 lone solves (profiling the packed walk alone)")
     ap.add_argument("--only-topk", action="store_true",
@@ -428,6 +452,7 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "i32",
+        "walk_words": "21-bit fields, three to a 64-bit word (exact)" if wide else "int32",
         "data": "synthetic",
         "config": {"workload": "single dense QUBO n=44, int32 Q upper-triangular, entries "
                                "U[-10000,10000], seed 4", "n": n, "states_per_step": 2 ** n,
@@ -447,6 +472,8 @@ def main():
     line["roofline"]["frac_of_probe"] = achieved * slots / probe
     if not args.no_packed:
         line["single_packed"] = single_packed(q)
+        if wide:
+            line["int32_words"] = int32_words(q, Q)
     if not args.no_batch:
         line["batched"] = batched(q)
         line["batched_fp32"] = batched(q, kind="fp32")

@@ -87,7 +87,11 @@ typedef struct {
                             on the packed layout (k > 1)                   */
     int vgpr_levels;     /* Gray levels with VGPR-resident rows (0 when direct)    */
     uint64_t states;     /* states evaluated = 2^n                                 */
-    double kernel_ms;    /* GPU time of the walk (device clock)                    */
+    double kernel_ms;    /* GPU time of the walk by the device clock: from the end
+                            of the (first) instance's descents in the table build
+                            to the finish's start, so with the rest of that build,
+                            the walk's launch and, k > 1, the bound's seed; 0 for
+                            direct plans.  Batch handles: the whole replay         */
     double total_ms;     /* host wall time of the whole call                       */
 } qubo_result_t;
 
@@ -126,13 +130,15 @@ typedef struct {
                             or fourth wave per SIMD, the higher rows being read
                             from L2 when they flip.  4 keeps levels 0-2 and 5
                             in VGPRs and levels 3-4 in LDS (8 KB per wave), or,
-                            walking one instance alone for its best state,
-                            levels 0-3 in VGPRs and 4-8 in LDS (32 KB per
-                            block of four waves), or, where int32 chunk
+                            walking one instance alone, levels 0-3 in VGPRs
+                            and 4-8 in LDS (32 KB per block of four waves;
+                            k > 1: 0-2 and 3-8), or, where int32 chunk
                             energies span less than 2^21 values (exactly
                             proven) and A >= 20, three of them to a 64-bit
-                            word with levels 0-2 in VGPRs and 3-8 in LDS,
-                            with the same results; 3
+                            word, in 21 bits each, with levels 0-2 in VGPRs
+                            and 3-8 in LDS, with the same results.  Any other
+                            value keeps each energy of tiers 1 to 3 in an
+                            int32 word of its own; 3
                             keeps levels 0-2 in VGPRs, levels 3-4 in LDS and
                             reads every level from 5 up from L2              */
     int item_first;
@@ -152,8 +158,12 @@ typedef struct {
  * float64 energies and ordered by (energy, index); the i-th reported energy
  * is within out->tol of the exact i-th smallest energy.  Batches and the
  * server return the best state only.  Uses the current HIP device and a
- * stream of the calling thread.  Errors: QUBO_EINVAL for a bad k (checked
- * before any device work). */
+ * stream of the calling thread.  This call and the other ones of a single
+ * instance or a one-shot batch (but qubo_solve_noalloc) keep the memory of the
+ * thread's last calls on the device, at most 128 MiB of device memory and 4 MiB
+ * of mapped host memory, until the thread ends (of ended threads' host memory
+ * the process keeps up to 16 MiB for others).  Errors: QUBO_EINVAL for a bad k
+ * (checked before any device work). */
 qubo_status_t qubo_solve(const void *Q, int n, qubo_dtype_t dtype, int k,
                          qubo_result_t *out, qubo_state_t *topk);
 
@@ -216,7 +226,7 @@ qubo_status_t qubo_batch_create(int count, const void *const *Q, const int *n,
  * wait for it. */
 qubo_status_t qubo_batch_run(qubo_batch_t *batch, void *hip_stream);
 qubo_status_t qubo_batch_results(qubo_batch_t *batch, qubo_result_t *out);
-/* Total states of the batch and the walk-kernel time of the last replay. */
+/* Total states of the batch and the GPU time of the last replay (HIP events). */
 qubo_status_t qubo_batch_stats(qubo_batch_t *batch, double *states, double *kernel_ms);
 void qubo_batch_destroy(qubo_batch_t *batch);
 
@@ -240,7 +250,7 @@ qubo_status_t qubo_reduce_outer(const int32_t *Q, int n, int k, uint64_t xf,
  * variables).  int32 input only (QUBO_EINVAL otherwise); 2 <= n <= 64,
  * 1 <= k <= 12, 1 <= n - k <= 60.  out: the best state and the first
  * reduced instance's plan fields; states = 2^n (saturated at n = 64);
- * kernel_ms = the batch's walk time. */
+ * kernel_ms as for qubo_solve_batch's results. */
 qubo_status_t qubo_solve_outer(const void *Q, int n, qubo_dtype_t dtype, int k,
                                qubo_result_t *out);
 
@@ -265,7 +275,11 @@ qubo_status_t qubo_server_wait(qubo_server_t *srv, uint64_t ticket, double timeo
 qubo_status_t qubo_server_stats(qubo_server_t *srv, double *p50_ms, double *p99_ms,
                                 double *states_per_s);
 /* Scheduler counters: device memory held by admitted requests now and at
- * its peak, the peak number of admitted requests, and walk ticks launched. */
+ * its peak, the peak number of admitted requests, and walk ticks launched.
+ * The server holds more than mem_in_use: finished requests' blocks are kept for
+ * the next ones, with those in use within mem_budget_bytes, until the server
+ * has been idle for 20 ms; and, outside the budget, about 10 KB of device memory
+ * a slot and 62 KB of mapped host memory a slot (up to 128 slots; 1 KB beyond). */
 qubo_status_t qubo_server_info(qubo_server_t *srv, size_t *mem_in_use, size_t *mem_peak,
                                int *active_peak, uint64_t *ticks);
 /* Stops accepting work, finishes every submitted request, frees the server. */
@@ -290,7 +304,7 @@ void qubo_server_destroy(qubo_server_t *srv);
  * items in one slice; n <= 14 plans are always one slice).  max_slices: stop
  * after this many slices in this call (0 = run to the end).
  * Returns QUBO_OK with *out = the final result once every item is done
- * (states = 2^n; kernel_ms = walk time summed over all slices of all calls;
+ * (states = 2^n; kernel_ms is summed over all slices of all calls;
  * total_ms = this call), QUBO_EAGAIN when max_slices slices ran and items
  * remain (*out untouched: read progress with qubo_checkpoint_info), and
  * QUBO_EINVAL for a checkpoint that is malformed, belongs to another input
@@ -308,7 +322,7 @@ typedef struct {
     qubo_state_t best;    /* lexicographic minimum over the finished items     */
     int p;                /* fixed-point exponent (float32 input)              */
     double tol;           /* as qubo_result_t.tol                              */
-    double walk_ms;       /* walk-kernel time summed over finished slices      */
+    double walk_ms;       /* kernel_ms summed over finished slices             */
 } qubo_checkpoint_t;
 
 qubo_status_t qubo_solve_checkpointed(const void *Q, int n, qubo_dtype_t dtype,

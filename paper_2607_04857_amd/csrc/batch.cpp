@@ -34,7 +34,13 @@ namespace {
 
 // Work items that a batch has at least, where its steps allow (eight per
 // resident wave of the default variant): 100 instances of n = 15..25 walk in
-// 55 us instead of 137, 1000 of n = 12..26 in 261 us instead of 328.
+// 55 us instead of 137, 1000 of n = 12..26 in 261 us instead of 328.  A replay
+// of equal instances with this rule, and with the best and the longest of the
+// items of 2^6 to 2^13 steps, us: 64 of n = 24 77, 76, 734; 300 of n = 24 188,
+// 164 (2^8), 787; 1000 of n = 22 242, 225 (2^7), 383; 4096 of n = 22 677, 664
+// (2^9), 726; 4096 of n = 24 1293, 1263 (2^10), 1707; 1000 of n = 26 923, 914
+// (2^10), 1245.  Items of 2^6 steps, with as much set-up as walk, would take 791
+// and 1844 for the 4096 of n = 22 and 24.
 constexpr double kBatchItems = 32768.0;
 
 void batch_free(qubo_batch *b)

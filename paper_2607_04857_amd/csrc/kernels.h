@@ -198,9 +198,9 @@ struct FinalRes {
     double E64;        // float64 rescore from Qf (fp32 instances)
     int32_t status;    // 0 ok, nonzero: self-check failure
     int32_t pad;
-    uint64_t walk_ticks;   // lone solves: from the table build's end to the finish's
-                           // start (from before the top-k seed to its compaction), in
-                           // ticks of the device's constant clock
+    uint64_t walk_ticks;   // from the end of instance 0's descents in the table build
+                           // to the finish's start (k > 1: to the compaction's, the
+                           // seed included), in ticks of the device's constant clock
 };
 
 // Where a top-k finish leaves its results: device or mapped host memory.

@@ -457,9 +457,10 @@ static qubo_status_t plan_walk(const qubo_options_t *opt, Plan &P, std::string *
         // An instance sharing the GPU (batch, server) gets up to 64 items
         // where its prefix allows, of at least 2^kManyMinL steps: a small one
         // then finishes on several waves instead of one (server latency), a
-        // large one keeps 2^14-step items, and no item is so short that its
-        // set-up (finding its instance among thousands, loading that
-        // instance's rows, the state from scratch) outweighs its walk.
+        // large one keeps 2^14-step items, and an item's set-up (finding its
+        // instance among thousands, loading that instance's rows, the state
+        // from scratch: 2 us) weighs little against its walk.  A batch with few
+        // items, and the server, have shorter ones.
         if (many && P.A - L < 6) L = std::max(std::min(P.A, kManyMinL), P.A - 6);
         if (!many) L = std::max(P.A - (P.A < 22 ? 13 : P.A < 24 ? 15 : P.A < 32 ? 16 : 18), kSuper);
         if (L > P.A) L = P.A;

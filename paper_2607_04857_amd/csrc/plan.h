@@ -17,9 +17,10 @@ namespace qplan {
 // Kernel geometry shared by planner and kernels.
 constexpr int kWave = 64;          // lanes per wavefront
 constexpr int kSuper = 6;          // log2 of the unrolled Gray super-block (64 steps)
-constexpr int kManyMinL = 10;      // log2 of the shortest item of an instance in a batch or
-                                   // the server (4096 copies of n = 22: 4.0 ms per replay
-                                   // with 2^6-step items, 1.3 ms with 2^10-step ones)
+constexpr int kManyMinL = 10;      // log2 of the shortest item that the plan of an instance
+                                   // in a batch or the server has by itself; both shorten
+                                   // items further where they are few (batch.cpp,
+                                   // serve_policy.h)
 constexpr int64_t kWideSpan = int64_t(1) << 21;   // values of a field of a wide word
 constexpr int kWideMinA = 20;   // whole call, host and device Q, int32 -> wide words: A = 19
                                 // 62.4 -> 61.7 and 68.3 -> 70.1 us, A = 20 74.2 -> 70.4 and

@@ -116,7 +116,7 @@ qubo_status_t job_result(const Job &job, int i, const qk::FinalRes &fr, qubo_res
 hipStream_t thread_stream(qubo_status_t *st);
 
 // Lay out, upload, run and read back a one-instance job on `stream`
-// (synchronous); fills kernel_ms (walk events) and total_ms.
+// (synchronous); fills kernel_ms (walk_ticks) and total_ms.
 qubo_status_t solve_planned(Job &job, hipStream_t stream, int waves_per_cu, qubo_result_t *out,
                             qubo_state_t *topk = nullptr);
 

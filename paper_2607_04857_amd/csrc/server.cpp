@@ -87,7 +87,7 @@ struct qubo_server {
     size_t budget = 0;
     int max_slots = 0;
     int cus = 0;                  // compute units of the device
-    uint64_t tick_items = 0;      // work items per tick (two per resident wave)
+    uint64_t tick_items = 0;      // units (kUnitLog) per tick, two per resident wave
     hipStream_t stream = nullptr;
     int32_t *d_karena = nullptr;  // max_slots K tables
     size_t counters_at = 0;       // offset of the item counters in TickBuf::d_block
@@ -518,9 +518,8 @@ qubo_status_t server_init(qubo_server *s, size_t budget, int max_slots)
     qubo_status_t st = qrt::device_info(&di);
     if (st != QUBO_OK) return st;
     s->cus = di.cus;
-    // two items per resident wave of the default walk variant (B = 10, LDS
-    // row cache): every wave of a tick then gets the same share, so the
-    // tick ends without a half-idle tail
+    // two units (a served request's items are mostly a quarter of one) per
+    // resident wave of the default walk variant (B = 10, LDS row cache)
     s->tick_items = uint64_t(di.cus) * uint64_t(qk::walk_occupancy(16, 4, 2)) * 2;
     QRT_HIP(hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking), "hipStreamCreate");
     QRT_HIP(hipMalloc(&s->d_karena, size_t(max_slots) * qk::kKTable * sizeof(int32_t)), "hipMalloc");
