@@ -124,7 +124,7 @@ __global__ __launch_bounds__(256) void upload_kernel(Upload up)
 // is sums of a few entries, so what bounds the build is latency, and no part
 // waits for another.  M_int is never formed: its lane and column parts (ML,
 // MH) are, and the bound constants have closed forms over the suffix bits.
-// Measured: a lone build 9-16 us and 4096 batch instances 132 us; 60-92 us and
+// Measured: a lone build 9-16 us and 4096 batch instances 157 us; 60-92 us and
 // 950 us when 8 blocks per instance wrote the whole M_int (2A x 2^B words) and
 // reduced the bound constants over its columns.
 enum { kPartSeed = 0, kPartK, kPartEB, kPartRows, kTableParts, kPartUpload = kTableParts };
