@@ -46,8 +46,8 @@ size_t admit_count(const std::vector<size_t> &queued_bytes, size_t mem_used, siz
 std::vector<size_t> blocks_to_free(const std::vector<size_t> &sizes, size_t need);
 
 // Largest tick budget multiplier: at 64 a tick gives each resident wave
-// about 128 items, so the drain at the tick's end (at most one item per
-// wave) costs under 1% of the tick.
+// about 128 units (of 2^12 Gray steps, or longer items), so the drain at the
+// tick's end (at most one item per wave) costs under 1% of the tick.
 constexpr uint64_t kMaxTickScale = 64;
 
 // Budget multiplier for a tick: 1, doubled while the unissued work exceeds
@@ -55,7 +55,7 @@ constexpr uint64_t kMaxTickScale = 64;
 // tick boundaries under a backlog, where requests wait anyway).
 uint64_t tick_scale(uint64_t backlog_items, uint64_t tick_items);
 
-// Items each walking request issues in one tick.  left: unissued items per
+// Items (the server: units) each walking request issues in one tick.  left: unissued items per
 // request, ascending (fewest first); tick_items: items per tick at scale 1.
 // Returns one share per request (same order): share[k] <= left[k], every
 // request with items left gets at least one, and the shares sum to at most
